@@ -11,10 +11,9 @@ constexpr int kTile = 8192;              // elements per flat tile (power of two
 constexpr int kTileShift = 13;
 constexpr int kT2Group = 16;             // TopK: consecutive tiles of a layer that add their level-2 counts into one slot
 constexpr int kQuadIters = (kTile / 4 + 1 + kFlatThreads - 1) / kFlatThreads;  // 9
-constexpr int kMatRows = 64;             // matrix tile: 64 rows x 256 columns
+constexpr int kMatRows = 64;             // matrix tile: up to 64 rows (Ws::mrows) x 256 columns
 constexpr int kMatCols = 256;
-constexpr int kQRows = 128;              // rows of a tile of the right product Q = Delta^T P^ (64: 5 us slower on
-                                         // ResNet-18 shapes, twice the partial sums; 256: too few workgroups at W = 1)
+constexpr int kQRows = 128;              // most rows of a tile of the right product Q = Delta^T P^ (Ws::qrows)
 constexpr int kHistBins = 2048;          // 11 key bits per radix level
 // a wave quarter has at most ceil((kTile / 4 + 1) / 4) 16-byte groups: iterations of 64 lanes
 constexpr int kSpanIters = ((kTile / 4 + 1 + 3) / 4 + kWave - 1) / kWave;   // 9
@@ -30,11 +29,11 @@ struct LayerDev {
   int32_t rank[2];       // effective rank at level 0 (non-critical) / 1 (critical)
   int32_t k[2];          // TopK kept count at level 0 / 1
   int32_t n_colchunks;   // ceil(cols / kMatCols)
-  int32_t n_rowblocks;   // ceil(rows / kQRows)
+  int32_t n_rowblocks;   // ceil(rows / Ws::qrows)
   int32_t tile0;         // first flat tile of the layer
   int32_t ntiles;        // number of flat tiles
   int32_t t2slot0;       // TopK: the layer's first slot in a worker's level-2 count array (one slot per kT2Group tiles)
-  int32_t mt0;           // PowerSGD matrix layer: its first 64 x 256 matrix tile (it has n_colchunks * ceil(rows / 64))
+  int32_t mt0;           // PowerSGD matrix layer: its first matrix tile (it has n_colchunks * ceil(rows / Ws::mrows))
   int64_t qoff;          // slot of the layer's first wave quarter in the per-worker quarter arrays
                          // (4 * tile0 + layer index: one spare slot per layer for the totals)
   int64_t q_off;         // into Q      (cols rows of kMaxRank floats, zero beyond rmax)
@@ -89,13 +88,13 @@ struct Ws {
   float* e;                    // W x e_stride error memory (holds Delta during a step)
   int64_t e_stride;
   double* norm_part;           // per flat tile: sum of squares of A (kept up to date by the pass that adds the gradient)
-  double* norm_part_m;         // PowerSGD: the same per 64 x 256 matrix tile
+  double* norm_part_m;         // PowerSGD: the same per matrix tile
   uint32_t* a_fresh;           // one word: nonzero = the accumulation window has just restarted: A counts as zero
                                //   (the next pass over it stores the gradient instead of adding it)
   double* sq_part;             // per flat tile: sum over the window of ||g_0||^2 (MSDR detector)
   const FlatTile* ftiles;
   const MatTile* mtiles;
-  const MatTile* qmtiles;      // kQRows x 256 tiles of the matrix layers (right product)
+  const MatTile* qmtiles;      // qrows x 256 tiles of the matrix layers (right product)
   const QTile* qtiles;
   const int32_t* vectiles;     // flat-tile ids of 1-D layers (PowerSGD)
   const int32_t* matlayers;    // layer ids of matrix layers (PowerSGD)
@@ -105,7 +104,7 @@ struct Ws {
   double* Ppart; int64_t ppart_stride;   // per worker and 256-column chunk: that chunk's share of P_w, fp64
   double* Pwork;               // p_total doubles: working columns of the orthogonalisation of tall layers
   const PTile* ptiles;         // row blocks of the matrix layers (mean of P)
-  double* Qpart; int64_t qpart_stride;   // per worker and 64-row block: that block's share of Q_w, fp64
+  double* Qpart; int64_t qpart_stride;   // per worker and block of qrows rows: that block's share of Q_w, fp64
   float* vecmean;
   uint32_t* pending;           // one word: workers whose e still holds Delta (residual not formed yet)
   // TopK
@@ -137,6 +136,9 @@ struct Ws {
   int64_t n_model;             // elements that belong to a layer
   int64_t N;
   int32_t W, L, rmax;
+  int32_t mrows, qrows;        // PowerSGD: rows of a matrix tile / of a tile of the right product
+  int32_t pmean_in_orth;       // PowerSGD: the orthogonalisation sums the partials of P itself
+  int32_t q_reversed;          // PowerSGD: the right product takes the tiles in reverse order
   int32_t n_ftiles, n_mtiles, n_qmtiles, n_qtiles, n_vectiles, n_mat, n_ptiles;
   int32_t n_t2slots;           // TopK: slots of t2 per worker
   float eta;

@@ -9,21 +9,46 @@
 // before it adds the new gradient.  That saves one read and one write of the matrix per worker
 // and step.  psgd_residual_kernel makes the memory explicit when somebody wants to look at it.
 //
-// Matrix tile: 64 rows x 256 columns, one workgroup of 4 waves.  A lane owns 4 columns
-// (vec4 layers: 4 adjacent columns, one 16-byte access per row; other layers: columns
-// lane, lane+64, lane+128, lane+192, 4-byte accesses).  A wave owns rows wave, wave+4, ...
+// Matrix tile: ws.mrows rows x 256 columns, one workgroup of 4 waves.  A lane owns 4 adjacent columns
+// and a wave owns rows wave, wave + 4, ...; how a lane reaches its columns depends on the layer (RowMode).
 #pragma once
 #include "acc_common.h"
 
 namespace acc {
 
-template <bool V4>
-__device__ __forceinline__ void lane_cols(int col0, int lane, int cols, int (&col)[4], bool (&cm)[4]) {
-#pragma unroll
-  for (int v = 0; v < 4; ++v) {
-    col[v] = V4 ? col0 + lane * 4 + v : col0 + lane + 64 * v;
-    cm[v] = col[v] < cols;
+// How the rows of a matrix layer are accessed.  kRowAligned: every row starts on a 16-byte boundary and
+// holds whole groups of four.  kRowUnaligned: rows of at least four elements that start anywhere; a
+// 16-byte access needs no more than 4-byte alignment on this part (64 lanes still cover one dense
+// kilobyte), and the lane whose four columns reach past the row reads the row's last four instead and
+// owns only what is its own.  kRowNarrow: fewer than four columns, element by element.
+enum RowMode { kRowAligned = 0, kRowUnaligned = 1, kRowNarrow = 2 };
+
+__device__ __forceinline__ int row_mode(const LayerDev& L) {
+  return L.vec4 ? kRowAligned : (L.cols >= 4 ? kRowUnaligned : kRowNarrow);
+}
+
+// c: first column the lane accesses; own0: first of its four columns that it owns (0: all of them, 4 or
+// more: none).  kRowNarrow: c = 0, own0 = number of columns for lane 0 and 0 for the others (owned: the
+// columns below it).
+struct LaneCols { int c, own0; };
+
+template <int MODE>
+__device__ __forceinline__ LaneCols lane_cols(int col0, int lane, int cols) {
+  LaneCols lc;
+  if (MODE == kRowNarrow) {
+    lc.c = 0;
+    lc.own0 = lane == 0 ? cols : 0;
+  } else {
+    const int col = col0 + 4 * lane;
+    lc.c = min(col, cols - 4);
+    lc.own0 = min(col - lc.c, 4);
   }
+  return lc;
+}
+
+template <int MODE>
+__device__ __forceinline__ bool owns(const LaneCols& lc, int v) {
+  return MODE == kRowNarrow ? v < lc.own0 : (MODE == kRowAligned ? lc.own0 == 0 : v >= lc.own0);
 }
 
 // Streaming access for what a step touches once, so that Delta stays in the caches between the
@@ -32,54 +57,83 @@ constexpr bool kPsgdStreamG = true;     // gradients: read once per step
 constexpr bool kPsgdStreamA = true;     // accumulator: read and written once per step
 constexpr bool kPsgdStreamOut = true;   // averaged gradient: written once, read by nobody here
 
-// STREAM: streaming (non-temporal) access on the 16-byte path, for data touched once per step.
-template <bool V4, bool STREAM = false>
-__device__ __forceinline__ void load_row(const float* __restrict__ p, int64_t rowbase,
-                                         const int (&col)[4], const bool (&cm)[4], float (&d)[4]) {
-  if (V4) {
-    if (cm[0]) {
-      const float4 t = STREAM ? ld16_stream(p + rowbase + col[0])
-                              : *reinterpret_cast<const float4*>(p + rowbase + col[0]);
-      d[0] = t.x; d[1] = t.y; d[2] = t.z; d[3] = t.w;
-    } else {
-      d[0] = d[1] = d[2] = d[3] = 0.f;
-    }
+typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+
+// The lane's four elements of a row, loaded whatever the lane owns (every address lies inside the row);
+// row: the row's first element.  STREAM: non-temporal.
+template <int MODE, bool STREAM = false>
+__device__ __forceinline__ void load_row(const float* __restrict__ row, int c, int cols, float (&d)[4]) {
+  if (MODE == kRowAligned) {
+    const float4 t = STREAM ? ld16_stream(row + c) : *reinterpret_cast<const float4*>(row + c);
+    d[0] = t.x; d[1] = t.y; d[2] = t.z; d[3] = t.w;
+  } else if (MODE == kRowUnaligned) {
+    const f4u* q = reinterpret_cast<const f4u*>(row + c);
+    const f4u t = STREAM ? __builtin_nontemporal_load(q) : *q;
+    d[0] = t.x; d[1] = t.y; d[2] = t.z; d[3] = t.w;
   } else {
 #pragma unroll
-    for (int v = 0; v < 4; ++v) d[v] = cm[v] ? p[rowbase + col[v]] : 0.f;
+    for (int v = 0; v < 4; ++v) d[v] = row[min(v, cols - 1)];
   }
 }
 
-template <bool V4, bool STREAM = false>
-__device__ __forceinline__ void store_row(float* __restrict__ p, int64_t rowbase,
-                                          const int (&col)[4], const bool (&cm)[4],
-                                          const float (&d)[4]) {
-  if (V4) {
-    if (cm[0]) {
-      if (STREAM) st16_stream(p + rowbase + col[0], make_float4(d[0], d[1], d[2], d[3]));
-      else *reinterpret_cast<float4*>(p + rowbase + col[0]) = make_float4(d[0], d[1], d[2], d[3]);
+// Stores what the lane owns.  Streaming stores on aligned rows only: an unaligned row shares its first and
+// last cache line with its neighbours, which the caches put together.
+template <int MODE, bool STREAM = false>
+__device__ __forceinline__ void store_row(float* __restrict__ row, const LaneCols& lc, const float (&d)[4]) {
+  if (MODE == kRowAligned) {
+    if (lc.own0 == 0) {
+      if (STREAM) st16_stream(row + lc.c, make_float4(d[0], d[1], d[2], d[3]));
+      else *reinterpret_cast<float4*>(row + lc.c) = make_float4(d[0], d[1], d[2], d[3]);
+    }
+  } else if (MODE == kRowUnaligned) {
+    if (lc.own0 == 0) {
+      f4u t;
+      t.x = d[0]; t.y = d[1]; t.z = d[2]; t.w = d[3];
+      *reinterpret_cast<f4u*>(row + lc.c) = t;
+    } else {
+#pragma unroll
+      for (int v = 1; v < 4; ++v)
+        if (v >= lc.own0) row[lc.c + v] = d[v];
     }
   } else {
 #pragma unroll
     for (int v = 0; v < 4; ++v)
-      if (cm[v]) p[rowbase + col[v]] = d[v];
+      if (owns<MODE>(lc, v)) row[v] = d[v];
   }
 }
 
 // The rows of Q (kMaxRank floats each on the device, zero beyond rmax) of the four columns a lane
-// owns: one aligned 16-byte load per row.  (Sixteen single-word loads at a 64-byte stride between
-// lanes kept the texture path busy for longer than the rows of the tile themselves.)
-__device__ __forceinline__ void load_q_rows(const Ws& ws, const LayerDev& L, const int (&col)[4],
-                                            const bool (&cm)[4], float (&q)[4][kMaxRank]) {
+// accesses: one aligned 16-byte load per row.  (Sixteen single-word loads at a 64-byte stride between
+// lanes kept the texture path busy for longer than the rows of the tile themselves.)  What the lane
+// does not own is set to zero by the caller (own_q_rows), once the loads are needed.
+template <int MODE>
+__device__ __forceinline__ void load_q_rows(const Ws& ws, const LayerDev& L, const LaneCols& lc,
+                                            float (&q)[4][kMaxRank]) {
 #pragma unroll
   for (int v = 0; v < 4; ++v) {
-    float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (cm[v]) t = *reinterpret_cast<const float4*>(ws.Q + L.q_off + (int64_t)col[v] * kMaxRank);
+    const int col = MODE == kRowNarrow ? min(v, L.cols - 1) : lc.c + v;
+    const float4 t = *reinterpret_cast<const float4*>(ws.Q + L.q_off + (int64_t)col * kMaxRank);
     q[v][0] = t.x; q[v][1] = t.y; q[v][2] = t.z; q[v][3] = t.w;
   }
 }
 
+template <int MODE>
+__device__ __forceinline__ void own_q_rows(const LaneCols& lc, float (&q)[4][kMaxRank]) {
+#pragma unroll
+  for (int v = 0; v < 4; ++v)
+#pragma unroll
+    for (int k = 0; k < kMaxRank; ++k) q[v][k] = owns<MODE>(lc, v) ? q[v][k] : 0.f;
+}
+
 // ---- phase 0: Delta = g + e (in place of e), A += g (worker 0), P partial = Delta Q ---------
+
+// (double)f, converted where it is written.  The conversions of the lane's rows of Q are loop-invariant and
+// were kept across the row loop, 32 registers for what sixteen cheap instructions per row give.
+__device__ __forceinline__ double cvt_here(float f) {
+  double d;
+  asm volatile("v_cvt_f64_f32 %0, %1" : "=v"(d) : "v"(f));
+  return d;
+}
 
 // One entry of P^ Q~^T: sum_k p[k] q[k] over all kMaxRank columns, where the caller has set p[k]
 // to 0 beyond the rank in use (a product with 0 leaves the sum as it is).  Every kernel that
@@ -92,120 +146,174 @@ __device__ __forceinline__ float low_rank_entry(const float (&p)[kMaxRank], cons
   return s;
 }
 
+// The rows a wave has requested together.  The first pass keeps two of these in flight: while one is
+// worked on the next is on its way.  It is bound by memory where the chip is full and by latency where few
+// workgroups share it; a wave that waited for each pair of rows before it asked for the next was slower at
+// both ends, states beyond the caches: four small layers at W = 2 15.4 us, 8.2 so with 16-row tiles;
+// ResNet-18 shapes at W = 4 120 us, 110.7 so (5.2 -> 5.65 TB/s); 40 layers of ragged rows at W = 3, where the
+// 16-byte accesses replace 4-byte ones as well, 79.6 us, 71.2 so.
+constexpr int kEfRows = 2;
+struct EfRows { float g[kEfRows][4], e[kEfRows][4], a[kEfRows][4]; };
+
+// The tile's pointers and lane geometry; Asrc: where A's old value is loaded from (the accumulation
+// window has just restarted: the gradient once more, from the cache, and its value is ignored).
+struct EfTile {
+  const float* g;
+  float* e;
+  const float* Asrc;
+  float* A;
+  double* ppart;       // this layer's and chunk's share of the worker's P partials, row 0
+  int cols, row_end;
+  LaneCols lc;
+};
+
+// Rows i0 and i0 + 4 (a row beyond the tile: every lane asks for one and the same 16 bytes of the last
+// row and nobody looks at them; a request behind a branch would make every wait a wait for all requests).
+template <int MODE, bool HASA>
+__device__ __forceinline__ void ef_load(const EfTile& t, int i0, EfRows& r) {
+#pragma unroll
+  for (int b = 0; b < kEfRows; ++b) {
+    const int i = i0 + 4 * b;
+    const int64_t rb = (int64_t)min(i, t.row_end - 1) * t.cols;
+    const int c = i < t.row_end ? t.lc.c : 0;
+    load_row<MODE, kPsgdStreamG && MODE == kRowAligned>(t.g + rb, c, t.cols, r.g[b]);
+    load_row<MODE>(t.e + rb, c, t.cols, r.e[b]);
+    if (HASA) load_row<MODE, kPsgdStreamA && MODE == kRowAligned>(t.Asrc + rb, c, t.cols, r.a[b]);
+  }
+}
+
 // rp > 0: the memory still holds the previous step's Delta; its residual is Delta - P^ Q~^T with
-// the previous P^ (rows in ws.Phat) and Q~ (= the warm start, first rp columns).
-template <int R, bool V4>
-__device__ void ef_p_tile(const Ws& ws, const LayerDev& L, const MatTile& t, const float* __restrict__ g,
-                          float* __restrict__ e, float* __restrict__ A, double* __restrict__ ppart, int rp,
-                          float (*ps)[kMaxRank], bool a_fresh, double* red4) {
+// the previous P^ (its rows of the tile are in ps) and Q~ (= the warm start, first rp columns).
+template <int R, int MODE, bool HASA>
+__device__ __forceinline__ void ef_rows(const EfTile& t, int i0, EfRows& r, const float (&q)[4][kMaxRank], int rp,
+                                        const float (*ps)[kMaxRank], int row0, int rmax, bool a_fresh, double& a_sq) {
+  const int lane = threadIdx.x & 63;
+  double part[R >= 3 ? 1 : kEfRows][R];                    // a row that does not exist contributes zeros
+#pragma unroll
+  for (int b = 0; b < (R >= 3 ? 1 : kEfRows); ++b)
+#pragma unroll
+    for (int k = 0; k < R; ++k) part[b][k] = 0.0;
+#pragma unroll
+  for (int b = 0; b < kEfRows; ++b) {
+    const int i = i0 + 4 * b;
+    if (i < t.row_end) {                                   // wave-uniform
+      const int64_t rb = (int64_t)i * t.cols;
+      if (rp > 0) {                                        // wave-uniform: the pending residual first
+        float pp[kMaxRank];
+#pragma unroll
+        for (int k = 0; k < kMaxRank; ++k) pp[k] = ps[i - row0][k];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) r.e[b][v] = r.e[b][v] - low_rank_entry(pp, q[v]);
+      }
+      float d[4];
+#pragma unroll
+      for (int v = 0; v < 4; ++v) d[v] = owns<MODE>(t.lc, v) ? r.g[b][v] + r.e[b][v] : 0.f;
+      store_row<MODE>(t.e + rb, t.lc, d);
+      if (HASA) {
+        float a[4];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) a[v] = owns<MODE>(t.lc, v) ? (a_fresh ? 0.f : r.a[b][v]) + r.g[b][v] : 0.f;
+        store_row<MODE, kPsgdStreamA>(t.A + rb, t.lc, a);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) a_sq += (double)a[v] * (double)a[v];
+      }
+      // the lane's share of the chunk's share of P_w's row, in fp64: products of fp32 values are
+      // exact there, the sums carry an error far below the fp32 rounding of the stored P_w
+      double dd[4];
+#pragma unroll
+      for (int v = 0; v < 4; ++v) dd[v] = (double)d[v];
+#pragma unroll
+      for (int k = 0; k < R; ++k) {
+        double s = dd[0] * cvt_here(q[0][k]);
+        s = fma(dd[1], cvt_here(q[1][k]), s);
+        s = fma(dd[2], cvt_here(q[2][k]), s);
+        s = fma(dd[3], cvt_here(q[3][k]), s);
+        part[R >= 3 ? 0 : b][k] = s;
+      }
+      if constexpr (R >= 3) {
+        // Three or four values per row: folded row by row (as many instructions as folding both
+        // rows together, half the registers).  The lower 32 lanes end with columns 0 and 1 of
+        // P (even / odd rows of 16 lanes), the upper 32 with columns 2 and 3.
+        const double y02 = fold32_d(part[0][0], part[0][2]);
+        const double y13 = fold32_d(part[0][1], R > 3 ? part[0][R - 1] : 0.0);
+        const double y = row_sum_d(fold16_d(y02, y13));
+        const int kcol = 2 * (lane >> 5) + ((lane >> 4) & 1);
+        if ((lane & 15) == 0 && kcol < R) t.ppart[(int64_t)i * rmax + kcol] = y;
+      }
+    }
+  }
+  if constexpr (R <= 2) {
+    // One or two values per row: both rows' values are folded over the wave together (the upper
+    // 32 lanes keep the second row, the odd rows of 16 lanes the second column of P), so that
+    // the lane exchanges of a full butterfly per value (27 instructions each in fp64) shrink
+    // to about 20 for all of them.
+    const int hb = lane >> 5, rp16 = (lane >> 4) & 1;       // which row of the pair / which column
+    const int i_mine = i0 + 4 * hb;
+    double* dst = t.ppart + (int64_t)i_mine * rmax;
+    const bool writer = (lane & 15) == 0 && i_mine < t.row_end;
+    if constexpr (R == 1) {
+      double y = fold32_d(part[0][0], part[1][0]);
+      y = row_sum_d(y);
+      y = fold16_d(y, y);                                    // both rows of 16 lanes of a half
+      if (writer && rp16 == 0) dst[0] = y;
+    } else {
+      const double y0 = fold32_d(part[0][0], part[1][0]), y1 = fold32_d(part[0][1], part[1][1]);
+      const double y = row_sum_d(fold16_d(y0, y1));         // even rows of 16 lanes: column 0, odd rows: column 1
+      if (writer) dst[rp16] = y;
+    }
+  }
+}
+
+template <int R, int MODE, bool HASA>
+__device__ __forceinline__ double ef_loop(const EfTile& t, int i0, EfRows& cur, const float (&q)[4][kMaxRank], int rp,
+                                          const float (*ps)[kMaxRank], int row0, int rmax, bool a_fresh) {
+  double a_sq = 0.0;     // worker 0: the lane's share of the tile's sum of squares of A
+  for (; i0 < t.row_end; i0 += 4 * kEfRows) {
+    EfRows nxt;
+    ef_load<MODE, HASA>(t, i0 + 4 * kEfRows, nxt);
+    ef_rows<R, MODE, HASA>(t, i0, cur, q, rp, ps, row0, rmax, a_fresh, a_sq);
+    cur = nxt;
+  }
+  return a_sq;
+}
+
+template <int MODE, bool HASA>
+__device__ __forceinline__ void ef_p_tile(const Ws& ws, const LayerDev& L, const MatTile& mt, const float* __restrict__ g,
+                                          float* __restrict__ e, double* __restrict__ ppart, int level, int rp_used,
+                                          uint32_t pending, uint32_t fresh, int w, float (*ps)[kMaxRank], double* red4) {
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  int col[4]; bool cm[4];
-  lane_cols<V4>(t.col0, lane, L.cols, col, cm);
-  if (rp > 0) {
-    // the previous P^ rows of the tile (zero-padded) go to LDS with one load per thread, requested
-    // together with Q's rows, so that the row loop waits for no load of theirs
-    const int pr = threadIdx.x >> 2, pk = threadIdx.x & 3;
-    const int i = t.row0 + pr;
-    ps[pr][pk] = (i < L.rows && pk < rp) ? ws.Phat[L.p_off + (int64_t)i * ws.rmax + pk] : 0.f;
-  }
+  EfTile t;
+  const bool a_fresh = HASA && fresh != 0u;                // uniform over the workgroup
+  t.lc = lane_cols<MODE>(mt.col0, lane, L.cols);
+  t.cols = L.cols;
+  t.row_end = min(mt.row0 + ws.mrows, L.rows);
+  t.g = g + L.offset;
+  t.e = e + L.offset;
+  t.A = HASA ? ws.A + L.offset : nullptr;
+  t.Asrc = a_fresh ? t.g : t.A;
+  t.ppart = ppart + L.ppart_off + (int64_t)(mt.col0 / kMatCols) * L.rows * ws.rmax;
+  // requested together: the first rows, Q's rows, and the previous P^ rows of the tile (for LDS)
+  const int i0 = mt.row0 + wave;
+  EfRows first;
+  ef_load<MODE, HASA>(t, i0, first);
   float q[4][kMaxRank];
-  load_q_rows(ws, L, col, cm, q);
-
-  if (rp > 0) __syncthreads();                             // uniform over the workgroup
-  const int row_end = min(t.row0 + kMatRows, L.rows);
-  const int chunk = t.col0 / kMatCols;
-  constexpr int B = 2;   // rows in flight per wave (one row is as fast; more rows cost registers and occupancy)
-  double a_sq = 0.0;     // worker 0: the lane's share of the tile's sum of squares of A
-  for (int i0 = t.row0 + wave; i0 < row_end; i0 += 4 * B) {
-    float gd[B][4], ed[B][4], ad[B][4];
-    double part[R >= 3 ? 1 : B][R];                          // a row that does not exist contributes zeros
-#pragma unroll
-    for (int b = 0; b < (R >= 3 ? 1 : B); ++b)
-#pragma unroll
-      for (int k = 0; k < R; ++k) part[b][k] = 0.0;
-#pragma unroll
-    for (int b = 0; b < B; ++b) {
-      const int i = i0 + 4 * b;
-      if (i < row_end) {
-        const int64_t rb = L.offset + (int64_t)i * L.cols;
-        load_row<V4, kPsgdStreamG>(g, rb, col, cm, gd[b]);
-        load_row<V4>(e, rb, col, cm, ed[b]);
-        if (A && !a_fresh) load_row<V4, kPsgdStreamA>(A, rb, col, cm, ad[b]);
-        else ad[b][0] = ad[b][1] = ad[b][2] = ad[b][3] = 0.f;
-      }
-    }
-#pragma unroll
-    for (int b = 0; b < B; ++b) {
-      const int i = i0 + 4 * b;
-      if (i < row_end) {                       // wave-uniform
-        const int64_t rb = L.offset + (int64_t)i * L.cols;
-        if (rp > 0) {                          // wave-uniform: the pending residual first
-          float pp[kMaxRank];
-#pragma unroll
-          for (int k = 0; k < kMaxRank; ++k) pp[k] = ps[i - t.row0][k];
-#pragma unroll
-          for (int v = 0; v < 4; ++v) ed[b][v] = ed[b][v] - low_rank_entry(pp, q[v]);
-        }
-        float d[4];
-#pragma unroll
-        for (int v = 0; v < 4; ++v) d[v] = gd[b][v] + ed[b][v];
-        store_row<V4>(e, rb, col, cm, d);
-        if (A) {
-#pragma unroll
-          for (int v = 0; v < 4; ++v) ad[b][v] += gd[b][v];
-          store_row<V4, kPsgdStreamA>(A, rb, col, cm, ad[b]);
-#pragma unroll
-          for (int v = 0; v < 4; ++v) a_sq += (double)ad[b][v] * (double)ad[b][v];   // masked columns hold zeros
-        }
-        // the lane's share of the chunk's share of P_w's row, in fp64: products of fp32 values are
-        // exact there, the sums carry an error far below the fp32 rounding of the stored P_w
-        double dd[4];
-#pragma unroll
-        for (int v = 0; v < 4; ++v) dd[v] = (double)d[v];
-#pragma unroll
-        for (int k = 0; k < R; ++k) {
-          double s = dd[0] * (double)q[0][k];
-          s = fma(dd[1], (double)q[1][k], s);
-          s = fma(dd[2], (double)q[2][k], s);
-          s = fma(dd[3], (double)q[3][k], s);
-          part[R >= 3 ? 0 : b][k] = s;
-        }
-        if constexpr (R >= 3) {
-          // Three or four values per row: folded row by row (as many instructions as folding both
-          // rows together, half the registers).  The lower 32 lanes end with columns 0 and 1 of
-          // P (even / odd rows of 16 lanes), the upper 32 with columns 2 and 3.
-          const double y02 = fold32_d(part[0][0], part[0][2]);
-          const double y13 = fold32_d(part[0][1], R > 3 ? part[0][R - 1] : 0.0);
-          const double y = row_sum_d(fold16_d(y02, y13));
-          const int kcol = 2 * (lane >> 5) + ((lane >> 4) & 1);
-          if ((lane & 15) == 0 && kcol < R)
-            ppart[L.ppart_off + ((int64_t)chunk * L.rows + i) * ws.rmax + kcol] = y;
-        }
-      }
-    }
-    if constexpr (R <= 2) {
-      // One or two values per row: both rows' values are folded over the wave together (the upper
-      // 32 lanes keep the second row, the odd rows of 16 lanes the second column of P), so that
-      // the lane exchanges of a full butterfly per value (27 instructions each in fp64) shrink
-      // to about 20 for all of them.
-      const int hb = lane >> 5, rp16 = (lane >> 4) & 1;     // which row of the pair / which column
-      const int i_mine = i0 + 4 * hb;
-      double* dst = ppart + L.ppart_off + ((int64_t)chunk * L.rows + i_mine) * ws.rmax;
-      const bool writer = (lane & 15) == 0 && i_mine < row_end;
-      if constexpr (R == 1) {
-        double y = fold32_d(part[0][0], part[1][0]);
-        y = row_sum_d(y);
-        y = fold16_d(y, y);                                  // both rows of 16 lanes of a half
-        if (writer && rp16 == 0) dst[0] = y;
-      } else {
-        const double y0 = fold32_d(part[0][0], part[1][0]), y1 = fold32_d(part[0][1], part[1][1]);
-        const double y = row_sum_d(fold16_d(y0, y1));       // even rows of 16 lanes: column 0, odd rows: column 1
-        if (writer) dst[rp16] = y;
-      }
-    }
+  load_q_rows<MODE>(ws, L, t.lc, q);
+  const int pr = threadIdx.x >> 2, pk = threadIdx.x & 3;
+  const float ph = ws.Phat[L.p_off + (int64_t)min(mt.row0 + pr, L.rows - 1) * ws.rmax + min(pk, ws.rmax - 1)];
+  const int rp = ((pending >> w) & 1u) ? rp_used : 0;      // rank of the previous step's factors
+  const int r = level ? L.rank[1] : L.rank[0];
+  ps[pr][pk] = pk < rp ? ph : 0.f;
+  own_q_rows<MODE>(t.lc, q);
+  __syncthreads();
+  double a_sq;
+  switch (r) {
+    case 1: a_sq = ef_loop<1, MODE, HASA>(t, i0, first, q, rp, ps, mt.row0, ws.rmax, a_fresh); break;
+    case 2: a_sq = ef_loop<2, MODE, HASA>(t, i0, first, q, rp, ps, mt.row0, ws.rmax, a_fresh); break;
+    case 3: a_sq = ef_loop<3, MODE, HASA>(t, i0, first, q, rp, ps, mt.row0, ws.rmax, a_fresh); break;
+    default: a_sq = ef_loop<4, MODE, HASA>(t, i0, first, q, rp, ps, mt.row0, ws.rmax, a_fresh); break;
   }
-  if (A) {                                                 // uniform over the workgroup
+  if (HASA) {
     const double tsum = block_sum4_d(a_sq, red4);
     if (threadIdx.x == 0) ws.norm_part_m[blockIdx.x] = tsum;
   }
@@ -217,16 +325,13 @@ __device__ void ef_p_tile(const Ws& ws, const LayerDev& L, const MatTile& t, con
 __global__ __launch_bounds__(256) void psgd_ef_p_kernel(const Ws ws, const GradPtrs gp, int w0) {
   __shared__ float ps[kMatRows][kMaxRank];
   __shared__ double red4[4];
-  const uint32_t pending = *ws.pending;
   const int w = w0 + blockIdx.y;
   const float* __restrict__ g = gp.p[w];
   float* __restrict__ e = ws.e + (int64_t)w * ws.e_stride;
-  float* __restrict__ A = (w == 0) ? ws.A : nullptr;
-  // the accumulation window has just restarted: A counts as zero and is not read
-  const bool a_fresh = A && *ws.a_fresh != 0u;             // uniform over the workgroup
   if ((int)blockIdx.x >= ws.n_mtiles) {
     // 1-D layers: only the accumulation A += g of worker 0 happens here (and the tile's sum of squares)
     if (w != 0) return;
+    const bool a_fresh = *ws.a_fresh != 0u;
     const int tile_id = ws.vectiles[blockIdx.x - ws.n_mtiles];
     const FlatTile ft = ws.ftiles[tile_id];
     const LayerDev& L = ws.layers[ft.layer];
@@ -244,25 +349,19 @@ __global__ __launch_bounds__(256) void psgd_ef_p_kernel(const Ws ws, const GradP
     if (threadIdx.x == 0) ws.norm_part[tile_id] = a_sq;
     return;
   }
+  const uint32_t pending = *ws.pending, fresh = *ws.a_fresh;
   const MatTile t = ws.mtiles[blockIdx.x];
   const LayerDev& L = ws.layers[t.layer];
-  const int r = L.rank[ws.level[t.layer]];
-  const int rp = ((pending >> w) & 1u) ? ws.rank_used[t.layer] : 0;   // rank of the previous step's factors
+  const int level = ws.level[t.layer], rp_used = ws.rank_used[t.layer];
   double* ppart = ws.Ppart + (int64_t)w * ws.ppart_stride;
-  if (L.vec4) {
-    switch (r) {
-      case 1: ef_p_tile<1, true>(ws, L, t, g, e, A, ppart, rp, ps, a_fresh, red4); break;
-      case 2: ef_p_tile<2, true>(ws, L, t, g, e, A, ppart, rp, ps, a_fresh, red4); break;
-      case 3: ef_p_tile<3, true>(ws, L, t, g, e, A, ppart, rp, ps, a_fresh, red4); break;
-      default: ef_p_tile<4, true>(ws, L, t, g, e, A, ppart, rp, ps, a_fresh, red4); break;
-    }
-  } else {
-    switch (r) {
-      case 1: ef_p_tile<1, false>(ws, L, t, g, e, A, ppart, rp, ps, a_fresh, red4); break;
-      case 2: ef_p_tile<2, false>(ws, L, t, g, e, A, ppart, rp, ps, a_fresh, red4); break;
-      case 3: ef_p_tile<3, false>(ws, L, t, g, e, A, ppart, rp, ps, a_fresh, red4); break;
-      default: ef_p_tile<4, false>(ws, L, t, g, e, A, ppart, rp, ps, a_fresh, red4); break;
-    }
+  // worker 0 also updates A
+  switch (2 * row_mode(L) + (w == 0 ? 1 : 0)) {
+    case 2 * kRowAligned: ef_p_tile<kRowAligned, false>(ws, L, t, g, e, ppart, level, rp_used, pending, fresh, w, ps, red4); break;
+    case 2 * kRowAligned + 1: ef_p_tile<kRowAligned, true>(ws, L, t, g, e, ppart, level, rp_used, pending, fresh, w, ps, red4); break;
+    case 2 * kRowUnaligned: ef_p_tile<kRowUnaligned, false>(ws, L, t, g, e, ppart, level, rp_used, pending, fresh, w, ps, red4); break;
+    case 2 * kRowUnaligned + 1: ef_p_tile<kRowUnaligned, true>(ws, L, t, g, e, ppart, level, rp_used, pending, fresh, w, ps, red4); break;
+    case 2 * kRowNarrow: ef_p_tile<kRowNarrow, false>(ws, L, t, g, e, ppart, level, rp_used, pending, fresh, w, ps, red4); break;
+    default: ef_p_tile<kRowNarrow, true>(ws, L, t, g, e, ppart, level, rp_used, pending, fresh, w, ps, red4); break;
   }
 }
 
@@ -280,40 +379,93 @@ __global__ __launch_bounds__(256) void psgd_ef_p_kernel(const Ws ws, const GradP
 constexpr int kOrthThreads = 1024;
 constexpr int kOrthWaves = kOrthThreads / kWave;
 
-// P_bar[i][k] = fl32( (sum_w fl32(sum_c partial[w][c][i][k])) / W ), chunks in index order.
+// sum_w fl32(sum_b partial[w][b]) in fp64 (P_w and Q_w are fp32 quantities): workers and blocks in index
+// order, the partial sums requested sixteen at a time whatever worker they belong to, from clamped
+// positions, so that a thread waits for few round trips.  Everything but src is wave-uniform.
+// (16, 18 and 24 at a time are 1 to 3 us slower per step on layers with few partials: the positions
+// beyond the last one are requested all the same.)
+constexpr int kPartLoads = 8;
+__device__ __forceinline__ double sum_partials(const double* __restrict__ src, int64_t wstride, int64_t bstride, int W,
+                                               int nb) {
+  double total = 0.0, s = 0.0;
+  int lw = 0, lb = 0, w = 0, b = 0;                        // next one to request / to add
+  while (w < W) {
+    double v[kPartLoads];
+#pragma unroll
+    for (int u = 0; u < kPartLoads; ++u) {
+      v[u] = src[(int64_t)lw * wstride + (int64_t)lb * bstride];
+      if (lb + 1 < nb) ++lb;
+      else if (lw + 1 < W) { lb = 0; ++lw; }
+    }
+#pragma unroll
+    for (int u = 0; u < kPartLoads; ++u) {
+      if (w < W) {
+        s += v[u];
+        if (++b == nb) { total += (double)(float)s; s = 0.0; b = 0; ++w; }
+      }
+    }
+  }
+  return total;
+}
+
+// 1-D layers are sent raw: mean over the workers in worker order (fp64, rounded once) of one flat tile.
+// Four elements per thread and four workers' gradients are requested together: they come from memory,
+// and one after the other they were what the orthogonalisation launch waited for (3 of its 7 us).
+__device__ __forceinline__ void vec_mean_tile(const Ws& ws, const GradPtrs& gp, int vt) {
+  constexpr int E = 4, U = 4;
+  const FlatTile ft = ws.ftiles[ws.vectiles[vt]];
+  const LayerDev& L = ws.layers[ft.layer];
+  const int64_t base = L.offset + ft.start;
+  float* __restrict__ mean = ws.vecmean + L.vec_off + ft.start;
+  for (int i0 = threadIdx.x; i0 < ft.count; i0 += E * blockDim.x) {
+    double s[E];
+#pragma unroll
+    for (int x = 0; x < E; ++x) s[x] = 0.0;
+    for (int w0 = 0; w0 < ws.W; w0 += U) {
+      float g[U][E];
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int x = 0; x < E; ++x)
+          g[u][x] = gp.p[min(w0 + u, ws.W - 1)][base + min(i0 + x * (int)blockDim.x, ft.count - 1)];
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int x = 0; x < E; ++x)
+          if (w0 + u < ws.W) s[x] += (double)g[u][x];
+    }
+#pragma unroll
+    for (int x = 0; x < E; ++x)
+      if (i0 + x * (int)blockDim.x < ft.count) mean[i0 + x * blockDim.x] = (float)(s[x] / (double)ws.W);
+  }
+}
+
+// P_bar[i][k] = fl32( (sum_w fl32(sum_c partial[w][c][i][k])) / W ).
 // One workgroup per 16 rows of a layer; thread = (share, row, column of P), four shares per entry:
 // share s sums the workers s, s + 4, ... (each worker's chunks in fp64, rounded to the fp32 value
 // P_w), then the four shares are added in order.  Many small workgroups: the partial sums of a
 // layer (1.2 MB for the largest ResNet-18 layer at four workers) are read by many compute units
-// at once, and a thread waits for few dependent batches of loads.
+// at once, and a thread waits for few dependent batches of loads.  Where a layer has few of them
+// (Ws::pmean_in_orth) the orthogonalisation sums them itself and this launch is left out.
 constexpr int kPmeanRows = 16;
-constexpr int kPmeanLoads = 8;   // partial sums a thread has in flight
 
-__global__ __launch_bounds__(256) void psgd_pmean_kernel(const Ws ws) {
+__global__ __launch_bounds__(256) void psgd_pmean_kernel(const Ws ws, const GradPtrs gp) {
   __shared__ double share_sum[4][kPmeanRows * 4];
+  if ((int)blockIdx.x >= ws.n_ptiles) {
+    vec_mean_tile(ws, gp, blockIdx.x - ws.n_ptiles);
+    return;
+  }
   const PTile t = ws.ptiles[blockIdx.x];
   const LayerDev& L = ws.layers[t.layer];
-  const int r = L.rank[ws.level[t.layer]];
-  const int share = threadIdx.x >> 6, slot = threadIdx.x & 63;
+  const int level = ws.level[t.layer];
+  const int r = level ? L.rank[1] : L.rank[0];
+  const int share = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), slot = threadIdx.x & 63;
   const int i = t.row0 + (slot >> 2), k = slot & 3;
   const bool live = i < L.rows && k < r;
   double total = 0.0;
-  if (live) {
-    const int nc = L.n_colchunks;
-    const int64_t cstride = (int64_t)L.rows * ws.rmax;
-    const double* base = ws.Ppart + L.ppart_off + (int64_t)i * ws.rmax + k;
-    for (int w = share; w < ws.W; w += 4) {
-      const double* src = base + (int64_t)w * ws.ppart_stride;
-      double s = 0.0;
-      for (int c0 = 0; c0 < nc; c0 += kPmeanLoads) {
-        double v[kPmeanLoads];
-#pragma unroll
-        for (int u = 0; u < kPmeanLoads; ++u) v[u] = src[(int64_t)min(c0 + u, nc - 1) * cstride];
-#pragma unroll
-        for (int u = 0; u < kPmeanLoads; ++u) s += (c0 + u < nc) ? v[u] : 0.0;
-      }
-      total += (double)(float)s;                            // P_w is an fp32 quantity
-    }
+  if (live && share < ws.W) {
+    const double* base = ws.Ppart + L.ppart_off + (int64_t)i * ws.rmax + k + (int64_t)share * ws.ppart_stride;
+    total = sum_partials(base, 4 * ws.ppart_stride, (int64_t)L.rows * ws.rmax, (ws.W - share + 3) >> 2, L.n_colchunks);
   }
   share_sum[share][slot] = total;
   __syncthreads();
@@ -323,51 +475,79 @@ __global__ __launch_bounds__(256) void psgd_pmean_kernel(const Ws ws) {
   }
 }
 
-// Sum over the threads of the orthogonalisation workgroup, same value for every thread.  `slot`
-// alternates between calls so that one barrier per call is enough.
+// Sums over the threads of the orthogonalisation workgroup of M values each, the same for every
+// thread.  `slot` alternates between calls so that one barrier per call is enough.
 // Only the first nwaves waves of the workgroup are still running (the others have left).
-__device__ __forceinline__ double block_sum_orth(double v, double (*red)[kOrthWaves], int& slot, int nwaves) {
-  v = wave_sum_d(v);
-  if (nwaves == 1) return v;
+template <int M>
+__device__ __forceinline__ void block_sum_orth(double (&v)[M], double (*red)[kOrthWaves][kMaxRank], int& slot, int nwaves) {
+#pragma unroll
+  for (int m = 0; m < M; ++m) v[m] = wave_sum_d(v[m]);
+  if (nwaves == 1) return;
   const int wave = threadIdx.x >> 6;
-  if ((threadIdx.x & 63) == 0) red[slot][wave] = v;
+  if ((threadIdx.x & 63) == 0) {
+#pragma unroll
+    for (int m = 0; m < M; ++m) red[slot][wave][m] = v[m];
+  }
   __syncthreads();
-  double r = 0.0;
-  for (int i = 0; i < nwaves; ++i) r += red[slot][i];
+  // every row of 16 lanes reads the (at most sixteen) waves' sums and adds them up by lane exchanges: one
+  // LDS round trip instead of one per wave
+  const int from = threadIdx.x & (kOrthWaves - 1);
+  static_assert(kOrthWaves == 16, "a row of lanes holds one sum per wave");
+#pragma unroll
+  for (int m = 0; m < M; ++m) v[m] = row_sum_d(from < nwaves ? red[slot][from][m] : 0.0);
   slot ^= 1;
-  return r;
 }
 
-// Modified Gram-Schmidt over the r columns of P_bar (in ws.Phat, fp32), in column order, in
+// Modified Gram-Schmidt of column K and what it takes from the columns after it: |v_K|^2 and the
+// products v_K . v_j come out of one reduction over the workgroup (r of them instead of r (r + 1) / 2:
+// the reductions, each a barrier, are what this kernel spends its time on).
+template <int R, int K, class SumF>
+__device__ __forceinline__ void orth_column(double (&v)[R], SumF sum) {
+  if constexpr (K < R) {
+    double s[R - K];
+#pragma unroll
+    for (int j = K; j < R; ++j) s[j - K] = v[K] * v[j];
+    sum(s);
+    const double nrm = sqrt(s[0]);
+    const bool some = nrm > 0.0;
+    v[K] = some ? v[K] / nrm : 0.0;
+#pragma unroll
+    for (int j = K + 1; j < R; ++j) v[j] = fma(some ? -(s[j - K] / nrm) : 0.0, v[K], v[j]);
+    orth_column<R, K + 1>(v, sum);
+  }
+}
+
+// Modified Gram-Schmidt over the r columns of P_bar (fp32), in column order, in
 // fp64; a column of zero length stays zero; P^ (fp32) replaces P_bar.  Layers of up to
 // kOrthThreads rows live in registers, one row per thread; taller ones in an fp64 copy in
-// global memory (each thread only ever touches its own rows).
+// global memory (each thread only ever touches its own rows).  P_bar is in ws.Phat, or -- Ws::pmean_in_orth,
+// layers of up to kOrthThreads rows -- summed up here from the partials (pbar: LDS).
 template <int R>
-__device__ void orth_layer(const Ws& ws, const LayerDev& L, double (*red)[kOrthWaves]) {
+__device__ void orth_layer(const Ws& ws, const LayerDev& L, double (*red)[kOrthWaves][kMaxRank], float* pbar) {
   const int n = L.rows;
   const int tid = threadIdx.x;
   float* ph = ws.Phat + L.p_off;
   int slot = 0;
   if (n <= kOrthThreads) {
+    if (ws.pmean_in_orth) {                                  // uniform
+      for (int x = tid; x < n * R; x += kOrthThreads) {
+        const double* src = ws.Ppart + L.ppart_off + (int64_t)(x / R) * ws.rmax + x % R;
+        pbar[x] = (float)(sum_partials(src, ws.ppart_stride, (int64_t)n * ws.rmax, ws.W, L.n_colchunks) / (double)ws.W);
+      }
+      __syncthreads();
+    }
     const int nwaves = (n + kWave - 1) / kWave;
     if (tid >= nwaves * kWave) return;                       // whole waves
     const bool holder = tid < n;
     double v[R];
+    if (ws.pmean_in_orth) {
 #pragma unroll
-    for (int k = 0; k < R; ++k) v[k] = holder ? (double)ph[(int64_t)tid * ws.rmax + k] : 0.0;
+      for (int k = 0; k < R; ++k) v[k] = holder ? (double)pbar[tid * R + k] : 0.0;
+    } else {
 #pragma unroll
-    for (int k = 0; k < R; ++k) {
-#pragma unroll
-      for (int j = 0; j < R; ++j) {
-        if (j < k) {
-          const double d = block_sum_orth(v[j] * v[k], red, slot, nwaves);
-          v[k] = fma(-d, v[j], v[k]);
-        }
-      }
-      const double nn = block_sum_orth(v[k] * v[k], red, slot, nwaves);
-      const double nrm = sqrt(nn);
-      v[k] = (nrm > 0.0) ? v[k] / nrm : 0.0;
+      for (int k = 0; k < R; ++k) v[k] = holder ? (double)ph[(int64_t)tid * ws.rmax + k] : 0.0;
     }
+    orth_column<R, 0>(v, [&](auto& s) { block_sum_orth(s, red, slot, nwaves); });
     if (holder) {
 #pragma unroll
       for (int k = 0; k < R; ++k) ph[(int64_t)tid * ws.rmax + k] = (float)v[k];
@@ -379,20 +559,20 @@ __device__ void orth_layer(const Ws& ws, const LayerDev& L, double (*red)[kOrthW
       for (int k = 0; k < R; ++k) pw[(int64_t)i * ws.rmax + k] = (double)ph[(int64_t)i * ws.rmax + k];
     for (int k = 0; k < R; ++k) {
       for (int j = 0; j < k; ++j) {
-        double d = 0.0;
+        double d[1] = {0.0};
         for (int i = tid; i < n; i += kOrthThreads)
-          d = fma(pw[(int64_t)i * ws.rmax + j], pw[(int64_t)i * ws.rmax + k], d);
-        d = block_sum_orth(d, red, slot, kOrthWaves);
+          d[0] = fma(pw[(int64_t)i * ws.rmax + j], pw[(int64_t)i * ws.rmax + k], d[0]);
+        block_sum_orth(d, red, slot, kOrthWaves);
         for (int i = tid; i < n; i += kOrthThreads)
-          pw[(int64_t)i * ws.rmax + k] = fma(-d, pw[(int64_t)i * ws.rmax + j], pw[(int64_t)i * ws.rmax + k]);
+          pw[(int64_t)i * ws.rmax + k] = fma(-d[0], pw[(int64_t)i * ws.rmax + j], pw[(int64_t)i * ws.rmax + k]);
       }
-      double nn = 0.0;
+      double nn[1] = {0.0};
       for (int i = tid; i < n; i += kOrthThreads) {
         const double x = pw[(int64_t)i * ws.rmax + k];
-        nn = fma(x, x, nn);
+        nn[0] = fma(x, x, nn[0]);
       }
-      nn = block_sum_orth(nn, red, slot, kOrthWaves);
-      const double nrm = sqrt(nn);
+      block_sum_orth(nn, red, slot, kOrthWaves);
+      const double nrm = sqrt(nn[0]);
       for (int i = tid; i < n; i += kOrthThreads) {
         const double x = (nrm > 0.0) ? pw[(int64_t)i * ws.rmax + k] / nrm : 0.0;
         pw[(int64_t)i * ws.rmax + k] = x;
@@ -403,30 +583,24 @@ __device__ void orth_layer(const Ws& ws, const LayerDev& L, double (*red)[kOrthW
 }
 
 __global__ __launch_bounds__(kOrthThreads) void psgd_orth_kernel(const Ws ws, const GradPtrs gp) {
-  __shared__ double red[2][kOrthWaves];
+  __shared__ double red[2][kOrthWaves][kMaxRank];
+  __shared__ float pbar[kOrthThreads * kMaxRank];
   // worker 0's first pass has added its gradient to A: the window is no longer fresh
   if (blockIdx.x == 0 && threadIdx.x == 0) *ws.a_fresh = 0u;
   if ((int)blockIdx.x >= ws.n_mat) {
-    // 1-D layers are sent raw: mean over workers in worker order
-    const FlatTile ft = ws.ftiles[ws.vectiles[blockIdx.x - ws.n_mat]];
-    const LayerDev& L = ws.layers[ft.layer];
-    for (int i = threadIdx.x; i < ft.count; i += kOrthThreads) {
-      const int64_t a = L.offset + ft.start + i;
-      double s = (double)gp.p[0][a];
-      for (int w = 1; w < ws.W; ++w) s += (double)gp.p[w][a];
-      ws.vecmean[L.vec_off + ft.start + i] = (float)(s / (double)ws.W);
-    }
+    vec_mean_tile(ws, gp, blockIdx.x - ws.n_mat);
     return;
   }
   const int li = ws.matlayers[blockIdx.x];
   const LayerDev& L = ws.layers[li];
-  const int r = L.rank[ws.level[li]];
+  const int level = ws.level[li];
+  const int r = level ? L.rank[1] : L.rank[0];
   if (threadIdx.x == 0) ws.rank_used[li] = r;
   switch (r) {
-    case 1: orth_layer<1>(ws, L, red); break;
-    case 2: orth_layer<2>(ws, L, red); break;
-    case 3: orth_layer<3>(ws, L, red); break;
-    default: orth_layer<4>(ws, L, red); break;
+    case 1: orth_layer<1>(ws, L, red, pbar); break;
+    case 2: orth_layer<2>(ws, L, red, pbar); break;
+    case 3: orth_layer<3>(ws, L, red, pbar); break;
+    default: orth_layer<4>(ws, L, red, pbar); break;
   }
 }
 
@@ -436,51 +610,56 @@ __global__ __launch_bounds__(kOrthThreads) void psgd_orth_kernel(const Ws ws, co
 // to a small fraction of its terms for the columns of P^ that the new gradient determines, and an
 // fp32 sum would lose those columns of Q (the oracle's contraction is fp64, rounded once).
 
-// Tile: kQRows rows x 256 columns, one workgroup of 4 waves; a wave owns rows wave, wave + 4, ...
+// Tile: ws.qrows rows x 256 columns, one workgroup of 4 waves; a wave owns rows wave, wave + 4, ...
 // and keeps the sums of its four columns per lane in registers; the four waves' sums meet in LDS.
-template <int R, bool V4>
-__device__ void q_tile(const Ws& ws, const LayerDev& L, const MatTile& t, const float* __restrict__ e,
-                       double* __restrict__ qpart, double (*red)[16][64], float (*ps)[kMaxRank]) {
+// Bound by memory, or by latency where few workgroups share the chip, like the first pass: the next batch of
+// rows is requested before the current one is used (ResNet-18 shapes 39.1 -> 33.0 us at W = 4, 16.0 -> 11.4 at
+// W = 1; 2 rows per batch: 2 us more per step at W = 4; 8: within 1 us, for 32 more registers).
+constexpr int kQBatch = 4;   // rows a wave requests together; two such batches are in flight
+
+template <int MODE>
+__device__ __forceinline__ void q_load(const float* __restrict__ e, int cols, int row_end, const LaneCols& lc, int i0,
+                                       float (&d)[kQBatch][4]) {
+#pragma unroll
+  for (int b = 0; b < kQBatch; ++b) {
+    const int i = i0 + 4 * b;                                // beyond the tile: one 16-byte address, see ef_load
+    load_row<MODE>(e + (int64_t)min(i, row_end - 1) * cols, i < row_end ? lc.c : 0, cols, d[b]);
+  }
+}
+
+template <int R, int MODE>
+__device__ __forceinline__ void q_loop(const Ws& ws, const LayerDev& L, const MatTile& t, const float* __restrict__ e,
+                                       double* __restrict__ qpart, double (*red)[16][64], const float (*ps)[kMaxRank],
+                                       const LaneCols& lc, int row_end, float (&cur)[kQBatch][4]) {
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  int col[4]; bool cm[4];
-  lane_cols<V4>(t.col0, lane, L.cols, col, cm);
-  // the tile's rows of P^ go to LDS
-  for (int s = threadIdx.x; s < kQRows * kMaxRank; s += 256) {
-    const int pr = s >> 2, pk = s & 3;
-    const int i = t.row0 + pr;
-    ps[pr][pk] = (i < L.rows && pk < R) ? ws.Phat[L.p_off + (int64_t)i * ws.rmax + pk] : 0.f;
-  }
-  __syncthreads();
   double acc[4][R];
 #pragma unroll
   for (int v = 0; v < 4; ++v)
 #pragma unroll
     for (int k = 0; k < R; ++k) acc[v][k] = 0.0;
-  const int row_end = min(t.row0 + kQRows, L.rows);
-  constexpr int B = 4;   // rows in flight per wave (2 and 8 are no faster)
-  for (int i0 = t.row0 + wave; i0 < row_end; i0 += 4 * B) {
-    float d[B][4];
+  for (int i0 = t.row0 + wave; i0 < row_end; i0 += 4 * kQBatch) {
+    float nxt[kQBatch][4];
+    q_load<MODE>(e, L.cols, row_end, lc, i0 + 4 * kQBatch, nxt);
 #pragma unroll
-    for (int b = 0; b < B; ++b) {
-      const int i = i0 + 4 * b;
-      if (i < row_end) load_row<V4>(e, L.offset + (int64_t)i * L.cols, col, cm, d[b]);
-    }
-#pragma unroll
-    for (int b = 0; b < B; ++b) {
+    for (int b = 0; b < kQBatch; ++b) {
       const int i = i0 + 4 * b;
       if (i < row_end) {                                     // wave-uniform
         double p[R], dd[4];
 #pragma unroll
         for (int k = 0; k < R; ++k) p[k] = (double)ps[i - t.row0][k];
 #pragma unroll
-        for (int v = 0; v < 4; ++v) dd[v] = (double)d[b][v];
+        for (int v = 0; v < 4; ++v) dd[v] = (double)cur[b][v];
 #pragma unroll
         for (int v = 0; v < 4; ++v)
 #pragma unroll
           for (int k = 0; k < R; ++k) acc[v][k] = fma(dd[v], p[k], acc[v][k]);
       }
     }
+#pragma unroll
+    for (int b = 0; b < kQBatch; ++b)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) cur[b][v] = nxt[b][v];
   }
   // the four waves' sums, in the fixed order (wave 0 + wave 2) + (wave 1 + wave 3)
   if (wave >= 2) {
@@ -504,12 +683,12 @@ __device__ void q_tile(const Ws& ws, const LayerDev& L, const MatTile& t, const 
       for (int k = 0; k < R; ++k) red[wave][v * R + k][lane] = acc[v][k];
   }
   __syncthreads();
-  // thread (wave, lane) finishes column slot v = wave of that lane
+  // thread (wave, lane) finishes column slot v = wave of that lane, if the lane owns it
   {
     const int v = wave;
-    const int cv = V4 ? t.col0 + lane * 4 + v : t.col0 + lane + 64 * v;
-    if (cv < L.cols) {
-      const int rb = t.row0 / kQRows;
+    const int cv = lc.c + v;
+    if (owns<MODE>(lc, v)) {
+      const int rb = t.row0 / ws.qrows;
       double* dst = qpart + L.qpart_off + ((int64_t)rb * L.cols + cv) * ws.rmax;
 #pragma unroll
       for (int k = 0; k < R; ++k) {
@@ -520,133 +699,128 @@ __device__ void q_tile(const Ws& ws, const LayerDev& L, const MatTile& t, const 
   }
 }
 
+template <int MODE>
+__device__ __forceinline__ void q_tile(const Ws& ws, const LayerDev& L, const MatTile& t, const float* __restrict__ e_w,
+                                       double* __restrict__ qpart, int level, double (*red)[16][64],
+                                       float (*ps)[kMaxRank]) {
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const LaneCols lc = lane_cols<MODE>(t.col0, lane, L.cols);
+  const float* __restrict__ e = e_w + L.offset;
+  const int row_end = min(t.row0 + ws.qrows, L.rows);
+  // the first rows of Delta and the tile's rows of P^ (for LDS) are requested together
+  float first[kQBatch][4];
+  q_load<MODE>(e, L.cols, row_end, lc, t.row0 + wave, first);
+  const int r = level ? L.rank[1] : L.rank[0];
+  for (int s = threadIdx.x; s < ws.qrows * kMaxRank; s += 256) {
+    const int pr = s >> 2, pk = s & 3;
+    const int i = t.row0 + pr;
+    ps[pr][pk] = (i < L.rows && pk < r) ? ws.Phat[L.p_off + (int64_t)i * ws.rmax + pk] : 0.f;
+  }
+  __syncthreads();
+  switch (r) {
+    case 1: q_loop<1, MODE>(ws, L, t, e, qpart, red, ps, lc, row_end, first); break;
+    case 2: q_loop<2, MODE>(ws, L, t, e, qpart, red, ps, lc, row_end, first); break;
+    case 3: q_loop<3, MODE>(ws, L, t, e, qpart, red, ps, lc, row_end, first); break;
+    default: q_loop<4, MODE>(ws, L, t, e, qpart, red, ps, lc, row_end, first); break;
+  }
+}
+
 __global__ __launch_bounds__(256) void psgd_q_kernel(const Ws ws, int w0) {
   __shared__ double red[2][16][64];
   __shared__ float ps[kQRows][kMaxRank];
-  const int w = w0 + blockIdx.y;
-  const MatTile t = ws.qmtiles[blockIdx.x];
+  // A memory larger than the Infinity Cache is taken from its end: what the first pass wrote last is
+  // still there.
+  const int bx = ws.q_reversed ? gridDim.x - 1 - blockIdx.x : blockIdx.x;
+  const int w = w0 + (ws.q_reversed ? gridDim.y - 1 - blockIdx.y : blockIdx.y);
+  const MatTile t = ws.qmtiles[bx];
   const LayerDev& L = ws.layers[t.layer];
-  const int r = L.rank[ws.level[t.layer]];
+  const int level = ws.level[t.layer];
   const float* __restrict__ e = ws.e + (int64_t)w * ws.e_stride;
   double* qpart = ws.Qpart + (int64_t)w * ws.qpart_stride;
-  if (L.vec4) {
-    switch (r) {
-      case 1: q_tile<1, true>(ws, L, t, e, qpart, red, ps); break;
-      case 2: q_tile<2, true>(ws, L, t, e, qpart, red, ps); break;
-      case 3: q_tile<3, true>(ws, L, t, e, qpart, red, ps); break;
-      default: q_tile<4, true>(ws, L, t, e, qpart, red, ps); break;
-    }
-  } else {
-    switch (r) {
-      case 1: q_tile<1, false>(ws, L, t, e, qpart, red, ps); break;
-      case 2: q_tile<2, false>(ws, L, t, e, qpart, red, ps); break;
-      case 3: q_tile<3, false>(ws, L, t, e, qpart, red, ps); break;
-      default: q_tile<4, false>(ws, L, t, e, qpart, red, ps); break;
-    }
+  switch (row_mode(L)) {
+    case kRowAligned: q_tile<kRowAligned>(ws, L, t, e, qpart, level, red, ps); break;
+    case kRowUnaligned: q_tile<kRowUnaligned>(ws, L, t, e, qpart, level, red, ps); break;
+    default: q_tile<kRowNarrow>(ws, L, t, e, qpart, level, red, ps); break;
   }
 }
 
 // ---- aggregate 1: Q_bar = mean over workers of (sum over row blocks) -------------------------
 
-// Q_bar[c][k] = fl32( (sum_w fl32(sum_rb partial[w][rb][c][k])) / W ), row blocks and workers in
-// index order; the partial sums of one worker are independent loads, issued eight at a time
-// (unconditionally, from clamped addresses, so that all eight are in flight together).
-template <int R, int U = 8>
-__device__ __forceinline__ void qmean_col(const Ws& ws, const LayerDev& L, int c) {
-  const double* base = ws.Qpart + L.qpart_off + (int64_t)c * ws.rmax;
-  const int64_t pstride = (int64_t)L.cols * ws.rmax;
-  const int nb = L.n_rowblocks;
-  double total[R];
-#pragma unroll
-  for (int k = 0; k < R; ++k) total[k] = 0.0;
-  for (int w = 0; w < ws.W; ++w) {
-    const double* src = base + (int64_t)w * ws.qpart_stride;
-    double s[R];
-#pragma unroll
-    for (int k = 0; k < R; ++k) s[k] = 0.0;
-    for (int b0 = 0; b0 < nb; b0 += U) {
-      double v[U][R];
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const double* q = src + (int64_t)min(b0 + u, nb - 1) * pstride;
-#pragma unroll
-        for (int k = 0; k < R; ++k) v[u][k] = q[k];
-      }
-#pragma unroll
-      for (int u = 0; u < U; ++u)
-#pragma unroll
-        for (int k = 0; k < R; ++k) s[k] += (b0 + u < nb) ? v[u][k] : 0.0;
-    }
-#pragma unroll
-    for (int k = 0; k < R; ++k) total[k] += (double)(float)s[k];   // Q_w is an fp32 quantity
-  }
-  float* dst = ws.Q + L.q_off + (int64_t)c * kMaxRank;    // rows of Q are kMaxRank floats apart
-#pragma unroll
-  for (int k = 0; k < R; ++k) dst[k] = (float)(total[k] / (double)ws.W);
-}
+// Q_bar[c][k] = fl32( (sum_w fl32(sum_rb partial[w][rb][c][k])) / W ).  One thread per entry, four per
+// column: a thread per column left a quarter of the workgroups and four times the loads to each.
+constexpr int kQmeanCols = 64;   // columns of a workgroup: kMatCols / kQmeanCols of them take a QTile
 
 __global__ __launch_bounds__(256) void psgd_qmean_kernel(const Ws ws) {
   const QTile t = ws.qtiles[blockIdx.x];
   const LayerDev& L = ws.layers[t.layer];
-  const int r = L.rank[ws.level[t.layer]];
-  const int c = t.col0 + threadIdx.x;
-  if (c >= L.cols) return;
-  switch (r) {
-    case 1: qmean_col<1>(ws, L, c); break;
-    case 2: qmean_col<2>(ws, L, c); break;
-    case 3: qmean_col<3>(ws, L, c); break;
-    default: qmean_col<4>(ws, L, c); break;
-  }
+  const int level = ws.level[t.layer];
+  const int r = level ? L.rank[1] : L.rank[0];
+  const int c = t.col0 + blockIdx.y * kQmeanCols + (threadIdx.x >> 2), k = threadIdx.x & 3;
+  if (c >= L.cols || k >= r) return;
+  const double sum = sum_partials(ws.Qpart + L.qpart_off + (int64_t)c * ws.rmax + k, ws.qpart_stride,
+                                  (int64_t)L.cols * ws.rmax, ws.W, L.n_rowblocks);
+  ws.Q[L.q_off + (int64_t)c * kMaxRank + k] = (float)(sum / (double)ws.W);   // rows of Q are kMaxRank floats apart
 }
 
 // ---- decompress: D = P^ Q_bar^T (the residual stays implicit) ----------------------------------
 
-// MODE 0: writes D of the tile to sink.out.  MODE 1: e = Delta - D in place.  MODE 2: D drives the
-// optimizer step on sink.wt / sink.vel and is not stored.
-template <int MODE, bool V4>
-__device__ void decomp_tile(const Ws& ws, const LayerDev& L, const MatTile& t, float* __restrict__ e,
-                            const Sink& sink, int r, float (*ps)[kMaxRank]) {
-  constexpr bool RESIDUAL = MODE == 1;
-  constexpr bool UPD = MODE == 2;
+// WHAT 0: writes D of the tile to sink.out.  1: e = Delta - D in place.  2: D drives the optimizer step
+// on sink.wt / sink.vel and is not stored.
+enum DecompWhat { kDecompStore = 0, kDecompResidual = 1, kDecompUpdate = 2 };
+
+template <int WHAT, int MODE>
+__device__ __forceinline__ void decomp_tile(const Ws& ws, const LayerDev& L, const MatTile& t, float* __restrict__ e,
+                                            const Sink& sink, int r, float (*ps)[kMaxRank]) {
+  constexpr bool RESIDUAL = WHAT == kDecompResidual;
+  constexpr bool UPD = WHAT == kDecompUpdate;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  int col[4]; bool cm[4];
-  lane_cols<V4>(t.col0, lane, L.cols, col, cm);
-  const int row_end = min(t.row0 + kMatRows, L.rows);
-  const float* __restrict__ ph = ws.Phat + L.p_off;
-  // the tile's 64 rows of P^ (zero-padded to four columns) go to LDS with one load per thread,
-  // requested together with Q's rows: the row loop then waits for no global load of its own
-  {
-    const int pr = threadIdx.x >> 2, pk = threadIdx.x & 3;
-    const int i = t.row0 + pr;
-    ps[pr][pk] = (i < row_end && pk < r) ? ph[(int64_t)i * ws.rmax + pk] : 0.f;
-  }
-  float q[4][kMaxRank];
-  load_q_rows(ws, L, col, cm, q);
-  __syncthreads();
+  const LaneCols lc = lane_cols<MODE>(t.col0, lane, L.cols);
+  const int cols = L.cols;
+  const int row_end = min(t.row0 + ws.mrows, L.rows);
   constexpr int B = 4;
   // Weights and velocity are read and written by every step, so they are accessed like the error
   // memory, not streamed like the gradients: where they fit the caches next to it (VGG-19 shapes,
   // W = 1) the fused update is 17 us faster that way, elsewhere it makes no difference.
   constexpr bool NT = false;
-  for (int i0 = t.row0 + wave; i0 < row_end; i0 += 4 * B) {
-    float d[B][4], vv[UPD ? B : 1][4];
-    if (RESIDUAL || UPD) {
+  constexpr bool IN = RESIDUAL || UPD;                     // the pass reads something per element
+  float* const src = (UPD ? sink.wt : e) + L.offset;       // not used when D is only stored
+  float* const vel = UPD ? sink.vel + L.offset : nullptr;
+  float* const out = IN ? nullptr : sink.out + L.offset;
+  // rows i0, i0 + 4, ...; beyond the tile one 16-byte address, see ef_load
+  auto request = [&](int i0, float (&d)[IN ? B : 1][4], float (&vv)[UPD ? B : 1][4]) {
+    if (IN) {
 #pragma unroll
       for (int b = 0; b < B; ++b) {
         const int i = i0 + 4 * b;
-        if (i < row_end) {
-          const int64_t rb = L.offset + (int64_t)i * L.cols;
-          load_row<V4, UPD && NT>(UPD ? sink.wt : e, rb, col, cm, d[b]);   // weights, velocity: once per step
-          if (UPD) load_row<V4, NT>(sink.vel, rb, col, cm, vv[UPD ? b : 0]);
-        }
+        const int64_t rb = (int64_t)min(i, row_end - 1) * cols;
+        const int c = i < row_end ? lc.c : 0;
+        load_row<MODE, UPD && NT>(src + rb, c, cols, d[IN ? b : 0]);
+        if (UPD) load_row<MODE, NT>(vel + rb, c, cols, vv[UPD ? b : 0]);
       }
     }
+  };
+  // requested together: the first rows, Q's rows, and the tile's rows of P^ (zero-padded to four columns,
+  // for LDS): the row loop then waits for no load but those of the rows ahead
+  float d[IN ? B : 1][4], vv[UPD ? B : 1][4];
+  request(t.row0 + wave, d, vv);
+  float q[4][kMaxRank];
+  load_q_rows<MODE>(ws, L, lc, q);
+  {
+    const int pr = threadIdx.x >> 2, pk = threadIdx.x & 3;
+    const float ph = ws.Phat[L.p_off + (int64_t)min(t.row0 + pr, L.rows - 1) * ws.rmax + min(pk, ws.rmax - 1)];
+    ps[pr][pk] = pk < r ? ph : 0.f;
+  }
+  __syncthreads();
+  for (int i0 = t.row0 + wave; i0 < row_end; i0 += 4 * B) {
+    float dn[IN ? B : 1][4], vn[UPD ? B : 1][4];
+    request(i0 + 4 * B, dn, vn);
 #pragma unroll
     for (int b = 0; b < B; ++b) {
       const int i = i0 + 4 * b;
       if (i < row_end) {
-        const int64_t rb = L.offset + (int64_t)i * L.cols;
+        const int64_t rb = (int64_t)i * cols;
         float p[kMaxRank];
 #pragma unroll
         for (int k = 0; k < kMaxRank; ++k) p[k] = ps[i - t.row0][k];
@@ -656,18 +830,36 @@ __device__ void decomp_tile(const Ws& ws, const LayerDev& L, const MatTile& t, f
         if (RESIDUAL) {
           float res[4];
 #pragma unroll
-          for (int v = 0; v < 4; ++v) res[v] = d[b][v] - D[v];
-          store_row<V4>(e, rb, col, cm, res);
+          for (int v = 0; v < 4; ++v) res[v] = d[IN ? b : 0][v] - D[v];
+          store_row<MODE>(src + rb, lc, res);
         } else if (UPD) {
 #pragma unroll
-          for (int v = 0; v < 4; ++v) nesterov(D[v], d[b][v], vv[UPD ? b : 0][v], sink.lr, sink.mu, sink.wd);
-          store_row<V4, NT>(sink.wt, rb, col, cm, d[b]);
-          store_row<V4, NT>(sink.vel, rb, col, cm, vv[UPD ? b : 0]);
+          for (int v = 0; v < 4; ++v) nesterov(D[v], d[IN ? b : 0][v], vv[UPD ? b : 0][v], sink.lr, sink.mu, sink.wd);
+          store_row<MODE, NT>(src + rb, lc, d[IN ? b : 0]);
+          store_row<MODE, NT>(vel + rb, lc, vv[UPD ? b : 0]);
         } else {
-          store_row<V4, kPsgdStreamOut>(sink.out, rb, col, cm, D);
+          store_row<MODE, kPsgdStreamOut>(out + rb, lc, D);
         }
       }
     }
+#pragma unroll
+    for (int b = 0; b < (IN ? B : 1); ++b)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) d[b][v] = IN ? dn[b][v] : 0.f;
+#pragma unroll
+    for (int b = 0; b < (UPD ? B : 1); ++b)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) vv[b][v] = UPD ? vn[b][v] : 0.f;
+  }
+}
+
+template <int WHAT>
+__device__ __forceinline__ void decomp_any(const Ws& ws, const LayerDev& L, const MatTile& t, float* __restrict__ e,
+                                           const Sink& sink, int r, float (*ps)[kMaxRank]) {
+  switch (row_mode(L)) {                                     // uniform over the workgroup
+    case kRowAligned: decomp_tile<WHAT, kRowAligned>(ws, L, t, e, sink, r, ps); break;
+    case kRowUnaligned: decomp_tile<WHAT, kRowUnaligned>(ws, L, t, e, sink, r, ps); break;
+    default: decomp_tile<WHAT, kRowNarrow>(ws, L, t, e, sink, r, ps); break;
   }
 }
 
@@ -702,8 +894,7 @@ __device__ __forceinline__ void decomp_body(const Ws& ws, const Sink& sink) {
   const MatTile t = ws.mtiles[blockIdx.x];
   const LayerDev& L = ws.layers[t.layer];
   const int r = ws.rank_used[t.layer];                     // written by the orthogonalisation of this step
-  if (L.vec4) decomp_tile<UPD ? 2 : 0, true>(ws, L, t, nullptr, sink, r, ps);
-  else decomp_tile<UPD ? 2 : 0, false>(ws, L, t, nullptr, sink, r, ps);
+  decomp_any<UPD ? kDecompUpdate : kDecompStore>(ws, L, t, nullptr, sink, r, ps);
 }
 
 __global__ __launch_bounds__(256) void psgd_decomp_kernel(const Ws ws, const Sink sink) {
@@ -727,8 +918,7 @@ __global__ __launch_bounds__(256) void psgd_residual_kernel(const Ws ws) {
   const int r = ws.rank_used[t.layer];
   const Sink none = {nullptr, nullptr, nullptr, 0.f, 0.f, 0.f};
   __shared__ float ps[kMatRows][kMaxRank];
-  if (L.vec4) decomp_tile<1, true>(ws, L, t, e, none, r, ps);
-  else decomp_tile<1, false>(ws, L, t, e, none, r, ps);
+  decomp_any<kDecompResidual>(ws, L, t, e, none, r, ps);
 }
 
 __global__ void psgd_clear_pending_kernel(const Ws ws) {

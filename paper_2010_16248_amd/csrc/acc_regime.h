@@ -28,7 +28,7 @@ __global__ __launch_bounds__(256) void norm_refresh_kernel(const Ws ws) {
     const int mt = (int)blockIdx.x - ws.n_ftiles;
     const MatTile t = ws.mtiles[mt];
     const LayerDev& L = ws.layers[t.layer];
-    const int rows = min(kMatRows, L.rows - t.row0), cols = min(kMatCols, L.cols - t.col0);
+    const int rows = min(ws.mrows, L.rows - t.row0), cols = min(kMatCols, L.cols - t.col0);
     for (int x = tid; x < rows * cols; x += kFlatThreads) {
       const float a = ws.A[L.offset + (int64_t)(t.row0 + x / cols) * L.cols + t.col0 + x % cols];
       s += (double)a * (double)a;
@@ -87,7 +87,7 @@ __device__ __forceinline__ double layer_sumsq(const Ws& ws, const LayerDev& L, i
   if (*ws.a_fresh != 0u) return 0.0;
   double s = 0.0;
   if (L.is_matrix) {
-    const int nmt = L.n_colchunks * ((L.rows + kMatRows - 1) / kMatRows);
+    const int nmt = L.n_colchunks * ((L.rows + ws.mrows - 1) / ws.mrows);
     for (int t = lane; t < nmt; t += kWave) s += ws.norm_part_m[L.mt0 + t];
   } else {
     for (int t = lane; t < L.ntiles; t += kWave) s += ws.norm_part[L.tile0 + t];

@@ -40,6 +40,8 @@ struct Plan {
   std::vector<int32_t> vectiles;
   std::vector<int32_t> matlayers;
   int32_t rmax = 0;
+  int32_t pmean_in_orth = 0, q_reversed = 0;   // PowerSGD: see Ws
+  int32_t mrows = kMatRows, qrows = kQRows;   // PowerSGD: rows of the two kinds of matrix tiles
   int64_t N = 0, e_stride = 0;
   int64_t q_total = 0;   // floats of Q in the caller's layout (rows of rmax floats)
   int64_t q_dev = 0;     // floats of Q on the device: every row padded to kMaxRank floats
@@ -62,7 +64,31 @@ int fail(char* buf, int code, const char* msg) {
   return code;
 }
 
-int make_plan(const acc_config* c, Plan& p, char* err) {
+// Rows of the matrix tiles.  A wave has a few rows in flight and waits for the first of them, so few tall
+// tiles leave the chip idle and many flat ones spend their time on their own start (a tile's rows of Q, the
+// sums of its columns).  First pass and decompression: 32 rows, 16 up to kFlatTileGroups workgroups (ResNet-18
+// shapes at W = 1, 1476 workgroups: a step 106 us at 32, 103 at 16; VGG-19 shapes at W = 1, 2626: 114.3 and 115.0;
+// ResNet-18 at W = 4: 172.8 at 32, 179 at 64).  Right product: 128 rows, fewer while that leaves compute units
+// without a workgroup (four small layers, 56 workgroups: a step 28.5 us at 128, 26.7 at 64, 26.9 at 32; ResNet-18
+// at W = 1, 356: 103.1 at 128, 104.9 at 64: twice the partial sums).
+constexpr int kComputeUnits = 256;
+constexpr int kFlatTileGroups = 8 * kComputeUnits;
+
+void choose_tiling(const acc_config* c, Plan& p) {
+  auto workgroups = [&](int rows) {
+    int64_t n = 0;
+    for (int i = 0; i < c->n_layers; ++i) {
+      const acc_layer& l = c->layers[i];
+      if (l.is_matrix) n += (int64_t)((l.cols + kMatCols - 1) / kMatCols) * ((l.rows + rows - 1) / rows);
+    }
+    return n * c->n_workers;
+  };
+  p.mrows = workgroups(32) <= kFlatTileGroups ? 16 : 32;
+  while (p.qrows > 32 && workgroups(p.qrows) < kComputeUnits) p.qrows /= 2;
+}
+
+// coarse: the tallest tiles, which need the least workspace.
+int make_plan_tiled(const acc_config* c, Plan& p, char* err, bool coarse) {
   if (!c) return fail(err, ACC_EINVAL, "config is NULL");
   if (c->method != ACC_POWERSGD && c->method != ACC_TOPK && c->method != ACC_BATCH)
     return fail(err, ACC_EINVAL, "unknown method");
@@ -109,7 +135,8 @@ int make_plan(const acc_config* c, Plan& p, char* err) {
   p.e_stride = align_up(p.N, 64);
   p.rmax = (c->method == ACC_POWERSGD) ? std::max(c->rank_crit, c->rank_noncrit) : 0;
   p.layers.resize(nl);
-  int64_t ntile = 0;
+  if (c->method == ACC_POWERSGD && !coarse) choose_tiling(c, p);
+  int64_t ntile = 0, pmean_most = 0;   // pmean_most: partial sums of P of one layer, all workers
   for (int i = 0; i < nl; ++i) {
     const acc_layer& l = c->layers[i];
     LayerDev& d = p.layers[i];
@@ -144,8 +171,8 @@ int make_plan(const acc_config* c, Plan& p, char* err) {
         d.rank[1] = std::max(1, std::min(c->rank_crit, cap));
         d.n_colchunks = (l.cols + kMatCols - 1) / kMatCols;
         d.mt0 = (int32_t)p.mtiles.size();
-        const int n_rb = (l.rows + kMatRows - 1) / kMatRows;
-        d.n_rowblocks = (l.rows + kQRows - 1) / kQRows;
+        const int n_rb = (l.rows + p.mrows - 1) / p.mrows;
+        d.n_rowblocks = (l.rows + p.qrows - 1) / p.qrows;
         d.q_off = p.q_dev;
         p.q_total += (int64_t)l.cols * p.rmax;
         p.q_dev += (int64_t)l.cols * kMaxRank;
@@ -157,23 +184,19 @@ int make_plan(const acc_config* c, Plan& p, char* err) {
         p.qpart_stride += (int64_t)d.n_rowblocks * l.cols * p.rmax;
         p.matlayers.push_back(i);
         for (int rb = 0; rb < d.n_rowblocks; ++rb)
-          for (int cc = 0; cc < d.n_colchunks; ++cc) p.qmtiles.push_back(MatTile{i, rb * kQRows, cc * kMatCols, 0});
+          for (int cc = 0; cc < d.n_colchunks; ++cc) p.qmtiles.push_back(MatTile{i, rb * p.qrows, cc * kMatCols, 0});
         for (int rb = 0; rb < n_rb; ++rb)
           for (int cc = 0; cc < d.n_colchunks; ++cc) {
             MatTile mt;
             mt.layer = i;
-            mt.row0 = rb * kMatRows;
+            mt.row0 = rb * p.mrows;
             mt.col0 = cc * kMatCols;
             mt.pad = 0;
             p.mtiles.push_back(mt);
           }
         for (int r0 = 0; r0 < l.rows; r0 += kPmeanRows) p.ptiles.push_back(PTile{i, r0});
-        for (int cc = 0; cc < d.n_colchunks; ++cc) {
-          QTile qt;
-          qt.layer = i;
-          qt.col0 = cc * kMatCols;
-          p.qtiles.push_back(qt);
-        }
+        for (int cc = 0; cc < d.n_colchunks; ++cc) p.qtiles.push_back(QTile{i, cc * kMatCols});
+        pmean_most = std::max(pmean_most, l.rows > kOrthThreads ? INT64_MAX : (int64_t)l.rows * p.rmax * d.n_colchunks * c->n_workers);
       } else {
         d.vec_off = p.vec_total;
         p.vec_total += n;
@@ -190,6 +213,14 @@ int make_plan(const acc_config* c, Plan& p, char* err) {
       p.pay_stride += std::max(d.k[0], d.k[1]);
     }
   }
+  // The orthogonalisation's one workgroup per layer sums the partials of P itself while that is at most 36
+  // loads per thread (ResNet-18 shapes at W = 1: a step 102.0 us, 103.9 with the sums in a launch of their own;
+  // a layer of 47 loads per thread: 119.3 and 116.4; 144, ResNet-18 at W = 4: 199 and 173).
+  p.pmean_in_orth = pmean_most <= (int64_t)kOrthThreads * 36 ? 1 : 0;
+  // The right product takes the tiles from the last to the first when the error memory is larger than what the
+  // 256 MB Infinity Cache still holds of it: VGG-19 shapes at W = 8 (658 MB) 571 -> 549 us per step, LSTM set at
+  // W = 4 (820 MB) 1095 -> 1075; ResNet-18 at W = 4 (179 MB, all of it there) 172.8 -> 175.5, so not below.
+  p.q_reversed = 4 * p.e_stride * c->n_workers > (int64_t(224) << 20) ? 1 : 0;
   p.q_stride = 4 * ntile + nl;
 
   // workspace layout, 256-byte aligned regions
@@ -252,6 +283,17 @@ int make_plan(const acc_config* c, Plan& p, char* err) {
     reg(p.r_tpending, 4);
   }
   p.total_bytes = off;
+  return ACC_OK;
+}
+
+// Flatter tiles than the coarse ones need a little more workspace (tile tables, partial sums of Q): a
+// configuration that fits the static workspace only with the coarse ones gets those.
+int make_plan(const acc_config* c, Plan& p, char* err) {
+  const int rc = make_plan_tiled(c, p, err, false);
+  if (rc != ACC_OK || c->method != ACC_POWERSGD || p.total_bytes <= (int64_t)ACC_STATIC_WORKSPACE_BYTES) return rc;
+  Plan coarse;
+  if (make_plan_tiled(c, coarse, err, true) == ACC_OK && coarse.total_bytes <= (int64_t)ACC_STATIC_WORKSPACE_BYTES)
+    p = std::move(coarse);
   return ACC_OK;
 }
 
@@ -479,8 +521,9 @@ int launch_phase0(acc_ctx* c, int w0, int nw) {
 int launch_agg0(acc_ctx* c) {
   const Ws& ws = c->ws;
   if (c->cfg.method == ACC_POWERSGD) {
-    if (ws.n_ptiles > 0) ACC_LAUNCH(c, psgd_pmean_kernel, dim3(ws.n_ptiles), dim3(256), ws);
-    const int gx = ws.n_mat + ws.n_vectiles;
+    // the mean of the 1-D layers rides with the first of the two launches
+    if (!ws.pmean_in_orth) ACC_LAUNCH(c, psgd_pmean_kernel, dim3(ws.n_ptiles + ws.n_vectiles), dim3(256), ws, c->grads);
+    const int gx = ws.n_mat + (ws.pmean_in_orth ? ws.n_vectiles : 0);
     if (gx > 0) ACC_LAUNCH(c, psgd_orth_kernel, dim3(gx), dim3(kOrthThreads), ws, c->grads);
   }
   return ACC_OK;
@@ -494,7 +537,7 @@ int launch_phase1(acc_ctx* c, int w0, int nw) {
 
 int launch_agg1(acc_ctx* c) {
   const Ws& ws = c->ws;
-  if (ws.n_qtiles > 0) ACC_LAUNCH(c, psgd_qmean_kernel, dim3(ws.n_qtiles), dim3(256), ws);
+  if (ws.n_qtiles > 0) ACC_LAUNCH(c, psgd_qmean_kernel, dim3(ws.n_qtiles, kMatCols / kQmeanCols), dim3(256), ws);
   return ACC_OK;
 }
 
@@ -711,6 +754,10 @@ static int32_t init_common(const acc_config* cfg, void* workspace_dev, size_t wo
   ws.W = cfg->n_workers;
   ws.L = cfg->n_layers;
   ws.rmax = p.rmax;
+  ws.mrows = p.mrows;
+  ws.pmean_in_orth = p.pmean_in_orth;
+  ws.q_reversed = p.q_reversed;
+  ws.qrows = p.qrows;
   ws.n_ftiles = (int32_t)p.ftiles.size();
   ws.n_t2slots = (int32_t)p.n_t2slots;
   ws.n_mtiles = (int32_t)p.mtiles.size();

@@ -323,3 +323,69 @@ def test_call_by_call_equals_step_all_and_is_deterministic():
         for a, b in zip(outs, results[0][0]):
             H.assert_bits_equal(a, b, "decompressed mean")
         assert np.array_equal(st, results[0][1])
+
+
+EDGE_SHAPES = [(r, c, 1) for r, c in ((1, 1), (15, 2), (17, 3), (33, 4), (16, 5), (65, 6), (5, 7), (31, 63), (129, 255),
+                                      (16, 256), (17, 257), (33, 259), (3, 513))] + [(1, 1031, 0)]
+
+
+@pytest.mark.parametrize("name,shapes,W", [
+    # 16-row tiles, 32-row tiles of the right product, P summed up in the orthogonalisation
+    ("few_tiles", EDGE_SHAPES, 2),
+    # 16-row tiles, 128-row tiles of the right product, P summed up by its own launch
+    ("more_tiles", EDGE_SHAPES + [(700, 1300, 1)], 8),
+    # 32-row tiles, a layer too tall for the registers, a memory beyond the Infinity Cache (tiles in reverse order)
+    ("many_tiles", EDGE_SHAPES + [(1030, 1999, 1)], 30),
+])
+def test_tilings_and_unaligned_rows(name, shapes, W):
+    """Rows of 1 to 3, of exactly 4 and of a ragged number of columns, starting on no 16-byte boundary, under each of
+    the tilings, against the oracle; and the deferred residual against the explicit one, bit for bit."""
+    print("case tilings", name, flush=True)
+    layers = wl.make_layers(shapes)
+    lt = H.layer_tuples(layers)
+    N = wl.total_params(layers)
+    rng = np.random.default_rng(len(shapes) + W)
+    q0 = rng.standard_normal(sum(c for (_, r, c, m) in lt if m) * 4).astype(np.float32)
+
+    def batch():
+        return [(rng.standard_normal(N, dtype=np.float32) * np.float32(0.01)) for _ in range(W)]
+
+    gpu, ora = H.make_pair(B.ACC_POWERSGD, layers, W, 4, 3, 100, 0.5, 1, q0)
+    grads = batch()
+    _forced_step(gpu, ora, grads, name)
+    twin = B.Accordion(B.ACC_POWERSGD, lt, W, 4, 3, 100, 0.5, 1, q0)
+    twin.set_state(gpu.get_state())
+    dev, outs = [H.to_dev(g) for g in batch()], []
+    for acc, flush in ((gpu, False), (twin, True)):
+        for step in range(2):
+            out = H.dev_out(N)
+            acc.step_all(dev, out)
+            if flush:
+                acc.flush()
+        acc.detect_regime(0.1, 0.1)
+        outs.append((out.cpu().numpy(), acc.get_state(), acc.get_norms()[1]))
+    H.assert_bits_equal(outs[0][0], outs[1][0], f"{name}: D")
+    assert np.array_equal(outs[0][1], outs[1][1]), f"{name}: state"
+    assert np.array_equal(outs[0][2], outs[1][2]), f"{name}: norms"
+    # the window summed: the step against the oracle and two more of one batch
+    total = ora.A.astype(np.float64) + 2.0 * dev[0].cpu().numpy().astype(np.float64)
+    for li, (off, rows, cols, _) in enumerate(lt):
+        ref = np.linalg.norm(total[off:off + rows * cols])
+        assert abs(outs[0][2][li] - ref) <= 1e-6 * ref, f"{name}: norm of layer {li}"
+    gpu.destroy()
+    twin.destroy()
+
+
+def test_a_configuration_at_the_limit_of_the_static_workspace_keeps_its_tiles():
+    """Flatter tiles need a little more workspace; what fits the static array with the tallest tiles only gets those."""
+    print("case static workspace limit", flush=True)
+    layers = [(0, 100, 15100, 1)]
+    q0 = np.random.default_rng(0).standard_normal(15100 * 4).astype(np.float32)
+    cfg, keep = B.make_config(B.ACC_POWERSGD, layers, 4, 4, 1)
+    assert (31 << 20) < B.accordion_workspace_bytes(cfg) <= 32 << 20
+    gpu = B.Accordion(B.ACC_POWERSGD, layers, 4, 4, 1, q_init=q0, static_workspace=True)
+    ora = orc.AccordionOracle(B.ACC_POWERSGD, layers, 4, 4, 1, 100, 0.5, 1, q0)
+    for step in range(2):
+        rng = np.random.default_rng(step)
+        _forced_step(gpu, ora, [rng.standard_normal(1510000).astype(np.float32) for _ in range(4)], f"step {step}")
+    gpu.destroy()
