@@ -10,13 +10,10 @@ constexpr int kFlatThreads = 256;        // workgroup of every flat-tile kernel
 constexpr int kTile = 8192;              // elements per flat tile (power of two)
 constexpr int kTileShift = 13;
 constexpr int kT2Group = 16;             // TopK: consecutive tiles of a layer that add their level-2 counts into one slot
-constexpr int kQuadIters = (kTile / 4 + 1 + kFlatThreads - 1) / kFlatThreads;  // 9
 constexpr int kMatRows = 64;             // matrix tile: up to 64 rows (Ws::mrows) x 256 columns
 constexpr int kMatCols = 256;
 constexpr int kQRows = 128;              // most rows of a tile of the right product Q = Delta^T P^ (Ws::qrows)
 constexpr int kHistBins = 2048;          // 11 key bits per radix level
-// a wave quarter has at most ceil((kTile / 4 + 1) / 4) 16-byte groups: iterations of 64 lanes
-constexpr int kSpanIters = ((kTile / 4 + 1 + 3) / 4 + kWave - 1) / kWave;   // 9
 constexpr int kMaxW = 32;
 constexpr int kMaxRank = 4;
 
@@ -286,13 +283,46 @@ __device__ __forceinline__ double row_sum_d(double v) {
   return v;
 }
 
-// ---- masked 16-byte access on a flat buffer ---------------------------------------
-// base is a multiple of 4 (elements) and the buffer is 16-byte aligned; elements outside
-// [lo, hi) are neither read nor written.
+// ---- 16-byte access on a flat buffer -----------------------------------------------
+// A group is four consecutive elements.  Layers start anywhere in the flat buffers, and this part's
+// 16-byte accesses need 4-byte alignment only, so the groups of a tile are counted from its first
+// element and every group is whole but the last one of a layer whose size is no multiple of four.
+// (Counted from the 16-byte boundary before the tile, every tile of a layer that starts off one needed
+// a mask per element in every pass.)
+typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
 
+__device__ __forceinline__ float4 ld16(const float* p) {
+  const f4u v = *reinterpret_cast<const f4u*>(p);
+  return make_float4(v.x, v.y, v.z, v.w);
+}
+__device__ __forceinline__ void st16(float* p, const float4& v) {
+  f4u t;
+  t.x = v.x; t.y = v.y; t.z = v.z; t.w = v.w;
+  *reinterpret_cast<f4u*>(p) = t;
+}
+
+// Streaming ("non-temporal") access: for data that this step reads or writes once and no
+// later kernel of the step touches (the gradients coming in, the averaged gradient and the payload
+// going out), so that it does not push the error memory out of the caches or sit there dirty
+// until the kernel ends.
+__device__ __forceinline__ float4 ld16_stream(const float* p) {
+  const f4u v = __builtin_nontemporal_load(reinterpret_cast<const f4u*>(p));
+  return make_float4(v.x, v.y, v.z, v.w);
+}
+__device__ __forceinline__ void st16_stream(float* p, const float4& v) {
+  f4u t;
+  t.x = v.x; t.y = v.y; t.z = v.z; t.w = v.w;
+  __builtin_nontemporal_store(t, reinterpret_cast<f4u*>(p));
+}
+
+// Two arms of a branch that access the same addresses with and without the streaming hint are merged by
+// the compiler into one access (which loses the hint) unless something in one of them differs.
+__device__ __forceinline__ void keep_apart() { asm volatile(""); }
+
+// Masked access: elements outside [lo, hi) are neither read (they count as zero) nor written.
 __device__ __forceinline__ float4 ld_quad(const float* __restrict__ p, int64_t base, int64_t lo,
                                           int64_t hi) {
-  if (base >= lo && base + 4 <= hi) return *reinterpret_cast<const float4*>(p + base);
+  if (base >= lo && base + 4 <= hi) return ld16(p + base);
   float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
   if (base + 0 >= lo && base + 0 < hi) v.x = p[base + 0];
   if (base + 1 >= lo && base + 1 < hi) v.y = p[base + 1];
@@ -304,7 +334,7 @@ __device__ __forceinline__ float4 ld_quad(const float* __restrict__ p, int64_t b
 __device__ __forceinline__ void st_quad(float* __restrict__ p, int64_t base, int64_t lo, int64_t hi,
                                         float4 v) {
   if (base >= lo && base + 4 <= hi) {
-    *reinterpret_cast<float4*>(p + base) = v;
+    st16(p + base, v);
     return;
   }
   if (base + 0 >= lo && base + 0 < hi) p[base + 0] = v.x;
@@ -313,29 +343,14 @@ __device__ __forceinline__ void st_quad(float* __restrict__ p, int64_t base, int
   if (base + 3 >= lo && base + 3 < hi) p[base + 3] = v.w;
 }
 
-// Streaming ("non-temporal") 16-byte access: for data that this step reads or writes once and no
-// later kernel of the step touches (the gradients coming in, the averaged gradient and the payload
-// going out), so that it does not push the error memory out of the caches or sit there dirty
-// until the kernel ends.
-typedef float f4v __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ float4 ld16_stream(const float* p) {
-  const f4v v = __builtin_nontemporal_load(reinterpret_cast<const f4v*>(p));
-  return make_float4(v.x, v.y, v.z, v.w);
-}
-__device__ __forceinline__ void st16_stream(float* p, const float4& v) {
-  f4v t;
-  t.x = v.x; t.y = v.y; t.z = v.z; t.w = v.w;
-  __builtin_nontemporal_store(t, reinterpret_cast<f4v*>(p));
-}
-
-// Access to 16-byte group q of a tile.  AL (a workgroup-uniform property of the tile): the tile
-// starts on a 16-byte boundary and holds a whole number of groups, so no element needs a mask.
+// Access to group q of a tile.  AL (a workgroup-uniform property of the tile): it holds a whole number
+// of groups, so no element needs a mask.
 // STREAM: non-temporal access on the mask-free path (the masked path is rare and stays plain).
 template <bool AL, bool STREAM = false>
 __device__ __forceinline__ float4 ldq(const float* __restrict__ p, int64_t a0, int64_t lo, int64_t hi,
                                       int q, bool in) {
   if (!in) return make_float4(0.f, 0.f, 0.f, 0.f);
-  if (AL) return STREAM ? ld16_stream(p + a0 + 4 * (int64_t)q) : *reinterpret_cast<const float4*>(p + a0 + 4 * (int64_t)q);
+  if (AL) return STREAM ? ld16_stream(p + a0 + 4 * (int64_t)q) : ld16(p + a0 + 4 * (int64_t)q);
   return ld_quad(p, a0 + 4 * (int64_t)q, lo, hi);
 }
 
@@ -344,7 +359,7 @@ __device__ __forceinline__ float4 ldq(const float* __restrict__ p, int64_t a0, i
 // the predicated load costs four moves of zeros and a branch around the load.
 template <bool STREAM = false>
 __device__ __forceinline__ float4 ldq_clamped(const float* __restrict__ p, int64_t a0, int q) {
-  return STREAM ? ld16_stream(p + a0 + 4 * (int64_t)q) : *reinterpret_cast<const float4*>(p + a0 + 4 * (int64_t)q);
+  return STREAM ? ld16_stream(p + a0 + 4 * (int64_t)q) : ld16(p + a0 + 4 * (int64_t)q);
 }
 
 template <bool AL, bool STREAM = false>
@@ -352,7 +367,7 @@ __device__ __forceinline__ void stq(float* __restrict__ p, int64_t a0, int64_t l
                                     float4 v) {
   if (AL) {
     if (STREAM) st16_stream(p + a0 + 4 * (int64_t)q, v);
-    else *reinterpret_cast<float4*>(p + a0 + 4 * (int64_t)q) = v;
+    else st16(p + a0 + 4 * (int64_t)q, v);
   } else {
     st_quad(p, a0 + 4 * (int64_t)q, lo, hi, v);
   }
@@ -394,18 +409,18 @@ __device__ __forceinline__ float comp(const float4& v, int c) {
 // Geometry of one flat tile in absolute element indices.
 struct TileGeom {
   int64_t lo, hi;   // the tile's elements: [lo, hi)
-  int64_t a0;       // lo rounded down to a multiple of 4
-  int32_t nquads;   // 16-byte groups that intersect [lo, hi)
-  bool aligned;     // lo and hi are multiples of 4: every group is whole
+  int64_t a0;       // first element of group 0: lo
+  int32_t nquads;   // groups of four
+  bool aligned;     // every group is whole
 };
 
 __device__ __forceinline__ TileGeom tile_geom(const LayerDev& L, const FlatTile& t) {
   TileGeom g;
   g.lo = L.offset + t.start;
   g.hi = g.lo + t.count;
-  g.a0 = g.lo & ~int64_t(3);
-  g.nquads = (int32_t)((g.hi - g.a0 + 3) >> 2);
-  g.aligned = ((g.lo | g.hi) & 3) == 0;
+  g.a0 = g.lo;
+  g.nquads = (t.count + 3) >> 2;
+  g.aligned = (t.count & 3) == 0;
   return g;
 }
 

@@ -57,18 +57,12 @@ constexpr bool kPsgdStreamG = true;     // gradients: read once per step
 constexpr bool kPsgdStreamA = true;     // accumulator: read and written once per step
 constexpr bool kPsgdStreamOut = true;   // averaged gradient: written once, read by nobody here
 
-typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
-
 // The lane's four elements of a row, loaded whatever the lane owns (every address lies inside the row);
 // row: the row's first element.  STREAM: non-temporal.
 template <int MODE, bool STREAM = false>
 __device__ __forceinline__ void load_row(const float* __restrict__ row, int c, int cols, float (&d)[4]) {
-  if (MODE == kRowAligned) {
-    const float4 t = STREAM ? ld16_stream(row + c) : *reinterpret_cast<const float4*>(row + c);
-    d[0] = t.x; d[1] = t.y; d[2] = t.z; d[3] = t.w;
-  } else if (MODE == kRowUnaligned) {
-    const f4u* q = reinterpret_cast<const f4u*>(row + c);
-    const f4u t = STREAM ? __builtin_nontemporal_load(q) : *q;
+  if (MODE != kRowNarrow) {
+    const float4 t = STREAM ? ld16_stream(row + c) : ld16(row + c);
     d[0] = t.x; d[1] = t.y; d[2] = t.z; d[3] = t.w;
   } else {
 #pragma unroll
@@ -83,13 +77,11 @@ __device__ __forceinline__ void store_row(float* __restrict__ row, const LaneCol
   if (MODE == kRowAligned) {
     if (lc.own0 == 0) {
       if (STREAM) st16_stream(row + lc.c, make_float4(d[0], d[1], d[2], d[3]));
-      else *reinterpret_cast<float4*>(row + lc.c) = make_float4(d[0], d[1], d[2], d[3]);
+      else st16(row + lc.c, make_float4(d[0], d[1], d[2], d[3]));
     }
   } else if (MODE == kRowUnaligned) {
     if (lc.own0 == 0) {
-      f4u t;
-      t.x = d[0]; t.y = d[1]; t.z = d[2]; t.w = d[3];
-      *reinterpret_cast<f4u*>(row + lc.c) = t;
+      st16(row + lc.c, make_float4(d[0], d[1], d[2], d[3]));
     } else {
 #pragma unroll
       for (int v = 1; v < 4; ++v)

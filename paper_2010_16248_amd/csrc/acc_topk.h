@@ -1765,8 +1765,10 @@ __device__ __forceinline__ void compact_mean_tile(const Ws& ws, const FlatTile& 
       const int q = span.qbeg + (c * G + j) * kWave + lane;
       if (UPD) {                                           // the group's weights and velocity
         if (sink.stream_wv) {                               // uniform: see stream_wv() on the host side
+          keep_apart();
           wq[j] = ld_span<AL, true>(sink.wt, tg, span, q);
           vq[j] = ld_span<AL, true>(sink.vel, tg, span, q);
+          keep_apart();
         } else {
           wq[j] = ld_span<AL>(sink.wt, tg, span, q);
           vq[j] = ld_span<AL>(sink.vel, tg, span, q);
@@ -1779,8 +1781,10 @@ __device__ __forceinline__ void compact_mean_tile(const Ws& ws, const FlatTile& 
         if (UPD) {
           nesterov4(v, wq[j], vq[j], sink);
           if (sink.stream_wv) {
+            keep_apart();
             stq<AL, true>(sink.wt, tg.a0, tg.lo, tg.hi, q, wq[j]);
             stq<AL, true>(sink.vel, tg.a0, tg.lo, tg.hi, q, vq[j]);
+            keep_apart();
           } else {
             stq<AL>(sink.wt, tg.a0, tg.lo, tg.hi, q, wq[j]);
             stq<AL>(sink.vel, tg.a0, tg.lo, tg.hi, q, vq[j]);
@@ -1802,8 +1806,8 @@ __device__ __forceinline__ void compact_mean_tile(const Ws& ws, const FlatTile& 
 // LDS, workers in order from +0; the sums, divided by W, go out as the quarter's part of the
 // averaged gradient.  acc: the wave's kQuarterFloats floats of LDS.
 constexpr int kGatherChunks = 4;                            // 64-entry chunks of a candidate list requested together (2 to 8: within 2 us)
-constexpr int kQuarterGroups = (kTile / 4 + 1 + 3) / 4;     // 513: 16-byte groups of a wave quarter at most
-constexpr int kQuarterFloats = 4 * kQuarterGroups + 12;     // rounded up to whole 64-byte rows
+constexpr int kQuarterGroups = kTile / 16;                  // groups of a wave quarter at most
+constexpr int kQuarterFloats = 4 * kQuarterGroups;
 constexpr int kPayRing = 128;                               // a wave's payload ring in LDS: entries (indices, then values)
 
 template <bool AL, bool UPD>
@@ -1970,8 +1974,10 @@ __device__ __forceinline__ void gather_mean_tile(const Ws& ws, const FlatTile& f
     float4 wq = make_float4(0.f, 0.f, 0.f, 0.f), vq = wq;
     if (UPD) {
       if (sink.stream_wv) {                                 // uniform: see stream_wv() on the host side
+        keep_apart();
         wq = ld_span<AL, true>(sink.wt, tg, span, q);
         vq = ld_span<AL, true>(sink.vel, tg, span, q);
+        keep_apart();
       } else {
         wq = ld_span<AL>(sink.wt, tg, span, q);
         vq = ld_span<AL>(sink.vel, tg, span, q);
@@ -1984,8 +1990,10 @@ __device__ __forceinline__ void gather_mean_tile(const Ws& ws, const FlatTile& f
       if (UPD) {
         nesterov4(v, wq, vq, sink);
         if (sink.stream_wv) {
+          keep_apart();
           stq<AL, true>(sink.wt, tg.a0, tg.lo, tg.hi, q, wq);
           stq<AL, true>(sink.vel, tg.a0, tg.lo, tg.hi, q, vq);
+          keep_apart();
         } else {
           stq<AL>(sink.wt, tg.a0, tg.lo, tg.hi, q, wq);
           stq<AL>(sink.vel, tg.a0, tg.lo, tg.hi, q, vq);

@@ -569,3 +569,29 @@ def test_state_machine_errors_come_from_the_host():
     assert np.all(out.cpu().numpy()[:20] == 1.0)         # k = 20 of 40 equal entries: first 20
     assert np.all(out.cpu().numpy()[20:] == 0.0)
     gpu.destroy()
+
+
+@pytest.mark.parametrize("pad", [0, 1, 2, 3])
+def test_layers_that_start_and_end_anywhere(pad):
+    """Every remainder of a layer's size by four, below, at and above the size of a tile, each starting at every
+    remainder too (layers that do not start on a 16-byte boundary): the last group of a layer is the only
+    partial one.  TopK and the batch-size mode."""
+    print(f"case start and end, pad {pad}", flush=True)
+    sizes = [pad] * (pad > 0) + [1, 2, 3, 5, 8190, 8191, 8192, 8193, 8195, 2 * 8192 - 1, 2 * 8192 + 2, 3 * 8192 + 3]
+    layers = wl.make_layers([(1, n, 0) for n in sizes])
+    N, W = wl.total_params(layers), 2
+    rng = np.random.default_rng(40 + pad)
+    gpu, ora = H.make_pair(B.ACC_TOPK, layers, W, 10, 1)
+    bat = B.Accordion(B.ACC_BATCH, H.layer_tuples(layers), W, 1, 1, 100, 0.5, 0, None, batch_multiplier=2)
+    out, total = H.dev_out(N), None
+    for step in range(4):
+        grads = [rng.standard_normal(N).astype(np.float32) for _ in range(W)]
+        _check_step(gpu, ora, grads, f"pad {pad} step {step}", check_state=step % 2 == 1)
+        bat.step_all([H.to_dev(g) for g in grads], out)
+        if step % 2 == 0:
+            total = grads
+        else:
+            sums = [t + g for t, g in zip(total, grads)]
+            H.assert_bits_equal(out.cpu().numpy(), (sums[0] + sums[1]) / np.float32(4.0), f"pad {pad} step {step}: batch")
+    gpu.destroy()
+    bat.destroy()
