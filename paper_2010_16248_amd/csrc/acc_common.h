@@ -192,30 +192,37 @@ __device__ __forceinline__ double wave_sum_d(double v) {
   return (readlane_d(v, 0) + readlane_d(v, 16)) + (readlane_d(v, 32) + readlane_d(v, 48));
 }
 
+template <int CTRL, int ROW_MASK = 0xf>
+__device__ __forceinline__ uint32_t dpp_u(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROW_MASK, 0xf, false);
+}
+
+// Inclusive prefix sum over lanes 0..lane (lane exchanges through DPP moves, no LDS traffic).  All 64
+// lanes must be active.
+__device__ __forceinline__ uint32_t wave_incl_scan_u32(uint32_t v) {
+  v += dpp_u<0x111>(v);        // row_shr 1, 2, 4, 8: inside the rows of 16 lanes
+  v += dpp_u<0x112>(v);
+  v += dpp_u<0x114>(v);
+  v += dpp_u<0x118>(v);
+  v += dpp_u<0x142, 0xa>(v);   // row_bcast15: rows 1 and 3 take the row before
+  v += dpp_u<0x143, 0xc>(v);   // row_bcast31: rows 2 and 3 take the first two
+  return v;
+}
+
+// Sum over each row of 16 lanes, returned to all its lanes.
+__device__ __forceinline__ uint32_t row_sum_u32(uint32_t v) {
+  v += dpp_u<0xB1>(v);
+  v += dpp_u<0x4E>(v);
+  v += dpp_u<0x141>(v);
+  v += dpp_u<0x140>(v);
+  return v;
+}
+
+// Sum over the 64 lanes, the same value for every lane.  All 64 lanes must be active.
 __device__ __forceinline__ uint32_t wave_sum_u32(uint32_t v) {
-#pragma unroll
-  for (int d = 1; d < kWave; d <<= 1) v += (uint32_t)__shfl_xor((int)v, d, kWave);
-  return v;
-}
-
-// Inclusive prefix sum over lanes 0..lane.
-__device__ __forceinline__ uint32_t wave_incl_scan_u32(uint32_t v, int lane) {
-#pragma unroll
-  for (int d = 1; d < kWave; d <<= 1) {
-    uint32_t y = (uint32_t)__shfl_up((int)v, d, kWave);
-    if (lane >= d) v += y;
-  }
-  return v;
-}
-
-// Inclusive suffix sum over lanes lane..63.
-__device__ __forceinline__ uint32_t wave_incl_suffix_u32(uint32_t v, int lane) {
-#pragma unroll
-  for (int d = 1; d < kWave; d <<= 1) {
-    uint32_t y = (uint32_t)__shfl_down((int)v, d, kWave);
-    if (lane + d < kWave) v += y;
-  }
-  return v;
+  v = row_sum_u32(v);
+  return ((uint32_t)__builtin_amdgcn_readlane((int)v, 0) + (uint32_t)__builtin_amdgcn_readlane((int)v, 16)) +
+         ((uint32_t)__builtin_amdgcn_readlane((int)v, 32) + (uint32_t)__builtin_amdgcn_readlane((int)v, 48));
 }
 
 // Lane mask of a predicate, taken straight from the compare (no round trip through a register

@@ -102,37 +102,71 @@ __device__ __forceinline__ void hist_add(uint32_t* hist, bool valid_not_bin0, ui
   if (valid_not_bin0) atomicAdd(&hist[bin], 1u);
 }
 
-// hist: kHistBins counts in LDS.  Finds the largest bin b with count(bins >= b) >= k.
-// Result in out[0..2] (LDS): bin, entries above the bin, entries in the bin.  Every thread of
-// the workgroup calls it (two barriers); threads 0..255 own eight bins each.
-__device__ __forceinline__ void pick_bin(const uint32_t* hist, uint32_t k, uint32_t* out,
-                                         uint32_t* scratch) {
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int wave = tid >> 6;
-  const bool owner = tid < 256;
-  uint32_t h[8];
-  uint32_t part = 0;
-#pragma unroll
-  for (int i = 0; i < 8; ++i) { h[i] = owner ? hist[tid * 8 + i] : 0u; part += h[i]; }
-  const uint32_t suf = wave_incl_suffix_u32(part, lane);
-  if (owner && lane == 0) scratch[wave] = suf;   // wave total
-  if (tid < 3) out[tid] = 0;
-  __syncthreads();
-  if (owner) {
-    uint32_t run = suf - part;                   // entries in bins of later threads of my wave
-    for (int v = wave + 1; v < 4; ++v) run += scratch[v];
-#pragma unroll
-    for (int i = 7; i >= 0; --i) {
-      if (run < k && run + h[i] >= k) {
-        out[0] = (uint32_t)(tid * 8 + i);
-        out[1] = run;
-        out[2] = h[i];
-      }
-      run += h[i];
-    }
+// ---- finding the bin of the k-th largest --------------------------------------------------------
+// The largest bin b with count(bins >= b) >= k, the entries above it and the entries in it (all zero if
+// there is none).  The decision kernels run one workgroup per layer and wait for their own barriers and
+// lane exchanges, so a histogram that fits a wave is searched by every wave on its own (no barrier), and a
+// larger one with two.
+struct Pick { uint32_t bin, above, count; };
+
+__device__ __forceinline__ Pick pick_from_lanes(bool found, uint32_t bin, uint32_t above, uint32_t count) {
+  const uint64_t m = ballot64(found);
+  Pick p = {0u, 0u, 0u};
+  if (m != 0) {                                              // wave-uniform
+    const int src = __builtin_ctzll(m);
+    p.bin = (uint32_t)__builtin_amdgcn_readlane((int)bin, src);
+    p.above = (uint32_t)__builtin_amdgcn_readlane((int)above, src);
+    p.count = (uint32_t)__builtin_amdgcn_readlane((int)count, src);
   }
+  return p;
+}
+
+// 64 bins: lane b holds bin b's count.
+__device__ __forceinline__ Pick wave_pick64(uint32_t c, uint32_t k, int lane) {
+  const uint32_t incl = wave_incl_scan_u32(c);
+  const uint32_t above = (uint32_t)__builtin_amdgcn_readlane((int)incl, kWave - 1) - incl;
+  return pick_from_lanes(above < k && above + c >= k, (uint32_t)lane, above, c);
+}
+
+// 256 bins in LDS (16-byte aligned).
+__device__ __forceinline__ Pick wave_pick256(const uint32_t* hist, uint32_t k, int lane) {
+  const uint4 c = reinterpret_cast<const uint4*>(hist)[lane];
+  const uint32_t part = (c.x + c.y) + (c.z + c.w);
+  const uint32_t incl = wave_incl_scan_u32(part);
+  uint32_t run = (uint32_t)__builtin_amdgcn_readlane((int)incl, kWave - 1) - incl;
+  const uint32_t h[4] = {c.x, c.y, c.z, c.w};
+  uint32_t bin = 0u, above = 0u, count = 0u;
+  bool found = false;
+#pragma unroll
+  for (int i = 3; i >= 0; --i) {
+    if (run < k && run + h[i] >= k) { found = true; bin = 4u * (uint32_t)lane + i; above = run; count = h[i]; }
+    run += h[i];
+  }
+  return pick_from_lanes(found, bin, above, count);
+}
+
+// kHistBins bins, thread t of the workgroup of kPickThreads holds bins 2t (h0) and 2t + 1 (h1).
+// block_above: entries in the bins of later threads and, in total, of all; wtot: kPickWaves words of LDS.
+// Every thread calls it (one barrier).
+__device__ __forceinline__ uint32_t block_above(uint32_t h0, uint32_t h1, uint32_t* wtot, uint32_t& total) {
+  const int lane = threadIdx.x & 63;
+  const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t incl = wave_incl_scan_u32(h0 + h1);
+  const uint32_t mine = (uint32_t)__builtin_amdgcn_readlane((int)incl, kWave - 1);
+  if (lane == 0) wtot[wave] = mine;
   __syncthreads();
+  static_assert(kPickWaves == 16, "a row of lanes reads one total per wave");
+  const uint32_t t = wtot[lane & 15];
+  total = row_sum_u32(t);
+  return row_sum_u32((uint32_t)(lane & 15) > wave ? t : 0u) + (mine - incl);
+}
+
+// out[0..2] = the Pick of k (LDS words that hold zeros; the caller's barrier follows).
+__device__ __forceinline__ void block_find(uint32_t above, uint32_t h0, uint32_t h1, uint32_t k, uint32_t* out) {
+  const uint32_t b = 2u * threadIdx.x;
+  if (above < k && above + h1 >= k) { out[0] = b + 1u; out[1] = above; out[2] = h1; }
+  const uint32_t above0 = above + h1;
+  if (above0 < k && above0 + h0 >= k) { out[0] = b; out[1] = above0; out[2] = h0; }
 }
 
 // ---- wave quarters --------------------------------------------------------------------------
@@ -715,13 +749,16 @@ __device__ __forceinline__ uint32_t for_quarter_keys(const Ws& ws, const LayerDe
   return above;
 }
 
-// A layer of a single tile, decided by one workgroup from Delta: the keys go to LDS, three
-// histogram levels (11 + 11 + 9 bits) give the threshold, and the counts of its four quarters
-// give their payload positions.
+// A layer of a single tile, decided by one workgroup from Delta: its keys stay in registers (two groups
+// of four per thread), three histogram levels (11 + 11 + 9 bits, an LDS array each, cleared together) give
+// the threshold, and the counts of its four quarters give their payload positions.
+// lds: 3 * kHistBins + kPickWaves + 16 words.
+constexpr int kSmallLds = 3 * kHistBins + kPickWaves + 16;
+
 __device__ __forceinline__ void pick_small_layer(const Ws& ws, const LayerDev& L, int w, int li, uint32_t k,
-                                                 uint32_t* hist, uint32_t* skeys, uint32_t* out,
-                                                 uint32_t* scratch, uint32_t* qcnt) {
+                                                 uint32_t* lds) {
   const int tid = threadIdx.x;
+  const int lane = tid & 63;
   FlatTile ft;
   ft.layer = li;
   ft.start = 0;
@@ -729,50 +766,63 @@ __device__ __forceinline__ void pick_small_layer(const Ws& ws, const LayerDev& L
   ft.qslot0 = 0;
   const TileGeom tg = tile_geom(L, ft);
   const float* __restrict__ e = ws.e + (int64_t)w * ws.e_stride;
-  const int count = ft.count;
-  const int head = (int)(tg.lo - tg.a0);                   // elements of the first group before the tile
-  for (int q = tid; q < tg.nquads; q += kPickThreads) {
-    const float4 d = ld_quad(e, tg.a0 + 4 * (int64_t)q, tg.lo, tg.hi);
+  static_assert(kTile / 4 == 2 * kPickThreads, "two groups per thread");
+  uint32_t key[2][4];
+  bool valid[2][4];
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const int i = 4 * q + c - head;
-      if (i >= 0 && i < count) skeys[i] = key_of(comp(d, c));
-    }
+  for (int j = 0; j < 2; ++j) {
+    const int q = tid + j * kPickThreads;
+    float4 d = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (q < tg.nquads) d = ld_quad(e, tg.a0 + 4 * (int64_t)q, tg.lo, tg.hi);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) { key[j][c] = key_of(comp(d, c)); valid[j][c] = 4 * q + c < ft.count; }
   }
-  for (int b = tid; b < kHistBins; b += kPickThreads) hist[b] = 0u;
-  if (tid < 8) qcnt[tid] = 0u;
+  uint32_t* const wtot = lds + 3 * kHistBins;
+  uint32_t* const out = wtot + kPickWaves;                   // 3 x 3 words, then the four quarters' counts
+  uint32_t* const qcnt = out + 9;
+  for (int b = tid; b < kSmallLds; b += kPickThreads) lds[b] = 0u;
   __syncthreads();
-  for (int i = tid; i < count; i += kPickThreads) atomicAdd(&hist[skeys[i] >> 20], 1u);
-  __syncthreads();
-  pick_bin(hist, k, out, scratch);
-  const uint32_t b1 = out[0], need2 = k - out[1];
-  __syncthreads();
-  for (int b = tid; b < kHistBins; b += kPickThreads) hist[b] = 0u;
-  __syncthreads();
-  for (int i = tid; i < count; i += kPickThreads) {
-    const uint32_t key = skeys[i];
-    if ((key >> 20) == b1) atomicAdd(&hist[(key >> 9) & 0x7ffu], 1u);
+  uint32_t need = k, prefix = 0u, count_in = 0u;
+  // levels: key bits 30..20, 19..9, 8..0
+#pragma unroll
+  for (int lev = 0; lev < 3; ++lev) {
+    uint32_t* const hist = lds + lev * kHistBins;
+    const int shift = lev == 0 ? 20 : (lev == 1 ? 9 : 0);
+    const uint32_t mask = lev == 2 ? 0x1ffu : 0x7ffu;
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const bool in = valid[j][c] && (lev == 0 || (key[j][c] >> (lev == 1 ? 20 : 9)) == prefix);
+        if (in) atomicAdd(&hist[(key[j][c] >> shift) & mask], 1u);
+      }
+    __syncthreads();
+    const uint32_t h0 = hist[2 * tid], h1 = hist[2 * tid + 1];
+    uint32_t total;
+    const uint32_t above = block_above(h0, h1, wtot, total);
+    block_find(above, h0, h1, need, out + 3 * lev);
+    __syncthreads();
+    const uint32_t bin = out[3 * lev];
+    prefix = lev == 0 ? bin : (prefix << (lev == 1 ? 11 : 9)) | bin;
+    need -= out[3 * lev + 1];
+    count_in = out[3 * lev + 2];
   }
-  __syncthreads();
-  pick_bin(hist, need2, out, scratch);
-  const uint32_t b12 = (b1 << 11) | out[0], need3 = need2 - out[1];
-  __syncthreads();
-  for (int b = tid; b < kHistBins; b += kPickThreads) hist[b] = 0u;
-  __syncthreads();
-  for (int i = tid; i < count; i += kPickThreads) {
-    const uint32_t key = skeys[i];
-    if ((key >> 9) == b12) atomicAdd(&hist[key & 0x1ffu], 1u);
-  }
-  __syncthreads();
-  pick_bin(hist, need3, out, scratch);
-  const uint32_t T = (b12 << 9) | out[0];
-  const uint32_t ktie = need3 - out[1];
-  const uint32_t alleq = (ktie == out[2]) ? 1u : 0u;
-  // counts of the four wave quarters the compaction kernel will use
+  const uint32_t T = prefix, ktie = need;
+  const uint32_t alleq = (ktie == count_in) ? 1u : 0u;
+  // counts of the four wave quarters the compaction kernel will use: entries above T | equal to T << 16
   const int qw = (tg.nquads + 3) >> 2;
-  for (int i = tid; i < count; i += kPickThreads) {
-    const uint32_t key = skeys[i];
-    if (key >= T) atomicAdd(&qcnt[(key > T ? 0 : 4) + ((i + head) >> 2) / qw], 1u);
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    uint32_t n = 0u;
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+      if (valid[j][c]) n += (key[j][c] > T ? 1u : 0u) + (key[j][c] == T ? 0x10000u : 0u);
+    const int qd = (tid + j * kPickThreads) / qw;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const uint32_t sum = wave_sum_u32(qd == v ? n : 0u);
+      if (lane == 0 && sum != 0u) atomicAdd(&qcnt[v], sum);
+    }
   }
   __syncthreads();
   if (tid == 0) {
@@ -781,8 +831,8 @@ __device__ __forceinline__ void pick_small_layer(const Ws& ws, const LayerDev& L
     for (int v = 0; v < 4; ++v) {
       ws.gtpre[qbase + v] = g;
       ws.eqpre[qbase + v] = q;
-      g += qcnt[v];
-      q += qcnt[4 + v];
+      g += qcnt[v] & 0xffffu;
+      q += qcnt[v] >> 16;
     }
     ws.gtpre[qbase + 4] = g;
     ws.eqpre[qbase + 4] = q;
@@ -791,9 +841,18 @@ __device__ __forceinline__ void pick_small_layer(const Ws& ws, const LayerDev& L
   }
 }
 
+// One workgroup per (worker, layer), bound by latency: two round trips to memory and, where each of the three
+// histograms was searched in LDS with its own barriers (thirteen in all), those barriers: 9.0 us per step on
+// ResNet-18 shapes at any W.  A thread keeps its two bins of the level-1 histogram in registers, both levels'
+// thresholds are looked up in one scan, and the level-2 search is one wave's: three barriers, 5.2 us.
 __global__ __launch_bounds__(kPickThreads) void topk_pick12_kernel(const Ws ws, int w0) {
-  __shared__ uint32_t hist[kHistBins];
-  __shared__ uint32_t out[3], scratch[4];
+  // a thread sums four adjacent level-2 counts (one 16-byte load) of every kStripes-th slot
+  constexpr int kCols4 = kSub2 / 4;
+  constexpr int kStripes = kPickThreads / kCols4;           // slots summed side by side
+  static_assert(kSub2 % 4 == 0 && kStripes >= 1, "four counts per load");
+  __shared__ uint4 sub[kStripes][kCols4];
+  __shared__ uint32_t wtot[kPickWaves];
+  __shared__ uint32_t out[6];                               // the Pick of k, then of the other level's k
   const int li = blockIdx.x;
   const int w = w0 + blockIdx.y;
   const int tid = threadIdx.x;
@@ -812,8 +871,8 @@ __global__ __launch_bounds__(kPickThreads) void topk_pick12_kernel(const Ws ws, 
   const uint32_t l_cols = ld_here(reinterpret_cast<const uint32_t*>(&Lp->cols));
   const uint32_t lvl_v = ld_here(reinterpret_cast<const uint32_t*>(ws.level + li));
   const uint32_t guess0 = ld_here(ws.guess + wl * 2), guess1 = ld_here(ws.guess + wl * 2 + 1);
-  uint32_t* gh = ws.hist1 + wl * kHistBins;
-  uint32_t h0 = ld_here(gh + tid), h1 = ld_here(gh + tid + kPickThreads);
+  uint2* gh = reinterpret_cast<uint2*>(ws.hist1 + wl * kHistBins) + tid;
+  uint32_t h0 = ld_here(&gh->x), h1 = ld_here(&gh->y);      // bins 2 tid and 2 tid + 1
   const int L_ntiles = (int)rfl(l_ntiles), L_t2slot0 = (int)rfl(l_t2slot0);
   const uint32_t n_layer = rfl(l_rows) * rfl(l_cols);
   const int lv = (int)rfl(lvl_v);
@@ -822,12 +881,6 @@ __global__ __launch_bounds__(kPickThreads) void topk_pick12_kernel(const Ws ws, 
   if (w == 0 && li == 0 && tid == 0) *ws.a_fresh = 0u;
   if (L_ntiles == 1) return;                               // decided by the last pick kernel, from Delta
   SelState* sp = ws.sel + wl;
-  __shared__ uint32_t sub[kSub2];
-  __shared__ uint32_t nb0;
-  // a thread sums four adjacent counts (one 16-byte load) of every kStripes-th slot
-  constexpr int kCols4 = kSub2 / 4;
-  constexpr int kStripes = kPickThreads / kCols4;           // slots summed side by side
-  static_assert(kSub2 % 4 == 0 && kStripes >= 1, "four counts per load");
   const int col4 = tid % kCols4, stripe = tid / kCols4;
   uint4* t2 = reinterpret_cast<uint4*>(ws.t2 + ((int64_t)w * ws.n_t2slots + L_t2slot0) * kSub2) + col4;
   const int nslots = (L_ntiles + kT2Group - 1) / kT2Group;
@@ -847,49 +900,47 @@ __global__ __launch_bounds__(kPickThreads) void topk_pick12_kernel(const Ws ws, 
     }
   }
   const uint32_t guess = rfl(lv ? guess1 : guess0);
-  gh[tid] = 0u;
-  gh[tid + kPickThreads] = 0u;
-  hist[tid] = h0;
-  hist[tid + kPickThreads] = h1;
-  if (tid < kSub2) sub[tid] = 0u;
-  if (tid == 0) nb0 = 0u;
-  __syncthreads();
-  if (s2.x) atomicAdd(&sub[4 * col4 + 0], s2.x);
-  if (s2.y) atomicAdd(&sub[4 * col4 + 1], s2.y);
-  if (s2.z) atomicAdd(&sub[4 * col4 + 2], s2.z);
-  if (s2.w) atomicAdd(&sub[4 * col4 + 3], s2.w);
-  {
-    // bin 0 (exact zeros and the smallest denormals) was not histogrammed: the rest of the layer
-    const uint32_t part = wave_sum_u32(h0 + h1 - (tid == 0 ? h0 : 0u));
-    if (lane == 0 && part) atomicAdd(&nb0, part);
-  }
-  __syncthreads();
-  if (tid == 0) hist[0] = n_layer - nb0;
-  __syncthreads();
-  pick_bin(hist, k, out, scratch);
-  const uint32_t b1 = out[0], need2 = k - out[1];
+  *gh = make_uint2(0u, 0u);
+  if (stripe < kStripes) sub[stripe][col4] = s2;
+  if (tid < 6) out[tid] = 0u;
+  uint32_t total;
+  const uint32_t above = block_above(h0, h1, wtot, total);
+  // bin 0 (exact zeros and the smallest denormals) was not histogrammed: the rest of the layer
+  const uint32_t bin0 = n_layer - total;
+  if (tid == 0) h0 = bin0;
+  block_find(above, h0, h1, k, out);
   // The other level's guess, from the same histogram: the bin its k-th largest key would lie in
   // in this step's Delta.  It serves the first step after a level switch, when the level's own
   // history is stale (or missing); after that the threshold is followed as usual.
-  if (k_other != k) {                                      // uniform over the workgroup
-    __syncthreads();                                       // everybody has read out[]
-    pick_bin(hist, k_other, out, scratch);
-    if (tid == 0) {
-      const uint32_t bo = out[0];
-      // (the memory will adapt to the new level for some steps: a wide guess)
-      ws.guess[wl * 2 + (1 - lv)] = (bo == 0u) ? kGuessZero
-          : make_guess((int)bo - kGuessMovingBelow, guess_bins_for(k_other, n_layer));
-    }
-    __syncthreads();
-  }
+  if (k_other != k) block_find(above, h0, h1, k_other, out + 3);
+  __syncthreads();
+  if (tid >= kWave) return;                                  // the rest is one wave's work
+  const uint32_t b1 = out[0], need2 = k - out[1], bo = out[3];
   const bool guessed = guess != kNoGuess && guess != kGuessZero;
   const uint32_t glo = guessed ? guess_lo(guess) : 0u;     // the bins pass A counted: glo .. glo + nb - 1
   const bool hit = guessed && b1 >= glo && b1 - glo < guess_nb(guess);
   // bin 0 guessed and found: pass A listed every non-zero entry and counted the zeros (mode 2)
   const bool zhit = guess == kGuessZero && b1 == 0u;
   const uint32_t side = hit ? b1 - glo : 0u;
-  if (tid == 0) {
-    sp->b1 = b1; sp->need2 = need2; sp->k = k; sp->side = side; sp->zeros = 0u; sp->bin0 = hist[0];
+  // level 2: the summed counts of bin b1
+  uint32_t c = 0u;
+#pragma unroll
+  for (int st = 0; st < kStripes; ++st) c += reinterpret_cast<const uint32_t*>(&sub[st][0])[side * kL2Bins + lane];
+  uint32_t zeros = 0u;
+  if (zhit) {
+    // the counts are those of the non-zero keys of bin 0; the rest of bin 0 are exact zeros, which
+    // belong to level-2 bin 0
+    zeros = bin0 - min(wave_sum_u32(c), bin0);
+    if (lane == 0) c += zeros;
+  }
+  const Pick p2 = wave_pick64(c, need2, lane);
+  if (lane == 0) {
+    if (k_other != k) {
+      // (the memory will adapt to the new level for some steps: a wide guess)
+      ws.guess[wl * 2 + (1 - lv)] = (bo == 0u) ? kGuessZero
+          : make_guess((int)bo - kGuessMovingBelow, guess_bins_for(k_other, n_layer));
+    }
+    sp->b1 = b1; sp->need2 = need2; sp->k = k; sp->side = side; sp->zeros = zeros; sp->bin0 = bin0;
     sp->mode = hit ? 0u : (zhit ? 2u : 1u);
     // the candidate lists of this layer cannot serve the compaction (a miss, or a band, which does
     // not list what lies above it): it reads Delta instead.  (Bin 0 guessed and found: the lists
@@ -897,42 +948,13 @@ __global__ __launch_bounds__(kPickThreads) void topk_pick12_kernel(const Ws ws, 
     if ((!hit && !zhit) || (guessed && guess_nb(guess) < (uint32_t)kGuessBins))
       atomicOr(&ws.lflag[li], 1u);                         // cleared by the next step's first pass
     if (!hit && !zhit) atomicAdd(&ws.stats[0], 1ull);      // layers re-staged (diagnostic counter)
-  }
-  if (zhit) {
-    // level-2 counts of the non-zero keys of bin 0 (summed over the tiles above); the rest of
-    // bin 0 are exact zeros, which belong to level-2 bin 0
-    __shared__ uint32_t zeros_s;
-    if (tid == 0) {
-      uint32_t nnz0 = 0;
-      for (int b = 0; b < kL2Bins; ++b) nnz0 += sub[b];
-      zeros_s = hist[0] - min(nnz0, hist[0]);
-      sp->zeros = zeros_s;
+    if (hit || zhit) {
+      sp->b2 = p2.bin;
+      sp->need3 = need2 - p2.above;                        // still needed from bin (b1, b2)
     }
-    __syncthreads();
-    for (int b = tid; b < kHistBins; b += kPickThreads)
-      hist[b] = (b < kL2Bins) ? sub[b] + (b == 0 ? zeros_s : 0u) : 0u;
-    __syncthreads();
-    pick_bin(hist, need2, out, scratch);
-    if (tid == 0) {
-      sp->b2 = out[0];
-      sp->need3 = need2 - out[1];
-    }
-    return;
   }
-  if (!hit) {
-    // its keys get staged tile by tile, with their level-2 counts added up here
-    if (tid < kL2Bins) ws.hist2m[wl * kL2Bins + tid] = 0u;
-    return;
-  }
-  __syncthreads();
-  // level 2: the summed counts of bin b1 (a threshold in bin 0 never gets here)
-  for (int b = tid; b < kHistBins; b += kPickThreads) hist[b] = (b < kL2Bins) ? sub[side * kL2Bins + b] : 0u;
-  __syncthreads();
-  pick_bin(hist, need2, out, scratch);
-  if (tid == 0) {
-    sp->b2 = out[0];
-    sp->need3 = need2 - out[1];                            // still needed from bin (b1, b2)
-  }
+  // a missed layer's keys get staged tile by tile, with their level-2 counts added up here
+  if (!hit && !zhit) ws.hist2m[wl * kL2Bins + lane] = 0u;
 }
 
 // A workgroup takes kCountTiles consecutive tiles, a wave one quarter of each; everything the tiles
@@ -1015,8 +1037,8 @@ __global__ __launch_bounds__(256) void topk_count3_kernel(const Ws ws, int w0) {
 }
 
 // Two sizes of the last pick kernel: kLdsList keys of bin (b1, b2) of a layer gathered in LDS
-// (packed), kLdsQuarters quarters of a layer whose counts are kept in LDS.  The small one (60 KB
-// of LDS) takes the layers up to 6.3 M entries; the layers beyond that go to the big one (152 KB,
+// (packed), kLdsQuarters quarters of a layer whose counts are kept in LDS.  The small one (54 KB
+// of LDS) takes the layers up to 6.3 M entries; the layers beyond that go to the big one (145 KB,
 // one workgroup per compute unit; launched only for models that have such a layer), which
 // serves up to 25 M entries from LDS.  Larger layers, or more keys around the threshold, work
 // from device memory (slower, same results).
@@ -1025,13 +1047,16 @@ constexpr int kLdsListBig = 24576, kLdsQuartersBig = 12288;
 static_assert(2 * kLdsQuarters <= kLdsList && 2 * kLdsQuartersBig <= kLdsListBig,
               "the prefixes of a layer are staged in the key list");
 
+// Bound by latency like the first pick kernel: the state a workgroup needs is requested together at the top,
+// levels 3 and 4 have a histogram each, cleared there, that every wave searches on its own, and the counts
+// of single-tile layers come from registers (ResNet-18 shapes 12.5 -> 9.0 us at W = 4, K = 10 %, 16.7 -> 8.4 at K = 99 %).
 template <int kLdsList, int kLdsQuarters, bool BIG>
 __device__ __forceinline__ void pick3_body(const Ws& ws, int w0, uint32_t step_id) {
-  __shared__ uint32_t hist[kHistBins];
+  __shared__ __attribute__((aligned(16))) uint32_t hist3[256];
+  __shared__ uint32_t hist4[kL2Bins];
   __shared__ uint32_t llist[kLdsList];
   // per quarter (2048 entries): entries above T | listed keys equal to T << 12 | exact zeros << 17
   __shared__ uint32_t lcnt[kLdsQuarters];
-  __shared__ uint32_t out[3], scratch[4];
   __shared__ uint32_t wsum[2][kPickWaves];
   __shared__ uint32_t flag, lcount;
   const int li = blockIdx.x;
@@ -1039,20 +1064,26 @@ __device__ __forceinline__ void pick3_body(const Ws& ws, int w0, uint32_t step_i
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int64_t wl = (int64_t)w * ws.L + li;
+  SelState* sp = ws.sel + wl;
+  // requested together: the selection's state (what thread 0 needs at the very end too)
+  const uint32_t s_b1 = ld_here(&sp->b1), s_b2 = ld_here(&sp->b2), s_need2 = ld_here(&sp->need2), s_need3 = ld_here(&sp->need3),
+                 s_zeros = ld_here(&sp->zeros), s_mode = ld_here(&sp->mode), s_bin0 = ld_here(&sp->bin0),
+                 s_fresh = ld_here(&sp->fresh_nnz);
+  const uint32_t* bh = reinterpret_cast<const uint32_t*>(ws.b1hist + wl * 2);
+  const uint32_t bh00 = ld_here(bh), bh01 = ld_here(bh + 1), bh10 = ld_here(bh + 2), bh11 = ld_here(bh + 3);
+  const int lv = (int)rfl(ld_here(reinterpret_cast<const uint32_t*>(ws.level + li)));
   const LayerDev& L = ws.layers[li];
   if (L.ntiles == 1) {
     // A layer of a single tile needs none of the passes in between: its workgroup, idle otherwise,
     // decides it here from Delta (in the first pick kernel, where this used to happen, these layers
     // were the ones that kernel waited for: 3 us of every step).
-    static_assert(kLdsList >= kTile && 2 * kPickWaves >= 8, "the key list holds a tile's keys");
-    if (!BIG) pick_small_layer(ws, L, w, li, (uint32_t)L.k[ws.level[li]], hist, llist, out, scratch, &wsum[0][0]);
+    static_assert(kLdsList >= kSmallLds, "the key list holds the histograms of a single tile");
+    if (!BIG) pick_small_layer(ws, L, w, li, (uint32_t)L.k[lv], llist);
     return;
   }
   const int nq = 4 * L.ntiles;
   if (BIG != (nq > acc::kLdsQuarters)) return;             // the other instantiation's layer
-  const int64_t wl = (int64_t)w * ws.L + li;
-  SelState* sp = ws.sel + wl;
-  const int lv = ws.level[li];
   const int64_t qbase = (int64_t)w * ws.q_stride + L.qoff;
   // gtq: per quarter, the entries above bin (b1, b2); eqq: the number of keys inside (b1, b2), of
   // which the first kQListCap are listed.  Thread t owns a contiguous chunk of quarters.
@@ -1062,31 +1093,27 @@ __device__ __forceinline__ void pick3_body(const Ws& ws, int w0, uint32_t step_i
   const uint4* qlist4 = reinterpret_cast<const uint4*>(ws.qlist + qbase * kQListCap);
   const int chunk = (nq + kPickThreads - 1) / kPickThreads;
   const int q_lo = min(tid * chunk, nq), q_hi = min(q_lo + chunk, nq);
-  if (tid == 0) { flag = 0u; lcount = 0u; }
-  // requested now, used by thread 0 at the very end (the guess for the next step)
-  const uint2 prev_hist = ws.b1hist[wl * 2 + lv];
-  const uint32_t b1 = sp->b1, zeros = sp->zeros, mode = sp->mode;
-  uint32_t b2 = sp->b2;
-  uint32_t need = sp->need3;
-  __syncthreads();
+  const uint2 prev_hist = lv ? make_uint2(rfl(bh10), rfl(bh11)) : make_uint2(rfl(bh00), rfl(bh01));
+  const uint32_t b1 = rfl(s_b1), zeros = rfl(s_zeros), mode = rfl(s_mode);
+  uint32_t b2 = rfl(s_b2);
+  uint32_t need = rfl(s_need3);
+  if (tid == 0) { flag = mode == 1u ? 1u : 0u; lcount = 0u; }
+  if (tid < 256) hist3[tid] = 0u;
+  if (tid < kL2Bins) hist4[tid] = 0u;
   if (mode == 1u) {                                        // uniform over the workgroup
     // The guess missed: the counting kernel's workgroups have staged the keys of b1 tile by tile
     // and summed their level-2 counts.  b2 comes from those; what the quarter lists would have
     // given is taken by sweeps over the staged keys (one workgroup for the whole layer: slower
     // than the listed path, and rare).
-    for (int b = tid; b < kHistBins; b += kPickThreads) {
-      uint32_t h = (b < kL2Bins) ? ws.hist2m[wl * kL2Bins + b] : 0u;
-      if (b == 0 && b1 == 0u) h += zeros;                    // exact zeros: level-2 bin 0 of bin 0
-      hist[b] = h;
-    }
-    __syncthreads();
-    const uint32_t need2 = sp->need2;
-    pick_bin(hist, need2, out, scratch);
-    b2 = out[0];
-    need = need2 - out[1];
-    if (tid == 0) { flag = 1u; sp->b2 = b2; sp->need3 = need; }
-    __syncthreads();                                       // everybody has read out[]
+    uint32_t h = ws.hist2m[wl * kL2Bins + lane];
+    if (lane == 0 && b1 == 0u) h += zeros;                 // exact zeros: level-2 bin 0 of bin 0
+    const uint32_t need2 = rfl(s_need2);
+    const Pick p2 = wave_pick64(h, need2, lane);
+    b2 = p2.bin;
+    need = need2 - p2.above;
+    if (tid == 0) { sp->b2 = b2; sp->need3 = need; }
   }
+  __syncthreads();
   const bool zero_bin = (b1 == 0u && b2 == 0u);            // bin (b1, b2) holds the exact zeros
   // Gather the listed keys of the whole layer in LDS, packed as (quarter << 14 | low 14 key
   // bits): the upper 17 key bits are those of (b1, b2).  A quarter's count and its list slot are
@@ -1108,9 +1135,9 @@ __device__ __forceinline__ void pick3_body(const Ws& ws, int w0, uint32_t step_i
     const bool over = valid && (n > (uint32_t)kQListCap || !packable);
     if (over) flag = 1u;                                   // a list overflowed: the sweeps decide
     const uint32_t ne = (valid && !over) ? n : 0u;
-    const uint32_t incl = wave_incl_scan_u32(ne, lane);
+    if (ballot64(ne != 0u) == 0) return;                   // wave-uniform
+    const uint32_t incl = wave_incl_scan_u32(ne);
     const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)incl, kWave - 1);
-    if (total == 0u) return;                               // wave-uniform
     uint32_t base = 0u;
     if (lane == kWave - 1) base = atomicAdd(&lcount, total);
     base = (uint32_t)__builtin_amdgcn_readlane((int)base, kWave - 1);
@@ -1160,11 +1187,6 @@ __device__ __forceinline__ void pick3_body(const Ws& ws, int w0, uint32_t step_i
   const uint32_t ln = lcount;
   const bool listed = flag == 0u;                          // every quarter's list is complete
   const bool in_lds = ln <= (uint32_t)kLdsList;            // ... and all of them fit in LDS
-  auto clear_hist = [&]() {
-    __syncthreads();
-    for (int b = tid; b < kHistBins; b += kPickThreads) hist[b] = 0u;
-    __syncthreads();
-  };
   // f(low 14 key bits, quarter) for every listed key of the layer: from LDS, or -- a very large
   // layer -- from the quarters' lists again (each thread its own quarters)
   auto for_listed = [&](auto f) {
@@ -1181,22 +1203,20 @@ __device__ __forceinline__ void pick3_body(const Ws& ws, int w0, uint32_t step_i
   uint32_t T, ktie, alleq;
   if (listed) {
     // level 3: key bits 13..6
-    clear_hist();
-    for_listed([&](uint32_t low, int) { atomicAdd(&hist[low >> 6], 1u); });
-    if (zero_bin && tid == 0) atomicAdd(&hist[0], zeros);
+    for_listed([&](uint32_t low, int) { atomicAdd(&hist3[low >> 6], 1u); });
+    if (zero_bin && tid == 0) atomicAdd(&hist3[0], zeros);
     __syncthreads();
-    pick_bin(hist, need, out, scratch);
-    const uint32_t b3 = out[0];
-    need -= out[1];
+    const Pick p3 = wave_pick256(hist3, need, lane);
+    const uint32_t b3 = p3.bin;
+    need -= p3.above;
     // level 4: key bits 5..0
-    clear_hist();
-    for_listed([&](uint32_t low, int) { if ((low >> 6) == b3) atomicAdd(&hist[low & 0x3fu], 1u); });
-    if (zero_bin && b3 == 0u && tid == 0) atomicAdd(&hist[0], zeros);
+    for_listed([&](uint32_t low, int) { if ((low >> 6) == b3) atomicAdd(&hist4[low & 0x3fu], 1u); });
+    if (zero_bin && b3 == 0u && tid == 0) atomicAdd(&hist4[0], zeros);
     __syncthreads();
-    pick_bin(hist, need, out, scratch);
-    T = (b1 << 20) | (b2 << 14) | (b3 << 6) | out[0];
-    ktie = need - out[1];                                  // 1 <= ktie <= entries equal to T
-    alleq = (ktie == out[2]) ? 1u : 0u;
+    const Pick p4 = wave_pick64(hist4[lane], need, lane);
+    T = (b1 << 20) | (b2 << 14) | (b3 << 6) | p4.bin;
+    ktie = need - p4.above;                                // 1 <= ktie <= entries equal to T
+    alleq = (ktie == p4.count) ? 1u : 0u;
     // per quarter: the listed keys above T and equal to T
     const uint32_t t_low = T & 0x3fffu;
     if (in_lds && lds_q) {
@@ -1239,24 +1259,22 @@ __device__ __forceinline__ void pick3_body(const Ws& ws, int w0, uint32_t step_i
       }
     };
     auto nothing = [](int, uint32_t) {};
-    clear_hist();
-    sweep([&](uint32_t key, bool valid) { if (valid && bin2_of(key) == b2) atomicAdd(&hist[bin3_of(key)], 1u); },
+    sweep([&](uint32_t key, bool valid) { if (valid && bin2_of(key) == b2) atomicAdd(&hist3[bin3_of(key)], 1u); },
           nothing);
-    if (zero_bin && tid == 0) atomicAdd(&hist[0], zeros);
+    if (zero_bin && tid == 0) atomicAdd(&hist3[0], zeros);
     __syncthreads();
-    pick_bin(hist, need, out, scratch);
-    const uint32_t b3 = out[0];
-    need -= out[1];
-    clear_hist();
+    const Pick p3 = wave_pick256(hist3, need, lane);
+    const uint32_t b3 = p3.bin;
+    need -= p3.above;
     const uint32_t hi3 = (b1 << 14) | (b2 << 8) | b3;      // key >> 6 of the keys of (b1, b2, b3)
-    sweep([&](uint32_t key, bool valid) { if (valid && (key >> 6) == hi3) atomicAdd(&hist[bin4_of(key)], 1u); },
+    sweep([&](uint32_t key, bool valid) { if (valid && (key >> 6) == hi3) atomicAdd(&hist4[bin4_of(key)], 1u); },
           nothing);
-    if (zero_bin && b3 == 0u && tid == 0) atomicAdd(&hist[0], zeros);
+    if (zero_bin && b3 == 0u && tid == 0) atomicAdd(&hist4[0], zeros);
     __syncthreads();
-    pick_bin(hist, need, out, scratch);
-    T = (hi3 << 6) | out[0];
-    ktie = need - out[1];
-    alleq = (ktie == out[2]) ? 1u : 0u;
+    const Pick p4 = wave_pick64(hist4[lane], need, lane);
+    T = (hi3 << 6) | p4.bin;
+    ktie = need - p4.above;
+    alleq = (ktie == p4.count) ? 1u : 0u;
     uint32_t n_gt = 0, n_eq = 0;
     sweep([&](uint32_t key, bool valid) {
             const uint64_t mv = ballot64(valid);
@@ -1292,11 +1310,13 @@ __device__ __forceinline__ void pick3_body(const Ws& ws, int w0, uint32_t step_i
       s_gt += g;
       s_eq += e;
     }
-    const uint32_t i_gt = wave_incl_scan_u32(s_gt, lane), i_eq = wave_incl_scan_u32(s_eq, lane);
+    const uint32_t i_gt = wave_incl_scan_u32(s_gt), i_eq = wave_incl_scan_u32(s_eq);
     if (lane == kWave - 1) { wsum[0][wave] = i_gt; wsum[1][wave] = i_eq; }
     __syncthreads();
-    uint32_t o_gt = i_gt - s_gt, o_eq = i_eq - s_eq;
-    for (int v = 0; v < wave; ++v) { o_gt += wsum[0][v]; o_eq += wsum[1][v]; }
+    // the waves before this one: a row of lanes reads one total per wave
+    const bool before = (lane & 15) < wave;
+    uint32_t o_gt = i_gt - s_gt + row_sum_u32(before ? wsum[0][lane & 15] : 0u);
+    uint32_t o_eq = i_eq - s_eq + row_sum_u32(before ? wsum[1][lane & 15] : 0u);
     uint32_t* gtpre = ws.gtpre + qbase;
     uint32_t* eqpre = ws.eqpre + qbase;
     if (chunk == 1) {
@@ -1367,8 +1387,8 @@ __device__ __forceinline__ void pick3_body(const Ws& ws, int w0, uint32_t step_i
     // emptied down to less than k non-zero entries the threshold drops to zero.  This step leaves
     // nnz - k of its non-zero entries behind and the next gradient adds about as many as it did
     // the last time everything non-zero was kept.
-    const uint32_t nnz = n_layer - min(sp->bin0, n_layer);
-    uint32_t fresh = sp->fresh_nnz;
+    const uint32_t nnz = n_layer - min(rfl(s_bin0), n_layer);
+    uint32_t fresh = rfl(s_fresh);
     if (b1 == 0u && nnz != 0u) { fresh = nnz; sp->fresh_nnz = nnz; }
     const bool runs_dry = fresh != 0u && (uint64_t)(nnz - min(k_now, nnz)) + fresh <= (uint64_t)k_now;
     ws.guess[wl * 2 + lv] = (b1 == 0u || runs_dry) ? kGuessZero

@@ -595,3 +595,19 @@ def test_layers_that_start_and_end_anywhere(pad):
             H.assert_bits_equal(out.cpu().numpy(), (sums[0] + sums[1]) / np.float32(4.0), f"pad {pad} step {step}: batch")
     gpu.destroy()
     bat.destroy()
+
+
+@pytest.mark.parametrize("case", ["normal", "quantised", "all_equal", "all_zero", "sparse"])
+@pytest.mark.parametrize("crit", [1, 10, 99])
+def test_single_tile_layers(case, crit):
+    """Layers that one workgroup decides from registers: sizes around a wave, a group per thread and the tile, with
+    ties that span quarters, exact zeros and almost everything or almost nothing kept."""
+    print(f"case single tile {case} K {crit}", flush=True)
+    layers = wl.make_layers([(1, n, 0) for n in (1, 4, 63, 65, 255, 1023, 4095, 4097, 8189, 8192)])
+    N, W = wl.total_params(layers), 2
+    rng = np.random.default_rng(crit)
+    gpu, ora = H.make_pair(B.ACC_TOPK, layers, W, crit, 5)
+    for step in range(3):
+        grads = [_case_values(rng, case, N).astype(np.float32) for _ in range(W)]
+        _check_step(gpu, ora, grads, f"{case} K {crit} step {step}", check_state=step == 1)
+    gpu.destroy()
