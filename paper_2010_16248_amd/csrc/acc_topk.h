@@ -199,6 +199,15 @@ __device__ __forceinline__ float4 ld_span(const float* __restrict__ p, const Til
   return ldq<AL, STREAM>(p, tg.a0, tg.lo, tg.hi, q, q < sp.qend);
 }
 
+// Group q of the wave's span, requested whether or not the lane has one (beyond the span every lane asks
+// for the tile's first group, and nobody looks at it): a predicated load is a branch, and behind
+// branches the compiler waits for more requests than the one it needs.
+template <bool AL, bool STREAM = false>
+__device__ __forceinline__ float4 ld_ahead(const float* __restrict__ p, const TileGeom& tg, const WaveSpan& sp, int q) {
+  if (AL) return ldq_clamped<STREAM>(p, tg.a0, q < sp.qend ? q : 0);
+  return ld_span<AL, STREAM>(p, tg, sp, q);
+}
+
 // Is element c of group q (which lies in the wave's span iff in_span) an element of the tile?
 template <bool AL>
 __device__ __forceinline__ bool elem_valid(const TileGeom& tg, int q, int c, bool in_span) {
@@ -1828,6 +1837,7 @@ __device__ __forceinline__ void compact_mean_tile(const Ws& ws, const FlatTile& 
 constexpr int kGatherChunks = 4;                            // 64-entry chunks of a candidate list requested together (2 to 8: within 2 us)
 constexpr int kQuarterGroups = kTile / 16;                  // groups of a wave quarter at most
 constexpr int kQuarterFloats = 4 * kQuarterGroups;
+constexpr int kSinkGroups = 4;                              // groups of weights and velocity a lane requests together
 constexpr int kPayRing = 128;                               // a wave's payload ring in LDS: entries (indices, then values)
 
 template <bool AL, bool UPD>
@@ -1870,6 +1880,32 @@ __device__ __forceinline__ void gather_mean_tile(const Ws& ws, const FlatTile& f
   };
   uint32_t cv[U], ci[U];
   load_batch(0, 0u, cv, ci);
+  // The weights and the velocity of the quarter in two batches of kSinkGroups groups per lane: the first is
+  // requested before the workers' lists are gone through, the second before the first is used.  (One
+  // group at a time, requested when it was needed, left a quarter eight dependent round trips: ResNet-18
+  // shapes at W = 1, where they are nearly all the pass reads, 50.9 us, 45.8 so; two or eight groups: 1 us more.)  LDS bounds the waves per compute
+  // unit here, not the registers this takes.
+  constexpr int SG = UPD ? kSinkGroups : 1;
+  auto load_sink = [&](int g0, float4 (&wq)[SG], float4 (&vq)[SG]) {
+    if (!UPD) return;
+    if (sink.stream_wv) {                                   // uniform: see stream_wv() on the host side
+      keep_apart();
+#pragma unroll
+      for (int j = 0; j < SG; ++j) {
+        wq[j] = ld_ahead<AL, true>(sink.wt, tg, span, span.qbeg + g0 + j * kWave + lane);
+        vq[j] = ld_ahead<AL, true>(sink.vel, tg, span, span.qbeg + g0 + j * kWave + lane);
+      }
+      keep_apart();
+    } else {
+#pragma unroll
+      for (int j = 0; j < SG; ++j) {
+        wq[j] = ld_ahead<AL>(sink.wt, tg, span, span.qbeg + g0 + j * kWave + lane);
+        vq[j] = ld_ahead<AL>(sink.vel, tg, span, span.qbeg + g0 + j * kWave + lane);
+      }
+    }
+  };
+  float4 wq[SG], vq[SG];
+  load_sink(0, wq, vq);
   float4* acc4 = reinterpret_cast<float4*>(acc);
   for (int g = lane; g < ng; g += kWave) acc4[g] = make_float4(0.f, 0.f, 0.f, 0.f);
   __builtin_amdgcn_wave_barrier();
@@ -1988,39 +2024,36 @@ __device__ __forceinline__ void gather_mean_tile(const Ws& ws, const FlatTile& f
   const float fw = (float)W;
   const bool pow2 = (W & (W - 1)) == 0;                     // then x / W and x * (1 / W) round alike
   const float rw = 1.0f / fw;
-  for (int g0 = 0; g0 < ng; g0 += kWave) {
-    const int g = g0 + lane;
-    const int q = span.qbeg + g;
-    float4 wq = make_float4(0.f, 0.f, 0.f, 0.f), vq = wq;
-    if (UPD) {
-      if (sink.stream_wv) {                                 // uniform: see stream_wv() on the host side
-        keep_apart();
-        wq = ld_span<AL, true>(sink.wt, tg, span, q);
-        vq = ld_span<AL, true>(sink.vel, tg, span, q);
-        keep_apart();
-      } else {
-        wq = ld_span<AL>(sink.wt, tg, span, q);
-        vq = ld_span<AL>(sink.vel, tg, span, q);
+  for (int g0 = 0; g0 < ng; g0 += SG * kWave) {
+    float4 wn[SG], vn[SG];
+    load_sink(g0 + SG * kWave, wn, vn);
+#pragma unroll
+    for (int j = 0; j < SG; ++j) {
+      const int g = g0 + j * kWave + lane;
+      const int q = span.qbeg + g;
+      if (g < ng) {
+        const float4 a = acc4[g];
+        const float4 v = pow2 ? make_float4(a.x * rw, a.y * rw, a.z * rw, a.w * rw)
+                              : make_float4(a.x / fw, a.y / fw, a.z / fw, a.w / fw);
+        if (UPD) {
+          nesterov4(v, wq[j], vq[j], sink);
+          if (sink.stream_wv) {
+            keep_apart();
+            stq<AL, true>(sink.wt, tg.a0, tg.lo, tg.hi, q, wq[j]);
+            stq<AL, true>(sink.vel, tg.a0, tg.lo, tg.hi, q, vq[j]);
+            keep_apart();
+          } else {
+            stq<AL>(sink.wt, tg.a0, tg.lo, tg.hi, q, wq[j]);
+            stq<AL>(sink.vel, tg.a0, tg.lo, tg.hi, q, vq[j]);
+          }
+        } else {
+          stq<AL, kStreamOut>(sink.out, tg.a0, tg.lo, tg.hi, q, v);
+        }
       }
     }
-    if (g < ng) {
-      const float4 a = acc4[g];
-      const float4 v = pow2 ? make_float4(a.x * rw, a.y * rw, a.z * rw, a.w * rw)
-                            : make_float4(a.x / fw, a.y / fw, a.z / fw, a.w / fw);
-      if (UPD) {
-        nesterov4(v, wq, vq, sink);
-        if (sink.stream_wv) {
-          keep_apart();
-          stq<AL, true>(sink.wt, tg.a0, tg.lo, tg.hi, q, wq);
-          stq<AL, true>(sink.vel, tg.a0, tg.lo, tg.hi, q, vq);
-          keep_apart();
-        } else {
-          stq<AL>(sink.wt, tg.a0, tg.lo, tg.hi, q, wq);
-          stq<AL>(sink.vel, tg.a0, tg.lo, tg.hi, q, vq);
-        }
-      } else {
-        stq<AL, kStreamOut>(sink.out, tg.a0, tg.lo, tg.hi, q, v);
-      }
+#pragma unroll
+    for (int j = 0; j < SG; ++j) {
+      if (UPD) { wq[j] = wn[j]; vq[j] = vn[j]; }
     }
   }
 }
