@@ -72,11 +72,27 @@ constexpr int kBandBins = 8, kBandKeepDiv = 6;
 __device__ __forceinline__ int guess_bins_for(uint32_t k, uint32_t n) {
   return (uint64_t)k * kBandKeepDiv > (uint64_t)n ? kBandBins : kGuessBins;
 }
-__device__ __forceinline__ uint32_t make_guess(int lo, int nb) {
-  return (uint32_t)max(1, min(kHistBins - nb, lo)) | ((uint32_t)nb << 16);
+// A guess of kGuessBins bins may start inside its lowest bin, at one of its level-2 cells (a 64th of a bin):
+// the entries below that cell are no candidates.  The threshold of a run at rest moves by a cell or two per
+// step, and under error feedback the entries are densest just below it, so a floor at a whole bin lists
+// twice what is kept.  kFloorCells + kFloorPerMove m cells below the expected place, m = the largest recent
+// move, which fades slowly (faded_move); a level's first steps, and thresholds that move by half a bin
+// per step, keep the floor at a whole bin.  Against a floor at a whole bin, us per step, three states in turn:
+// ResNet-18 shapes K = 10 %, W = 4 203.1 -> 198.5, K = 1 %, W = 8 328 -> 305, LSTM set W = 16 2994 -> 2905, odd sizes
+// 115.6 -> 107.1, ten missed guesses in 1340 steps of 84 decisions.  Four cells less below a threshold at rest
+// or a move that fades by a quarter per step: 1 % faster there with ten times the misses; 16 + 6 m: 1 % slower, three misses.
+constexpr int kFloorCells = 8, kFloorPerMove = 4, kMoveMost = 31;
+__device__ __forceinline__ int faded_move(int m, uint32_t step) {
+  return m >= 8 ? m - m / 8 : max(0, m - ((step & 3u) == 0u ? 1 : 0));
+}
+__device__ __forceinline__ uint32_t make_guess(int lo, int nb, int cell = 0) {
+  const int at = max(1, min(kHistBins - nb, lo));
+  return (uint32_t)at | ((uint32_t)nb << 16) | (at == lo ? (uint32_t)cell << 24 : 0u);
 }
 __device__ __forceinline__ uint32_t guess_lo(uint32_t g) { return g & 0xffffu; }
-__device__ __forceinline__ uint32_t guess_nb(uint32_t g) { return g >> 16; }
+__device__ __forceinline__ uint32_t guess_nb(uint32_t g) { return (g >> 16) & 0xffu; }
+// the smallest key that is listed
+__device__ __forceinline__ uint32_t guess_floor(uint32_t g) { return (g & 0xffffu) << 20 | (g >> 24) << 14; }
 __device__ __forceinline__ uint32_t bin2_of(uint32_t key) { return (key >> 14) & 0x3fu; }
 __device__ __forceinline__ uint32_t bin3_of(uint32_t key) { return (key >> 6) & 0xffu; }
 __device__ __forceinline__ uint32_t bin4_of(uint32_t key) { return key & 0x3fu; }
@@ -297,8 +313,8 @@ __device__ __forceinline__ void cand_make_room(const Ws& ws, int64_t qslot, cons
   if (c.n_lds > (uint32_t)(kCandLds - 4 * kWave)) cand_write_out(ws, qslot, cl, c, lane, false);
 }
 
-// Pass A, one group: the candidates among the four elements of every lane (bins glo and up;
-// glo >= 1, so a candidate is never an exact zero, and zeros are not counted: should the
+// Pass A, one group: the candidates among the four elements of every lane (keys floor_key and up, which lies
+// in bin glo; glo >= 1, so a candidate is never an exact zero, and zeros are not counted: should the
 // threshold turn out to lie in bin 0 the guess has missed and the staging after a miss counts
 // them).  BAND: only the bins glo .. glo + gnb - 1 are listed, what lies above is counted.
 // mv: lane masks of the valid elements
@@ -310,8 +326,8 @@ __device__ __forceinline__ void cand_make_room(const Ws& ws, int64_t qslot, cons
 template <bool MASKED, bool BAND, bool ZERO = false>
 __device__ __forceinline__ void stage_candidates(const CandList& cl, uint32_t* sub2, StageCounts& c,
                                                  uint64_t mv0, uint64_t mv1, uint64_t mv2, uint64_t mv3,
-                                                 const float4& d, uint32_t glo, uint32_t gnb, uint32_t i_rel,
-                                                 int lane) {
+                                                 const float4& d, uint32_t glo, uint32_t gnb, uint32_t floor_key,
+                                                 uint32_t i_rel, int lane) {
   uint32_t key[4], rel[4];
   uint64_t m[4];
 #pragma unroll
@@ -328,7 +344,7 @@ __device__ __forceinline__ void stage_candidates(const CandList& cl, uint32_t* s
       const bool above = (int32_t)rel[x] >= (int32_t)gnb;
       c.v_hi += (above && (!MASKED || lane_bit(mvx))) ? 1u : 0u;
     } else {
-      m[x] = ballot64((int32_t)rel[x] >= 0);
+      m[x] = ballot64(key[x] >= floor_key);
     }
     if (MASKED) m[x] &= mvx;
   }
@@ -488,8 +504,8 @@ __device__ __forceinline__ void ef_hist_tile(const Ws& ws, const GradPtrs& gp, i
   const bool a_fresh = A && window_fresh;                  // uniform over the workgroup
   double a_sq = 0.0;                                       // worker 0: the lane's share of the tile's sum of squares of A
   const int64_t wl = (int64_t)w * ws.L + ft.layer;
-  uint32_t glo = 0x7ffffff0u, gnb = 0u;                    // no bin matches without a guess
-  if (SELECT && !ZB && guess != kNoGuess) { glo = guess_lo(guess); gnb = guess_nb(guess); }
+  uint32_t glo = 0x7ffffff0u, gnb = 0u, floor_key = 0xffffffffu;   // no key matches without a guess
+  if (SELECT && !ZB && guess != kNoGuess) { glo = guess_lo(guess); gnb = guess_nb(guess); floor_key = guess_floor(guess); }
   const bool band = gnb != 0u && gnb < (uint32_t)kGuessBins;   // uniform over the workgroup
   // two groups per lane are requested before anything else
   constexpr int U = 2;   // (one group is as fast where the memory fits the caches, three or four are no faster anywhere)
@@ -548,10 +564,10 @@ __device__ __forceinline__ void ef_hist_tile(const Ws& ws, const GradPtrs& gp, i
             hist_add(hist, (key >> 20) != 0u, key >> 20);
           }
           if (ZB) {
-            stage_candidates<false, false, true>(cl, sub2, cnt, 0ull, 0ull, 0ull, 0ull, d, 0u, 1u, i_rel, lane);
+            stage_candidates<false, false, true>(cl, sub2, cnt, 0ull, 0ull, 0ull, 0ull, d, 0u, 1u, 0u, i_rel, lane);
           } else {
-            if (band) stage_candidates<false, true>(cl, sub2, cnt, 0ull, 0ull, 0ull, 0ull, d, glo, gnb, i_rel, lane);
-            else stage_candidates<false, false>(cl, sub2, cnt, 0ull, 0ull, 0ull, 0ull, d, glo, gnb, i_rel, lane);
+            if (band) stage_candidates<false, true>(cl, sub2, cnt, 0ull, 0ull, 0ull, 0ull, d, glo, gnb, floor_key, i_rel, lane);
+            else stage_candidates<false, false>(cl, sub2, cnt, 0ull, 0ull, 0ull, 0ull, d, glo, gnb, floor_key, i_rel, lane);
           }
         } else {
           const uint64_t m_span = ballot64(qa);
@@ -564,10 +580,10 @@ __device__ __forceinline__ void ef_hist_tile(const Ws& ws, const GradPtrs& gp, i
             hist_add(hist, valid && (key >> 20) != 0u, key >> 20);
           }
           if (ZB) {
-            stage_candidates<true, false, true>(cl, sub2, cnt, mv[0], mv[1], mv[2], mv[3], d, 0u, 1u, i_rel, lane);
+            stage_candidates<true, false, true>(cl, sub2, cnt, mv[0], mv[1], mv[2], mv[3], d, 0u, 1u, 0u, i_rel, lane);
           } else {
-            if (band) stage_candidates<true, true>(cl, sub2, cnt, mv[0], mv[1], mv[2], mv[3], d, glo, gnb, i_rel, lane);
-            else stage_candidates<true, false>(cl, sub2, cnt, mv[0], mv[1], mv[2], mv[3], d, glo, gnb, i_rel, lane);
+            if (band) stage_candidates<true, true>(cl, sub2, cnt, mv[0], mv[1], mv[2], mv[3], d, glo, gnb, floor_key, i_rel, lane);
+            else stage_candidates<true, false>(cl, sub2, cnt, mv[0], mv[1], mv[2], mv[3], d, glo, gnb, floor_key, i_rel, lane);
           }
         }
         cand_make_room(ws, qslot_mine, cl, cnt, lane);
@@ -927,14 +943,16 @@ __global__ __launch_bounds__(kPickThreads) void topk_pick12_kernel(const Ws ws, 
   const uint32_t b1 = out[0], need2 = k - out[1], bo = out[3];
   const bool guessed = guess != kNoGuess && guess != kGuessZero;
   const uint32_t glo = guessed ? guess_lo(guess) : 0u;     // the bins pass A counted: glo .. glo + nb - 1
-  const bool hit = guessed && b1 >= glo && b1 - glo < guess_nb(guess);
+  const bool in_guess = guessed && b1 >= glo && b1 - glo < guess_nb(guess);
   // bin 0 guessed and found: pass A listed every non-zero entry and counted the zeros (mode 2)
   const bool zhit = guess == kGuessZero && b1 == 0u;
-  const uint32_t side = hit ? b1 - glo : 0u;
+  const uint32_t side = in_guess ? b1 - glo : 0u;
   // level 2: the summed counts of bin b1
   uint32_t c = 0u;
 #pragma unroll
   for (int st = 0; st < kStripes; ++st) c += reinterpret_cast<const uint32_t*>(&sub[st][0])[side * kL2Bins + lane];
+  // A guess that starts inside bin b1 holds only if the threshold lies at or above its floor
+  const bool hit = in_guess && (side != 0u || wave_sum_u32(c) >= need2);
   uint32_t zeros = 0u;
   if (zhit) {
     // the counts are those of the non-zero keys of bin 0; the rest of bin 0 are exact zeros, which
@@ -1078,7 +1096,7 @@ __device__ __forceinline__ void pick3_body(const Ws& ws, int w0, uint32_t step_i
   // requested together: the selection's state (what thread 0 needs at the very end too)
   const uint32_t s_b1 = ld_here(&sp->b1), s_b2 = ld_here(&sp->b2), s_need2 = ld_here(&sp->need2), s_need3 = ld_here(&sp->need3),
                  s_zeros = ld_here(&sp->zeros), s_mode = ld_here(&sp->mode), s_bin0 = ld_here(&sp->bin0),
-                 s_fresh = ld_here(&sp->fresh_nnz);
+                 s_fresh = ld_here(&sp->fresh_nnz), s_T = ld_here(&sp->T);
   const uint32_t* bh = reinterpret_cast<const uint32_t*>(ws.b1hist + wl * 2);
   const uint32_t bh00 = ld_here(bh), bh01 = ld_here(bh + 1), bh10 = ld_here(bh + 2), bh11 = ld_here(bh + 3);
   const int lv = (int)rfl(ld_here(reinterpret_cast<const uint32_t*>(ws.level + li)));
@@ -1365,14 +1383,18 @@ __device__ __forceinline__ void pick3_body(const Ws& ws, int w0, uint32_t step_i
   if (tid == 0) {
     sp->T = T; sp->ktie = ktie; sp->alleq = alleq; sp->mode = 0u;
     // Next step's guess at this level, from the bin this step ended in and the last two moves.
-    // b1hist: (b1 | (last move + 64) << 16 | steps at rest << 24, step)
+    // b1hist: (b1 | m << 11 | (last move + 64) << 16 | steps at rest << 24, step); m: see kFloorCells
     const uint2 prev = prev_hist;
     const bool consecutive = prev.y + 1u == step_id;
-    int v = consecutive ? (int)b1 - (int)(prev.x & 0xffffu) : 0;
+    int v = consecutive ? (int)b1 - (int)(prev.x & 0x7ffu) : 0;
     v = max(-64, min(64, v));
     // steps in a row without a move (two equal steps right after a level switch are no rest yet)
     const int rest = (consecutive && v == 0) ? min(15, (int)(prev.x >> 24) + 1) : 0;
-    ws.b1hist[wl * 2 + lv] = make_uint2(b1 | ((uint32_t)(v + 64) << 16) | ((uint32_t)rest << 24), step_id);
+    // the move in cells (the state still held the previous step's threshold when it was read)
+    const int cells = (int)(T >> 14), moved = cells - (int)(rfl(s_T) >> 14);
+    const int m_prev = (int)((prev.x >> 11) & 0x1fu);
+    const int m = consecutive ? min(kMoveMost, max(abs(moved), faded_move(m_prev, step_id))) : kMoveMost;
+    ws.b1hist[wl * 2 + lv] = make_uint2(b1 | ((uint32_t)m << 11) | ((uint32_t)(v + 64) << 16) | ((uint32_t)rest << 24), step_id);
     // A move down is followed at once (the guess must start below the threshold); a move up only
     // with a lag of two bins: the guess reaches four to six bins above its centre anyway, and a
     // jump up is often followed by smaller steps.
@@ -1383,7 +1405,7 @@ __device__ __forceinline__ void pick3_body(const Ws& ws, int w0, uint32_t step_i
       // a switch to it the threshold is that of gradient plus a full memory, from the second on that
       // of the gradient alone, octaves below.  So the step after a switch is guessed where the
       // threshold was the last time this level ran, and a jump of many bins is not taken for a drift.
-      const int remembered = (int)(prev.x & 0xffffu);
+      const int remembered = (int)(prev.x & 0x7ffu);
       if (!consecutive && remembered != 0 && remembered < (int)b1) centre = remembered;
       else if (consecutive && abs(v) > 6) centre = (int)b1;
     }
@@ -1400,8 +1422,11 @@ __device__ __forceinline__ void pick3_body(const Ws& ws, int w0, uint32_t step_i
     uint32_t fresh = rfl(s_fresh);
     if (b1 == 0u && nnz != 0u) { fresh = nnz; sp->fresh_nnz = nnz; }
     const bool runs_dry = fresh != 0u && (uint64_t)(nnz - min(k_now, nnz)) + fresh <= (uint64_t)k_now;
-    ws.guess[wl * 2 + lv] = (b1 == 0u || runs_dry) ? kGuessZero
-        : make_guess(centre - below, guess_bins_for(k_now, n_layer));
+    const int nb = guess_bins_for(k_now, n_layer);
+    const int fine = cells + min(moved, 0) - (kFloorCells + kFloorPerMove * m);
+    int lo = centre - below, cell = 0;
+    if (nb == kGuessBins && consecutive && (fine >> 6) >= lo) { lo = fine >> 6; cell = fine & 63; }
+    ws.guess[wl * 2 + lv] = (b1 == 0u || runs_dry) ? kGuessZero : make_guess(lo, nb, cell);
   }
 }
 

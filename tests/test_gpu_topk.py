@@ -611,3 +611,32 @@ def test_single_tile_layers(case, crit):
         grads = [_case_values(rng, case, N).astype(np.float32) for _ in range(W)]
         _check_step(gpu, ora, grads, f"{case} K {crit} step {step}", check_state=step == 1)
     gpu.destroy()
+
+
+@pytest.mark.parametrize("crit", [1, 10])
+def test_a_guess_that_starts_inside_a_bin(crit):
+    """After enough steps at rest the guess starts a few level-2 cells below the threshold instead of at a whole
+    bin.  Then memory and gradients shrink together, by 4 % and by 20 %: the threshold falls below the guess's start,
+    inside its bin or just out of it, then far out.  Every step exact, the resting ones without a missed guess."""
+    print(f"case guess inside a bin K {crit}", flush=True)
+    layers = wl.make_layers([(1, 40 * 8192 + 3, 0), (1, 5, 0), (1, 12 * 8192 + 1, 0)])
+    N, W = wl.total_params(layers), 2
+    rng = np.random.default_rng(crit)
+    gpu, ora = H.make_pair(B.ACC_TOPK, layers, W, crit, 5)
+    misses, scale = [], np.float32(1.0)
+    for step in range(56):
+        if step in (46, 52):
+            factor = np.float32(0.96 if step == 46 else 0.8)
+            scale *= factor
+            ora.e *= factor
+            gpu.set_state(H.oracle_state_blob(gpu, ora))
+        grads = [rng.standard_normal(N, dtype=np.float32) * scale for _ in range(W)]
+        if step < 40:                                        # the checks of the early steps are other tests' work
+            ora.step(grads)
+            gpu.step_all([H.to_dev(g) for g in grads], H.dev_out(N))
+        else:
+            _check_step(gpu, ora, grads, f"K {crit} step {step}", check_state=step == 44)
+        misses.append(gpu.topk_stats()[0])
+    assert misses[45] == misses[30], "missed guesses at rest"
+    assert misses[46] > misses[45] and misses[52] > misses[51], "the threshold fell and the guess still held"
+    gpu.destroy()
