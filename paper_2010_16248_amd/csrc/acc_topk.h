@@ -8,7 +8,7 @@
 //                      from e first), A += g (worker 0) with its sum of squares, level-1 histogram
 //                      per (worker, layer).  The level-1 bin b1 that will hold the k-th largest key
 //                      is not known yet, so the pass works on a GUESS (from the previous steps at
-//                      this level): every entry at or above the lowest guessed bin goes into its
+//                      this level): every entry at or above the guess's floor goes into its
 //                      wave quarter's candidate list as (offset, value), and the tile's level-2
 //                      counts of the kGuessBins guessed bins are written.
 //   P12 topk_pick12    one workgroup per (worker, layer): b1 from the histogram; if it is one
@@ -52,8 +52,8 @@ static_assert(kHistBins == 2 * kPickThreads, "the pick kernels load two histogra
 constexpr int kQListCap = 16;            // keys of bin (b1, b2) listed per wave quarter
 constexpr int kL2Bins = 64;              // level 2: key bits 19..14
 // A guess names kGuessBins adjacent level-1 bins, lo .. lo + kGuessBins - 1 (lo >= 1): the first
-// pass lists every entry of bin lo and above as a candidate and counts the level-2 bins of the
-// guessed ones.  Bins above the threshold cost no candidates (their entries are kept anyway), so the
+// pass lists every entry of bin lo (from a floor in it, see make_guess) and above as a candidate and counts
+// the level-2 bins of the guessed ones.  Bins above the threshold cost no candidates (their entries are kept anyway), so the
 // guess always reaches far up; what varies is how far below the expected bin it starts: one bin
 // while the threshold rests (no move for two steps in a row), three while it moves -- after a level
 // switch the error memory adapts for ten steps or so, during which the threshold moves by one to
@@ -249,7 +249,7 @@ __device__ __forceinline__ int64_t quarter_slot(const Ws& ws, const LayerDev& L,
 // or above the lowest guessed bin, as (offset inside the quarter, value), in index order.  When the
 // guess holds, the kept entries are among them, and the passes after it -- the counting kernel, the
 // compaction and the mean -- read these 6 bytes per candidate (under error feedback, which piles
-// the entries up just below the threshold, 17 to 27 % of the entries at K = 10 % and 8 to 18 % at
+// the entries up just below the threshold: with a floor at whole bins 17 to 27 % of the entries at K = 10 % and 8 to 18 % at
 // K = 1 %) instead of Delta once more.  A wave collects its candidates in LDS
 // and writes them out, consecutive lanes to consecutive addresses, whenever another iteration
 // (up to 256 entries) might not fit.  A quarter with more than kCandCap candidates keeps the
