@@ -9,7 +9,15 @@ constexpr int kWave = 64;
 constexpr int kFlatThreads = 256;        // workgroup of every flat-tile kernel
 constexpr int kTile = 8192;              // elements per flat tile (power of two)
 constexpr int kTileShift = 13;
-constexpr int kT2Group = 16;             // TopK: consecutive tiles of a layer that add their level-2 counts into one slot
+// TopK: consecutive tiles of a layer that add their level-2 counts into one slot, as a power of two: sixteen, more
+// for layers of more than 512 tiles, so that the one compute unit that sums up a layer's slots reads 32 at most
+// (a layer of 22 M entries, 2688 tiles: 24.7 us with sixteen; a step of the LSTM set 2871 -> 2849 us at W = 16, 469 -> 455
+// at W = 2).
+__host__ __device__ __forceinline__ int t2_group_shift(int ntiles) {
+  int shift = 4;
+  while (((ntiles - 1) >> shift) >= 32) ++shift;
+  return shift;
+}
 constexpr int kMatRows = 64;             // matrix tile: up to 64 rows (Ws::mrows) x 256 columns
 constexpr int kMatCols = 256;
 constexpr int kQRows = 128;              // most rows of a tile of the right product Q = Delta^T P^ (Ws::qrows)
@@ -29,7 +37,7 @@ struct LayerDev {
   int32_t n_rowblocks;   // ceil(rows / Ws::qrows)
   int32_t tile0;         // first flat tile of the layer
   int32_t ntiles;        // number of flat tiles
-  int32_t t2slot0;       // TopK: the layer's first slot in a worker's level-2 count array (one slot per kT2Group tiles)
+  int32_t t2slot0;       // TopK: the layer's first slot in a worker's level-2 count array (one slot per 1 << t2_group_shift tiles)
   int32_t mt0;           // PowerSGD matrix layer: its first matrix tile (it has n_colchunks * ceil(rows / Ws::mrows))
   int64_t qoff;          // slot of the layer's first wave quarter in the per-worker quarter arrays
                          // (4 * tile0 + layer index: one spare slot per layer for the totals)
@@ -106,7 +114,7 @@ struct Ws {
   uint32_t* pending;           // one word: workers whose e still holds Delta (residual not formed yet)
   // TopK
   uint32_t* hist1;             // W x L x kHistBins, zero between steps
-  uint32_t* t2;                // W x n_t2slots x 640: level-2 counts of the ten guessed bins, summed over kT2Group tiles
+  uint32_t* t2;                // W x n_t2slots x 640: level-2 counts of the ten guessed bins, summed over a group of tiles
   uint32_t* qlist;             // W x q_stride x kQListCap: per quarter, its keys in bin (b1, b2)
   SelState* sel;               // W x L
   uint32_t* hist2m;            // W x L x 64: level-2 counts of b1 of a layer whose guess missed

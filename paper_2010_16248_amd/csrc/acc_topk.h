@@ -606,10 +606,10 @@ __device__ __forceinline__ void ef_hist_tile(const Ws& ws, const GradPtrs& gp, i
       const uint32_t h = hist[b];
       if (h) atomicAdd(&gh[b], h);
     }
-    // the tile's level-2 counts are added to the slot its group of kT2Group tiles shares (integer
+    // the tile's level-2 counts are added to the slot its group of tiles shares (integer
     // atomics; the pick kernel reads and clears the slots): one compute unit works on a whole
     // layer there, and a slot per tile is 2 MB to read for a layer of 22 M entries
-    const int slot = L.t2slot0 + (ft.start >> kTileShift) / kT2Group;
+    const int slot = L.t2slot0 + ((ft.start >> kTileShift) >> t2_group_shift(L.ntiles));
     for (int b = tid; b < kSub2; b += kFlatThreads)
       if (sub2[b] != 0u) atomicAdd(&ws.t2[((int64_t)w * ws.n_t2slots + slot) * kSub2 + b], sub2[b]);
   }
@@ -908,7 +908,7 @@ __global__ __launch_bounds__(kPickThreads) void topk_pick12_kernel(const Ws ws, 
   SelState* sp = ws.sel + wl;
   const int col4 = tid % kCols4, stripe = tid / kCols4;
   uint4* t2 = reinterpret_cast<uint4*>(ws.t2 + ((int64_t)w * ws.n_t2slots + L_t2slot0) * kSub2) + col4;
-  const int nslots = (L_ntiles + kT2Group - 1) / kT2Group;
+  const int nslots = ((L_ntiles - 1) >> t2_group_shift(L_ntiles)) + 1;
   uint4 s2 = make_uint4(0u, 0u, 0u, 0u);
   constexpr int kT2Loads = 8;                               // independent loads in flight
   for (int sl0 = (stripe < kStripes ? stripe : nslots); sl0 < nslots; sl0 += kT2Loads * kStripes) {

@@ -47,7 +47,7 @@ struct Plan {
   int64_t q_dev = 0;     // floats of Q on the device: every row padded to kMaxRank floats
   int64_t p_total = 0, ppart_stride = 0, qpart_stride = 0, vec_total = 0;
   int64_t pay_stride = 0, q_stride = 0;
-  int64_t n_t2slots = 0;    // TopK: slots of level-2 counts per worker (one per kT2Group tiles of a layer)
+  int64_t n_t2slots = 0;    // TopK: slots of level-2 counts per worker (see t2_group_shift)
   bool pick3_big = false;   // TopK: some layer has more quarters than the small last pick kernel takes
   // workspace regions
   Region r_layers, r_ftiles, r_mtiles, r_qmtiles, r_qtiles, r_ptiles, r_vectiles, r_matlayers;
@@ -161,7 +161,7 @@ int make_plan_tiled(const acc_config* c, Plan& p, char* err, bool coarse) {
     ntile += d.ntiles;
     if (4 * (int64_t)d.ntiles > kLdsQuarters) p.pick3_big = true;
     d.t2slot0 = (int32_t)p.n_t2slots;
-    p.n_t2slots += (d.ntiles + kT2Group - 1) / kT2Group;
+    p.n_t2slots += ((d.ntiles - 1) >> t2_group_shift(d.ntiles)) + 1;
     p.n_model += n;
     if (ntile > (int64_t(1) << 30)) return fail(err, ACC_EINVAL, "too many tiles");
     if (c->method == ACC_POWERSGD) {
