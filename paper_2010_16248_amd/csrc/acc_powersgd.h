@@ -372,32 +372,58 @@ constexpr int kOrthThreads = 1024;
 constexpr int kOrthWaves = kOrthThreads / kWave;
 
 // sum_w fl32(sum_b partial[w][b]) in fp64 (P_w and Q_w are fp32 quantities): workers and blocks in index
-// order, the partial sums requested sixteen at a time whatever worker they belong to, from clamped
-// positions, so that a thread waits for few round trips.  Everything but src is wave-uniform.
-// (16, 18 and 24 at a time are 1 to 3 us slower per step on layers with few partials: the positions
-// beyond the last one are requested all the same.)
-constexpr int kPartLoads = 8;
-__device__ __forceinline__ double sum_partials(const double* __restrict__ src, int64_t wstride, int64_t bstride, int W,
-                                               int nb) {
+// order, U partial sums requested together, so that a thread waits for few round trips.  U blocks of one worker
+// are a stretch of one stride; where fewer are left, the positions are walked one by one over the workers' ends,
+// and the last one is asked for again instead of one beyond it.  Everything but src is wave-uniform.
+template <int U>
+__device__ __forceinline__ double sum_partials_by(const double* __restrict__ src, int64_t wstride, int64_t bstride, int W,
+                                                  int nb) {
+  const int64_t to_next_worker = wstride - (int64_t)(nb - 1) * bstride;
   double total = 0.0, s = 0.0;
-  int lw = 0, lb = 0, w = 0, b = 0;                        // next one to request / to add
+  int64_t at = 0;                                          // position of partial[w][b]
+  int w = 0, b = 0;
   while (w < W) {
-    double v[kPartLoads];
+    double v[U];
+    if (b + U <= nb) {
 #pragma unroll
-    for (int u = 0; u < kPartLoads; ++u) {
-      v[u] = src[(int64_t)lw * wstride + (int64_t)lb * bstride];
-      if (lb + 1 < nb) ++lb;
-      else if (lw + 1 < W) { lb = 0; ++lw; }
-    }
+      for (int u = 0; u < U; ++u) v[u] = src[at + u * bstride];
 #pragma unroll
-    for (int u = 0; u < kPartLoads; ++u) {
-      if (w < W) {
-        s += v[u];
-        if (++b == nb) { total += (double)(float)s; s = 0.0; b = 0; ++w; }
+      for (int u = 0; u < U; ++u) s += v[u];
+      b += U;
+      at += U * bstride;
+      if (b == nb) { total += (double)(float)s; s = 0.0; b = 0; ++w; at += to_next_worker - bstride; }
+    } else {
+      int lw = w, lb = b;                                  // next one to request
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        v[u] = src[at];
+        if (lb + 1 < nb) { ++lb; at += bstride; }
+        else if (lw + 1 < W) { lb = 0; ++lw; at += to_next_worker; }
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        if (w < W) {
+          s += v[u];
+          if (++b == nb) { total += (double)(float)s; s = 0.0; b = 0; ++w; }
+        }
       }
     }
   }
   return total;
+}
+
+// Bound by its round trips: eight requests at a time, fewer where there are fewer partial sums in all.  (Walked one by
+// one throughout, the address arithmetic was a third of the time on many blocks, and eight requests for a single
+// partial sum two thirds of it.  Mean of Q, us: 782 blocks at W = 4 293, 141 so; one block of 2 M columns 54.2, 19.5;
+// mean of P: 10 rows of 36 chunks at W = 16 17.7, 11.7.  Sixteen and more at a time are 1 to 3 us slower per step.)
+constexpr int kPartLoads = 8;
+__device__ __forceinline__ double sum_partials(const double* __restrict__ src, int64_t wstride, int64_t bstride, int W,
+                                               int nb) {
+  const int64_t n = (int64_t)W * nb;
+  if (n == 1) return 0.0 + (double)(float)(0.0 + src[0]);   // the sums start from +0
+  if (n == 2) return sum_partials_by<2>(src, wstride, bstride, W, nb);
+  if (n <= 4) return sum_partials_by<4>(src, wstride, bstride, W, nb);
+  return sum_partials_by<kPartLoads>(src, wstride, bstride, W, nb);
 }
 
 // 1-D layers are sent raw: mean over the workers in worker order (fp64, rounded once) of one flat tile.

@@ -389,3 +389,20 @@ def test_a_configuration_at_the_limit_of_the_static_workspace_keeps_its_tiles():
         rng = np.random.default_rng(step)
         _forced_step(gpu, ora, [rng.standard_normal(1510000).astype(np.float32) for _ in range(4)], f"step {step}")
     gpu.destroy()
+
+
+@pytest.mark.parametrize("W", [1, 2, 3, 4, 5, 9])
+def test_partial_sums_of_every_count(W):
+    """One, two, three to four, seven to nine and sixteen to seventeen partial sums per worker, of P (256-column chunks)
+    and of Q (blocks of rows): a request that ends at, before and after a worker's last one."""
+    print("case partial sums, W", W, flush=True)
+    counts = [1, 2, 3, 4, 7, 8, 9, 16, 17]
+    shapes = [(6, 256 * n - 3, 1) for n in counts] + [(32 * n - 5, 5, 1) for n in counts] + [(128 * 9 - 5, 4, 1)]
+    layers = wl.make_layers(shapes)
+    N = wl.total_params(layers)
+    rng = np.random.default_rng(W)
+    q0 = rng.standard_normal(sum(c for (_, c, _) in shapes) * 3).astype(np.float32)
+    gpu, ora = H.make_pair(B.ACC_POWERSGD, layers, W, 3, 1, 100, 0.5, 1, q0)
+    for step in range(2):
+        _forced_step(gpu, ora, [(rng.standard_normal(N) * 0.01).astype(np.float32) for _ in range(W)], f"W {W} step {step}")
+    gpu.destroy()
