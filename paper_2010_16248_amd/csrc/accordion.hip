@@ -73,6 +73,7 @@ int fail(char* buf, int code, const char* msg) {
 // at W = 1, 356: 103.1 at 128, 104.9 at 64: twice the partial sums).
 constexpr int kComputeUnits = 256;
 constexpr int kFlatTileGroups = 8 * kComputeUnits;
+constexpr int kOrthLoads = 24;   // three requests of kPartLoads; see make_plan_tiled
 
 void choose_tiling(const acc_config* c, Plan& p) {
   auto workgroups = [&](int rows) {
@@ -136,7 +137,7 @@ int make_plan_tiled(const acc_config* c, Plan& p, char* err, bool coarse) {
   p.rmax = (c->method == ACC_POWERSGD) ? std::max(c->rank_crit, c->rank_noncrit) : 0;
   p.layers.resize(nl);
   if (c->method == ACC_POWERSGD && !coarse) choose_tiling(c, p);
-  int64_t ntile = 0, pmean_most = 0;   // pmean_most: partial sums of P of one layer, all workers
+  int64_t ntile = 0, orth_loads = 0;   // orth_loads: most partial sums of P that a thread of the orthogonalisation would add
   for (int i = 0; i < nl; ++i) {
     const acc_layer& l = c->layers[i];
     LayerDev& d = p.layers[i];
@@ -196,7 +197,10 @@ int make_plan_tiled(const acc_config* c, Plan& p, char* err, bool coarse) {
           }
         for (int r0 = 0; r0 < l.rows; r0 += kPmeanRows) p.ptiles.push_back(PTile{i, r0});
         for (int cc = 0; cc < d.n_colchunks; ++cc) p.qtiles.push_back(QTile{i, cc * kMatCols});
-        pmean_most = std::max(pmean_most, l.rows > kOrthThreads ? INT64_MAX : (int64_t)l.rows * p.rmax * d.n_colchunks * c->n_workers);
+        // an entry of P belongs to one thread, which adds its chunks and workers one after the other
+        const int64_t entries = (int64_t)l.rows * std::max(d.rank[0], d.rank[1]);
+        orth_loads = std::max(orth_loads, l.rows > kOrthThreads ? INT64_MAX
+                                : (entries + kOrthThreads - 1) / kOrthThreads * d.n_colchunks * c->n_workers);
       } else {
         d.vec_off = p.vec_total;
         p.vec_total += n;
@@ -213,10 +217,13 @@ int make_plan_tiled(const acc_config* c, Plan& p, char* err, bool coarse) {
       p.pay_stride += std::max(d.k[0], d.k[1]);
     }
   }
-  // The orthogonalisation's one workgroup per layer sums the partials of P itself while that is at most 36
-  // loads per thread (ResNet-18 shapes at W = 1: a step 102.0 us, 103.9 with the sums in a launch of their own;
-  // a layer of 47 loads per thread: 119.3 and 116.4; 144, ResNet-18 at W = 4: 199 and 173).
-  p.pmean_in_orth = pmean_most <= (int64_t)kOrthThreads * 36 ? 1 : 0;
+  // The orthogonalisation's one workgroup per layer sums the partials of P itself while none of its threads has
+  // more than kOrthLoads of them to add at the higher rank: that is where it stops gaining there (the lower rank has
+  // fewer and gains).  us per step so, and with the sums in a launch of their own, at the higher | the lower rank:
+  // 16 loads (six layers of 256 x 4096, W = 1) 49.2, 50.5 | 45.1, 46.9; 24 (256 x 6144, W = 1) 64.8, 65.5 | 60.1, 62.2;
+  // 24 (512 x 1536, W = 2) 67.9, 67.0 | 62.0, 63.3; 32 (256 x 8192, W = 1) 78.4, 78.4 | 73.6, 75.4; 36 (ResNet-18 shapes,
+  // W = 1) 76.6, 74.9 | 69.5, 70.8; 576 (twelve layers of 10 x 9216, W = 16) 161, 118.5.
+  p.pmean_in_orth = orth_loads <= kOrthLoads ? 1 : 0;
   // The right product takes the tiles from the last to the first when the error memory is larger than what the
   // 256 MB Infinity Cache still holds of it: VGG-19 shapes at W = 8 (658 MB) 571 -> 549 us per step, LSTM set at
   // W = 4 (820 MB) 1095 -> 1075; ResNet-18 at W = 4 (179 MB, all of it there) 172.8 -> 175.5, so not below.

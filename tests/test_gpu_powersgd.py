@@ -406,3 +406,34 @@ def test_partial_sums_of_every_count(W):
     for step in range(2):
         _forced_step(gpu, ora, [(rng.standard_normal(N) * 0.01).astype(np.float32) for _ in range(W)], f"W {W} step {step}")
     gpu.destroy()
+
+
+@pytest.mark.parametrize("name,shapes,W,crit,launched", [
+    # few entries of P, each with many partial sums: one thread would add 36 x 16 of them
+    ("short_wide", [(10, 9216, 1)] * 2, 16, 4, True),
+    ("two_rows", [(2, 60000, 1), (1, 77, 0)], 1, 2, True),
+    # the largest layer of ResNet-18 at W = 1: two entries of 18 chunks per thread at rank 4, one at rank 2
+    ("resnet_rank4", [(512, 4608, 1), (1, 512, 0)], 1, 4, True),
+    ("resnet_rank2", [(512, 4608, 1), (1, 512, 0)], 1, 2, False),
+    # the line: 24 partial sums per thread, 25
+    ("at_the_line", [(256, 24 * 256, 1)], 1, 4, False),
+    ("past_the_line", [(256, 24 * 256 + 1, 1)], 1, 4, True),
+    ("one_row_more", [(257, 12 * 256 + 1, 1)], 1, 4, True),
+    # layers that the orthogonalisation does not hold in registers
+    ("tall", [(1025, 8, 1)], 1, 1, True),
+])
+def test_where_the_partial_sums_of_p_are_added(name, shapes, W, crit, launched):
+    """In the orthogonalisation while none of its threads has many to add, else by a launch of their own: which
+    of the two ran, and the step against the oracle."""
+    print("case sums of P", name, flush=True)
+    layers = wl.make_layers(shapes)
+    N = wl.total_params(layers)
+    rng = np.random.default_rng(len(name))
+    q0 = rng.standard_normal(sum(c for (_, c, m) in shapes if m) * crit).astype(np.float32)
+    gpu, ora = H.make_pair(B.ACC_POWERSGD, layers, W, crit, 1, 100, 0.5, 1, q0)
+    gpu.set_profiling(1)
+    _forced_step(gpu, ora, [(rng.standard_normal(N) * 0.01).astype(np.float32) for _ in range(W)], name)
+    stages = gpu.get_profile()
+    assert stages["psgd_orth_kernel"][1] == 1
+    assert ("psgd_pmean_kernel" in stages) == launched, name
+    gpu.destroy()
