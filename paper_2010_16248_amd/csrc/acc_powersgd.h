@@ -622,7 +622,7 @@ __global__ __launch_bounds__(kOrthThreads) void psgd_orth_kernel(const Ws ws, co
   }
 }
 
-// ---- phase 1: Q partial = Delta^T P^ over one 64-row block -----------------------------------
+// ---- phase 1: Q partial = Delta^T P^ over one block of Ws::qrows rows ------------------------
 //
 // fp64 accumulation here too: where the memory dominates gradient + memory, Delta^T p^_k cancels
 // to a small fraction of its terms for the columns of P^ that the new gradient determines, and an
@@ -631,10 +631,13 @@ __global__ __launch_bounds__(kOrthThreads) void psgd_orth_kernel(const Ws ws, co
 // Tile: ws.qrows rows x 256 columns, one workgroup of 4 waves; a wave owns rows wave, wave + 4, ...
 // and keeps the sums of its four columns per lane in registers; the four waves' sums meet in LDS.
 // Bound by memory, or by latency where few workgroups share the chip, like the first pass: the next batch of
-// rows is requested before the current one is used (ResNet-18 shapes 39.1 -> 33.0 us at W = 4, 16.0 -> 11.4 at
-// W = 1; 2 rows per batch: 2 us more per step at W = 4; 8: within 1 us, for 32 more registers).
+// rows is requested before the current one is used (ResNet-18 shapes 39.1 -> 32.0 us at W = 4, 16.0 -> 10.0 at
+// W = 1; 2 rows per batch: 2 us more per step at W = 4; 8: within 1 us, for 32 more registers).  Rows beyond the tile
+// are asked for only where a batch straddles its end, not by the first batch nor by one after the last (100 layers of
+// 2 x 20000 at W = 4 118.5 -> 112.6 us, 200 of 512 x 9 33.0 -> 30.9).
 constexpr int kQBatch = 4;   // rows a wave requests together; two such batches are in flight
 
+// (From clamped addresses: a request behind a branch would make every wait in the loop a wait for all of them.)
 template <int MODE>
 __device__ __forceinline__ void q_load(const float* __restrict__ e, int cols, int row_end, const LaneCols& lc, int i0,
                                        float (&d)[kQBatch][4]) {
@@ -656,9 +659,7 @@ __device__ __forceinline__ void q_loop(const Ws& ws, const LayerDev& L, const Ma
   for (int v = 0; v < 4; ++v)
 #pragma unroll
     for (int k = 0; k < R; ++k) acc[v][k] = 0.0;
-  for (int i0 = t.row0 + wave; i0 < row_end; i0 += 4 * kQBatch) {
-    float nxt[kQBatch][4];
-    q_load<MODE>(e, L.cols, row_end, lc, i0 + 4 * kQBatch, nxt);
+  auto use = [&](int i0) {
 #pragma unroll
     for (int b = 0; b < kQBatch; ++b) {
       const int i = i0 + 4 * b;
@@ -674,11 +675,18 @@ __device__ __forceinline__ void q_loop(const Ws& ws, const LayerDev& L, const Ma
           for (int k = 0; k < R; ++k) acc[v][k] = fma(dd[v], p[k], acc[v][k]);
       }
     }
+  };
+  int i0 = t.row0 + wave;
+  for (; i0 + 4 * kQBatch < row_end; i0 += 4 * kQBatch) {
+    float nxt[kQBatch][4];
+    q_load<MODE>(e, L.cols, row_end, lc, i0 + 4 * kQBatch, nxt);
+    use(i0);
 #pragma unroll
     for (int b = 0; b < kQBatch; ++b)
 #pragma unroll
       for (int v = 0; v < 4; ++v) cur[b][v] = nxt[b][v];
   }
+  use(i0);
   // the four waves' sums, in the fixed order (wave 0 + wave 2) + (wave 1 + wave 3)
   if (wave >= 2) {
 #pragma unroll
@@ -726,9 +734,14 @@ __device__ __forceinline__ void q_tile(const Ws& ws, const LayerDev& L, const Ma
   const LaneCols lc = lane_cols<MODE>(t.col0, lane, L.cols);
   const float* __restrict__ e = e_w + L.offset;
   const int row_end = min(t.row0 + ws.qrows, L.rows);
-  // the first rows of Delta and the tile's rows of P^ (for LDS) are requested together
+  // the first rows of Delta and the tile's rows of P^ (for LDS) are requested together; the wait for the latter
+  // covers the former, so branches cost nothing here
   float first[kQBatch][4];
-  q_load<MODE>(e, L.cols, row_end, lc, t.row0 + wave, first);
+#pragma unroll
+  for (int b = 0; b < kQBatch; ++b) {
+    const int i = t.row0 + wave + 4 * b;
+    if (i < row_end) load_row<MODE>(e + (int64_t)i * L.cols, lc.c, L.cols, first[b]);   // wave-uniform
+  }
   const int r = level ? L.rank[1] : L.rank[0];
   for (int s = threadIdx.x; s < ws.qrows * kMaxRank; s += 256) {
     const int pr = s >> 2, pk = s & 3;

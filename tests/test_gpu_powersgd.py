@@ -437,3 +437,19 @@ def test_where_the_partial_sums_of_p_are_added(name, shapes, W, crit, launched):
     assert stages["psgd_orth_kernel"][1] == 1
     assert ("psgd_pmean_kernel" in stages) == launched, name
     gpu.destroy()
+
+
+@pytest.mark.parametrize("cols", [3, 9, 260])
+def test_right_product_of_every_number_of_rows_in_a_tile(cols):
+    """One to forty rows, in tiles of 32: no row, one row, a whole and a partial batch of rows per wave, before the
+    last batch and in it, with and without a batch after the first."""
+    print("case rows of a tile, cols", cols, flush=True)
+    shapes = [(n, cols, 1) for n in range(1, 41)]
+    layers = wl.make_layers(shapes)
+    N = wl.total_params(layers)
+    rng = np.random.default_rng(cols)
+    q0 = rng.standard_normal(cols * 2 * len(shapes)).astype(np.float32)
+    gpu, ora = H.make_pair(B.ACC_POWERSGD, layers, 1, 2, 1, 100, 0.5, 1, q0)
+    for step in range(2):
+        _forced_step(gpu, ora, [(rng.standard_normal(N) * 0.01).astype(np.float32)], f"cols {cols} step {step}")
+    gpu.destroy()
