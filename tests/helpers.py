@@ -53,3 +53,27 @@ def oracle_state_blob(gpu, ora):
     """The oracle's state in the library's state layout (teacher forcing)."""
     q = np.concatenate([ora.Q[li].reshape(-1) for li in sorted(ora.Q)]) if ora.Q else np.zeros(0, np.float32)
     return gpu.pack_state(ora.e, ora.A, q, ora.norm_old, ora.has_old, ora.level)
+
+
+def powersgd_workspace_bytes(layers, W, rmax, rows_first, rows_right):
+    """accordion_workspace_bytes of a PowerSGD configuration whose matrix tiles have rows_first rows (first pass,
+    decompression) and rows_right rows (right product), region by region: tells which tiles a configuration got."""
+    lt = layer_tuples(layers)
+    end = max(off + r * c for off, r, c, _ in lt)
+    N64 = (end + 63) // 64 * 64
+    mats = [(r, c) for _, r, c, m in lt if m]
+
+    def up(a, b):
+        return -(-a // b)
+
+    def tiles(rows):
+        return sum(up(r, rows) * up(c, 256) for r, c in mats)
+
+    nl, flat = len(lt), sum(up(r * c, 8192) for _, r, c, _ in lt)
+    p_total = sum(r for r, _ in mats) * rmax
+    regions = [120 * nl, 16 * flat, 16 * tiles(rows_first), 16 * tiles(rows_right), 8 * sum(up(c, 256) for _, c in mats),
+               8 * sum(up(r, 16) for r, _ in mats), 4 * sum(up(r * c, 8192) for _, r, c, m in lt if not m), 4 * len(mats)]
+    regions += [4 * nl] * 6 + [48, 4 * N64, 4 * N64 * W, 8 * flat, 8 * tiles(rows_first), 4, 0, 32]
+    regions += [16 * sum(c for _, c in mats), 4 * p_total, 8 * p_total, 8 * W * rmax * sum(r * up(c, 256) for r, c in mats),
+                8 * W * rmax * sum(c * up(r, rows_right) for r, c in mats), 4 * sum(r * c for _, r, c, m in lt if not m), 4]
+    return sum(up(b, 256) * 256 for b in regions)

@@ -453,3 +453,26 @@ def test_right_product_of_every_number_of_rows_in_a_tile(cols):
     for step in range(2):
         _forced_step(gpu, ora, [(rng.standard_normal(N) * 0.01).astype(np.float32)], f"cols {cols} step {step}")
     gpu.destroy()
+
+
+def test_a_step_in_a_workspace_that_holds_only_the_tallest_tiles(monkeypatch):
+    """A buffer of the size that 64- and 128-row tiles need, where the configuration's own choice is flatter: the
+    context takes the tall tiles and stays inside (the tail behind the buffer keeps its pattern)."""
+    import torch
+    print("case least workspace", flush=True)
+    shapes = [(64, 576, 1), (1, 64, 0), (129, 255, 1), (300, 514, 1), (10, 512, 1)]
+    layers, W = wl.make_layers(shapes), 2
+    least = H.powersgd_workspace_bytes(layers, W, 4, 64, 128)
+    cfg, keep = B.make_config(B.ACC_POWERSGD, layers, W, 4, 1)
+    assert least < B.accordion_workspace_bytes(cfg)
+    rng = np.random.default_rng(5)
+    q0 = rng.standard_normal(sum(c for (_, c, m) in shapes if m) * 4).astype(np.float32)
+    monkeypatch.setattr(B, "accordion_workspace_bytes", lambda cfg: least)
+    gpu, ora = H.make_pair(B.ACC_POWERSGD, layers, W, 4, 1, 100, 0.5, 1, q0)
+    behind = gpu.workspace[gpu._ws_ptr - gpu.workspace.data_ptr() + least:]
+    behind.fill_(0xA5)
+    for step in range(3):
+        grads = [(rng.standard_normal(wl.total_params(layers)) * 0.01).astype(np.float32) for _ in range(W)]
+        _forced_step(gpu, ora, grads, f"step {step}")
+    assert torch.all(behind == 0xA5)
+    gpu.destroy()
