@@ -151,27 +151,6 @@ struct Ws {
 
 // ---- wave64 helpers ---------------------------------------------------------------
 
-template <int CTRL>
-__device__ __forceinline__ float dpp_f(float v) {
-  return __builtin_bit_cast(
-      float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, false));
-}
-
-// Sum over the 64 lanes, same value (bit for bit) returned to every lane.
-// All 64 lanes must be active.  Order: quads, 8, 16 by DPP, then the four rows.
-__device__ __forceinline__ float wave_sum(float v) {
-  v += dpp_f<0xB1>(v);    // quad_perm [1,0,3,2]
-  v += dpp_f<0x4E>(v);    // quad_perm [2,3,0,1]
-  v += dpp_f<0x141>(v);   // row_half_mirror
-  v += dpp_f<0x140>(v);   // row_mirror
-  const int b = __builtin_bit_cast(int, v);
-  const float r0 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(b, 0));
-  const float r1 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(b, 16));
-  const float r2 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(b, 32));
-  const float r3 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(b, 48));
-  return (r0 + r1) + (r2 + r3);
-}
-
 __device__ __forceinline__ double wave_sum_f64(double v) {
 #pragma unroll
   for (int d = 1; d < kWave; d <<= 1) v += __shfl_xor(v, d, kWave);
@@ -190,8 +169,8 @@ __device__ __forceinline__ double readlane_d(double v, int l) {
                           __builtin_amdgcn_readlane(__double2loint(v), l));
 }
 
-// fp64 sum over the 64 lanes in the order of wave_sum (lane exchanges through DPP moves, no LDS
-// traffic), same value returned to every lane.  All 64 lanes must be active.
+// fp64 sum over the 64 lanes (lane exchanges through DPP moves, no LDS traffic), same value (bit for bit)
+// returned to every lane.  All 64 lanes must be active.  Order: quads, 8, 16 by DPP, then the four rows.
 __device__ __forceinline__ double wave_sum_d(double v) {
   v += dpp_d<0xB1>(v);
   v += dpp_d<0x4E>(v);
@@ -334,39 +313,36 @@ __device__ __forceinline__ void st16_stream(float* p, const float4& v) {
 // the compiler into one access (which loses the hint) unless something in one of them differs.
 __device__ __forceinline__ void keep_apart() { asm volatile(""); }
 
-// Masked access: elements outside [lo, hi) are neither read (they count as zero) nor written.
-__device__ __forceinline__ float4 ld_quad(const float* __restrict__ p, int64_t base, int64_t lo,
-                                          int64_t hi) {
-  if (base >= lo && base + 4 <= hi) return ld16(p + base);
+// Masked access: elements from hi on are neither read (they count as zero) nor written.
+__device__ __forceinline__ float4 ld_quad(const float* __restrict__ p, int64_t base, int64_t hi) {
+  if (base + 4 <= hi) return ld16(p + base);
   float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-  if (base + 0 >= lo && base + 0 < hi) v.x = p[base + 0];
-  if (base + 1 >= lo && base + 1 < hi) v.y = p[base + 1];
-  if (base + 2 >= lo && base + 2 < hi) v.z = p[base + 2];
-  if (base + 3 >= lo && base + 3 < hi) v.w = p[base + 3];
+  if (base + 0 < hi) v.x = p[base + 0];
+  if (base + 1 < hi) v.y = p[base + 1];
+  if (base + 2 < hi) v.z = p[base + 2];
+  if (base + 3 < hi) v.w = p[base + 3];
   return v;
 }
 
-__device__ __forceinline__ void st_quad(float* __restrict__ p, int64_t base, int64_t lo, int64_t hi,
-                                        float4 v) {
-  if (base >= lo && base + 4 <= hi) {
+__device__ __forceinline__ void st_quad(float* __restrict__ p, int64_t base, int64_t hi, float4 v) {
+  if (base + 4 <= hi) {
     st16(p + base, v);
     return;
   }
-  if (base + 0 >= lo && base + 0 < hi) p[base + 0] = v.x;
-  if (base + 1 >= lo && base + 1 < hi) p[base + 1] = v.y;
-  if (base + 2 >= lo && base + 2 < hi) p[base + 2] = v.z;
-  if (base + 3 >= lo && base + 3 < hi) p[base + 3] = v.w;
+  if (base + 0 < hi) p[base + 0] = v.x;
+  if (base + 1 < hi) p[base + 1] = v.y;
+  if (base + 2 < hi) p[base + 2] = v.z;
+  if (base + 3 < hi) p[base + 3] = v.w;
 }
 
 // Access to group q of a tile.  AL (a workgroup-uniform property of the tile): it holds a whole number
 // of groups, so no element needs a mask.
 // STREAM: non-temporal access on the mask-free path (the masked path is rare and stays plain).
 template <bool AL, bool STREAM = false>
-__device__ __forceinline__ float4 ldq(const float* __restrict__ p, int64_t a0, int64_t lo, int64_t hi,
-                                      int q, bool in) {
+__device__ __forceinline__ float4 ldq(const float* __restrict__ p, int64_t a0, int64_t hi, int q, bool in) {
   if (!in) return make_float4(0.f, 0.f, 0.f, 0.f);
   if (AL) return STREAM ? ld16_stream(p + a0 + 4 * (int64_t)q) : ld16(p + a0 + 4 * (int64_t)q);
-  return ld_quad(p, a0 + 4 * (int64_t)q, lo, hi);
+  return ld_quad(p, a0 + 4 * (int64_t)q, hi);
 }
 
 // Group q of a tile with AL, loaded whatever lane asks: the caller has clamped q into the tile
@@ -378,13 +354,12 @@ __device__ __forceinline__ float4 ldq_clamped(const float* __restrict__ p, int64
 }
 
 template <bool AL, bool STREAM = false>
-__device__ __forceinline__ void stq(float* __restrict__ p, int64_t a0, int64_t lo, int64_t hi, int q,
-                                    float4 v) {
+__device__ __forceinline__ void stq(float* __restrict__ p, int64_t a0, int64_t hi, int q, float4 v) {
   if (AL) {
     if (STREAM) st16_stream(p + a0 + 4 * (int64_t)q, v);
     else st16(p + a0 + 4 * (int64_t)q, v);
   } else {
-    st_quad(p, a0 + 4 * (int64_t)q, lo, hi, v);
+    st_quad(p, a0 + 4 * (int64_t)q, hi, v);
   }
 }
 
@@ -423,17 +398,15 @@ __device__ __forceinline__ float comp(const float4& v, int c) {
 
 // Geometry of one flat tile in absolute element indices.
 struct TileGeom {
-  int64_t lo, hi;   // the tile's elements: [lo, hi)
-  int64_t a0;       // first element of group 0: lo
+  int64_t a0, hi;   // the tile's elements: [a0, hi)
   int32_t nquads;   // groups of four
   bool aligned;     // every group is whole
 };
 
 __device__ __forceinline__ TileGeom tile_geom(const LayerDev& L, const FlatTile& t) {
   TileGeom g;
-  g.lo = L.offset + t.start;
-  g.hi = g.lo + t.count;
-  g.a0 = g.lo;
+  g.a0 = L.offset + t.start;
+  g.hi = g.a0 + t.count;
   g.nquads = (t.count + 3) >> 2;
   g.aligned = (t.count & 3) == 0;
   return g;

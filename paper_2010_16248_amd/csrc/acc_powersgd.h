@@ -331,10 +331,10 @@ __global__ __launch_bounds__(256) void psgd_ef_p_kernel(const Ws ws, const GradP
     double a_sq = 0.0;
     for (int q = threadIdx.x; q < tg.nquads; q += kFlatThreads) {
       const int64_t base = tg.a0 + 4 * (int64_t)q;
-      float4 a = a_fresh ? make_float4(0.f, 0.f, 0.f, 0.f) : ld_quad(ws.A, base, tg.lo, tg.hi);
-      const float4 gv = ld_quad(g, base, tg.lo, tg.hi);
+      float4 a = a_fresh ? make_float4(0.f, 0.f, 0.f, 0.f) : ld_quad(ws.A, base, tg.hi);
+      const float4 gv = ld_quad(g, base, tg.hi);
       a.x += gv.x; a.y += gv.y; a.z += gv.z; a.w += gv.w;
-      st_quad(ws.A, base, tg.lo, tg.hi, a);
+      st_quad(ws.A, base, tg.hi, a);
       a_sq += sq4(a);                                        // elements outside the tile were loaded as zeros
     }
     a_sq = block_sum4_d(a_sq, red4);

@@ -21,7 +21,7 @@ __global__ __launch_bounds__(256) void norm_refresh_kernel(const Ws ws) {
     const FlatTile ft = ws.ftiles[blockIdx.x];
     const LayerDev& L = ws.layers[ft.layer];
     const TileGeom tg = tile_geom(L, ft);
-    for (int q = tid; q < tg.nquads; q += kFlatThreads) s += sq4(ld_quad(ws.A, tg.a0 + 4 * (int64_t)q, tg.lo, tg.hi));
+    for (int q = tid; q < tg.nquads; q += kFlatThreads) s += sq4(ld_quad(ws.A, tg.a0 + 4 * (int64_t)q, tg.hi));
     s = block_sum4_d(s, red);
     if (tid == 0) ws.norm_part[blockIdx.x] = s;
   } else {
@@ -49,12 +49,12 @@ __global__ __launch_bounds__(256) void norm_partial_kernel(const Ws ws) {
   const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
   for (int q = tid; q < tg.nquads; q += kFlatThreads) {
     const int64_t base = tg.a0 + 4 * (int64_t)q;
-    const float4 a = ld_quad(ws.A, base, tg.lo, tg.hi);   // outside the tile: 0
+    const float4 a = ld_quad(ws.A, base, tg.hi);   // outside the tile: 0
     s += (double)a.x * (double)a.x;
     s += (double)a.y * (double)a.y;
     s += (double)a.z * (double)a.z;
     s += (double)a.w * (double)a.w;
-    st_quad(ws.A, base, tg.lo, tg.hi, zero);
+    st_quad(ws.A, base, tg.hi, zero);
   }
   s = wave_sum_f64(s);
   if ((tid & 63) == 0) red[tid >> 6] = s;
@@ -71,7 +71,7 @@ __global__ __launch_bounds__(256) void zero_accum_kernel(const Ws ws, int zero_a
   const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
   if (zero_a) {
     for (int q = threadIdx.x; q < tg.nquads; q += kFlatThreads)
-      st_quad(ws.A, tg.a0 + 4 * (int64_t)q, tg.lo, tg.hi, zero);
+      st_quad(ws.A, tg.a0 + 4 * (int64_t)q, tg.hi, zero);
   } else if (blockIdx.x == 0 && threadIdx.x == 0) {
     *ws.a_fresh = 1u;
   }
@@ -132,7 +132,7 @@ __global__ __launch_bounds__(256) void msdr_sq_kernel(const Ws ws, const float* 
   const TileGeom tg = tile_geom(L, ft);
   double s = 0.0;
   for (int q = tid; q < tg.nquads; q += kFlatThreads) {
-    const float4 a = ld_quad(g0, tg.a0 + 4 * (int64_t)q, tg.lo, tg.hi);
+    const float4 a = ld_quad(g0, tg.a0 + 4 * (int64_t)q, tg.hi);
     s += (double)a.x * (double)a.x;
     s += (double)a.y * (double)a.y;
     s += (double)a.z * (double)a.z;

@@ -212,7 +212,7 @@ constexpr bool kStreamOut = true;    // averaged gradient: written once, read by
 template <bool AL, bool STREAM = false>
 __device__ __forceinline__ float4 ld_span(const float* __restrict__ p, const TileGeom& tg,
                                           const WaveSpan& sp, int q) {
-  return ldq<AL, STREAM>(p, tg.a0, tg.lo, tg.hi, q, q < sp.qend);
+  return ldq<AL, STREAM>(p, tg.a0, tg.hi, q, q < sp.qend);
 }
 
 // Group q of the wave's span, requested whether or not the lane has one (beyond the span every lane asks
@@ -229,7 +229,7 @@ template <bool AL>
 __device__ __forceinline__ bool elem_valid(const TileGeom& tg, int q, int c, bool in_span) {
   if (AL) return in_span;
   const int64_t i = tg.a0 + 4 * (int64_t)q + c;
-  return in_span && i >= tg.lo && i < tg.hi;
+  return in_span && i < tg.hi;
 }
 
 // Lane mask of elem_valid for component c; for an aligned tile it is the span mask m_span.
@@ -547,10 +547,10 @@ __device__ __forceinline__ void ef_hist_tile(const Ws& ws, const GradPtrs& gp, i
       if (pend) ec[u] = drop_kept<AL>(tg, q, qa, ballot64(qa), ps, ec[u], lane);
       const float4 d = make_float4(gc[u].x + ec[u].x, gc[u].y + ec[u].y, gc[u].z + ec[u].z, gc[u].w + ec[u].w);
       if (qa) {
-        stq<AL>(e, tg.a0, tg.lo, tg.hi, q, d);
+        stq<AL>(e, tg.a0, tg.hi, q, d);
         if (A) {
           const float4 a = make_float4(ac[u].x + gc[u].x, ac[u].y + gc[u].y, ac[u].z + gc[u].z, ac[u].w + gc[u].w);
-          stq<AL, kStreamA>(A, tg.a0, tg.lo, tg.hi, q, a);
+          stq<AL, kStreamA>(A, tg.a0, tg.hi, q, a);
           a_sq += sq4(a);                                    // elements outside the tile were loaded as zeros
         }
       }
@@ -798,7 +798,7 @@ __device__ __forceinline__ void pick_small_layer(const Ws& ws, const LayerDev& L
   for (int j = 0; j < 2; ++j) {
     const int q = tid + j * kPickThreads;
     float4 d = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (q < tg.nquads) d = ld_quad(e, tg.a0 + 4 * (int64_t)q, tg.lo, tg.hi);
+    if (q < tg.nquads) d = ld_quad(e, tg.a0 + 4 * (int64_t)q, tg.hi);
 #pragma unroll
     for (int c = 0; c < 4; ++c) { key[j][c] = key_of(comp(d, c)); valid[j][c] = 4 * q + c < ft.count; }
   }
@@ -1554,7 +1554,7 @@ __device__ __forceinline__ void compact_selected(const TileGeom& tg, int64_t lay
     if (sel[1]) z.y = 0.f;
     if (sel[2]) z.z = 0.f;
     if (sel[3]) z.w = 0.f;
-    stq<AL>(e, tg.a0, tg.lo, tg.hi, q, z);
+    stq<AL>(e, tg.a0, tg.hi, q, z);
   }
   run.pos_run += total;
 }
@@ -1688,7 +1688,7 @@ __device__ __forceinline__ void compact_mean_tile(const Ws& ws, const FlatTile& 
   auto load_group = [&](const float* __restrict__ e, int c, int j, int q_end) {
     const int q = span.qbeg + (c * G + j) * kWave + lane;
     if (AL) return ldq_clamped(e, tg.a0, min(q, max(q_end - 1, span.qbeg)));
-    return ldq<AL>(e, tg.a0, tg.lo, tg.hi, q, q < q_end);
+    return ldq<AL>(e, tg.a0, tg.hi, q, q < q_end);
   };
   const float fw = (float)W;
   // x / W and x * (1 / W) are the same real number when W is a power of two, so both round alike
@@ -1839,15 +1839,15 @@ __device__ __forceinline__ void compact_mean_tile(const Ws& ws, const FlatTile& 
           nesterov4(v, wq[j], vq[j], sink);
           if (sink.stream_wv) {
             keep_apart();
-            stq<AL, true>(sink.wt, tg.a0, tg.lo, tg.hi, q, wq[j]);
-            stq<AL, true>(sink.vel, tg.a0, tg.lo, tg.hi, q, vq[j]);
+            stq<AL, true>(sink.wt, tg.a0, tg.hi, q, wq[j]);
+            stq<AL, true>(sink.vel, tg.a0, tg.hi, q, vq[j]);
             keep_apart();
           } else {
-            stq<AL>(sink.wt, tg.a0, tg.lo, tg.hi, q, wq[j]);
-            stq<AL>(sink.vel, tg.a0, tg.lo, tg.hi, q, vq[j]);
+            stq<AL>(sink.wt, tg.a0, tg.hi, q, wq[j]);
+            stq<AL>(sink.vel, tg.a0, tg.hi, q, vq[j]);
           }
         } else {
-          stq<AL, kStreamOut>(sink.out, tg.a0, tg.lo, tg.hi, q, v);
+          stq<AL, kStreamOut>(sink.out, tg.a0, tg.hi, q, v);
         }
       }
     }
@@ -2084,15 +2084,15 @@ __device__ __forceinline__ void gather_mean_tile(const Ws& ws, const FlatTile& f
           nesterov4(v, wq[j], vq[j], sink);
           if (sink.stream_wv) {
             keep_apart();
-            stq<AL, true>(sink.wt, tg.a0, tg.lo, tg.hi, q, wq[j]);
-            stq<AL, true>(sink.vel, tg.a0, tg.lo, tg.hi, q, vq[j]);
+            stq<AL, true>(sink.wt, tg.a0, tg.hi, q, wq[j]);
+            stq<AL, true>(sink.vel, tg.a0, tg.hi, q, vq[j]);
             keep_apart();
           } else {
-            stq<AL>(sink.wt, tg.a0, tg.lo, tg.hi, q, wq[j]);
-            stq<AL>(sink.vel, tg.a0, tg.lo, tg.hi, q, vq[j]);
+            stq<AL>(sink.wt, tg.a0, tg.hi, q, wq[j]);
+            stq<AL>(sink.vel, tg.a0, tg.hi, q, vq[j]);
           }
         } else {
-          stq<AL, kStreamOut>(sink.out, tg.a0, tg.lo, tg.hi, q, v);
+          stq<AL, kStreamOut>(sink.out, tg.a0, tg.hi, q, v);
         }
       }
     }
@@ -2212,19 +2212,19 @@ __device__ __forceinline__ void sparse_mean_body(const Ws& ws, const Sink& sink)
   for (int q = tid; q < tg.nquads; q += kFlatThreads) {
     const int64_t base = tg.a0 + 4 * (int64_t)q;
     float4 v;
-    const int64_t i0 = base - tg.lo;
-    v.x = (i0 + 0 >= 0 && i0 + 0 < ft.count) ? acc[i0 + 0] / fw : 0.f;
-    v.y = (i0 + 1 >= 0 && i0 + 1 < ft.count) ? acc[i0 + 1] / fw : 0.f;
-    v.z = (i0 + 2 >= 0 && i0 + 2 < ft.count) ? acc[i0 + 2] / fw : 0.f;
-    v.w = (i0 + 3 >= 0 && i0 + 3 < ft.count) ? acc[i0 + 3] / fw : 0.f;
+    const int i0 = 4 * q;
+    v.x = acc[i0] / fw;                                    // the tile's last group may be a partial one
+    v.y = i0 + 1 < ft.count ? acc[i0 + 1] / fw : 0.f;
+    v.z = i0 + 2 < ft.count ? acc[i0 + 2] / fw : 0.f;
+    v.w = i0 + 3 < ft.count ? acc[i0 + 3] / fw : 0.f;
     if (UPD) {
-      float4 wq = ld_quad(sink.wt, base, tg.lo, tg.hi);
-      float4 vq = ld_quad(sink.vel, base, tg.lo, tg.hi);
+      float4 wq = ld_quad(sink.wt, base, tg.hi);
+      float4 vq = ld_quad(sink.vel, base, tg.hi);
       nesterov4(v, wq, vq, sink);
-      st_quad(sink.wt, base, tg.lo, tg.hi, wq);
-      st_quad(sink.vel, base, tg.lo, tg.hi, vq);
+      st_quad(sink.wt, base, tg.hi, wq);
+      st_quad(sink.vel, base, tg.hi, vq);
     } else {
-      st_quad(sink.out, base, tg.lo, tg.hi, v);
+      st_quad(sink.out, base, tg.hi, v);
     }
   }
 }
@@ -2253,7 +2253,7 @@ __device__ __forceinline__ void residual_tile(const Ws& ws, int w, const FlatTil
     const bool qa = q < span.qend;
     const float4 d = ld_span<AL>(e, tg, span, q);
     const float4 z = drop_kept<AL>(tg, q, qa, ballot64(qa), ps, d, lane);
-    if (qa && (z.x != d.x || z.y != d.y || z.z != d.z || z.w != d.w)) stq<AL>(e, tg.a0, tg.lo, tg.hi, q, z);
+    if (qa && (z.x != d.x || z.y != d.y || z.z != d.z || z.w != d.w)) stq<AL>(e, tg.a0, tg.hi, q, z);
   }
 }
 
