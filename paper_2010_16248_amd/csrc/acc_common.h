@@ -120,8 +120,10 @@ struct Ws {
   uint32_t* hist2m;            // W x L x 64: level-2 counts of b1 of a layer whose guess missed
   uint32_t* lflag;             // L: nonzero = this step's compaction of the layer reads Delta (some worker's guess
                                //   missed, or the guess was a band), not the candidate lists
-  uint2* b1hist;               // W x L x 2 (level): {b1 | (last move + 64) << 16 | steps at rest << 24, step number} of the last step at this level
-  uint32_t* guess;             // W x L x 2 (level): lowest guessed level-1 bin | number of bins << 16, or a special value
+  uint2* b1hist;               // W x L x 2 (level): {b1 | largest recent move in level-2 cells << 11 | (last move in bins + 64) << 16 |
+                               //   steps at rest << 24, step number} of the last step at this level
+  uint32_t* guess;             // W x L x 2 (level): lowest guessed level-1 bin | number of bins << 16 | first level-2 cell of it << 24,
+                               //   or a special value
   uint4* qinfo;                // W x q_stride: per wave quarter {entries above what is listed (one-bin and band
                                //   lists), listed entries, 0, exact zeros (one-bin and zero-guess lists)}
   uint32_t* cand_val;          // W x q_stride x kCandCap: per wave quarter, the values of its candidates (or keys of one bin)

@@ -1382,7 +1382,9 @@ __device__ __forceinline__ void pick3_body(const Ws& ws, int w0, uint32_t step_i
   }
   if (tid == 0) {
     sp->T = T; sp->ktie = ktie; sp->alleq = alleq; sp->mode = 0u;
-    // Next step's guess at this level, from the bin this step ended in and the last two moves.
+    // Next step's guess at this level, from the bin this step ended in and the last two moves.  (The step number is an
+    // argument of the launch: in a replayed graph of one step no two steps are consecutive, and the guess stays at its
+    // widest, with its floor at a whole bin.)
     // b1hist: (b1 | m << 11 | (last move + 64) << 16 | steps at rest << 24, step); m: see kFloorCells
     const uint2 prev = prev_hist;
     const bool consecutive = prev.y + 1u == step_id;

@@ -70,7 +70,11 @@ int fail(char* buf, int code, const char* msg) {
 // shapes at W = 1, 1476 workgroups: a step 106 us at 32, 103 at 16; VGG-19 shapes at W = 1, 2626: 114.3 and 115.0;
 // ResNet-18 at W = 4: 172.8 at 32, 179 at 64).  Right product: 128 rows, fewer while that leaves compute units
 // without a workgroup (four small layers, 56 workgroups: a step 28.5 us at 128, 26.7 at 64, 26.9 at 32; ResNet-18
-// at W = 1, 356: 103.1 at 128, 104.9 at 64: twice the partial sums).
+// at W = 1, 356: 103.1 at 128, 104.9 at 64: twice the partial sums).  The workgroups counted are those of the whole
+// step's launches, all workers in one: the tiles of the decompression, which runs once for all of them, and of the
+// call-by-call path, one worker per launch, are the same ones, as the partial sums and the norms' tiles have to be.
+// (Call by call against 64- and 128-row tiles throughout: four small layers at W = 16 219 us a step and 436, odd sizes at
+// W = 3 151 and 194, ResNet-18 shapes at W = 4 212 and 232, VGG-19 shapes at W = 8 664 and 781, the loops' share included.)
 constexpr int kComputeUnits = 256;
 constexpr int kFlatTileGroups = 8 * kComputeUnits;
 constexpr int kOrthLoads = 24;   // three requests of kPartLoads; see make_plan_tiled
@@ -227,6 +231,7 @@ int make_plan_tiled(const acc_config* c, Plan& p, char* err, bool coarse) {
   // The right product takes the tiles from the last to the first when the error memory is larger than what the
   // 256 MB Infinity Cache still holds of it: VGG-19 shapes at W = 8 (658 MB) 571 -> 549 us per step, LSTM set at
   // W = 4 (820 MB) 1095 -> 1075; ResNet-18 at W = 4 (179 MB, all of it there) 172.8 -> 175.5, so not below.
+  // Call by call only the tiles of a worker are reversed: the order of the workers is the caller's.
   p.q_reversed = 4 * p.e_stride * c->n_workers > (int64_t(224) << 20) ? 1 : 0;
   p.q_stride = 4 * ntile + nl;
 
