@@ -329,15 +329,16 @@ EDGE_SHAPES = [(r, c, 1) for r, c in ((1, 1), (15, 2), (17, 3), (33, 4), (16, 5)
                                       (16, 256), (17, 257), (33, 259), (3, 513))] + [(1, 1031, 0)]
 
 
-@pytest.mark.parametrize("name,shapes,W", [
-    # 16-row tiles, 32-row tiles of the right product, P summed up in the orthogonalisation
-    ("few_tiles", EDGE_SHAPES, 2),
-    # 16-row tiles, 128-row tiles of the right product, P summed up by its own launch
-    ("more_tiles", EDGE_SHAPES + [(700, 1300, 1)], 8),
-    # 32-row tiles, a layer too tall for the registers, a memory beyond the Infinity Cache (tiles in reverse order)
-    ("many_tiles", EDGE_SHAPES + [(1030, 1999, 1)], 30),
+@pytest.mark.parametrize("name,shapes,W,heights,pmean,reversed_", [
+    # rows of the tiles of the first pass and of the right product; P summed up by a launch of its own; the right
+    # product from the last tile (a memory beyond the Infinity Cache)
+    ("few_tiles", EDGE_SHAPES, 2, (16, 32), False, False),
+    ("some_tiles", EDGE_SHAPES, 13, (16, 64), True, False),
+    ("more_tiles", EDGE_SHAPES + [(700, 1300, 1)], 8, (16, 128), True, False),
+    # with a layer too tall for the registers
+    ("many_tiles", EDGE_SHAPES + [(1030, 1999, 1)], 30, (32, 128), True, True),
 ])
-def test_tilings_and_unaligned_rows(name, shapes, W):
+def test_tilings_and_unaligned_rows(name, shapes, W, heights, pmean, reversed_):
     """Rows of 1 to 3, of exactly 4 and of a ragged number of columns, starting on no 16-byte boundary, under each of
     the tilings, against the oracle; and the deferred residual against the explicit one, bit for bit."""
     print("case tilings", name, flush=True)
@@ -351,8 +352,14 @@ def test_tilings_and_unaligned_rows(name, shapes, W):
         return [(rng.standard_normal(N, dtype=np.float32) * np.float32(0.01)) for _ in range(W)]
 
     gpu, ora = H.make_pair(B.ACC_POWERSGD, layers, W, 4, 3, 100, 0.5, 1, q0)
+    # the case is the one that its name says
+    assert gpu.workspace_bytes == H.powersgd_workspace_bytes(layers, W, 4, *heights), name
+    assert (4 * (-(-N // 64) * 64) * W > 224 << 20) == reversed_, name
     grads = batch()
+    gpu.set_profiling(1)
     _forced_step(gpu, ora, grads, name)
+    assert ("psgd_pmean_kernel" in gpu.get_profile()) == pmean, name
+    gpu.set_profiling(0)
     twin = B.Accordion(B.ACC_POWERSGD, lt, W, 4, 3, 100, 0.5, 1, q0)
     twin.set_state(gpu.get_state())
     dev, outs = [H.to_dev(g) for g in batch()], []

@@ -640,3 +640,21 @@ def test_a_guess_that_starts_inside_a_bin(crit):
     assert misses[45] == misses[30], "missed guesses at rest"
     assert misses[46] > misses[45] and misses[52] > misses[51], "the threshold fell and the guess still held"
     gpu.destroy()
+
+
+def test_layers_at_the_edges_of_the_level_2_slot_groups():
+    """512 tiles share 32 slots of sixteen tiles, 513 tiles 17 slots of 32, 511 and 497 tiles leave the last slot
+    unfilled or with one tile.  A count lost or added twice would miss the guess or move the threshold."""
+    print("case slot groups", flush=True)
+    sizes = [512 * 8192, 512 * 8192 + 1, 511 * 8192 - 3, 496 * 8192 + 2]
+    layers = wl.make_layers([(1, n, 0) for n in sizes])
+    N = wl.total_params(layers)
+    rng = np.random.default_rng(512)
+    gpu, ora = H.make_pair(B.ACC_TOPK, layers, 1, 10, 1)
+    batches = [rng.standard_normal(N, dtype=np.float32) for _ in range(2)]
+    misses = []
+    for step in range(4):
+        _check_step(gpu, ora, [batches[step % 2]], f"slot groups step {step}", check_state=step == 3)
+        misses.append(gpu.topk_stats()[0])
+    assert misses[0] == len(sizes) and misses[3] == misses[0], misses
+    gpu.destroy()
