@@ -66,11 +66,11 @@ int fail(char* buf, int code, const char* msg) {
 
 // Rows of the matrix tiles.  A wave has a few rows in flight and waits for the first of them, so few tall
 // tiles leave the chip idle and many flat ones spend their time on their own start (a tile's rows of Q, the
-// sums of its columns).  First pass and decompression: 32 rows, 16 up to kFlatTileGroups workgroups (ResNet-18
-// shapes at W = 1, 1476 workgroups: a step 106 us at 32, 103 at 16; VGG-19 shapes at W = 1, 2626: 114.3 and 115.0;
-// ResNet-18 at W = 4: 172.8 at 32, 179 at 64).  Right product: 128 rows, fewer while that leaves compute units
-// without a workgroup (four small layers, 56 workgroups: a step 28.5 us at 128, 26.7 at 64, 26.9 at 32; ResNet-18
-// at W = 1, 356: 103.1 at 128, 104.9 at 64: twice the partial sums).  The workgroups counted are those of the whole
+// sums of its columns).  First pass and decompression: 32 rows, 16 up to kFlatTileGroups workgroups (with the fused
+// update on ResNet-18 shapes at W = 1, 1476 workgroups: a step 105.8 us at 32, 103.5 at 16; VGG-19 shapes at W = 1,
+// 2626: 113.3 and 114.4; ResNet-18 at W = 4: 172.2 at 32, 180.8 at 64).  Right product: 128 rows, fewer while that leaves
+// compute units without a workgroup (four small layers, 56 workgroups: a step 29.9 us at 128, 28.7 at 64, 28.8 at 32;
+// ResNet-18 at W = 1 with the fused update, 356: 103.4 at 128, 105.3 at 64: twice the partial sums).  The workgroups counted are those of the whole
 // step's launches, all workers in one: the tiles of the decompression, which runs once for all of them, and of the
 // call-by-call path, one worker per launch, are the same ones, as the partial sums and the norms' tiles have to be.
 // (Call by call against 64- and 128-row tiles throughout: four small layers at W = 16 219 us a step and 436, odd sizes at
@@ -229,8 +229,8 @@ int make_plan_tiled(const acc_config* c, Plan& p, char* err, bool coarse) {
   // W = 1) 76.6, 74.9 | 69.5, 70.8; 576 (twelve layers of 10 x 9216, W = 16) 161, 118.5.
   p.pmean_in_orth = orth_loads <= kOrthLoads ? 1 : 0;
   // The right product takes the tiles from the last to the first when the error memory is larger than what the
-  // 256 MB Infinity Cache still holds of it: VGG-19 shapes at W = 8 (658 MB) 571 -> 549 us per step, LSTM set at
-  // W = 4 (820 MB) 1095 -> 1075; ResNet-18 at W = 4 (179 MB, all of it there) 172.8 -> 175.5, so not below.
+  // 256 MB Infinity Cache still holds of it: VGG-19 shapes at W = 8 (658 MB) 571 -> 548 us per step, LSTM set at
+  // W = 4 (820 MB) 1059 -> 1041; ResNet-18 at W = 4 (179 MB, all of it there) 172.1 -> 175.8, so not below.
   // Call by call only the tiles of a worker are reversed: the order of the workers is the caller's.
   p.q_reversed = 4 * p.e_stride * c->n_workers > (int64_t(224) << 20) ? 1 : 0;
   p.q_stride = 4 * ntile + nl;
