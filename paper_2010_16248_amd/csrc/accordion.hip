@@ -70,11 +70,12 @@ int fail(char* buf, int code, const char* msg) {
 // update on ResNet-18 shapes at W = 1, 1476 workgroups: a step 105.8 us at 32, 103.5 at 16; VGG-19 shapes at W = 1,
 // 2626: 113.3 and 114.4; ResNet-18 at W = 4: 172.2 at 32, 180.8 at 64).  Right product: 128 rows, fewer while that leaves
 // compute units without a workgroup (four small layers, 56 workgroups: a step 29.9 us at 128, 28.7 at 64, 28.8 at 32;
-// ResNet-18 at W = 1 with the fused update, 356: 103.4 at 128, 105.3 at 64: twice the partial sums).  The workgroups counted are those of the whole
-// step's launches, all workers in one: the tiles of the decompression, which runs once for all of them, and of the
-// call-by-call path, one worker per launch, are the same ones, as the partial sums and the norms' tiles have to be.
-// (Call by call against 64- and 128-row tiles throughout: four small layers at W = 16 219 us a step and 436, odd sizes at
-// W = 3 151 and 194, ResNet-18 shapes at W = 4 212 and 232, VGG-19 shapes at W = 8 664 and 781, the loops' share included.)
+// ResNet-18 at W = 1 with the fused update, 356: 103.4 at 128, 105.3 at 64: twice the partial sums).  The workgroups
+// counted are those of the whole step's launches, all workers in one: the tiles of the decompression, which runs once for
+// all of them, and of the call-by-call path, one worker per launch, are the same ones, as the partial sums and the norms'
+// tiles have to be.  (Call by call against 64- and 128-row tiles throughout: four small layers at W = 16 219 us a step and
+// 436, odd sizes at W = 3 151 and 194, ResNet-18 shapes at W = 4 212 and 232, VGG-19 shapes at W = 8 664 and 781, the
+// loops' share included.)
 constexpr int kComputeUnits = 256;
 constexpr int kFlatTileGroups = 8 * kComputeUnits;
 constexpr int kOrthLoads = 24;   // three requests of kPartLoads; see make_plan_tiled
