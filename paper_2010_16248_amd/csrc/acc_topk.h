@@ -37,6 +37,8 @@
 // The guess only decides which path is taken, never the result.  Cross-workgroup combination
 // is by integer atomics and fixed-order sums only, so every output is bit-reproducible.
 #pragma once
+#include <type_traits>
+
 #include "acc_common.h"
 
 namespace acc {
@@ -206,8 +208,7 @@ __device__ __forceinline__ WaveSpan wave_span(const TileGeom& tg, int wave) {
 constexpr bool kStreamG = true;      // gradients: read once per step
 constexpr bool kStreamA = true;      // accumulator: read and written once per step
 constexpr bool kStreamOut = true;    // averaged gradient: written once, read by nobody here
-// Delta stays plain: streaming its store in the first pass changes nothing, and streaming its load
-// in the compaction (which then writes the same lines) costs 30 us.
+// Delta: see EAccess.
 
 template <bool AL, bool STREAM = false>
 __device__ __forceinline__ float4 ld_span(const float* __restrict__ p, const TileGeom& tg,
@@ -512,12 +513,19 @@ __device__ __forceinline__ bool any_bits(const float4& v) {
 __device__ __forceinline__ bool on_a_line(const float* p) { return (reinterpret_cast<uintptr_t>(p) & 63u) == 0u; }
 
 // SELECT = false (layers of a single tile, which the pick kernel decides from Delta itself):
-// only the error-feedback add and the accumulation.  ZB: the guess is kGuessZero.
-template <bool AL, bool SELECT, bool ZB>
+// only the error-feedback add and the accumulation.  ZB: the guess is kGuessZero.  EM: how e is accessed.
+// kEPlain: memories that are left to the Infinity Cache whole (kCachedError on the host side).  Larger ones store only
+// what changes (kEChecked), and beyond that much of them the access is streaming as well (kEStream) unless a later kernel
+// of the step reads Delta (band guesses, the call-by-call path; ResNet-18 shapes at K = 99 %, W = 4: 226 us per step, 240
+// streamed).  Small sets wait for instructions, not for memory: four small layers at W = 2 take 36.2 us per step, 37.1 checked.
+enum EAccess { kEPlain, kEChecked, kEStream };
+template <bool AL, bool SELECT, bool ZB, EAccess EM = kEPlain>
 __device__ __forceinline__ void ef_hist_tile(const Ws& ws, const GradPtrs& gp, int w, int tile_id,
                                              const FlatTile& ft, const LayerDev& L, const TileGeom& tg,
                                              uint32_t* hist, const CandList& cl, uint32_t* sub2, double* red4, uint32_t guess,
                                              bool window_fresh, uint32_t pending) {
+  constexpr bool SE = EM == kEStream;
+  constexpr bool CHECK = AL && EM != kEPlain;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -540,7 +548,7 @@ __device__ __forceinline__ void ef_hist_tile(const Ws& ws, const GradPtrs& gp, i
   for (int u = 0; u < U; ++u) {
     const int q = span.qbeg + u * kWave + lane;
     gc[u] = ld_span<AL, kStreamG>(g, tg, span, q);
-    ec[u] = ld_span<AL>(e, tg, span, q);
+    ec[u] = ld_span<AL, SE>(e, tg, span, q);
     ac[u] = (A && !a_fresh) ? ld_span<AL, kStreamA>(A, tg, span, q) : zero4;
   }
   // the batched path leaves Delta of the previous step in e: its kept entries are dropped here.
@@ -563,7 +571,7 @@ __device__ __forceinline__ void ef_hist_tile(const Ws& ws, const GradPtrs& gp, i
     for (int u = 0; u < U; ++u) {
       const int q = q0 + (U + u) * kWave + lane;
       gn[u] = ld_span<AL, kStreamG>(g, tg, span, q);
-      en[u] = ld_span<AL>(e, tg, span, q);
+      en[u] = ld_span<AL, SE>(e, tg, span, q);
       an[u] = (A && !a_fresh) ? ld_span<AL, kStreamA>(A, tg, span, q) : zero4;
     }
     const bool full = q0 + U * kWave <= span.qend;          // wave-uniform
@@ -575,9 +583,9 @@ __device__ __forceinline__ void ef_hist_tile(const Ws& ws, const GradPtrs& gp, i
       if (pend) ec[u] = drop_kept<AL>(tg, q, qa, ballot64(qa), ps, ec[u], lane);
       const float4 d = make_float4(gc[u].x + ec[u].x, gc[u].y + ec[u].y, gc[u].z + ec[u].z, gc[u].w + ec[u].w);
       // (a gradient without zeros changes everything; that much is seen at once, for both memories)
-      const bool fed = !AL || ballot64(any_bits(gc[u])) == ~0ull;   // wave-uniform
+      const bool fed = !CHECK || ballot64(any_bits(gc[u])) == ~0ull;   // wave-uniform
       const bool st_e = fed || to_store(d, e_was, e_line);
-      if (qa && st_e) stq<AL>(e, tg.a0, tg.hi, q, d);
+      if (qa && st_e) stq<AL, SE>(e, tg.a0, tg.hi, q, d);
       if (A) {                                               // uniform over the workgroup
         const float4 a = make_float4(ac[u].x + gc[u].x, ac[u].y + gc[u].y, ac[u].z + gc[u].z, ac[u].w + gc[u].w);
         const bool st_a = fed || a_fresh || to_store(a, ac[u], a_line);
@@ -645,7 +653,10 @@ __device__ __forceinline__ void ef_hist_tile(const Ws& ws, const GradPtrs& gp, i
   }
 }
 
-__global__ __launch_bounds__(256) void topk_ef_hist_kernel(const Ws ws, const GradPtrs gp, int w0) {
+// LARGE: a context of more than e_cached elements of error memory (see EAccess).  e_reread: Delta is read again within the
+// step, whatever the guess.
+template <bool LARGE>
+__global__ __launch_bounds__(256) void topk_ef_hist_kernel(const Ws ws, const GradPtrs gp, int w0, int64_t e_cached, int e_reread) {
   __shared__ uint32_t hist[kHistBins];
   __shared__ uint32_t cand_val[4][kCandLdsSlots];
   __shared__ uint16_t cand_idx[4][kCandLdsSlots];
@@ -669,17 +680,37 @@ __global__ __launch_bounds__(256) void topk_ef_hist_kernel(const Ws ws, const Gr
   if (w == 0 && ft.start == 0 && threadIdx.x == 0) ws.lflag[ft.layer] = 0u;
   const bool fresh = rfl(fresh_w) != 0u;
   const uint32_t pending = rfl(pend_w);
+  // everything from here on is uniform over the workgroup
+  auto tile = [&](auto al, auto select, auto zb, auto em, uint32_t guess) {
+    ef_hist_tile<decltype(al)::value, decltype(select)::value, decltype(zb)::value, decltype(em)::value>(
+        ws, gp, w, blockIdx.x, ft, L, tg, hist, cl, sub2, red4, guess, fresh, pending);
+  };
+  constexpr std::true_type yes;
+  constexpr std::false_type no;
+  constexpr std::integral_constant<EAccess, kEPlain> plain;
   if (L.ntiles == 1) {
-    if (tg.aligned) ef_hist_tile<true, false, false>(ws, gp, w, blockIdx.x, ft, L, tg, hist, cl, sub2, red4, kNoGuess, fresh, pending);
-    else ef_hist_tile<false, false, false>(ws, gp, w, blockIdx.x, ft, L, tg, hist, cl, sub2, red4, kNoGuess, fresh, pending);
+    if (tg.aligned) tile(yes, no, no, plain, kNoGuess);
+    else tile(no, no, no, plain, kNoGuess);
+    return;
+  }
+  const uint32_t guess = rfl(rfl(lvl) != 0u ? guess1 : guess0);
+  const bool zero = guess == kGuessZero;
+  if (!tg.aligned) {
+    if (zero) tile(no, yes, yes, plain, guess);
+    else tile(no, yes, no, plain, guess);
+  } else if constexpr (!LARGE) {
+    if (zero) tile(yes, yes, yes, plain, guess);
+    else tile(yes, yes, no, plain, guess);
   } else {
-    const uint32_t guess = rfl(rfl(lvl) != 0u ? guess1 : guess0);
-    if (guess == kGuessZero) {                               // uniform over the workgroup
-      if (tg.aligned) ef_hist_tile<true, true, true>(ws, gp, w, blockIdx.x, ft, L, tg, hist, cl, sub2, red4, guess, fresh, pending);
-      else ef_hist_tile<false, true, true>(ws, gp, w, blockIdx.x, ft, L, tg, hist, cl, sub2, red4, guess, fresh, pending);
+    constexpr std::integral_constant<EAccess, kEChecked> checked;
+    constexpr std::integral_constant<EAccess, kEStream> stream;
+    const bool lists = zero || (guess != kNoGuess && guess_nb(guess) == (uint32_t)kGuessBins);   // the compaction reads lists
+    if (lists && e_reread == 0 && (int64_t)w * ws.e_stride + tg.a0 >= e_cached) {
+      if (zero) tile(yes, yes, yes, stream, guess);
+      else tile(yes, yes, no, stream, guess);
     } else {
-      if (tg.aligned) ef_hist_tile<true, true, false>(ws, gp, w, blockIdx.x, ft, L, tg, hist, cl, sub2, red4, guess, fresh, pending);
-      else ef_hist_tile<false, true, false>(ws, gp, w, blockIdx.x, ft, L, tg, hist, cl, sub2, red4, guess, fresh, pending);
+      if (zero) tile(yes, yes, yes, checked, guess);
+      else tile(yes, yes, no, checked, guess);
     }
   }
 }
@@ -1707,6 +1738,7 @@ __device__ __forceinline__ void compact_mean_tile(const Ws& ws, const FlatTile& 
   const float* const e_base = ws.e;
   int32_t* const pay_idx = ws.pay_idx;
   float* const pay_val = ws.pay_val;
+  const bool wv_stream = UPD && tg.a0 >= sink.wv_cached;
   // lane w holds worker w's selection state for this quarter
   QuarterSel mine = {0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u};
   if (lane < W) mine = load_quarter_sel(ws, lane, ft.layer, qslot_local);
@@ -1853,7 +1885,7 @@ __device__ __forceinline__ void compact_mean_tile(const Ws& ws, const FlatTile& 
     for (int j = 0; j < G; ++j) {
       const int q = span.qbeg + (c * G + j) * kWave + lane;
       if (UPD) {                                           // the group's weights and velocity
-        if (sink.stream_wv) {                               // uniform: see stream_wv() on the host side
+        if (wv_stream) {                                    // uniform
           keep_apart();
           wq[j] = ld_span<AL, true>(sink.wt, tg, span, q);
           vq[j] = ld_span<AL, true>(sink.vel, tg, span, q);
@@ -1869,7 +1901,7 @@ __device__ __forceinline__ void compact_mean_tile(const Ws& ws, const FlatTile& 
                               : make_float4(a.x / fw, a.y / fw, a.z / fw, a.w / fw);
         if (UPD) {
           nesterov4(v, wq[j], vq[j], sink);
-          if (sink.stream_wv) {
+          if (wv_stream) {
             keep_apart();
             stq<AL, true>(sink.wt, tg.a0, tg.hi, q, wq[j]);
             stq<AL, true>(sink.vel, tg.a0, tg.hi, q, vq[j]);
@@ -1917,6 +1949,7 @@ __device__ __forceinline__ void gather_mean_tile(const Ws& ws, const FlatTile& f
   float* const pay_val = ws.pay_val;
   const uint32_t* const cand_val = ws.cand_val;
   const uint16_t* const cand_idx = ws.cand_idx;
+  const bool wv_stream = UPD && tg.a0 >= sink.wv_cached;
   // lane w holds worker w's selection state and candidate count for this quarter
   QuarterSel mine = {0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u};
   uint32_t n_mine = 0u;
@@ -1952,7 +1985,7 @@ __device__ __forceinline__ void gather_mean_tile(const Ws& ws, const FlatTile& f
   constexpr int SG = UPD ? kSinkGroups : 1;
   auto load_sink = [&](int g0, float4 (&wq)[SG], float4 (&vq)[SG]) {
     if (!UPD) return;
-    if (sink.stream_wv) {                                   // uniform: see stream_wv() on the host side
+    if (wv_stream) {                                        // uniform
       keep_apart();
 #pragma unroll
       for (int j = 0; j < SG; ++j) {
@@ -2119,7 +2152,7 @@ __device__ __forceinline__ void gather_mean_tile(const Ws& ws, const FlatTile& f
                               : make_float4(a.x / fw, a.y / fw, a.z / fw, a.w / fw);
         if (UPD) {
           nesterov4(v, wq[j], vq[j], sink);
-          if (sink.stream_wv) {
+          if (wv_stream) {
             keep_apart();
             stq<AL, true>(sink.wt, tg.a0, tg.hi, q, wq[j]);
             stq<AL, true>(sink.vel, tg.a0, tg.hi, q, vq[j]);

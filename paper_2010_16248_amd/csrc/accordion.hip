@@ -477,28 +477,45 @@ bool prof_begin(acc_ctx* c, int stage, EventPair& p) {
 
 void prof_end(acc_ctx* c, EventPair& p) { c->pending.push_back(p); }
 
-#define ACC_LAUNCH(ctx, name, grid, block, ...)                              \
+// stage: the kernel's name; kernel: the kernel itself (an instantiation of a template has no name of its own).
+#define ACC_LAUNCH_AS(ctx, stage, kernel, grid, block, ...)                  \
   do {                                                                       \
     EventPair ep_;                                                           \
-    const bool prof_ = prof_begin(ctx, ST_##name, ep_);                      \
+    const bool prof_ = prof_begin(ctx, ST_##stage, ep_);                     \
     if (prof_) {                                                             \
       /* the two events take the dispatch's own begin and end timestamps */  \
-      hipExtLaunchKernelGGL(name, grid, block, 0, (ctx)->stream, ep_.a, ep_.b, 0, __VA_ARGS__); \
+      hipExtLaunchKernelGGL((kernel), grid, block, 0, (ctx)->stream, ep_.a, ep_.b, 0, __VA_ARGS__); \
       prof_end(ctx, ep_);                                                    \
     } else {                                                                 \
-      hipLaunchKernelGGL(name, grid, block, 0, (ctx)->stream, __VA_ARGS__);  \
+      hipLaunchKernelGGL((kernel), grid, block, 0, (ctx)->stream, __VA_ARGS__); \
     }                                                                        \
-    int rc_ = check_launch(ctx, #name);                                      \
+    int rc_ = check_launch(ctx, #stage);                                     \
     if (rc_ != ACC_OK) return rc_;                                           \
   } while (0)
+#define ACC_LAUNCH(ctx, name, grid, block, ...) ACC_LAUNCH_AS(ctx, name, name, grid, block, __VA_ARGS__)
 
 // --- launches of each stage for workers [w0, w0 + nw) ------------------------------------
 
+// What a batched TopK step leaves to the 256 MB Infinity Cache until the next one: the first kCachedError elements of the
+// workers' error memories and the first kCachedUpdate of weights and velocity.  The rest goes through streaming loads and
+// stores.  Everything accessed plainly, whatever does not fit is evicted while the next pass reads, dirty line by dirty line: e = g + e
+// over 3 x 179 MB in turn runs at 5.8 TB/s so, 6.2 streamed.  A memory that stays in the cache whole is faster plain, but a
+// training program's own passes lie between two steps.  us per step, three states in turn | one state again and again,
+// everything plain -> 32 MB of e and 16 MB of w and v plain (ResNet-18 shapes, K = 10 %): W = 4 194 -> 169 | 162 -> 164; W = 8 347 -> 320 | 343 -> 289;
+// fused update at W = 1 113 -> 96 | 89 -> 95, W = 4 216 -> 198 | 186 -> 186; VGG-19 W = 1 130 -> 123 | 117 -> 122, W = 4 338 -> 315 | 332 -> 288;
+// LSTM W = 16 2525 -> 2410 | 2543 -> 2432.  Nothing plain: W = 4 170 | 169; 64 MB of e: 180 | 163; 64 MB of w and v: W = 1 107 | 93.
+constexpr int64_t kCachedError = (int64_t(32) << 20) / 4, kCachedUpdate = (int64_t(16) << 20) / 8;
+
 // TopK selection of workers [w0, w0 + nw): the fused error-feedback pass, then the per-layer decisions
-// (level-1/2 bins, re-staging after a missed guess, level-3/4 counts, threshold and prefixes).
-int launch_topk_select(acc_ctx* c, int w0, int nw) {
+// (level-1/2 bins, re-staging after a missed guess, level-3/4 counts, threshold and prefixes).  e_reread: Delta is read
+// again within the step, whatever the guess.
+int launch_topk_select(acc_ctx* c, int w0, int nw, int e_reread) {
   const Ws& ws = c->ws;
-  ACC_LAUNCH(c, topk_ef_hist_kernel, dim3(ws.n_ftiles, nw), dim3(256), ws, c->grads, w0);
+  const dim3 tiles(ws.n_ftiles, nw);
+  if (ws.e_stride * ws.W > kCachedError)
+    ACC_LAUNCH_AS(c, topk_ef_hist_kernel, topk_ef_hist_kernel<true>, tiles, dim3(256), ws, c->grads, w0, kCachedError, e_reread);
+  else
+    ACC_LAUNCH_AS(c, topk_ef_hist_kernel, topk_ef_hist_kernel<false>, tiles, dim3(256), ws, c->grads, w0, kCachedError, e_reread);
   ACC_LAUNCH(c, topk_pick12_kernel, dim3(ws.L, nw), dim3(kPickThreads), ws, w0);
   ACC_LAUNCH(c, topk_count3_kernel, dim3((ws.n_ftiles + kCountTiles - 1) / kCountTiles, nw), dim3(256), ws, w0);
   ACC_LAUNCH(c, topk_pick3_kernel, dim3(ws.L, nw), dim3(kPickThreads), ws, w0, c->step_id);
@@ -524,7 +541,7 @@ int launch_phase0(acc_ctx* c, int w0, int nw) {
     const int gx = ws.n_mtiles + (w0 == 0 ? ws.n_vectiles : 0);
     if (gx > 0) ACC_LAUNCH(c, psgd_ef_p_kernel, dim3(gx, nw), dim3(256), ws, c->grads, w0);
   } else {
-    const int rc = launch_topk_select(c, w0, nw);
+    const int rc = launch_topk_select(c, w0, nw, 1);   // the compaction reads Delta once more
     if (rc != ACC_OK) return rc;
     ACC_LAUNCH(c, topk_compact_kernel, dim3(ws.n_ftiles, nw), dim3(256), ws, w0);
   }
@@ -555,15 +572,6 @@ int launch_agg1(acc_ctx* c) {
 }
 
 bool misaligned(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) != 0; }
-
-// Weights and velocity are read and written by every step, like the error memory.  Where both
-// fit the last-level cache together they are accessed plainly (ResNet-18 shapes at W = 1: the
-// fused TopK update is 11 us faster); where they do not, streaming them keeps the error memory
-// resident for the next pass (W = 4: 2 us).
-int32_t stream_wv(const acc_ctx* c) {
-  const int64_t resident = 4 * c->plan.e_stride * (int64_t)c->cfg.n_workers + 8 * c->plan.N;
-  return resident > (192ll << 20) ? 1 : 0;
-}
 
 Sink sink_out(float* out) { return Sink{out, nullptr, nullptr, 0.f, 0.f, 0.f, 0}; }
 
@@ -940,7 +948,7 @@ int32_t accordion_decompress_update(acc_ctx* c, float* weights_dev, float* veloc
   ACC_USABLE(c);
   const int rc = check_sgd(c, weights_dev, velocity_dev, lr, momentum, weight_decay);
   if (rc != ACC_OK) return rc;
-  return decompress_into(c, Sink{nullptr, weights_dev, velocity_dev, lr, momentum, weight_decay, stream_wv(c)});
+  return decompress_into(c, Sink{nullptr, weights_dev, velocity_dev, lr, momentum, weight_decay, kCachedUpdate});
 }
 
 static int32_t step_all_into(acc_ctx* c, const float* const* grads_host_array, const Sink& sink) {
@@ -964,7 +972,7 @@ static int32_t step_all_into(acc_ctx* c, const float* const* grads_host_array, c
   } else {
     // the compaction of all workers and the mean of their kept values share one pass over Delta
     rc = launch_detector_feed(c, 0);
-    if (rc == ACC_OK) rc = launch_topk_select(c, 0, W);
+    if (rc == ACC_OK) rc = launch_topk_select(c, 0, W, 0);
     if (rc == ACC_OK) rc = launch_topk_compact_mean(c, sink);
   }
   end_step(c);
@@ -983,7 +991,7 @@ int32_t accordion_step_all_update(acc_ctx* c, const float* const* grads_host_arr
   ACC_USABLE(c);
   const int rc = check_sgd(c, weights_dev, velocity_dev, lr, momentum, weight_decay);
   if (rc != ACC_OK) return rc;
-  return step_all_into(c, grads_host_array, Sink{nullptr, weights_dev, velocity_dev, lr, momentum, weight_decay, stream_wv(c)});
+  return step_all_into(c, grads_host_array, Sink{nullptr, weights_dev, velocity_dev, lr, momentum, weight_decay, kCachedUpdate});
 }
 
 int32_t accordion_set_stream(acc_ctx* c, void* hip_stream) {
