@@ -145,7 +145,7 @@ struct Ws {
   int32_t W, L, rmax;
   int32_t mrows, qrows;        // PowerSGD: rows of a matrix tile / of a tile of the right product
   int32_t pmean_in_orth;       // PowerSGD: the orthogonalisation sums the partials of P itself
-  int32_t q_reversed;          // PowerSGD: the right product takes the tiles in reverse order
+  int32_t q_stream;            // PowerSGD: the right product streams Delta
   int32_t n_ftiles, n_mtiles, n_qmtiles, n_qtiles, n_vectiles, n_mat, n_ptiles;
   int32_t n_t2slots;           // TopK: slots of t2 per worker
   float eta;
@@ -374,7 +374,7 @@ struct Sink {
   float* wt;
   float* vel;
   float lr, mu, wd;
-  int64_t wv_cached;   // TopK: weights and velocity are accessed with streaming loads / stores from this element on
+  int64_t wv_cached;   // weights and velocity are accessed with streaming loads / stores from this element on
 };
 
 // d' = d + wd w (if wd != 0);  v = mu v + d';  w = w - lr (d' + mu v).  Every product and every sum

@@ -637,18 +637,21 @@ __global__ __launch_bounds__(kOrthThreads) void psgd_orth_kernel(const Ws ws, co
 // 2 x 20000 at W = 4 118.5 -> 112.6 us, 200 of 512 x 9 33.0 -> 30.9).
 constexpr int kQBatch = 4;   // rows a wave requests together; two such batches are in flight
 
+// STREAM (Ws::q_stream): Delta is requested with the streaming hint.  It is not read again before the next step, and a plain
+// read leaves it in the Infinity Cache, dirty, for the next passes to evict; read so, its lines go back to memory here, at next
+// to no cost (see the host side).
 // (From clamped addresses: a request behind a branch would make every wait in the loop a wait for all of them.)
-template <int MODE>
+template <int MODE, bool STREAM>
 __device__ __forceinline__ void q_load(const float* __restrict__ e, int cols, int row_end, const LaneCols& lc, int i0,
                                        float (&d)[kQBatch][4]) {
 #pragma unroll
   for (int b = 0; b < kQBatch; ++b) {
     const int i = i0 + 4 * b;                                // beyond the tile: one 16-byte address, see ef_load
-    load_row<MODE>(e + (int64_t)min(i, row_end - 1) * cols, i < row_end ? lc.c : 0, cols, d[b]);
+    load_row<MODE, STREAM>(e + (int64_t)min(i, row_end - 1) * cols, i < row_end ? lc.c : 0, cols, d[b]);
   }
 }
 
-template <int R, int MODE>
+template <int R, int MODE, bool STREAM>
 __device__ __forceinline__ void q_loop(const Ws& ws, const LayerDev& L, const MatTile& t, const float* __restrict__ e,
                                        double* __restrict__ qpart, double (*red)[16][64], const float (*ps)[kMaxRank],
                                        const LaneCols& lc, int row_end, float (&cur)[kQBatch][4]) {
@@ -679,7 +682,7 @@ __device__ __forceinline__ void q_loop(const Ws& ws, const LayerDev& L, const Ma
   int i0 = t.row0 + wave;
   for (; i0 + 4 * kQBatch < row_end; i0 += 4 * kQBatch) {
     float nxt[kQBatch][4];
-    q_load<MODE>(e, L.cols, row_end, lc, i0 + 4 * kQBatch, nxt);
+    q_load<MODE, STREAM>(e, L.cols, row_end, lc, i0 + 4 * kQBatch, nxt);
     use(i0);
 #pragma unroll
     for (int b = 0; b < kQBatch; ++b)
@@ -725,7 +728,7 @@ __device__ __forceinline__ void q_loop(const Ws& ws, const LayerDev& L, const Ma
   }
 }
 
-template <int MODE>
+template <int MODE, bool STREAM>
 __device__ __forceinline__ void q_tile(const Ws& ws, const LayerDev& L, const MatTile& t, const float* __restrict__ e_w,
                                        double* __restrict__ qpart, int level, double (*red)[16][64],
                                        float (*ps)[kMaxRank]) {
@@ -740,7 +743,7 @@ __device__ __forceinline__ void q_tile(const Ws& ws, const LayerDev& L, const Ma
 #pragma unroll
   for (int b = 0; b < kQBatch; ++b) {
     const int i = t.row0 + wave + 4 * b;
-    if (i < row_end) load_row<MODE>(e + (int64_t)i * L.cols, lc.c, L.cols, first[b]);   // wave-uniform
+    if (i < row_end) load_row<MODE, STREAM>(e + (int64_t)i * L.cols, lc.c, L.cols, first[b]);   // wave-uniform
   }
   const int r = level ? L.rank[1] : L.rank[0];
   for (int s = threadIdx.x; s < ws.qrows * kMaxRank; s += 256) {
@@ -750,29 +753,33 @@ __device__ __forceinline__ void q_tile(const Ws& ws, const LayerDev& L, const Ma
   }
   __syncthreads();
   switch (r) {
-    case 1: q_loop<1, MODE>(ws, L, t, e, qpart, red, ps, lc, row_end, first); break;
-    case 2: q_loop<2, MODE>(ws, L, t, e, qpart, red, ps, lc, row_end, first); break;
-    case 3: q_loop<3, MODE>(ws, L, t, e, qpart, red, ps, lc, row_end, first); break;
-    default: q_loop<4, MODE>(ws, L, t, e, qpart, red, ps, lc, row_end, first); break;
+    case 1: q_loop<1, MODE, STREAM>(ws, L, t, e, qpart, red, ps, lc, row_end, first); break;
+    case 2: q_loop<2, MODE, STREAM>(ws, L, t, e, qpart, red, ps, lc, row_end, first); break;
+    case 3: q_loop<3, MODE, STREAM>(ws, L, t, e, qpart, red, ps, lc, row_end, first); break;
+    default: q_loop<4, MODE, STREAM>(ws, L, t, e, qpart, red, ps, lc, row_end, first); break;
   }
 }
 
 __global__ __launch_bounds__(256) void psgd_q_kernel(const Ws ws, int w0) {
   __shared__ double red[2][16][64];
   __shared__ float ps[kQRows][kMaxRank];
-  // A memory larger than the Infinity Cache is taken from its end: what the first pass wrote last is
-  // still there.
-  const int bx = ws.q_reversed ? gridDim.x - 1 - blockIdx.x : blockIdx.x;
-  const int w = w0 + (ws.q_reversed ? gridDim.y - 1 - blockIdx.y : blockIdx.y);
-  const MatTile t = ws.qmtiles[bx];
+  const int w = w0 + blockIdx.y;
+  const MatTile t = ws.qmtiles[blockIdx.x];
   const LayerDev& L = ws.layers[t.layer];
   const int level = ws.level[t.layer];
   const float* __restrict__ e = ws.e + (int64_t)w * ws.e_stride;
   double* qpart = ws.Qpart + (int64_t)w * ws.qpart_stride;
+  const bool stream = ws.q_stream != 0;                      // uniform
   switch (row_mode(L)) {
-    case kRowAligned: q_tile<kRowAligned>(ws, L, t, e, qpart, level, red, ps); break;
-    case kRowUnaligned: q_tile<kRowUnaligned>(ws, L, t, e, qpart, level, red, ps); break;
-    default: q_tile<kRowNarrow>(ws, L, t, e, qpart, level, red, ps); break;
+    case kRowAligned:
+      if (stream) q_tile<kRowAligned, true>(ws, L, t, e, qpart, level, red, ps);
+      else q_tile<kRowAligned, false>(ws, L, t, e, qpart, level, red, ps);
+      break;
+    case kRowUnaligned:
+      if (stream) q_tile<kRowUnaligned, true>(ws, L, t, e, qpart, level, red, ps);
+      else q_tile<kRowUnaligned, false>(ws, L, t, e, qpart, level, red, ps);
+      break;
+    default: q_tile<kRowNarrow, false>(ws, L, t, e, qpart, level, red, ps); break;
   }
 }
 
@@ -796,11 +803,12 @@ __global__ __launch_bounds__(256) void psgd_qmean_kernel(const Ws ws) {
 
 // ---- decompress: D = P^ Q_bar^T (the residual stays implicit) ----------------------------------
 
+// NT (the update of aligned rows): weights and velocity beyond Sink::wv_cached are streamed.
 // WHAT 0: writes D of the tile to sink.out.  1: e = Delta - D in place.  2: D drives the optimizer step
 // on sink.wt / sink.vel and is not stored.
 enum DecompWhat { kDecompStore = 0, kDecompResidual = 1, kDecompUpdate = 2 };
 
-template <int WHAT, int MODE>
+template <int WHAT, int MODE, bool NT = false>
 __device__ __forceinline__ void decomp_tile(const Ws& ws, const LayerDev& L, const MatTile& t, float* __restrict__ e,
                                             const Sink& sink, int r, float (*ps)[kMaxRank]) {
   constexpr bool RESIDUAL = WHAT == kDecompResidual;
@@ -811,10 +819,6 @@ __device__ __forceinline__ void decomp_tile(const Ws& ws, const LayerDev& L, con
   const int cols = L.cols;
   const int row_end = min(t.row0 + ws.mrows, L.rows);
   constexpr int B = 4;
-  // Weights and velocity are read and written by every step, so they are accessed like the error
-  // memory, not streamed like the gradients: where they fit the caches next to it (VGG-19 shapes,
-  // W = 1) the fused update is 17 us faster that way, elsewhere it makes no difference.
-  constexpr bool NT = false;
   constexpr bool IN = RESIDUAL || UPD;                     // the pass reads something per element
   float* const src = (UPD ? sink.wt : e) + L.offset;       // not used when D is only stored
   float* const vel = UPD ? sink.vel + L.offset : nullptr;
@@ -888,7 +892,12 @@ template <int WHAT>
 __device__ __forceinline__ void decomp_any(const Ws& ws, const LayerDev& L, const MatTile& t, float* __restrict__ e,
                                            const Sink& sink, int r, float (*ps)[kMaxRank]) {
   switch (row_mode(L)) {                                     // uniform over the workgroup
-    case kRowAligned: decomp_tile<WHAT, kRowAligned>(ws, L, t, e, sink, r, ps); break;
+    case kRowAligned:
+      if (WHAT == kDecompUpdate && L.offset + (int64_t)t.row0 * L.cols >= sink.wv_cached)
+        decomp_tile<WHAT, kRowAligned, WHAT == kDecompUpdate>(ws, L, t, e, sink, r, ps);
+      else
+        decomp_tile<WHAT, kRowAligned>(ws, L, t, e, sink, r, ps);
+      break;
     case kRowUnaligned: decomp_tile<WHAT, kRowUnaligned>(ws, L, t, e, sink, r, ps); break;
     default: decomp_tile<WHAT, kRowNarrow>(ws, L, t, e, sink, r, ps); break;
   }

@@ -40,7 +40,7 @@ struct Plan {
   std::vector<int32_t> vectiles;
   std::vector<int32_t> matlayers;
   int32_t rmax = 0;
-  int32_t pmean_in_orth = 0, q_reversed = 0;   // PowerSGD: see Ws
+  int32_t pmean_in_orth = 0, q_stream = 0;   // PowerSGD: see Ws
   int32_t mrows = kMatRows, qrows = kQRows;   // PowerSGD: rows of the two kinds of matrix tiles
   int64_t N = 0, e_stride = 0;
   int64_t q_total = 0;   // floats of Q in the caller's layout (rows of rmax floats)
@@ -229,11 +229,14 @@ int make_plan_tiled(const acc_config* c, Plan& p, char* err, bool coarse) {
   // 24 (512 x 1536, W = 2) 67.9, 67.0 | 62.0, 63.3; 32 (256 x 8192, W = 1) 78.4, 78.4 | 73.6, 75.4; 36 (ResNet-18 shapes,
   // W = 1) 76.6, 74.9 | 69.5, 70.8; 576 (twelve layers of 10 x 9216, W = 16) 161, 118.5.
   p.pmean_in_orth = orth_loads <= kOrthLoads ? 1 : 0;
-  // The right product takes the tiles from the last to the first when the error memory is larger than what the
-  // 256 MB Infinity Cache still holds of it: VGG-19 shapes at W = 8 (658 MB) 571 -> 548 us per step, LSTM set at
-  // W = 4 (820 MB) 1059 -> 1041; ResNet-18 at W = 4 (179 MB, all of it there) 172.1 -> 175.8, so not below.
-  // Call by call only the tiles of a worker are reversed: the order of the workers is the caller's.
-  p.q_reversed = 4 * p.e_stride * c->n_workers > (int64_t(224) << 20) ? 1 : 0;
+  // The right product, which reads Delta for the last time in the step, streams it unless the error memory may stay in the
+  // 256 MB Infinity Cache beside what else a program does.  Read plainly, Delta stays there dirty, and the passes after it
+  // wait for its lines to be evicted; read with the streaming hint, they go back to memory under this pass (e = g + e over
+  // 3 x 179 MB in turn and a read of e after each: 91 + 26 us plain, 91 + 9 so).  us per step, three states in turn | one state
+  // again and again, plain -> streamed: ResNet-18 shapes W = 4 172.2 -> 158.3 | 156.1 -> 157.7, W = 8 304 -> 277 | 291 -> 274, W = 2 (89 MB)
+  // 103.8 -> 102.5 | 100.9 -> 102.2, VGG-19 W = 4 300 -> 275 | 281 -> 272, LSTM W = 1 542 -> 513 | 497 -> 504, W = 4 1040 -> 997 | 1025 -> 997; below
+  // the line ResNet-18 W = 1 (45 MB) 75.3 -> 76.0, odd sizes W = 3 (67 MB) 119.6 -> 119.0 | 108 -> 111.
+  p.q_stream = 4 * p.e_stride * c->n_workers > (int64_t(72) << 20) ? 1 : 0;
   p.q_stride = 4 * ntile + nl;
 
   // workspace layout, 256-byte aligned regions
@@ -496,14 +499,15 @@ void prof_end(acc_ctx* c, EventPair& p) { c->pending.push_back(p); }
 
 // --- launches of each stage for workers [w0, w0 + nw) ------------------------------------
 
-// What a batched TopK step leaves to the 256 MB Infinity Cache until the next one: the first kCachedError elements of the
-// workers' error memories and the first kCachedUpdate of weights and velocity.  The rest goes through streaming loads and
+// What a step leaves to the 256 MB Infinity Cache until the next one: batched TopK steps the first kCachedError elements of the
+// workers' error memories, fused updates of either method the first kCachedUpdate of weights and velocity.  The rest goes through streaming loads and
 // stores.  Everything accessed plainly, whatever does not fit is evicted while the next pass reads, dirty line by dirty line: e = g + e
 // over 3 x 179 MB in turn runs at 5.8 TB/s so, 6.2 streamed.  A memory that stays in the cache whole is faster plain, but a
 // training program's own passes lie between two steps.  us per step, three states in turn | one state again and again,
 // everything plain -> 32 MB of e and 16 MB of w and v plain (ResNet-18 shapes, K = 10 %): W = 4 194 -> 169 | 162 -> 164; W = 8 347 -> 320 | 343 -> 289;
 // fused update at W = 1 113 -> 96 | 89 -> 95, W = 4 216 -> 198 | 186 -> 186; VGG-19 W = 1 130 -> 123 | 117 -> 122, W = 4 338 -> 315 | 332 -> 288;
-// LSTM W = 16 2525 -> 2410 | 2543 -> 2432.  Nothing plain: W = 4 170 | 169; 64 MB of e: 180 | 163; 64 MB of w and v: W = 1 107 | 93.
+// LSTM W = 16 2525 -> 2410 | 2543 -> 2432.  Nothing plain: W = 4 170 | 169; 64 MB of e: 180 | 163; 64 MB of w and v: W = 1 107 | 93.  PowerSGD
+// with the fused update, ResNet-18 W = 1 103.3 -> 96.3 | 90 -> 95.7, W = 4 (with Ws::q_stream) 203 -> 188 | 181 -> 182.
 constexpr int64_t kCachedError = (int64_t(32) << 20) / 4, kCachedUpdate = (int64_t(16) << 20) / 8;
 
 // TopK selection of workers [w0, w0 + nw): the fused error-feedback pass, then the per-layer decisions
@@ -778,7 +782,7 @@ static int32_t init_common(const acc_config* cfg, void* workspace_dev, size_t wo
   ws.rmax = p.rmax;
   ws.mrows = p.mrows;
   ws.pmean_in_orth = p.pmean_in_orth;
-  ws.q_reversed = p.q_reversed;
+  ws.q_stream = p.q_stream;
   ws.qrows = p.qrows;
   ws.n_ftiles = (int32_t)p.ftiles.size();
   ws.n_t2slots = (int32_t)p.n_t2slots;

@@ -383,6 +383,46 @@ def test_tilings_and_unaligned_rows(name, shapes, W, heights, pmean, reversed_):
     twin.destroy()
 
 
+@pytest.mark.parametrize("mode", ["step", "calls", "update"])
+def test_streamed_and_plain_access_give_the_same_bits(mode):
+    """The same matrices in a context whose memories may stay in the cache and, behind a long 1-D layer, in one whose
+    right product streams Delta (error memory above 72 MiB) and whose fused update streams weights and velocity (beyond two
+    million elements): D, updated weights and error memory are the same words.  Rows of every kind."""
+    print(f"case streamed {mode}", flush=True)
+    W, lead = 8, 2_400_000
+    shapes = EDGE_SHAPES + [(64, 1024, 1), (200, 260, 1)]
+    small, large = wl.make_layers(shapes), wl.make_layers([(1, lead, 0)] + shapes)
+    N = wl.total_params(small)
+    assert 4 * N * W < 72 << 20 < 4 * lead * W and lead > (16 << 20) // 8
+    rng = np.random.default_rng(len(mode))
+    q0 = rng.standard_normal(sum(c for _, c, m in shapes if m) * 4).astype(np.float32)
+    w0 = rng.standard_normal(lead + N, dtype=np.float32)
+    batches = [[rng.standard_normal(lead + N, dtype=np.float32) * np.float32(0.01) for _ in range(W)] for _ in range(3)]
+    results = []
+    for layers, cut in ((small, lead), (large, 0)):
+        gpu, _ = H.make_pair(B.ACC_POWERSGD, layers, W, 4, 3, 100, 0.5, 1, q0)
+        w_dev, v_dev, out = H.to_dev(w0[cut:]), H.to_dev(np.zeros(lead + N - cut, np.float32)), H.dev_out(lead + N - cut)
+        for batch in batches:
+            dev = [H.to_dev(g[cut:]) for g in batch]
+            if mode == "step":
+                gpu.step_all(dev, out)
+            elif mode == "update":
+                gpu.step_all_update(dev, w_dev, v_dev, 0.1, 0.9)
+            else:
+                for w in range(W):
+                    gpu.compress_step(w, dev[w], 0)
+                gpu.aggregate(0)
+                for w in range(W):
+                    gpu.compress_step(w, None, 1)
+                gpu.aggregate(1)
+                gpu.decompress(out)
+        e = gpu.unpack_state(gpu.get_state())["e"]
+        results.append([x.cpu().numpy()[-N:] for x in ((w_dev, v_dev) if mode == "update" else (out,))] + [e[:, -N:]])
+        gpu.destroy()
+    for a, b in zip(*results):
+        H.assert_bits_equal(a, b, mode)
+
+
 def test_a_configuration_at_the_limit_of_the_static_workspace_keeps_its_tiles():
     """Flatter tiles need a little more workspace; what fits the static array with the tallest tiles only gets those."""
     print("case static workspace limit", flush=True)
