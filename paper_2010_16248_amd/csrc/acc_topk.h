@@ -1722,7 +1722,8 @@ constexpr int kChunkWords = 2 * kChunkStride;      // indices, then values
 // (requested group by group once the chunk's sums are complete: requested earlier they cost
 // 32 registers across the last worker's turn and two waves of occupancy).
 // HOLES: the layer keeps more than half of its entries (static per level, the same for every worker).
-template <bool AL, bool UPD, bool HOLES>
+// NTD: Delta, which nothing reads again before the next step, is read with the streaming hint (Ws::delta_cached).
+template <bool AL, bool UPD, bool HOLES, bool NTD = false>
 __device__ __forceinline__ void compact_mean_tile(const Ws& ws, const FlatTile& ft, const LayerDev& L,
                                                   const TileGeom& tg, const Sink sink, uint32_t* stg, int wave) {
   constexpr int G = kChunkGroups;
@@ -1751,7 +1752,7 @@ __device__ __forceinline__ void compact_mean_tile(const Ws& ws, const FlatTile& 
   // nothing)
   auto load_group = [&](const float* __restrict__ e, int c, int j, int q_end) {
     const int q = span.qbeg + (c * G + j) * kWave + lane;
-    if (AL) return ldq_clamped(e, tg.a0, min(q, max(q_end - 1, span.qbeg)));
+    if (AL) return ldq_clamped<NTD>(e, tg.a0, min(q, max(q_end - 1, span.qbeg)));
     return ldq<AL>(e, tg.a0, tg.hi, q, q < q_end);
   };
   const float fw = (float)W;
@@ -1925,14 +1926,15 @@ __device__ __forceinline__ void compact_mean_tile(const Ws& ws, const FlatTile& 
 // in index order), writes them to the payload at consecutive positions (through a ring in LDS, whole
 // cache lines at a time) and adds the values into the quarter's dense sums in
 // LDS, workers in order from +0; the sums, divided by W, go out as the quarter's part of the
-// averaged gradient.  acc: the wave's kQuarterFloats floats of LDS.
+// averaged gradient.  acc: the wave's kQuarterFloats floats of LDS.  NTL: the lists are read with the streaming hint
+// (Ws::lists_stream).
 constexpr int kGatherChunks = 4;                            // 64-entry chunks of a candidate list requested together (2 to 8: within 2 us)
 constexpr int kQuarterGroups = kTile / 16;                  // groups of a wave quarter at most
 constexpr int kQuarterFloats = 4 * kQuarterGroups;
 constexpr int kSinkGroups = 4;                              // groups of weights and velocity a lane requests together
 constexpr int kPayRing = 128;                               // a wave's payload ring in LDS: entries (indices, then values)
 
-template <bool AL, bool UPD>
+template <bool AL, bool UPD, bool NTL = false>
 __device__ __forceinline__ void gather_mean_tile(const Ws& ws, const FlatTile& ft, const LayerDev& L,
                                                  const TileGeom& tg, const Sink sink, float* acc, uint32_t* ring,
                                                  int wave) {
@@ -1971,8 +1973,13 @@ __device__ __forceinline__ void gather_mean_tile(const Ws& ws, const FlatTile& f
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int64_t a = cand_at(ws, qslot, min(t0 / kWave + u, last), lane);
-      v[u] = cand_val[a];
-      ix[u] = cand_idx[a];
+      if (NTL) {
+        v[u] = __builtin_nontemporal_load(cand_val + a);
+        ix[u] = __builtin_nontemporal_load(cand_idx + a);
+      } else {
+        v[u] = cand_val[a];
+        ix[u] = cand_idx[a];
+      }
     }
   };
   uint32_t cv[U], ci[U];
@@ -2199,15 +2206,20 @@ __device__ __forceinline__ void compact_mean_body(const Ws& ws, const Sink& sink
   // the payload layout of the layer at its level (k is the same for every worker)
   const uint32_t n_layer = (uint32_t)L.rows * (uint32_t)L.cols;
   const bool holes = payload_has_holes(n_layer, min(rfl(ws.sel[ft.layer].k), n_layer));
+  const bool ntd = tg.a0 >= ws.delta_cached;                // uniform over the workgroup
   if (holes) {
-    if (tg.aligned) compact_mean_tile<true, UPD, true>(ws, ft, L, tg, sink, stg, wave);
+    if (tg.aligned && ntd) compact_mean_tile<true, UPD, true, true>(ws, ft, L, tg, sink, stg, wave);
+    else if (tg.aligned) compact_mean_tile<true, UPD, true>(ws, ft, L, tg, sink, stg, wave);
     else compact_mean_tile<false, UPD, true>(ws, ft, L, tg, sink, stg, wave);
   } else if (L.ntiles > 1 && rfl(ws.lflag[ft.layer]) == 0u) {
     // every worker's guess held and every list is complete: the candidates serve
-    if (tg.aligned) gather_mean_tile<true, UPD>(ws, ft, L, tg, sink, reinterpret_cast<float*>(stg), stg + kQuarterFloats, wave);
+    if (tg.aligned && ws.lists_stream)
+      gather_mean_tile<true, UPD, true>(ws, ft, L, tg, sink, reinterpret_cast<float*>(stg), stg + kQuarterFloats, wave);
+    else if (tg.aligned) gather_mean_tile<true, UPD>(ws, ft, L, tg, sink, reinterpret_cast<float*>(stg), stg + kQuarterFloats, wave);
     else gather_mean_tile<false, UPD>(ws, ft, L, tg, sink, reinterpret_cast<float*>(stg), stg + kQuarterFloats, wave);
   } else {
-    if (tg.aligned) compact_mean_tile<true, UPD, false>(ws, ft, L, tg, sink, stg, wave);
+    if (tg.aligned && ntd) compact_mean_tile<true, UPD, false, true>(ws, ft, L, tg, sink, stg, wave);
+    else if (tg.aligned) compact_mean_tile<true, UPD, false>(ws, ft, L, tg, sink, stg, wave);
     else compact_mean_tile<false, UPD, false>(ws, ft, L, tg, sink, stg, wave);
   }
 }

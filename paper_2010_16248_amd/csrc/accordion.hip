@@ -769,6 +769,15 @@ static int32_t init_common(const acc_config* cfg, void* workspace_dev, size_t wo
     ws.pay_stride = p.pay_stride;
     ws.overlap = at<unsigned long long>(c, p.r_overlap);
     ws.tpending = at<uint32_t>(c, p.r_tpending);
+    // The compaction is the last to read Delta (where it does: band guesses) and the candidate lists.  Read with the streaming
+    // hint, what lies dirty in the Infinity Cache goes back to memory under this pass instead of during the next one.  Delta:
+    // from 64 MB on, all of it where it exceeds the cache (ResNet-18 shapes K = 99 %, W = 4, 224 us per step plain, 217 from 64 MB
+    // on, 217.5 streamed throughout; one state again and again 198, 202, 215; LSTM set W = 4 949, 924, 902).  Lists: where there are
+    // more than 64 M elements (ResNet-18 shapes K = 10 %, W = 8 325 -> 304 | 292 -> 297, VGG-19 W = 4 318 -> 302 | 292 -> 300, odd sizes W = 12
+    // 340 -> 316 | 307 -> 310, LSTM W = 4 709 -> 704 | 688 -> 696; ResNet-18 W = 4, 45 M elements, 170.0 -> 169.4 | 164.7 -> 168.1: not below).
+    const int64_t elements = p.e_stride * cfg->n_workers;
+    ws.delta_cached = 4 * elements > (int64_t(224) << 20) ? 0 : (int64_t(16) << 20) / cfg->n_workers;
+    ws.lists_stream = elements > (int64_t(64) << 20) ? 1 : 0;
   }
   ws.bstate = at<uint32_t>(c, p.r_bstate);
   ws.bmult = cfg->method == ACC_BATCH ? cfg->batch_multiplier : 1;

@@ -693,3 +693,43 @@ def test_rows_that_a_step_leaves_alone(pad):
             grads.append(g.astype(np.float32))
         _check_step(gpu, ora, grads, f"pad {pad} step {step}", check_state=step in (1, 3, 4, 6))
     gpu.destroy()
+
+
+@pytest.mark.parametrize("crit", [10, 40, 99])
+def test_streamed_batched_steps_equal_call_by_call_ones(crit):
+    """A context of more than 64 M elements, whose batched steps stream the error memory (beyond 32 MB), the candidate lists
+    (K = 10 %) and Delta in the compaction (K = 40 % guesses a band, 99 % has the holes layout), against the call-by-call
+    path, which takes every selection from Delta: mean, payloads of the first and last worker, memory, accumulator."""
+    print(f"case streamed steps K={crit}", flush=True)
+    import torch
+    layers = wl.make_layers([(1, 3, 0), (3000, 401, 1), (1, 64, 0), (1200, 768, 1), (1, 8192, 0), (120, 1024, 1)])
+    N, W = wl.total_params(layers), 30
+    assert N * W > 64 << 20
+    gen = torch.Generator(device="cuda:0")
+    results = []
+    for mode in ("all", "calls"):
+        gpu = B.Accordion(B.ACC_TOPK, H.layer_tuples(layers), W, crit, 1)
+        gen.manual_seed(crit)
+        out, got = H.dev_out(N), []
+        for step in range(4):
+            dg = [torch.randn(N, generator=gen, device="cuda:0") for _ in range(W)]
+            l = layers[3]
+            for g in dg:
+                g[l.offset:l.offset + l.numel].view(l.rows, l.cols).mul_(torch.rand(l.rows, 1, generator=gen, device="cuda:0") < 0.06)
+            if mode == "all":
+                gpu.step_all(dg, out)
+            else:
+                for w in range(W):
+                    gpu.compress_step(w, dg[w], 0)
+                gpu.aggregate(0)
+                gpu.decompress(out)
+            got.append(out.cpu().numpy())
+        got += [gpu.get_payload(w, li) for w in (0, W - 1) for li in range(gpu.n_layers)]
+        got.append(gpu.get_state().copy())
+        results.append(got)
+        gpu.destroy()
+    for i, (a, b) in enumerate(zip(*results)):
+        if isinstance(a, tuple):
+            assert np.array_equal(a[0], b[0]) and np.array_equal(H.bits(a[1]), H.bits(b[1])), f"payload {i}"
+        else:
+            assert np.array_equal(np.ascontiguousarray(a).view(np.uint8), np.ascontiguousarray(b).view(np.uint8)), f"K {crit}: output {i}"
