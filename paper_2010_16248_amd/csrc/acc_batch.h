@@ -12,6 +12,8 @@
 // (slot = micro-step parity), so that the one thread that advances it never races with the
 // workgroups that read it.
 #pragma once
+#include <type_traits>
+
 #include "acc_common.h"
 
 namespace acc {
@@ -30,7 +32,13 @@ __device__ __forceinline__ const uint32_t* batch_slot(const Ws& ws, uint32_t par
   return ws.bstate + 4 * (parity & 1u);
 }
 
-template <bool AL, bool UPD>
+// NTS, NTA: the running sums (see kCachedSums on the host side) / the accumulator (one worker: 487 -> 471 us for six micro-steps
+// of VGG-19 shapes) are accessed with the streaming hint.
+// NW: the number of workers, 0: any.  (Four loads from clamped indices whatever the number asked memory for the same lines again:
+// ResNet-18 shapes at W = 1, eight micro-steps, 390 -> 298 us with the streamed accumulator; LSTM set W = 2, four micro-steps,
+// 1055 -> 920.)  Where few workgroups wait for their loads the branches inside the loop were what counted: four small layers,
+// four micro-steps, W = 2 43.4 -> 34.8 us, W = 16 189 -> 152.
+template <bool AL, bool UPD, int NW = 0, bool NTS = false, bool NTA = false>
 __device__ __forceinline__ void batch_tile(const Ws& ws, const GradPtrs& gp, const Sink& sink,
                                            const TileGeom& tg, uint32_t j, bool exch) {
   const int W = ws.W;
@@ -40,57 +48,73 @@ __device__ __forceinline__ void batch_tile(const Ws& ws, const GradPtrs& gp, con
   const float denom = (float)((uint32_t)W * (j + 1u));
   const float lr_eff = sink.lr * (float)(j + 1u);
   const float4 zero4 = make_float4(0.f, 0.f, 0.f, 0.f);
-  for (int q = threadIdx.x; q < tg.nquads; q += kFlatThreads) {
-    float4 a = ldq<AL, kBatchStream>(A, tg.a0, tg.hi, q, true);
-    float4 wq = zero4, vq = zero4;
-    if (UPD && exch) {
-      wq = ldq<AL, kBatchStream>(sink.wt, tg.a0, tg.hi, q, true);
-      vq = ldq<AL, kBatchStream>(sink.vel, tg.a0, tg.hi, q, true);
-    }
-    float4 acc = zero4;
-    for (int wb = 0; wb < W; wb += kBatchWorkers) {
-      float4 g[kBatchWorkers], s[kBatchWorkers];
-#pragma unroll
-      for (int u = 0; u < kBatchWorkers; ++u) {
-        const int w = min(wb + u, W - 1);                  // clamped: the loads go out unconditionally
-        g[u] = ldq<AL, kBatchStreamG>(gp.p[w], tg.a0, tg.hi, q, true);
-        s[u] = (j > 0u) ? ldq<AL>(S + (int64_t)w * e_stride, tg.a0, tg.hi, q, true) : zero4;
+  // a loop for each case: a request behind a branch would be waited for before the next one goes out
+  auto loop = [&](auto first_c, auto exch_c) {
+    constexpr bool FIRST = decltype(first_c)::value, EXCH = decltype(exch_c)::value;
+    for (int q = threadIdx.x; q < tg.nquads; q += kFlatThreads) {
+      float4 a = ldq<AL, NTA>(A, tg.a0, tg.hi, q, true);
+      float4 wq = zero4, vq = zero4;
+      if (UPD && EXCH) {
+        wq = ldq<AL, kBatchStream>(sink.wt, tg.a0, tg.hi, q, true);
+        vq = ldq<AL, kBatchStream>(sink.vel, tg.a0, tg.hi, q, true);
       }
+      float4 acc = zero4;
+      // N workers from wb on, their loads in flight together
+      auto workers = [&](int wb, auto n_workers) {
+        constexpr int N = decltype(n_workers)::value;
+        float4 g[N], s[N];
 #pragma unroll
-      for (int u = 0; u < kBatchWorkers; ++u) {
-        const int w = wb + u;
-        if (w < W) {                                       // workgroup-uniform
+        for (int u = 0; u < N; ++u) {
+          g[u] = ldq<AL, kBatchStreamG>(gp.p[wb + u], tg.a0, tg.hi, q, true);
+          s[u] = FIRST ? zero4 : ldq<AL, NTS>(S + (int64_t)(wb + u) * e_stride, tg.a0, tg.hi, q, true);
+        }
+#pragma unroll
+        for (int u = 0; u < N; ++u) {
+          const int w = wb + u;
           if (w == 0) a = make_float4(a.x + g[u].x, a.y + g[u].y, a.z + g[u].z, a.w + g[u].w);
           float4 t = g[u];
-          if (j > 0u) t = make_float4(s[u].x + t.x, s[u].y + t.y, s[u].z + t.z, s[u].w + t.w);
-          if (exch) {
-            acc = (w == 0) ? t : make_float4(acc.x + t.x, acc.y + t.y, acc.z + t.z, acc.w + t.w);
-          } else {
-            stq<AL>(S + (int64_t)w * e_stride, tg.a0, tg.hi, q, t);
-          }
+          if (!FIRST) t = make_float4(s[u].x + t.x, s[u].y + t.y, s[u].z + t.z, s[u].w + t.w);
+          if (EXCH) acc = (w == 0) ? t : make_float4(acc.x + t.x, acc.y + t.y, acc.z + t.z, acc.w + t.w);
+          else stq<AL, NTS>(S + (int64_t)w * e_stride, tg.a0, tg.hi, q, t);
+        }
+      };
+      if constexpr (NW > 0) {
+        workers(0, std::integral_constant<int, NW>());
+      } else {
+        int wb = 0;
+        for (; wb + kBatchWorkers <= W; wb += kBatchWorkers) workers(wb, std::integral_constant<int, kBatchWorkers>());
+        switch (W - wb) {                                  // uniform
+          case 1: workers(wb, std::integral_constant<int, 1>()); break;
+          case 2: workers(wb, std::integral_constant<int, 2>()); break;
+          case 3: workers(wb, std::integral_constant<int, 3>()); break;
+          default: break;
+        }
+      }
+      stq<AL, NTA>(A, tg.a0, tg.hi, q, a);
+      if (EXCH) {
+        const float4 d = make_float4(acc.x / denom, acc.y / denom, acc.z / denom, acc.w / denom);
+        if (UPD) {
+          nesterov(d.x, wq.x, vq.x, lr_eff, sink.mu, sink.wd);
+          nesterov(d.y, wq.y, vq.y, lr_eff, sink.mu, sink.wd);
+          nesterov(d.z, wq.z, vq.z, lr_eff, sink.mu, sink.wd);
+          nesterov(d.w, wq.w, vq.w, lr_eff, sink.mu, sink.wd);
+          stq<AL, kBatchStream>(sink.wt, tg.a0, tg.hi, q, wq);
+          stq<AL, kBatchStream>(sink.vel, tg.a0, tg.hi, q, vq);
+        } else {
+          stq<AL, kBatchStream>(sink.out, tg.a0, tg.hi, q, d);
         }
       }
     }
-    stq<AL, kBatchStream>(A, tg.a0, tg.hi, q, a);
-    if (exch) {
-      const float4 d = make_float4(acc.x / denom, acc.y / denom, acc.z / denom, acc.w / denom);
-      if (UPD) {
-        nesterov(d.x, wq.x, vq.x, lr_eff, sink.mu, sink.wd);
-        nesterov(d.y, wq.y, vq.y, lr_eff, sink.mu, sink.wd);
-        nesterov(d.z, wq.z, vq.z, lr_eff, sink.mu, sink.wd);
-        nesterov(d.w, wq.w, vq.w, lr_eff, sink.mu, sink.wd);
-        stq<AL, kBatchStream>(sink.wt, tg.a0, tg.hi, q, wq);
-        stq<AL, kBatchStream>(sink.vel, tg.a0, tg.hi, q, vq);
-      } else {
-        stq<AL, kBatchStream>(sink.out, tg.a0, tg.hi, q, d);
-      }
-    }
-  }
+  };
+  if (j == 0u && !exch) loop(std::true_type(), std::false_type());   // uniform
+  else if (!exch) loop(std::false_type(), std::false_type());
+  else if (j == 0u) loop(std::true_type(), std::true_type());
+  else loop(std::false_type(), std::true_type());
 }
 
 template <bool UPD>
 __device__ __forceinline__ void batch_micro_body(const Ws& ws, const GradPtrs& gp, const Sink& sink,
-                                                 uint32_t parity) {
+                                                 uint32_t parity, int64_t sums_cached) {
   const uint32_t j = batch_slot(ws, parity)[0];
   const uint32_t target = (ws.level[0] == 1) ? 1u : (uint32_t)ws.bmult;
   const bool exch = j + 1u >= target;
@@ -107,18 +131,32 @@ __device__ __forceinline__ void batch_micro_body(const Ws& ws, const GradPtrs& g
   const FlatTile ft = ws.ftiles[blockIdx.x];
   const LayerDev& L = ws.layers[ft.layer];
   const TileGeom tg = tile_geom(L, ft);
-  if (tg.aligned) batch_tile<true, UPD>(ws, gp, sink, tg, j, exch);
-  else batch_tile<false, UPD>(ws, gp, sink, tg, j, exch);
+  const bool nts = tg.a0 >= sums_cached;                   // uniform, like all that follows
+  auto tile = [&](auto n_workers, auto nta) {
+    if (nts) batch_tile<true, UPD, decltype(n_workers)::value, true, decltype(nta)::value>(ws, gp, sink, tg, j, exch);
+    else batch_tile<true, UPD, decltype(n_workers)::value, false, decltype(nta)::value>(ws, gp, sink, tg, j, exch);
+  };
+  if (!tg.aligned) {
+    batch_tile<false, UPD>(ws, gp, sink, tg, j, exch);
+    return;
+  }
+  switch (ws.W) {
+    case 1: tile(std::integral_constant<int, 1>(), std::true_type()); break;
+    case 2: tile(std::integral_constant<int, 2>(), std::false_type()); break;
+    case 3: tile(std::integral_constant<int, 3>(), std::false_type()); break;
+    case 4: tile(std::integral_constant<int, 4>(), std::false_type()); break;
+    default: tile(std::integral_constant<int, 0>(), std::false_type()); break;
+  }
 }
 
 __global__ __launch_bounds__(256) void batch_micro_kernel(const Ws ws, const GradPtrs gp, const Sink sink,
-                                                          uint32_t parity) {
-  batch_micro_body<false>(ws, gp, sink, parity);
+                                                          uint32_t parity, int64_t sums_cached) {
+  batch_micro_body<false>(ws, gp, sink, parity, sums_cached);
 }
 
 __global__ __launch_bounds__(256) void batch_micro_update_kernel(const Ws ws, const GradPtrs gp,
-                                                                 const Sink sink, uint32_t parity) {
-  batch_micro_body<true>(ws, gp, sink, parity);
+                                                                 const Sink sink, uint32_t parity, int64_t sums_cached) {
+  batch_micro_body<true>(ws, gp, sink, parity, sums_cached);
 }
 
 // One workgroup: c = sqrt(sum of all tile partials) (the norm of the whole model's accumulated

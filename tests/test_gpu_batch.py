@@ -42,6 +42,38 @@ def _check_state(gpu, ora, tag):
     assert gpu.payload_words() == (ora.words_last, ora.words_cum), tag
 
 
+@pytest.mark.parametrize("update", [False, True])
+@pytest.mark.parametrize("W", [1, 2, 3, 4, 6, 7, 9, 24])
+def test_every_number_of_workers(W, update):
+    """One to four workers have a loop of their own, more are taken four at a time with one, two, three or none left; 24
+    workers have more sums than stay in the cache, and stream the rest from the middle of a layer on."""
+    print(f"case batch workers W={W} update={update}", flush=True)
+    layers = _ragged_layers() if W < 24 else H.layer_tuples(wl.make_layers([(1, 4, 0), (1250, 1000, 1), (1251, 1000, 1)]))
+    gpu, ora = _make(layers, W, 3, initial_level=0)
+    N = ora.N
+    assert W < 24 or ((224 << 20) // 4 - N) // W < N - 8192
+    rng = np.random.default_rng([6, W])
+    out, w_ref = np.full(N, -7.0, np.float32), rng.standard_normal(N, dtype=np.float32)
+    v_ref = np.zeros(N, np.float32)
+    out_dev, w_dev, v_dev = H.to_dev(out), H.to_dev(w_ref), H.to_dev(v_ref)
+    for t in range(4):
+        grads = [rng.standard_normal(N, dtype=np.float32) for _ in range(W)]
+        dev = [H.to_dev(g) for g in grads]
+        if update:
+            ora.micro_step_update(grads, w_ref, v_ref, 0.1, 0.9)
+            gpu.step_all_update(dev, w_dev, v_dev, 0.1, 0.9)
+            H.assert_bits_equal(w_dev.cpu().numpy(), w_ref, f"micro-step {t}: weights")
+            H.assert_bits_equal(v_dev.cpu().numpy(), v_ref, f"micro-step {t}: velocity")
+        else:
+            d, _ = ora.micro_step(grads)
+            gpu.step_all(dev, out_dev)
+            if d is not None:
+                out[ora.mask] = d[ora.mask]
+            H.assert_bits_equal(out_dev.cpu().numpy(), out, f"micro-step {t}: out")
+    _check_state(gpu, ora, "at the end")
+    gpu.destroy()
+
+
 @pytest.mark.parametrize("W,M", [(1, 2), (3, 4), (5, 3)])
 def test_micro_steps_store_path(W, M):
     """Small batch (every micro-step exchanged), then the switch to the large batch by the
