@@ -1045,11 +1045,6 @@ __global__ __launch_bounds__(kPickThreads) void topk_pick12_kernel(const Ws ws, 
   if (!hit && !zhit) ws.hist2m[wl * kL2Bins + lane] = 0u;
 }
 
-// A workgroup takes kCountTiles consecutive tiles, a wave one quarter of each; everything the tiles
-// need is requested before the first of them is looked at.  (Two tiles per workgroup are no faster
-// than one, on 100 000 tiles as on 5 000.)
-constexpr int kCountTiles = 1;
-
 struct CountLds {
   // The staging lists of a missed layer's tile (values, then offsets), used by that rare path only.
   static constexpr int kListWords = 4 * kCandLdsSlots;
@@ -1059,69 +1054,109 @@ struct CountLds {
   uint4* qi;
 };
 
-struct CountTile { FlatTile ft; int64_t qslot; QuarterHead qh; uint32_t b1, b2, mode; int ntiles; };
+struct CountTile { FlatTile ft; int64_t qslot; uint32_t b1, b2, mode; int ntiles; };
 
-__device__ __forceinline__ void count3_tile(const Ws& ws, int w, const CountTile& t, const CountLds& lds,
-                                            int wave, int lane) {
-  const FlatTile& ft = t.ft;
-  if (t.ntiles == 1) return;                               // decided by the last pick kernel
+__device__ __forceinline__ void load_count_state(const Ws& ws, int w, CountTile& t) {
+  const SelState* sp = ws.sel + (int64_t)w * ws.L + t.ft.layer;
+  t.b1 = rfl(ld_here(&sp->b1)); t.b2 = rfl(ld_here(&sp->b2)); t.mode = rfl(ld_here(&sp->mode));
+  t.ntiles = (int)rfl(ld_here(reinterpret_cast<const uint32_t*>(&ws.layers[t.ft.layer].ntiles)));
+}
+
+// The guess missed: nothing useful was staged.  This tile's keys of b1 are staged now (one more read of Delta) with their
+// level-2 counts; the layer's pick kernel takes it from there.  Every thread of the workgroup calls it.
+__device__ __forceinline__ void count3_missed(const Ws& ws, int w, const FlatTile& ft, uint32_t b1, const CountLds& lds,
+                                              int wave) {
   const LayerDev& L = ws.layers[ft.layer];
-  const int tl = ft.start >> kTileShift;
-  const uint32_t b1 = t.b1, b2 = t.b2;
-  if (t.mode == 1u) {                                      // uniform over the workgroup
-    // The guess missed: nothing useful was staged.  This tile's keys of b1 are staged now (one
-    // more read of Delta) with their level-2 counts; the layer's pick kernel takes it from there.
-    const TileGeom tg = tile_geom(L, ft);
-    const CandList cl = {lds.rare + wave * kCandLdsSlots,
-                         reinterpret_cast<uint16_t*>(lds.rare + CountLds::kListWords) + wave * kCandLdsSlots, lds.qi};
-    if (tg.aligned) restage_tile<true>(ws, w, ft, L, tg, b1, cl, lds.sub2);
-    else restage_tile<false>(ws, w, ft, L, tg, b1, cl, lds.sub2);
-    __syncthreads();                                       // the block of LDS may serve the next tile
-    return;
-  }
-  uint32_t* list = ws.qlist + t.qslot * kQListCap;
-  uint32_t n_gt = 0, n_in = 0;                             // wave-uniform
-  const uint32_t above = for_quarter_keys(ws, L, w, tl, wave, t.qslot, t.qh, b1, lane, [&](uint32_t key, bool valid) {
+  const TileGeom tg = tile_geom(L, ft);
+  const CandList cl = {lds.rare + wave * kCandLdsSlots,
+                       reinterpret_cast<uint16_t*>(lds.rare + CountLds::kListWords) + wave * kCandLdsSlots, lds.qi};
+  if (tg.aligned) restage_tile<true>(ws, w, ft, L, tg, b1, cl, lds.sub2);
+  else restage_tile<false>(ws, w, ft, L, tg, b1, cl, lds.sub2);
+}
+
+// One wave quarter: the keys of cell (b1, b2) go to its short list; n_in: their number.  Returns the entries above the cell.
+__device__ __forceinline__ uint32_t count3_quarter(const Ws& ws, int w, const CountTile& t, int quarter, const QuarterHead& qh,
+                                                   int lane, uint32_t& n_in) {
+  const uint32_t b2 = t.b2;
+  uint32_t* list = ws.qlist + (t.qslot + quarter) * kQListCap;
+  uint32_t n_gt = 0, n_cell = 0;                           // wave-uniform
+  const uint32_t above = for_quarter_keys(ws, ws.layers[t.ft.layer], w, t.ft.start >> kTileShift, quarter, t.qslot + quarter, qh, t.b1, lane,
+                                          [&](uint32_t key, bool valid) {
     const uint32_t bb = bin2_of(key);
     const uint64_t mv = ballot64(valid);
     n_gt += (uint32_t)__popcll(ballot64(bb > b2) & mv);
     const uint64_t m2 = ballot64(bb == b2) & mv;
     if (m2 != 0) {
-      const uint32_t pos = n_in + lanes_below(m2, lane);
+      const uint32_t pos = n_cell + lanes_below(m2, lane);
       if (valid && bb == b2 && pos < (uint32_t)kQListCap) list[pos] = key;
-      n_in += (uint32_t)__popcll(m2);
+      n_cell += (uint32_t)__popcll(m2);
     }
   });
-  if (lane == 0) { ws.gtq[t.qslot] = above + n_gt; ws.eqq[t.qslot] = n_in; }
+  n_in = n_cell;
+  return above + n_gt;
 }
 
+// A workgroup takes one tile, a wave one quarter of it; its list is requested before the layer's entry and its state have
+// arrived.  (Two tiles per workgroup are no faster.)
 __global__ __launch_bounds__(256) void topk_count3_kernel(const Ws ws, int w0) {
   __shared__ __attribute__((aligned(16))) uint32_t rare[CountLds::kRareWords];
   __shared__ uint32_t sub2[kL2Bins];
   __shared__ uint4 qi[4];
-  const CountLds lds = {rare, sub2, qi};
   const int w = w0 + blockIdx.y;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int tile0 = (int)blockIdx.x * kCountTiles;
-  CountTile t[kCountTiles];
-#pragma unroll
-  for (int u = 0; u < kCountTiles; ++u) t[u].ft = ws.ftiles[min(tile0 + u, ws.n_ftiles - 1)];
-  // the lists are requested before the layers' entries and their states have arrived
-#pragma unroll
-  for (int u = 0; u < kCountTiles; ++u) {
-    t[u].qslot = (int64_t)w * ws.q_stride + t[u].ft.qslot0 + wave;
-    t[u].qh = load_quarter_head(ws, t[u].qslot, lane);
+  CountTile t;
+  t.ft = ws.ftiles[blockIdx.x];
+  t.qslot = (int64_t)w * ws.q_stride + t.ft.qslot0;
+  const QuarterHead qh = load_quarter_head(ws, t.qslot + wave, lane);
+  load_count_state(ws, w, t);
+  if (t.ntiles == 1) return;                               // decided by the last pick kernel
+  if (t.mode == 1u) {                                      // uniform over the workgroup
+    count3_missed(ws, w, t.ft, t.b1, CountLds{rare, sub2, qi}, wave);
+    return;
   }
+  uint32_t n_in;
+  const uint32_t n_above = count3_quarter(ws, w, t, wave, qh, lane, n_in);
+  if (lane == 0) { ws.gtq[t.qslot + wave] = n_above; ws.eqq[t.qslot + wave] = n_in; }
+}
+
+// The same with a tile per wave, its four lists requested together: a quarter of the workgroups, each of which
+// waits for the same chain of loads, and whole 16-byte records.  For very many tiles (see kWideCountTiles on the host side).
+__global__ __launch_bounds__(256) void topk_count3_wide_kernel(const Ws ws, int w0) {
+  __shared__ __attribute__((aligned(16))) uint32_t rare[CountLds::kRareWords];
+  __shared__ uint32_t sub2[kL2Bins];
+  __shared__ uint4 qi[4];
+  __shared__ uint32_t missed[4];                           // the bin to stage of a tile whose guess missed, else kNoGuess
+  const int w = w0 + blockIdx.y;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int tile = (int)blockIdx.x * 4 + wave;
+  CountTile t;
+  t.ft = ws.ftiles[min(tile, ws.n_ftiles - 1)];
+  t.qslot = (int64_t)w * ws.q_stride + t.ft.qslot0;
+  QuarterHead qh[4];
 #pragma unroll
-  for (int u = 0; u < kCountTiles; ++u) {
-    const SelState* sp = ws.sel + (int64_t)w * ws.L + t[u].ft.layer;
-    t[u].b1 = rfl(ld_here(&sp->b1)); t[u].b2 = rfl(ld_here(&sp->b2)); t[u].mode = rfl(ld_here(&sp->mode));
-    t[u].ntiles = (int)rfl(ld_here(reinterpret_cast<const uint32_t*>(&ws.layers[t[u].ft.layer].ntiles)));
+  for (int q = 0; q < 4; ++q) qh[q] = load_quarter_head(ws, t.qslot + q, lane);
+  load_count_state(ws, w, t);
+  const bool mine = tile < ws.n_ftiles && t.ntiles > 1;    // single tiles are decided by the last pick kernel
+  if (lane == 0) missed[wave] = mine && t.mode == 1u ? t.b1 : kNoGuess;
+  if (mine && t.mode != 1u) {
+    uint32_t above = 0u, in = 0u;                          // of quarter `lane`
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      uint32_t n_in;
+      const uint32_t n_above = count3_quarter(ws, w, t, q, qh[q], lane, n_in);
+      if (lane == q) { above = n_above; in = n_in; }
+    }
+    if (lane < 4) { ws.gtq[t.qslot + lane] = above; ws.eqq[t.qslot + lane] = in; }
   }
-#pragma unroll
-  for (int u = 0; u < kCountTiles; ++u)
-    if (tile0 + u < ws.n_ftiles) count3_tile(ws, w, t[u], lds, wave, lane);   // uniform over the workgroup
+  __syncthreads();
+  for (int u = 0; u < 4; ++u) {                            // uniform over the workgroup
+    const uint32_t b1 = rfl(missed[u]);
+    if (b1 == kNoGuess) continue;
+    count3_missed(ws, w, ws.ftiles[(int)blockIdx.x * 4 + u], b1, CountLds{rare, sub2, qi}, wave);
+    __syncthreads();                                       // the block of LDS serves the next tile
+  }
 }
 
 // Two sizes of the last pick kernel: kLdsList keys of bin (b1, b2) of a layer gathered in LDS

@@ -510,6 +510,11 @@ void prof_end(acc_ctx* c, EventPair& p) { c->pending.push_back(p); }
 // with the fused update, ResNet-18 W = 1 103.3 -> 96.3 | 90 -> 95.7, W = 4 (with Ws::q_stream) 203 -> 188 | 181 -> 182.
 constexpr int64_t kCachedError = (int64_t(32) << 20) / 4, kCachedUpdate = (int64_t(16) << 20) / 8;
 
+// Tiles of a launch from which the counting kernel takes a tile per wave.  us per step, a quarter per wave -> a tile per wave:
+// LSTM set W = 16 (100 000 tiles) 2395 -> 2373, K = 1 % 2081 -> 2053, W = 4 (25 000) 703.8 -> 701.7; ResNet-18 W = 8 (11 000) 300 -> 302,
+// four small layers W = 2 36.6 -> 40.4.
+constexpr int64_t kWideCountTiles = 20000;
+
 // TopK selection of workers [w0, w0 + nw): the fused error-feedback pass, then the per-layer decisions
 // (level-1/2 bins, re-staging after a missed guess, level-3/4 counts, threshold and prefixes).  e_reread: Delta is read
 // again within the step, whatever the guess.
@@ -521,7 +526,10 @@ int launch_topk_select(acc_ctx* c, int w0, int nw, int e_reread) {
   else
     ACC_LAUNCH_AS(c, topk_ef_hist_kernel, topk_ef_hist_kernel<false>, tiles, dim3(256), ws, c->grads, w0, kCachedError, e_reread);
   ACC_LAUNCH(c, topk_pick12_kernel, dim3(ws.L, nw), dim3(kPickThreads), ws, w0);
-  ACC_LAUNCH(c, topk_count3_kernel, dim3((ws.n_ftiles + kCountTiles - 1) / kCountTiles, nw), dim3(256), ws, w0);
+  if ((int64_t)ws.n_ftiles * nw >= kWideCountTiles)
+    ACC_LAUNCH_AS(c, topk_count3_kernel, topk_count3_wide_kernel, dim3((ws.n_ftiles + 3) / 4, nw), dim3(256), ws, w0);
+  else
+    ACC_LAUNCH(c, topk_count3_kernel, tiles, dim3(256), ws, w0);
   ACC_LAUNCH(c, topk_pick3_kernel, dim3(ws.L, nw), dim3(kPickThreads), ws, w0, c->step_id);
   if (c->plan.pick3_big) ACC_LAUNCH(c, topk_pick3_big_kernel, dim3(ws.L, nw), dim3(kPickThreads), ws, w0, c->step_id);
   return ACC_OK;

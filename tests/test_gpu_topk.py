@@ -733,3 +733,38 @@ def test_streamed_batched_steps_equal_call_by_call_ones(crit):
             assert np.array_equal(a[0], b[0]) and np.array_equal(H.bits(a[1]), H.bits(b[1])), f"payload {i}"
         else:
             assert np.array_equal(np.ascontiguousarray(a).view(np.uint8), np.ascontiguousarray(b).view(np.uint8)), f"K {crit}: output {i}"
+
+
+def test_a_tile_per_wave_in_the_counting_kernel():
+    """A batched step of more than 20 000 tiles, whose counting kernel takes a tile per wave, against the call-by-call path,
+    which takes a quarter per wave: layers of two tiles (the second of one element, of a few, or whole), of one and of three; the first
+    step's guess misses everywhere, a layer whose scale jumps misses later, one layer is all ties."""
+    print("case wide counting kernel", flush=True)
+    import torch
+    sizes = [8193, 8192 + 7, 2 * 8192, 5000, 2 * 8192 + 4097]
+    layers = wl.make_layers([(1, sizes[i % 5], 0) for i in range(350)])
+    N, W = wl.total_params(layers), 32
+    assert W * sum(-(-l.numel // 8192) for l in layers) >= 20000
+    gen = torch.Generator(device="cuda:0")
+    results = []
+    for mode in ("all", "calls"):
+        gpu = B.Accordion(B.ACC_TOPK, H.layer_tuples(layers), W, 10, 1)
+        gen.manual_seed(9)
+        out, got = H.dev_out(N), []
+        for step in range(4):
+            dg = [torch.randn(N, generator=gen, device="cuda:0") for _ in range(W)]
+            for g in dg:
+                g[layers[0].offset:layers[0].offset + layers[0].numel] *= 64.0 ** step
+                g[layers[2].offset:layers[2].offset + layers[2].numel] = 0.5
+            if mode == "all":
+                gpu.step_all(dg, out)
+            else:
+                for w in range(W):
+                    gpu.compress_step(w, dg[w], 0)
+                gpu.aggregate(0)
+                gpu.decompress(out)
+            got.append(out.cpu().numpy())
+        results.append(got + [gpu.get_state().copy()])
+        gpu.destroy()
+    for i, (a, b) in enumerate(zip(*results)):
+        assert np.array_equal(np.ascontiguousarray(a).view(np.uint8), np.ascontiguousarray(b).view(np.uint8)), f"output {i}"
