@@ -53,7 +53,7 @@ __device__ __forceinline__ bool owns(const LaneCols& lc, int v) {
 
 // Streaming access for what a step touches once, so that Delta stays in the caches between the
 // passes (first pass 119 -> 110 us on ResNet-18 shapes, W = 4).
-constexpr bool kPsgdStreamG = true;     // gradients: read once per step (odd sizes, W = 3: 118.5 us per step plain, 114.2 streamed)
+constexpr bool kPsgdStreamG = true;     // gradients: read once per step
 constexpr bool kPsgdStreamA = true;     // accumulator: read and written once per step
 constexpr bool kPsgdStreamOut = true;   // averaged gradient: written once, read by nobody here
 
@@ -168,7 +168,7 @@ __device__ __forceinline__ void ef_load(const EfTile& t, int i0, EfRows& r) {
     const int i = i0 + 4 * b;
     const int64_t rb = (int64_t)min(i, t.row_end - 1) * t.cols;
     const int c = i < t.row_end ? t.lc.c : 0;
-    load_row<MODE, kPsgdStreamG && MODE != kRowNarrow>(t.g + rb, c, t.cols, r.g[b]);
+    load_row<MODE, kPsgdStreamG && MODE == kRowAligned>(t.g + rb, c, t.cols, r.g[b]);
     load_row<MODE>(t.e + rb, c, t.cols, r.e[b]);
     if (HASA) load_row<MODE, kPsgdStreamA && MODE == kRowAligned>(t.Asrc + rb, c, t.cols, r.a[b]);
   }
