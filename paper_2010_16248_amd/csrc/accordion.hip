@@ -504,11 +504,12 @@ void prof_end(acc_ctx* c, EventPair& p) { c->pending.push_back(p); }
 // stores.  Everything accessed plainly, whatever does not fit is evicted while the next pass reads, dirty line by dirty line: e = g + e
 // over 3 x 179 MB in turn runs at 5.8 TB/s so, 6.2 streamed.  A memory that stays in the cache whole is faster plain, but a
 // training program's own passes lie between two steps.  us per step, three states in turn | one state again and again,
-// everything plain -> 32 MB of e and 16 MB of w and v plain (ResNet-18 shapes, K = 10 %): W = 4 194 -> 169 | 162 -> 164; W = 8 347 -> 320 | 343 -> 289;
-// fused update at W = 1 113 -> 96 | 89 -> 95, W = 4 216 -> 198 | 186 -> 186; VGG-19 W = 1 130 -> 123 | 117 -> 122, W = 4 338 -> 315 | 332 -> 288;
-// LSTM W = 16 2525 -> 2410 | 2543 -> 2432.  Nothing plain: W = 4 170 | 169; 64 MB of e: 180 | 163; 64 MB of w and v: W = 1 107 | 93.  PowerSGD
+// everything plain -> 64 MB of e and 16 MB of w and v plain (ResNet-18 shapes, K = 10 %): W = 4 194 -> 181 | 162 -> 162.5; W = 8 347 -> 327 | 343 -> 288;
+// fused update at W = 1 113 -> 94 | 89 -> 94; VGG-19 W = 4 338 -> 319 | 332 -> 284; LSTM W = 16 2525 -> 2410 | 2543 -> 2432.  Less of e plain
+// is better where nothing of a state stays (W = 4 169 | 164 with 32 MB, 170 | 169 with none) and worse in windows of four steps of
+// one state (VGG-19 at K = 99 % and 2 %, W = 2: plain 1442, 64 MB 1462, 32 MB 1483); 96 MB 187 | 162.  64 MB of w and v: W = 1 107 | 93.  PowerSGD
 // with the fused update, ResNet-18 W = 1 103.3 -> 96.3 | 90 -> 95.7, W = 4 (with Ws::q_stream) 203 -> 188 | 181 -> 182.
-constexpr int64_t kCachedError = (int64_t(32) << 20) / 4, kCachedUpdate = (int64_t(16) << 20) / 8;
+constexpr int64_t kCachedError = (int64_t(64) << 20) / 4, kCachedUpdate = (int64_t(16) << 20) / 8;
 
 // Tiles of a launch from which the counting kernel takes a tile per wave.  us per step, a quarter per wave -> a tile per wave:
 // LSTM set W = 16 (100 000 tiles) 2395 -> 2373, K = 1 % 2081 -> 2053, W = 4 (25 000) 703.8 -> 701.7; ResNet-18 W = 8 (11 000) 300 -> 302,
@@ -786,12 +787,13 @@ static int32_t init_common(const acc_config* cfg, void* workspace_dev, size_t wo
     ws.tpending = at<uint32_t>(c, p.r_tpending);
     // The compaction is the last to read Delta (where it does: band guesses) and the candidate lists.  Read with the streaming
     // hint, what lies dirty in the Infinity Cache goes back to memory under this pass instead of during the next one.  Delta:
-    // from 64 MB on, all of it where it exceeds the cache (ResNet-18 shapes K = 99 %, W = 4, 224 us per step plain, 217 from 64 MB
-    // on, 217.5 streamed throughout; one state again and again 198, 202, 215; LSTM set W = 4 949, 924, 902).  Lists: where there are
+    // where the error memory exceeds the cache (LSTM set K = 99 %, W = 4, 949 -> 902 us per step; ResNet-18 shapes W = 4, 179 MB, gain 7 of
+    // 224, but lose 4 of 197 where one state steps again and again, and VGG-19 W = 2 55 of 1440 in windows of four steps: not below).
+    // Lists: where there are
     // more than 64 M elements (ResNet-18 shapes K = 10 %, W = 8 325 -> 304 | 292 -> 297, VGG-19 W = 4 318 -> 302 | 292 -> 300, odd sizes W = 12
     // 340 -> 316 | 307 -> 310, LSTM W = 4 709 -> 704 | 688 -> 696; ResNet-18 W = 4, 45 M elements, 170.0 -> 169.4 | 164.7 -> 168.1: not below).
     const int64_t elements = p.e_stride * cfg->n_workers;
-    ws.delta_cached = 4 * elements > (int64_t(224) << 20) ? 0 : (int64_t(16) << 20) / cfg->n_workers;
+    ws.delta_stream = 4 * elements > (int64_t(224) << 20) ? 1 : 0;
     ws.lists_stream = elements > (int64_t(64) << 20) ? 1 : 0;
   }
   ws.bstate = at<uint32_t>(c, p.r_bstate);

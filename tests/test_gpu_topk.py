@@ -697,14 +697,14 @@ def test_rows_that_a_step_leaves_alone(pad):
 
 @pytest.mark.parametrize("crit", [10, 40, 99])
 def test_streamed_batched_steps_equal_call_by_call_ones(crit):
-    """A context of more than 64 M elements, whose batched steps stream the error memory (beyond 32 MB), the candidate lists
+    """A context of more than 64 M elements, whose batched steps stream the error memory (beyond 64 MB), the candidate lists
     (K = 10 %) and Delta in the compaction (K = 40 % guesses a band, 99 % has the holes layout), against the call-by-call
     path, which takes every selection from Delta: mean, payloads of the first and last worker, memory, accumulator."""
     print(f"case streamed steps K={crit}", flush=True)
     import torch
     layers = wl.make_layers([(1, 3, 0), (3000, 401, 1), (1, 64, 0), (1200, 768, 1), (1, 8192, 0), (120, 1024, 1)])
     N, W = wl.total_params(layers), 30
-    assert N * W > 64 << 20
+    assert N * W > 64 << 20 and 4 * N * W > 224 << 20
     gen = torch.Generator(device="cuda:0")
     results = []
     for mode in ("all", "calls"):

@@ -72,13 +72,13 @@ def test_topk_fused_update_is_bit_exact(wd, crit, noncrit, initial):
 
 @pytest.mark.parametrize("crit", [10, 40])
 def test_topk_update_beyond_what_stays_in_the_cache(crit):
-    """Error memories of more than 32 MB and weights of more than 2 M elements: the first pass and the fused update change
+    """Error memories of more than 64 MB and weights of more than 2 M elements: the first pass and the fused update change
     from plain to streaming access in the middle of a layer.  A dense layer, one of which few rows are used (its threshold is
     zero at K = 10 %), layers off the 16-byte boundary, a single tile; K = 40 % guesses a band, whose compaction reads Delta."""
     print(f"case topk update beyond the cache K={crit}", flush=True)
     layers = wl.make_layers([(1, 3, 0), (3000, 401, 1), (1, 64, 0), (1200, 768, 1), (1, 8192, 0), (120, 1024, 1)])
-    N, W = wl.total_params(layers), 4
-    assert N > (16 << 20) // 8 and (W - 1) * N < (32 << 20) // 4 < W * N
+    N, W = wl.total_params(layers), 8
+    assert N > (16 << 20) // 8 and (W - 1) * N < (64 << 20) // 4 < W * N
     gpu, ora = H.make_pair(B.ACC_TOPK, layers, W, crit, 1)
     rng = np.random.default_rng([5, crit])
     w_ref, v_ref = rng.standard_normal(N).astype(np.float32), np.zeros(N, np.float32)
