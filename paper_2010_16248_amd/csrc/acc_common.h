@@ -146,7 +146,6 @@ struct Ws {
   int32_t W, L, rmax;
   int32_t mrows, qrows;        // PowerSGD: rows of a matrix tile / of a tile of the right product
   int32_t pmean_in_orth;       // PowerSGD: the orthogonalisation sums the partials of P itself
-  int32_t q_stream;            // PowerSGD: the right product streams Delta
   int32_t n_ftiles, n_mtiles, n_qmtiles, n_qtiles, n_vectiles, n_mat, n_ptiles;
   int32_t n_t2slots;           // TopK: slots of t2 per worker
   float eta;

@@ -637,7 +637,7 @@ __global__ __launch_bounds__(kOrthThreads) void psgd_orth_kernel(const Ws ws, co
 // 2 x 20000 at W = 4 118.5 -> 112.6 us, 200 of 512 x 9 33.0 -> 30.9).
 constexpr int kQBatch = 4;   // rows a wave requests together; two such batches are in flight
 
-// STREAM (Ws::q_stream): Delta is requested with the streaming hint.  It is not read again before the next step, and a plain
+// STREAM (chosen on the host): Delta is requested with the streaming hint.  It is not read again before the next step, and a plain
 // read leaves it in the Infinity Cache, dirty, for the next passes to evict; read so, its lines go back to memory here, at next
 // to no cost (see the host side).
 // (From clamped addresses: a request behind a branch would make every wait in the loop a wait for all of them.)
@@ -760,6 +760,7 @@ __device__ __forceinline__ void q_tile(const Ws& ws, const LayerDev& L, const Ma
   }
 }
 
+template <bool STREAM>
 __global__ __launch_bounds__(256) void psgd_q_kernel(const Ws ws, int w0) {
   __shared__ double red[2][16][64];
   __shared__ float ps[kQRows][kMaxRank];
@@ -769,16 +770,9 @@ __global__ __launch_bounds__(256) void psgd_q_kernel(const Ws ws, int w0) {
   const int level = ws.level[t.layer];
   const float* __restrict__ e = ws.e + (int64_t)w * ws.e_stride;
   double* qpart = ws.Qpart + (int64_t)w * ws.qpart_stride;
-  const bool stream = ws.q_stream != 0;                      // uniform
   switch (row_mode(L)) {
-    case kRowAligned:
-      if (stream) q_tile<kRowAligned, true>(ws, L, t, e, qpart, level, red, ps);
-      else q_tile<kRowAligned, false>(ws, L, t, e, qpart, level, red, ps);
-      break;
-    case kRowUnaligned:
-      if (stream) q_tile<kRowUnaligned, true>(ws, L, t, e, qpart, level, red, ps);
-      else q_tile<kRowUnaligned, false>(ws, L, t, e, qpart, level, red, ps);
-      break;
+    case kRowAligned: q_tile<kRowAligned, STREAM>(ws, L, t, e, qpart, level, red, ps); break;
+    case kRowUnaligned: q_tile<kRowUnaligned, STREAM>(ws, L, t, e, qpart, level, red, ps); break;
     default: q_tile<kRowNarrow, false>(ws, L, t, e, qpart, level, red, ps); break;
   }
 }

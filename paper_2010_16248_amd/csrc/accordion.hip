@@ -40,7 +40,7 @@ struct Plan {
   std::vector<int32_t> vectiles;
   std::vector<int32_t> matlayers;
   int32_t rmax = 0;
-  int32_t pmean_in_orth = 0, q_stream = 0;   // PowerSGD: see Ws
+  int32_t pmean_in_orth = 0, q_stream = 0;   // PowerSGD: see Ws; the right product streams Delta
   int32_t mrows = kMatRows, qrows = kQRows;   // PowerSGD: rows of the two kinds of matrix tiles
   int64_t N = 0, e_stride = 0;
   int64_t q_total = 0;   // floats of Q in the caller's layout (rows of rmax floats)
@@ -574,7 +574,12 @@ int launch_agg0(acc_ctx* c) {
 
 int launch_phase1(acc_ctx* c, int w0, int nw) {
   const Ws& ws = c->ws;
-  if (ws.n_qmtiles > 0) ACC_LAUNCH(c, psgd_q_kernel, dim3(ws.n_qmtiles, nw), dim3(256), ws, w0);
+  if (ws.n_qmtiles == 0) return ACC_OK;
+  // a kernel for each: one that held both was 45 KB of code instead of 28, which a step that follows a program's own kernels
+  // has to fetch (ResNet-18 shapes at W = 1, plain either way: 83.3 us per step so, 80.8 with a kernel for each)
+  const dim3 grid(ws.n_qmtiles, nw);
+  if (c->plan.q_stream) ACC_LAUNCH_AS(c, psgd_q_kernel, psgd_q_kernel<true>, grid, dim3(256), ws, w0);
+  else ACC_LAUNCH_AS(c, psgd_q_kernel, psgd_q_kernel<false>, grid, dim3(256), ws, w0);
   return ACC_OK;
 }
 
@@ -808,7 +813,6 @@ static int32_t init_common(const acc_config* cfg, void* workspace_dev, size_t wo
   ws.rmax = p.rmax;
   ws.mrows = p.mrows;
   ws.pmean_in_orth = p.pmean_in_orth;
-  ws.q_stream = p.q_stream;
   ws.qrows = p.qrows;
   ws.n_ftiles = (int32_t)p.ftiles.size();
   ws.n_t2slots = (int32_t)p.n_t2slots;
