@@ -637,9 +637,9 @@ __global__ __launch_bounds__(kOrthThreads) void psgd_orth_kernel(const Ws ws, co
 // 2 x 20000 at W = 4 118.5 -> 112.6 us, 200 of 512 x 9 33.0 -> 30.9).
 constexpr int kQBatch = 4;   // rows a wave requests together; two such batches are in flight
 
-// STREAM (chosen on the host): Delta is requested with the streaming hint.  It is not read again before the next step, and a plain
+// STREAM: Delta is requested with the streaming hint.  It is not read again before the next step, and a plain
 // read leaves it in the Infinity Cache, dirty, for the next passes to evict; read so, its lines go back to memory here, at next
-// to no cost (see the host side).
+// to no cost.  Which rows of which contexts: see QStream.
 // (From clamped addresses: a request behind a branch would make every wait in the loop a wait for all of them.)
 template <int MODE, bool STREAM>
 __device__ __forceinline__ void q_load(const float* __restrict__ e, int cols, int row_end, const LaneCols& lc, int i0,
@@ -760,7 +760,13 @@ __device__ __forceinline__ void q_tile(const Ws& ws, const LayerDev& L, const Ma
   }
 }
 
-template <bool STREAM>
+// Which rows the right product reads with the streaming hint (chosen on the host, see make_plan_tiled).
+// A row that does not start on a cache line shares its first and last line with its neighbours, which other waves and other workgroups
+// read: streamed, the line has to be fetched again, so such rows are streamed only where the error memory would not stay in the
+// cache in any case.
+enum QStream { kQPlain = 0, kQAlignedRows = 1, kQAllRows = 2 };
+
+template <int QS>
 __global__ __launch_bounds__(256) void psgd_q_kernel(const Ws ws, int w0) {
   __shared__ double red[2][16][64];
   __shared__ float ps[kQRows][kMaxRank];
@@ -771,8 +777,8 @@ __global__ __launch_bounds__(256) void psgd_q_kernel(const Ws ws, int w0) {
   const float* __restrict__ e = ws.e + (int64_t)w * ws.e_stride;
   double* qpart = ws.Qpart + (int64_t)w * ws.qpart_stride;
   switch (row_mode(L)) {
-    case kRowAligned: q_tile<kRowAligned, STREAM>(ws, L, t, e, qpart, level, red, ps); break;
-    case kRowUnaligned: q_tile<kRowUnaligned, STREAM>(ws, L, t, e, qpart, level, red, ps); break;
+    case kRowAligned: q_tile<kRowAligned, (QS >= kQAlignedRows)>(ws, L, t, e, qpart, level, red, ps); break;
+    case kRowUnaligned: q_tile<kRowUnaligned, (QS >= kQAllRows)>(ws, L, t, e, qpart, level, red, ps); break;
     default: q_tile<kRowNarrow, false>(ws, L, t, e, qpart, level, red, ps); break;
   }
 }

@@ -40,7 +40,7 @@ struct Plan {
   std::vector<int32_t> vectiles;
   std::vector<int32_t> matlayers;
   int32_t rmax = 0;
-  int32_t pmean_in_orth = 0, q_stream = 0;   // PowerSGD: see Ws; the right product streams Delta
+  int32_t pmean_in_orth = 0, q_stream = 0;   // PowerSGD: see Ws, QStream
   int32_t mrows = kMatRows, qrows = kQRows;   // PowerSGD: rows of the two kinds of matrix tiles
   int64_t N = 0, e_stride = 0;
   int64_t q_total = 0;   // floats of Q in the caller's layout (rows of rmax floats)
@@ -143,6 +143,7 @@ int make_plan_tiled(const acc_config* c, Plan& p, char* err, bool coarse) {
   p.layers.resize(nl);
   if (c->method == ACC_POWERSGD && !coarse) choose_tiling(c, p);
   int64_t ntile = 0, orth_loads = 0;   // orth_loads: most partial sums of P that a thread of the orthogonalisation would add
+  int64_t aligned_rows = 0;            // elements of the matrix layers whose rows are aligned
   for (int i = 0; i < nl; ++i) {
     const acc_layer& l = c->layers[i];
     LayerDev& d = p.layers[i];
@@ -177,6 +178,7 @@ int make_plan_tiled(const acc_config* c, Plan& p, char* err, bool coarse) {
         d.rank[1] = std::max(1, std::min(c->rank_crit, cap));
         d.n_colchunks = (l.cols + kMatCols - 1) / kMatCols;
         d.mt0 = (int32_t)p.mtiles.size();
+        if (d.vec4) aligned_rows += n;
         const int n_rb = (l.rows + p.mrows - 1) / p.mrows;
         d.n_rowblocks = (l.rows + p.qrows - 1) / p.qrows;
         d.q_off = p.q_dev;
@@ -232,11 +234,17 @@ int make_plan_tiled(const acc_config* c, Plan& p, char* err, bool coarse) {
   // The right product, which reads Delta for the last time in the step, streams it unless the error memory may stay in the
   // 256 MB Infinity Cache beside what else a program does.  Read plainly, Delta stays there dirty, and the passes after it
   // wait for its lines to be evicted; read with the streaming hint, they go back to memory under this pass (e = g + e over
-  // 3 x 179 MB in turn and a read of e after each: 91 + 26 us plain, 91 + 9 so).  us per step, three states in turn | one state
-  // again and again, plain -> streamed: ResNet-18 shapes W = 4 172.2 -> 158.3 | 156.1 -> 157.7, W = 8 304 -> 277 | 291 -> 274, W = 2 (89 MB)
-  // 103.8 -> 102.5 | 100.9 -> 102.2, VGG-19 W = 4 300 -> 275 | 281 -> 272, LSTM W = 1 542 -> 513 | 497 -> 504, W = 4 1040 -> 997 | 1025 -> 997; below
-  // the line ResNet-18 W = 1 (45 MB) 75.3 -> 76.0, odd sizes W = 3 (67 MB) 119.6 -> 119.0 | 108 -> 111.
-  p.q_stream = 4 * p.e_stride * c->n_workers > (int64_t(72) << 20) ? 1 : 0;
+  // 3 x 179 MB in turn and a read of e after each: 91 + 26 us plain, 91 + 9 so).  us per step, plain -> streamed, three states in
+  // turn | one state again and again | one state and 1 GB of a program's own traffic between its steps | the same and the gradients written
+  // just before the step.  Aligned rows, where those of all workers take more than 72 MiB: ResNet-18 shapes W = 4 (170 MiB)
+  // 172 -> 158 | 156 -> 158 | 172 -> 165 | 157 -> 153, W = 2 (85 MiB) 103.7 -> 102.5 | 101.1 -> 102.4 | 114 -> 109 | 105 -> 103, VGG-19 W = 1 (78 MiB)
+  // 116 -> 115 | 113.7 -> 115.0 | 128 -> 123 | 119 -> 115, W = 4 (314 MiB) 319 -> 274 | 315 -> 272 | 321 -> 281 | 319 -> 282; LSTM W = 1 (196 MiB)
+  // 541 -> 513 | 496 -> 503 | 535 -> 529 | 514 -> 507; the next smaller set measured is ResNet-18 W = 1 (43 MiB): 75.3 -> 76.0 three states in turn.
+  // Unaligned rows (the odd-sized set, of which 6 % are aligned), from 224 MiB of error memory on: W = 3 (86 MiB) 119 -> 118.5 | 108 -> 111 |
+  // 120 -> 124 | 111 -> 116, W = 6 (173 MiB) 194 -> 192 | 181 -> 191 | 165 -> 171 | 159 -> 165, W = 7 (202 MiB) 223 -> 218 | 214 -> 217 | 193 -> 196 |
+  // 186 -> 189, W = 8 (231 MiB) 251 -> 242 | 244 -> 241 | 220 -> 220 | 215 -> 215, W = 12 (346 MiB) 361 -> 339 | 358 -> 337 | 362 -> 343 | 366 -> 346.
+  p.q_stream = 4 * p.e_stride * c->n_workers > (int64_t(224) << 20) ? kQAllRows
+               : 4 * aligned_rows * c->n_workers > (int64_t(72) << 20) ? kQAlignedRows : kQPlain;
   p.q_stride = 4 * ntile + nl;
 
   // workspace layout, 256-byte aligned regions
@@ -575,11 +583,14 @@ int launch_agg0(acc_ctx* c) {
 int launch_phase1(acc_ctx* c, int w0, int nw) {
   const Ws& ws = c->ws;
   if (ws.n_qmtiles == 0) return ACC_OK;
-  // a kernel for each: one that held both was 45 KB of code instead of 28, which a step that follows a program's own kernels
-  // has to fetch (ResNet-18 shapes at W = 1, plain either way: 83.3 us per step so, 80.8 with a kernel for each)
+  // a kernel for each: one that held both kinds of access was 45 KB of code instead of 28, which a step that follows a program's own
+  // kernels has to fetch (ResNet-18 shapes at W = 1, plain either way: 83.3 us per step so, 80.8 with a kernel for each)
   const dim3 grid(ws.n_qmtiles, nw);
-  if (c->plan.q_stream) ACC_LAUNCH_AS(c, psgd_q_kernel, psgd_q_kernel<true>, grid, dim3(256), ws, w0);
-  else ACC_LAUNCH_AS(c, psgd_q_kernel, psgd_q_kernel<false>, grid, dim3(256), ws, w0);
+  switch (c->plan.q_stream) {
+    case kQPlain: ACC_LAUNCH_AS(c, psgd_q_kernel, psgd_q_kernel<kQPlain>, grid, dim3(256), ws, w0); break;
+    case kQAlignedRows: ACC_LAUNCH_AS(c, psgd_q_kernel, psgd_q_kernel<kQAlignedRows>, grid, dim3(256), ws, w0); break;
+    default: ACC_LAUNCH_AS(c, psgd_q_kernel, psgd_q_kernel<kQAllRows>, grid, dim3(256), ws, w0); break;
+  }
   return ACC_OK;
 }
 

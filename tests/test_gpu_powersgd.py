@@ -329,16 +329,16 @@ EDGE_SHAPES = [(r, c, 1) for r, c in ((1, 1), (15, 2), (17, 3), (33, 4), (16, 5)
                                       (16, 256), (17, 257), (33, 259), (3, 513))] + [(1, 1031, 0)]
 
 
-@pytest.mark.parametrize("name,shapes,W,heights,pmean,reversed_", [
+@pytest.mark.parametrize("name,shapes,W,heights,pmean,streamed", [
     # rows of the tiles of the first pass and of the right product; P summed up by a launch of its own; the right
-    # product from the last tile (a memory beyond the Infinity Cache)
+    # product streams rows of every kind (an error memory of more than 224 MiB)
     ("few_tiles", EDGE_SHAPES, 2, (16, 32), False, False),
     ("some_tiles", EDGE_SHAPES, 13, (16, 64), True, False),
     ("more_tiles", EDGE_SHAPES + [(700, 1300, 1)], 8, (16, 128), True, False),
     # with a layer too tall for the registers
     ("many_tiles", EDGE_SHAPES + [(1030, 1999, 1)], 30, (32, 128), True, True),
 ])
-def test_tilings_and_unaligned_rows(name, shapes, W, heights, pmean, reversed_):
+def test_tilings_and_unaligned_rows(name, shapes, W, heights, pmean, streamed):
     """Rows of 1 to 3, of exactly 4 and of a ragged number of columns, starting on no 16-byte boundary, under each of
     the tilings, against the oracle; and the deferred residual against the explicit one, bit for bit."""
     print("case tilings", name, flush=True)
@@ -354,7 +354,7 @@ def test_tilings_and_unaligned_rows(name, shapes, W, heights, pmean, reversed_):
     gpu, ora = H.make_pair(B.ACC_POWERSGD, layers, W, 4, 3, 100, 0.5, 1, q0)
     # the case is the one that its name says
     assert gpu.workspace_bytes == H.powersgd_workspace_bytes(layers, W, 4, *heights), name
-    assert (4 * (-(-N // 64) * 64) * W > 224 << 20) == reversed_, name
+    assert (4 * (-(-N // 64) * 64) * W > 224 << 20) == streamed, name
     grads = batch()
     gpu.set_profiling(1)
     _forced_step(gpu, ora, grads, name)
@@ -384,23 +384,27 @@ def test_tilings_and_unaligned_rows(name, shapes, W, heights, pmean, reversed_):
 
 
 @pytest.mark.parametrize("mode", ["step", "calls", "update"])
-def test_streamed_and_plain_access_give_the_same_bits(mode):
-    """The same matrices in a context whose memories may stay in the cache and, behind a long 1-D layer, in one whose
-    right product streams Delta (error memory above 72 MiB) and whose fused update streams weights and velocity (beyond two
-    million elements): D, updated weights and error memory are the same words.  Rows of every kind."""
-    print(f"case streamed {mode}", flush=True)
-    W, lead = 8, 2_400_000
+@pytest.mark.parametrize("rows,is_matrix,above", [(2400, 1, 72), (7400, 0, 224)])
+def test_streamed_and_plain_access_give_the_same_bits(mode, rows, is_matrix, above):
+    """The same matrices in a context whose memories may stay in the cache and, behind a large layer, in one whose
+    right product streams Delta (aligned rows of more than 72 MiB: those; an error memory above 224 MiB: all rows but those of less
+    than four columns) and whose fused update streams weights and velocity (beyond two million elements): D, updated weights and
+    error memory are the same words.  Rows of every kind."""
+    print(f"case streamed {mode} above {above} MiB", flush=True)
+    W, lead = 8, 1000 * rows
     shapes = EDGE_SHAPES + [(64, 1024, 1), (200, 260, 1)]
-    small, large = wl.make_layers(shapes), wl.make_layers([(1, lead, 0)] + shapes)
+    small, large = wl.make_layers(shapes), wl.make_layers([(rows, 1000, is_matrix)] + shapes)
     N = wl.total_params(small)
-    assert 4 * N * W < 72 << 20 < 4 * lead * W and lead > (16 << 20) // 8
+    assert 4 * N * W < 72 << 20 and above << 20 < 4 * lead * W and lead > (16 << 20) // 8
+    assert above == 224 or 4 * (lead + N + 64) * W < 224 << 20
     rng = np.random.default_rng(len(mode))
     q0 = rng.standard_normal(sum(c for _, c, m in shapes if m) * 4).astype(np.float32)
+    q_lead = rng.standard_normal(4000 * is_matrix).astype(np.float32)
     w0 = rng.standard_normal(lead + N, dtype=np.float32)
     batches = [[rng.standard_normal(lead + N, dtype=np.float32) * np.float32(0.01) for _ in range(W)] for _ in range(3)]
     results = []
     for layers, cut in ((small, lead), (large, 0)):
-        gpu, _ = H.make_pair(B.ACC_POWERSGD, layers, W, 4, 3, 100, 0.5, 1, q0)
+        gpu, _ = H.make_pair(B.ACC_POWERSGD, layers, W, 4, 3, 100, 0.5, 1, q0 if cut else np.concatenate([q_lead, q0]))
         w_dev, v_dev, out = H.to_dev(w0[cut:]), H.to_dev(np.zeros(lead + N - cut, np.float32)), H.dev_out(lead + N - cut)
         for batch in batches:
             dev = [H.to_dev(g[cut:]) for g in batch]
