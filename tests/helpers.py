@@ -19,6 +19,23 @@ def make_pair(method, layers, W, crit, noncrit, k_den=100, eta=0.5, initial_leve
     return gpu, ora
 
 
+def make_pair_in(n, method, layers, *args):
+    """make_pair in flat buffers of n elements: the layers, elements of no layer, and a last layer of four that ends at n.  A
+    context of any size for the work of a small one."""
+    lt = layer_tuples(layers) + [(n - 4, 1, 4, 0)]
+    gpu, ora = make_pair(method, lt, *args)
+    assert gpu.n_params == n
+    ora.N, ora.e, ora.A = n, np.zeros((ora.W, n), np.float32), np.zeros(n, np.float32)
+    return gpu, ora
+
+
+def in_buffer(values, n):
+    """values at the start of a flat buffer of n elements, the rest zero."""
+    out = np.zeros(n, np.float32)
+    out[:values.size] = values
+    return out
+
+
 def to_dev(a):
     import torch
     return torch.from_numpy(np.ascontiguousarray(a)).to("cuda:0")

@@ -660,17 +660,26 @@ def test_layers_at_the_edges_of_the_level_2_slot_groups():
     gpu.destroy()
 
 
+@pytest.mark.parametrize("size", [0, 8_400_000])
 @pytest.mark.parametrize("pad", [0, 1, 4, 16])
-def test_rows_that_a_step_leaves_alone(pad):
+def test_rows_that_a_step_leaves_alone(pad, size):
     """Layers of which a step touches a few rows only, and some not at all: what the first pass does not change it need
     not store, in whole cache lines.  Starts on a 64-byte line, off a 16-byte boundary, on a 16-byte boundary off a line and
     again on a line; rows that end inside a line; negative zeros in the memory and in the gradients; a window end, after
-    which the accumulator is written whatever it held.  Memory and accumulator are compared with the oracle bit for bit."""
-    print(f"case untouched rows pad={pad}", flush=True)
+    which the accumulator is written whatever it held.  Memory and accumulator are compared with the oracle bit for bit.  The
+    comparison is made in contexts of more than 64 MB of error memory: the layers again in flat buffers of that size, where the third
+    worker's memory lies beyond the first 64 MB and is streamed as well."""
+    print(f"case untouched rows pad={pad} size={size}", flush=True)
     shapes = ([(1, pad, 0)] if pad else []) + [(300, 84, 1), (1, 12, 0), (200, 100, 1), (6, 50, 1), (40, 672, 1)]
     layers = wl.make_layers(shapes)
-    N, W = wl.total_params(layers), 2
-    gpu, ora = H.make_pair(B.ACC_TOPK, layers, W, 10, 1)
+    N, W = wl.total_params(layers), 3 if size else 2
+    cached = (64 << 20) // 4
+    if size:
+        assert size % 64 == 0 and size + N < cached <= 2 * size
+        gpu, ora = H.make_pair_in(size, B.ACC_TOPK, layers, W, 10, 1)
+    else:
+        assert N * W < cached
+        gpu, ora = H.make_pair(B.ACC_TOPK, layers, W, 10, 1)
     rng = np.random.default_rng([43, pad])
     for step in range(7):
         if step == 3:
@@ -678,7 +687,8 @@ def test_rows_that_a_step_leaves_alone(pad):
             ora.detect_regime(0.1, 0.1)
         if step == 5:                                        # negative zeros where the memory holds zeros
             for w in range(W):
-                ora.e[w][(ora.e[w] == 0) & (rng.random(N) < 0.5)] = np.float32(-0.0)
+                e = ora.e[w][:N]
+                e[(e == 0) & (rng.random(N) < 0.5)] = np.float32(-0.0)
             gpu.set_state(H.oracle_state_blob(gpu, ora))
         grads = []
         for w in range(W):
@@ -690,7 +700,7 @@ def test_rows_that_a_step_leaves_alone(pad):
                     v[rng.random(l.rows) < 0.1] *= -1.0      # zeros of either sign, but never on top of a negative one
             if step >= 5:
                 g = g + 0.0
-            grads.append(g.astype(np.float32))
+            grads.append(H.in_buffer(g.astype(np.float32), size or N))
         _check_step(gpu, ora, grads, f"pad {pad} step {step}", check_state=step in (1, 3, 4, 6))
     gpu.destroy()
 
