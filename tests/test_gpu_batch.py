@@ -74,6 +74,56 @@ def test_every_number_of_workers(W, update):
     gpu.destroy()
 
 
+@pytest.mark.parametrize("update", [False, True])
+@pytest.mark.parametrize("W", [1, 2, 3, 4])
+def test_few_workers_whose_sums_are_streamed(W, update):
+    """The loops of one to four workers where the running sums exceed what stays in the cache (224 MB, the accumulator of
+    several workers among them): plain access before that element, streaming access after it.  Small layers on both sides of it, behind
+    elements of no layer, and one layer across it; an aligned one and one whose tiles end inside a group."""
+    print(f"case batch streamed sums W={W} update={update}", flush=True)
+    cached = (224 << 20) // 4
+    n = -(-(cached // (W if W == 1 else W + 1) + 60000) // 64) * 64       # elements of the flat buffers
+    line = (cached - (n if W > 1 else 0)) // W                           # first streamed element of a worker's sums
+    shift = (line - 30000) // 64 * 64
+    sizes = [8192, 30001, 16384, 12, 8193]
+    local = H.layer_tuples(wl.make_layers([(1, s, 0) for s in sizes]))
+    N = sum(sizes)
+    layers = [(shift + off, r, c, m) for off, r, c, m in local] + [(n - 4, 1, 4, 0)]
+    assert shift + sizes[0] < line < shift + sizes[0] + sizes[1] and shift + N < n - 4 and n % 64 == 0
+    gpu = B.Accordion(B.ACC_BATCH, layers, W, 1, 1, 100, 0.5, 0, None, batch_multiplier=3)
+    assert gpu.n_params == n
+    ora = orc.BatchSizeOracle(local, W, 3, 0.5, 0, True)
+    rng = np.random.default_rng([7, W])
+    here = slice(shift, shift + N)
+
+    import torch
+
+    def spread(a):
+        t = torch.zeros(n, device="cuda:0")
+        t[here] = H.to_dev(a)
+        return t
+
+    w_ref, v_ref, out = rng.standard_normal(N, dtype=np.float32), np.zeros(N, np.float32), np.zeros(N, np.float32)
+    w_dev, v_dev, out_dev = spread(w_ref), spread(v_ref), spread(out)
+    for t in range(5):
+        grads = [rng.standard_normal(N, dtype=np.float32) for _ in range(W)]
+        dev = [spread(g) for g in grads]
+        if update:
+            ora.micro_step_update(grads, w_ref, v_ref, 0.1, 0.9)
+            gpu.step_all_update(dev, w_dev, v_dev, 0.1, 0.9)
+        else:
+            d, _ = ora.micro_step(grads)
+            gpu.step_all(dev, out_dev)
+            out = out if d is None else d
+        for got, ref, what in ((w_dev, w_ref, "weights"), (v_dev, v_ref, "velocity"), (out_dev, out, "out")):
+            H.assert_bits_equal(got[here].cpu().numpy(), ref, f"micro-step {t}: {what}")
+    st = gpu.unpack_state(gpu.get_state())                               # two micro-steps into the second batch
+    H.assert_bits_equal(st["e"][:, here], ora.S, "sums")
+    H.assert_bits_equal(st["A"][here], ora.A, "accumulator")
+    assert st["pending"] == ora.j == 2
+    gpu.destroy()
+
+
 @pytest.mark.parametrize("W,M", [(1, 2), (3, 4), (5, 3)])
 def test_micro_steps_store_path(W, M):
     """Small batch (every micro-step exchanged), then the switch to the large batch by the

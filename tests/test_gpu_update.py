@@ -70,18 +70,25 @@ def test_topk_fused_update_is_bit_exact(wd, crit, noncrit, initial):
     gpu.destroy()
 
 
-@pytest.mark.parametrize("crit", [10, 40])
-def test_topk_update_beyond_what_stays_in_the_cache(crit):
+@pytest.mark.parametrize("crit,size", [(10, 0), (40, 0), (10, 8_400_000), (40, 8_400_000), (99, 8_400_000)])
+def test_topk_update_beyond_what_stays_in_the_cache(crit, size):
     """Error memories of more than 64 MB and weights of more than 2 M elements: the first pass and the fused update change
     from plain to streaming access in the middle of a layer.  A dense layer, one of which few rows are used (its threshold is
-    zero at K = 10 %), layers off the 16-byte boundary, a single tile; K = 40 % guesses a band, whose compaction reads Delta."""
-    print(f"case topk update beyond the cache K={crit}", flush=True)
+    zero at K = 10 %), layers off the 16-byte boundary, a single tile; K = 40 % guesses a band, whose compaction reads Delta.  In flat
+    buffers of 8.4 M elements the compaction streams too: the candidate lists (more than 64 M elements) at K = 10 %, Delta (more than
+    224 MB) at K = 40 % and in the holes layout of K = 99 %."""
+    print(f"case topk update beyond the cache K={crit} size={size}", flush=True)
     layers = wl.make_layers([(1, 3, 0), (3000, 401, 1), (1, 64, 0), (1200, 768, 1), (1, 8192, 0), (120, 1024, 1)])
     N, W = wl.total_params(layers), 8
-    assert N > (16 << 20) // 8 and (W - 1) * N < (64 << 20) // 4 < W * N
-    gpu, ora = H.make_pair(B.ACC_TOPK, layers, W, crit, 1)
+    assert N > (16 << 20) // 8
+    if size:
+        assert size % 64 == 0 and size * W > 64 << 20 and 4 * size * W > 224 << 20
+        gpu, ora = H.make_pair_in(size, B.ACC_TOPK, layers, W, crit, 1)
+    else:
+        assert (W - 1) * N < (64 << 20) // 4 < W * N
+        gpu, ora = H.make_pair(B.ACC_TOPK, layers, W, crit, 1)
     rng = np.random.default_rng([5, crit])
-    w_ref, v_ref = rng.standard_normal(N).astype(np.float32), np.zeros(N, np.float32)
+    w_ref, v_ref = H.in_buffer(rng.standard_normal(N).astype(np.float32), size or N), np.zeros(size or N, np.float32)
     w_dev, v_dev = H.to_dev(w_ref), H.to_dev(v_ref)
     for step in range(3):
         grads = []
@@ -89,7 +96,7 @@ def test_topk_update_beyond_what_stays_in_the_cache(crit):
             g = rng.standard_normal(N, dtype=np.float32)
             l = layers[3]
             g[l.offset:l.offset + l.numel].reshape(l.rows, l.cols)[rng.random(l.rows) > 0.06] = 0
-            grads.append(g)
+            grads.append(H.in_buffer(g, size or N))
         ora.step_update(grads, w_ref, v_ref, LR, MU, 0.0)
         gpu.step_all_update([H.to_dev(g) for g in grads], w_dev, v_dev, LR, MU, 0.0)
         H.assert_bits_equal(w_dev.cpu().numpy(), w_ref, f"step {step}: weights")
