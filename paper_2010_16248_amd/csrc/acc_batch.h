@@ -19,10 +19,10 @@
 namespace acc {
 
 constexpr int kBatchWorkers = 4;   // workers whose loads are in flight together
-// The gradients stream in (read once), so that the running sums, the accumulator and, in the
-// small-batch regime, the averaged gradient stay in the caches from one micro-step to the next:
+// The gradients stream in (read once), so that the running sums, the accumulator (of several workers; of one worker: see NTA)
+// and, in the small-batch regime, the averaged gradient stay in the caches from one micro-step to the next:
 // 118 -> 95 us per micro-step on ResNet-18 shapes, W = 4.  Streaming the rest as well brings
-// nothing in the large-batch regime and costs 3 us in the small-batch one.
+// nothing in the large-batch regime there and costs 3 us in the small-batch one.
 constexpr bool kBatchStreamG = true;
 constexpr bool kBatchStream = false;
 
@@ -32,8 +32,13 @@ __device__ __forceinline__ const uint32_t* batch_slot(const Ws& ws, uint32_t par
   return ws.bstate + 4 * (parity & 1u);
 }
 
-// NTS, NTA: the running sums (see kCachedSums on the host side) / the accumulator (one worker: 487 -> 471 us for six micro-steps
-// of VGG-19 shapes) are accessed with the streaming hint.
+// NTS, NTA: the running sums (see kCachedSums on the host side) / the accumulator (one worker, whatever the size) are accessed with the
+// streaming hint.  NTA, us per four micro-steps plain -> streamed, three states in turn | one state | one state with 1 GB of a program's own
+// traffic between its micro-steps | the same and the gradients written just before them; one large batch: 0.8 M
+// elements 30.1 -> 30.5 | 23.5 -> 22.2 | 41 -> 38 | 37 -> 34, 4.3 M 68.7 -> 70.4 | 68.2 -> 69.0 | 95 -> 97 | 82 -> 78, 7.6 M 111 -> 109 | 109 -> 109 |
+// 144 -> 143 | 131 -> 126, 51 M (LSTM) 731 -> 593 | 730 -> 574 | 719 -> 697 | 695 -> 592; four small batches: 0.8 M 31.6 -> 31.7 | 24.9 -> 25.0 | 41 -> 38 |
+// 36 -> 36, 4.3 M 61.8 -> 65.2 | 61.3 -> 64.5 | 84 -> 91 | 69 -> 65, 11 M 130 -> 128 | 129 -> 126 | 162 -> 150 | 146 -> 130.  (Plain is the better one
+// around 4 M elements while nothing lies between the micro-steps; a rule for that would be one size's.)
 // NW: the number of workers, 0: any.  (Four loads from clamped indices whatever the number asked memory for the same lines again:
 // ResNet-18 shapes at W = 1, eight micro-steps, 390 -> 298 us with the streamed accumulator; LSTM set W = 2, four micro-steps,
 // 1055 -> 920.)  Where few workgroups wait for their loads the branches inside the loop were what counted: four small layers,
@@ -83,6 +88,7 @@ __device__ __forceinline__ void batch_tile(const Ws& ws, const GradPtrs& gp, con
       } else {
         int wb = 0;
         for (; wb + kBatchWorkers <= W; wb += kBatchWorkers) workers(wb, std::integral_constant<int, kBatchWorkers>());
+        static_assert(kBatchWorkers == 4, "the switch takes every number of workers that may be left");
         switch (W - wb) {                                  // uniform
           case 1: workers(wb, std::integral_constant<int, 1>()); break;
           case 2: workers(wb, std::integral_constant<int, 2>()); break;
