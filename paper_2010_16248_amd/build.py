@@ -13,7 +13,7 @@ LIB = os.path.join(HERE, "libaccordion.so")
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
     "-ffp-contract=off", "-fhip-fp32-correctly-rounded-divide-sqrt",
-    # packed fp32 instructions are not to be generated on the test machines
+    # no packed fp32 instructions: some of their forms have given wrong results on this hardware
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wall", "-Wno-unused-function",
 ]

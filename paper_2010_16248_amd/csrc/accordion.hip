@@ -508,15 +508,22 @@ void prof_end(acc_ctx* c, EventPair& p) { c->pending.push_back(p); }
 // --- launches of each stage for workers [w0, w0 + nw) ------------------------------------
 
 // What a step leaves to the 256 MB Infinity Cache until the next one: batched TopK steps the first kCachedError elements of the
-// workers' error memories, fused updates of either method the first kCachedUpdate of weights and velocity.  The rest goes through streaming loads and
-// stores.  Everything accessed plainly, whatever does not fit is evicted while the next pass reads, dirty line by dirty line: e = g + e
-// over 3 x 179 MB in turn runs at 5.8 TB/s so, 6.2 streamed.  A memory that stays in the cache whole is faster plain, but a
-// training program's own passes lie between two steps.  us per step, three states in turn | one state again and again,
-// everything plain -> 64 MB of e and 16 MB of w and v plain (ResNet-18 shapes, K = 10 %): W = 4 194 -> 181 | 162 -> 162.5; W = 8 347 -> 327 | 343 -> 288;
-// fused update at W = 1 113 -> 94 | 89 -> 94; VGG-19 W = 4 338 -> 319 | 332 -> 284; LSTM W = 16 2525 -> 2410 | 2543 -> 2432.  Less of e plain
-// is better where nothing of a state stays (W = 4 169 | 164 with 32 MB, 170 | 169 with none) and worse in windows of four steps of
-// one state (VGG-19 at K = 99 % and 2 %, W = 2: plain 1442, 64 MB 1462, 32 MB 1483); 96 MB 187 | 162.  64 MB of w and v: W = 1 107 | 93.  PowerSGD
-// with the fused update, ResNet-18 W = 1 103.3 -> 96.3 | 90 -> 95.7, W = 4 (with Ws::q_stream) 203 -> 188 | 181 -> 182.
+// workers' error memories, fused updates of either method the first kCachedUpdate of weights and velocity.  The rest goes through streaming
+// loads and stores.  Everything accessed plainly, whatever does not fit is evicted while the next pass reads, dirty line by dirty line:
+// e = g + e over 3 x 179 MB in turn runs at 5.8 TB/s so, 6.2 streamed.  us per step, everything plain -> so, three states in turn | one state
+// again and again | one state and 1 GB of a program's own traffic between its steps | the same and the gradients written just before:
+//   error memory: ResNet-18 shapes W = 4 K = 10 % 194 -> 181 | 161 -> 162 | 185 -> 183 | 166 -> 161, K = 1 % 172 -> 153 | 142 -> 146 | 166 -> 164 |
+//   147 -> 143; W = 2 119 -> 110 | 104 -> 105 | 121 -> 121 | 111 -> 111; VGG-19 W = 1 131 -> 124 | 116 -> 118 | 135 -> 135 | 124 -> 125,
+//   W = 4 340 -> 307 | 332 -> 291 | 336 -> 316 | 341 -> 302; odd sizes W = 3 106 -> 96 | 93 -> 94 | 108 -> 109 | 100 -> 101; LSTM W = 1 327 -> 288 |
+//   271 -> 263 | 318 -> 292 | 300 -> 265; two windows of five steps of ResNet-18 1681 -> 1679 | 1653 -> 1649 | 1882 -> 1844 | 1711 -> 1625, of four
+//   of VGG-19 at K = 99 % and 2 %, W = 2 1431 -> 1465 | 1412 -> 1442 | 1614 -> 1617 | 1474 -> 1471.  32 MB instead of 64: ResNet-18 W = 4 169 | 164, but
+//   those VGG-19 windows 1483; 96 MB 187 | 162; none 170 | 169.
+//   weights and velocity, TopK: ResNet-18 W = 1 113 -> 95 | 89 -> 94 | 114 -> 109 | 107 -> 103, W = 4 215 -> 208 | 179 -> 184 | 212 -> 208 | 187 -> 185;
+//   VGG-19 W = 1 186 -> 177 | 153 -> 158 | 186 -> 181 | 173 -> 169; LSTM W = 1 422 -> 393 | 418 -> 369 | 415 -> 400 | 381 -> 371; odd sizes W = 3 135 -> 128 |
+//   111 -> 116 | 136 -> 136 | 125 -> 125; PowerSGD: ResNet-18 W = 1 103 -> 96 | 90 -> 96 | 106 -> 106 | 101 -> 101, W = 2 131 -> 127 | 121 -> 126 | 136 -> 135 |
+//   130 -> 128; VGG-19 W = 1 170 -> 159 | 151 -> 158 | 171 -> 168 | 163 -> 161; LSTM W = 1 643 -> 624 | 642 -> 608 | 636 -> 634 | 612 -> 612.
+// So a state that finds the caches as it left them, and fits them, pays up to 6 %; wherever a program does anything between two steps
+// the policy gains or makes no difference.
 constexpr int64_t kCachedError = (int64_t(64) << 20) / 4, kCachedUpdate = (int64_t(16) << 20) / 8;
 
 // Tiles of a launch from which the counting kernel takes a tile per wave.  us per step, a quarter per wave -> a tile per wave:
