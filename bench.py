@@ -387,6 +387,8 @@ def measure(name, args, steps, warmup, pool, full):
         roofline = {"kernel": dom, "bound": "hbm", "achieved": round(ach, 1), "peak": HBM_PEAK_GBS,
                     "unit": "GB/s", "frac": round(ach / HBM_PEAK_GBS, 4), "traffic": k_traffic,
                     "traffic_source": traffic_src,
+                    # less than frac where the kernel leaves stores out (unchanged lines of a sparse layer)
+                    "counted_frac": round(k_traffic / avg_s / 1e9 / HBM_PEAK_GBS, 4) if k_traffic else None,
                     "avg_kernel_us": round(avg_s * 1e6, 2), "launches_timed": n,
                     "algorithmic_bytes_per_launch": alg_bytes}
 
@@ -477,6 +479,7 @@ def main():
                            "gradient_GB/s": o["value"],
                            "dominant_kernel": rf.get("kernel"), "dominant_kernel_us": rf.get("avg_kernel_us"),
                            "dominant_kernel_frac_of_peak": rf.get("frac"),
+                           "dominant_kernel_counted_frac": rf.get("counted_frac"),
                            "step_algorithmic_frac_of_peak": sb.get("algorithmic_frac_of_peak"),
                            "step_counted_frac_of_peak": sb.get("counted_frac_of_peak"),
                            "regime_tests_in_timed_region": o["config"]["regime_tests_in_timed_region"],
