@@ -388,7 +388,8 @@ def measure(name, args, steps, warmup, pool, full):
                     "unit": "GB/s", "frac": round(ach / HBM_PEAK_GBS, 4), "traffic": k_traffic,
                     "traffic_source": traffic_src,
                     # less than frac where the kernel leaves stores out (unchanged lines of a sparse layer)
-                    "counted_frac": round(k_traffic / avg_s / 1e9 / HBM_PEAK_GBS, 4) if k_traffic else None,
+                    "counted_frac": round(k_traffic / avg_s / 1e9 / HBM_PEAK_GBS, 4)
+                    if k_traffic and not (is_batch and fused) else None,
                     "avg_kernel_us": round(avg_s * 1e6, 2), "launches_timed": n,
                     "algorithmic_bytes_per_launch": alg_bytes}
 
