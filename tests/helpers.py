@@ -21,11 +21,15 @@ def make_pair(method, layers, W, crit, noncrit, k_den=100, eta=0.5, initial_leve
 
 def make_pair_in(n, method, layers, *args):
     """make_pair in flat buffers of n elements: the layers, elements of no layer, and a last layer of four that ends at n.  A
-    context of any size for the work of a small one."""
+    context of any size for the work of a small one.  ora.inside: the elements that belong to a layer; the others of an
+    output buffer are not written."""
     lt = layer_tuples(layers) + [(n - 4, 1, 4, 0)]
     gpu, ora = make_pair(method, lt, *args)
     assert gpu.n_params == n
     ora.N, ora.e, ora.A = n, np.zeros((ora.W, n), np.float32), np.zeros(n, np.float32)
+    ora.inside = np.zeros(n, bool)
+    for off, rows, cols, _ in lt:
+        ora.inside[off:off + rows * cols] = True
     return gpu, ora
 
 
