@@ -656,7 +656,7 @@ __device__ __forceinline__ void ef_hist_tile(const Ws& ws, const GradPtrs& gp, i
 // LARGE: a context of more than e_cached elements of error memory (see EAccess).  e_reread: Delta is read again within the
 // step, whatever the guess.
 template <bool LARGE>
-__global__ __launch_bounds__(256) void topk_ef_hist_kernel(const Ws ws, const GradPtrs gp, int w0, int64_t e_cached, int e_reread) {
+__device__ __forceinline__ void ef_hist_body(const Ws& ws, const GradPtrs& gp, int w0, int64_t e_cached, int e_reread) {
   __shared__ uint32_t hist[kHistBins];
   __shared__ uint32_t cand_val[4][kCandLdsSlots];
   __shared__ uint16_t cand_idx[4][kCandLdsSlots];
@@ -713,6 +713,17 @@ __global__ __launch_bounds__(256) void topk_ef_hist_kernel(const Ws ws, const Gr
       else tile(yes, yes, no, checked, guess);
     }
   }
+}
+
+// Two plain kernels, whose code lies beside that of the kernels that follow in a step.  As instantiations of one template it went to
+// the end of the library, and with other instantiations there the same instructions were slower (ResNet-18 shapes W = 4, one state again
+// and again, 163.5 us per step, 162.2 here; two windows of five steps 1694 and 1681).
+__global__ __launch_bounds__(256) void topk_ef_hist_kernel(const Ws ws, const GradPtrs gp, int w0, int64_t e_cached, int e_reread) {
+  ef_hist_body<false>(ws, gp, w0, e_cached, e_reread);
+}
+
+__global__ __launch_bounds__(256) void topk_ef_hist_large_kernel(const Ws ws, const GradPtrs gp, int w0, int64_t e_cached, int e_reread) {
+  ef_hist_body<true>(ws, gp, w0, e_cached, e_reread);
 }
 
 // ---- B: re-stage the keys of b1 for a layer whose guess missed -----------------------------------

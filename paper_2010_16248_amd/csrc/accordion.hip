@@ -538,9 +538,9 @@ int launch_topk_select(acc_ctx* c, int w0, int nw, int e_reread) {
   const Ws& ws = c->ws;
   const dim3 tiles(ws.n_ftiles, nw);
   if (ws.e_stride * ws.W > kCachedError)
-    ACC_LAUNCH_AS(c, topk_ef_hist_kernel, topk_ef_hist_kernel<true>, tiles, dim3(256), ws, c->grads, w0, kCachedError, e_reread);
+    ACC_LAUNCH_AS(c, topk_ef_hist_kernel, topk_ef_hist_large_kernel, tiles, dim3(256), ws, c->grads, w0, kCachedError, e_reread);
   else
-    ACC_LAUNCH_AS(c, topk_ef_hist_kernel, topk_ef_hist_kernel<false>, tiles, dim3(256), ws, c->grads, w0, kCachedError, e_reread);
+    ACC_LAUNCH_AS(c, topk_ef_hist_kernel, topk_ef_hist_kernel, tiles, dim3(256), ws, c->grads, w0, kCachedError, e_reread);
   ACC_LAUNCH(c, topk_pick12_kernel, dim3(ws.L, nw), dim3(kPickThreads), ws, w0);
   if ((int64_t)ws.n_ftiles * nw >= kWideCountTiles)
     ACC_LAUNCH_AS(c, topk_count3_kernel, topk_count3_wide_kernel, dim3((ws.n_ftiles + 3) / 4, nw), dim3(256), ws, w0);
