@@ -527,7 +527,7 @@ void prof_end(acc_ctx* c, EventPair& p) { c->pending.push_back(p); }
 constexpr int64_t kCachedError = (int64_t(64) << 20) / 4, kCachedUpdate = (int64_t(16) << 20) / 8;
 
 // Tiles of a launch from which the counting kernel takes a tile per wave.  us per step, a quarter per wave -> a tile per wave:
-// LSTM set W = 16 (100 000 tiles) 2395 -> 2373, K = 1 % 2081 -> 2053, W = 4 (25 000) 703.8 -> 701.7; ResNet-18 W = 8 (11 000) 300 -> 302,
+// LSTM set W = 16 (100 000 tiles) 2409 -> 2381, K = 1 % 2085 -> 2055, W = 4 (25 000) 709 -> 707; ResNet-18 W = 8 (11 000) 300 -> 302,
 // four small layers W = 2 36.6 -> 40.4.
 constexpr int64_t kWideCountTiles = 20000;
 
@@ -809,12 +809,15 @@ static int32_t init_common(const acc_config* cfg, void* workspace_dev, size_t wo
     ws.overlap = at<unsigned long long>(c, p.r_overlap);
     ws.tpending = at<uint32_t>(c, p.r_tpending);
     // The compaction is the last to read Delta (where it does: band guesses) and the candidate lists.  Read with the streaming
-    // hint, what lies dirty in the Infinity Cache goes back to memory under this pass instead of during the next one.  Delta:
-    // where the error memory exceeds the cache (LSTM set K = 99 %, W = 4, 949 -> 902 us per step; ResNet-18 shapes W = 4, 179 MB, gain 7 of
-    // 224, but lose 4 of 197 where one state steps again and again, and VGG-19 W = 2 55 of 1440 in windows of four steps: not below).
-    // Lists: where there are
-    // more than 64 M elements (ResNet-18 shapes K = 10 %, W = 8 325 -> 304 | 292 -> 297, VGG-19 W = 4 318 -> 302 | 292 -> 300, odd sizes W = 12
-    // 340 -> 316 | 307 -> 310, LSTM W = 4 709 -> 704 | 688 -> 696; ResNet-18 W = 4, 45 M elements, 170.0 -> 169.4 | 164.7 -> 168.1: not below).
+    // hint, what lies dirty in the Infinity Cache goes back to memory under this pass instead of during the next one.  us per step, plain ->
+    // streamed, three states in turn | one state again and again | one state and 1 GB of other traffic between its steps | the same and the
+    // gradients written just before.  Delta: where the error memory exceeds the cache (LSTM set K = 99 %, W = 4, 941 -> 894 | 937 -> 892 |
+    // 1018 -> 902 | 1025 -> 908; not below: ResNet-18 shapes K = 99 %, W = 4, 179 MB, 225 -> 219 | 199 -> 217 | 216 -> 228 | 197 -> 205, VGG-19 W = 2
+    // 224 -> 218 | 195 -> 218 | 219 -> 230 | 203 -> 210).  Lists: where there are more than 64 M elements (K = 10 %: ResNet-18 W = 8 326 -> 313 |
+    // 287 -> 292 | 316 -> 320 | 298 -> 303, VGG-19 W = 4 322 -> 308 | 284 -> 291 | 309 -> 317 | 293 -> 302, odd sizes W = 12 342 -> 330 | 301 -> 305 |
+    // 329 -> 333 | 313 -> 318, LSTM W = 4 705 -> 704 | 686 -> 688 | 712 -> 714 | 708 -> 706: 4 % where nothing of a state stays in the cache, for 1 to 3 %
+    // where some of it does; not below: LSTM W = 1, 51 M, 289 -> 296 | 263 -> 289 | 291 -> 310 | 265 -> 281, VGG-19 W = 1 123 -> 124 | 118 -> 123 |
+    // 137 -> 142 | 126 -> 131).
     const int64_t elements = p.e_stride * cfg->n_workers;
     ws.delta_stream = 4 * elements > (int64_t(224) << 20) ? 1 : 0;
     ws.lists_stream = elements > (int64_t(64) << 20) ? 1 : 0;
