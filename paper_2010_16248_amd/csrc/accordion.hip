@@ -508,7 +508,7 @@ void prof_end(acc_ctx* c, EventPair& p) { c->pending.push_back(p); }
 // --- launches of each stage for workers [w0, w0 + nw) ------------------------------------
 
 // What a step leaves to the 256 MB Infinity Cache until the next one: batched TopK steps the first kCachedError elements of the
-// workers' error memories, fused updates of either method the first kCachedUpdate of weights and velocity.  The rest goes through streaming
+// workers' error memories, fused updates the first kCachedUpdate of weights and velocity (or none, see update_cached).  The rest goes through streaming
 // loads and stores.  Everything accessed plainly, whatever does not fit is evicted while the next pass reads, dirty line by dirty line:
 // e = g + e over 3 x 179 MB in turn runs at 5.8 TB/s so, 6.2 streamed.  us per step, everything plain -> so, three states in turn | one state
 // again and again | one state and 1 GB of a program's own traffic between its steps | the same and the gradients written just before:
@@ -525,6 +525,19 @@ void prof_end(acc_ctx* c, EventPair& p) { c->pending.push_back(p); }
 // So a state that finds the caches as it left them, and fits them, pays up to 6 %; wherever a program does anything between two steps
 // the policy gains or makes no difference.
 constexpr int64_t kCachedError = (int64_t(64) << 20) / 4, kCachedUpdate = (int64_t(16) << 20) / 8;
+
+// The first element of weights and velocity that a fused update streams.  TopK: none is left to the cache where they and the error memory take
+// more than 192 MiB.  16 MB plain -> none, regimes as above; beyond: K = 25 % ResNet-18 W = 4 252.5 -> 247.8 | 231 -> 229 | 244 -> 241 | 236 -> 234,
+// VGG-19 W = 1 201 -> 195 | 183 -> 186 | 200 -> 201 | 193 -> 194; K = 10 % ResNet-18 W = 4 211 -> 208 | 187.5 -> 189.8 | 204 -> 204 | 193.5 -> 194.6, W = 8
+// 345 -> 338 | 316 -> 319 | 339 -> 341 | 335 -> 337, VGG-19 W = 1 181 -> 171 | 162 -> 164 | 177.5 -> 178 | 171.5 -> 172, W = 4 364 -> 355 | 334 -> 337 |
+// 357 -> 357 | 353 -> 355, LSTM W = 1 388 -> 385 | 369 -> 372 | 396 -> 397 | 383.5 -> 385; below: ResNet-18 W = 1 K = 1 % 98.1 -> 99.6 | 97 -> 98.3 |
+// 112 -> 111 | 107 -> 106, W = 2 K = 10 % (170 MiB) 144 -> 137 | 129 -> 131 | 142.6 -> 143 | 137 -> 138, odd sizes W = 3 (144 MiB) 133 -> 129 |
+// 119 -> 122.5 | 133 -> 134 | 128 -> 129.  PowerSGD: 16 MB at every size, ResNet-18 W = 2 129 -> 130.5 | 129 -> 130.5 | 138 -> 139 | 135.5 -> 136.5, VGG-19 W = 1
+// 157 -> 159 | 156 -> 158.5 | 167.5 -> 168.5 | 164.5 -> 165.5, W = 2 216 -> 216 | 212 -> 214.5 | 228 -> 229 | 221 -> 222, ResNet-18 W = 8 within 0.5 %.
+int64_t update_cached(const acc_ctx* c) {
+  const int64_t resident = 4 * c->plan.e_stride * (int64_t)c->cfg.n_workers + 8 * c->plan.N;
+  return c->cfg.method == ACC_TOPK && resident > (int64_t(192) << 20) ? 0 : kCachedUpdate;
+}
 
 // Tiles of a launch from which the counting kernel takes a tile per wave.  us per step, a quarter per wave -> a tile per wave:
 // LSTM set W = 16 (100 000 tiles) 2409 -> 2381, K = 1 % 2085 -> 2055, W = 4 (25 000) 709 -> 707; ResNet-18 W = 8 (11 000) 300 -> 302,
@@ -1003,7 +1016,7 @@ int32_t accordion_decompress_update(acc_ctx* c, float* weights_dev, float* veloc
   ACC_USABLE(c);
   const int rc = check_sgd(c, weights_dev, velocity_dev, lr, momentum, weight_decay);
   if (rc != ACC_OK) return rc;
-  return decompress_into(c, Sink{nullptr, weights_dev, velocity_dev, lr, momentum, weight_decay, kCachedUpdate});
+  return decompress_into(c, Sink{nullptr, weights_dev, velocity_dev, lr, momentum, weight_decay, update_cached(c)});
 }
 
 static int32_t step_all_into(acc_ctx* c, const float* const* grads_host_array, const Sink& sink) {
@@ -1046,7 +1059,7 @@ int32_t accordion_step_all_update(acc_ctx* c, const float* const* grads_host_arr
   ACC_USABLE(c);
   const int rc = check_sgd(c, weights_dev, velocity_dev, lr, momentum, weight_decay);
   if (rc != ACC_OK) return rc;
-  return step_all_into(c, grads_host_array, Sink{nullptr, weights_dev, velocity_dev, lr, momentum, weight_decay, kCachedUpdate});
+  return step_all_into(c, grads_host_array, Sink{nullptr, weights_dev, velocity_dev, lr, momentum, weight_decay, update_cached(c)});
 }
 
 int32_t accordion_set_stream(acc_ctx* c, void* hip_stream) {
