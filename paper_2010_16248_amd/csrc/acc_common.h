@@ -136,7 +136,7 @@ struct Ws {
   int64_t n_qslots;            // W * q_stride: all quarter slots (the stride between the chunks of a candidate list)
   int32_t* pay_idx;  float* pay_val;  int64_t pay_stride;
   unsigned long long* overlap; // L per-layer counters of the overlap read-back
-  int32_t delta_stream, lists_stream;   // the compaction streams Delta (where it reads it) / the candidate lists
+  int32_t delta_stream, delta_stream_holes, lists_stream;   // the compaction streams Delta (pairs / holes layout) / the candidate lists
   uint32_t* tpending;          // one word: workers whose e still holds Delta with the kept entries in it
   // batch-size mode
   uint32_t* bstate;            // two slots of four words, used alternately (micro-step parity)

@@ -1770,7 +1770,7 @@ constexpr int kChunkWords = 2 * kChunkStride;      // indices, then values
 // (requested group by group once the chunk's sums are complete: requested earlier they cost
 // 32 registers across the last worker's turn and two waves of occupancy).
 // HOLES: the layer keeps more than half of its entries (static per level, the same for every worker).
-// NTD: Delta, which nothing reads again before the next step, is read with the streaming hint (Ws::delta_stream).
+// NTD: Delta, which nothing reads again before the next step, is read with the streaming hint (Ws::delta_stream, delta_stream_holes).
 template <bool AL, bool UPD, bool HOLES, bool NTD = false>
 __device__ __forceinline__ void compact_mean_tile(const Ws& ws, const FlatTile& ft, const LayerDev& L,
                                                   const TileGeom& tg, const Sink sink, uint32_t* stg, int wave) {
@@ -2254,7 +2254,7 @@ __device__ __forceinline__ void compact_mean_body(const Ws& ws, const Sink& sink
   // the payload layout of the layer at its level (k is the same for every worker)
   const uint32_t n_layer = (uint32_t)L.rows * (uint32_t)L.cols;
   const bool holes = payload_has_holes(n_layer, min(rfl(ws.sel[ft.layer].k), n_layer));
-  const bool ntd = ws.delta_stream != 0;                    // uniform
+  const bool ntd = (holes ? ws.delta_stream_holes : ws.delta_stream) != 0;   // uniform
   if (holes) {
     if (tg.aligned && ntd) compact_mean_tile<true, UPD, true, true>(ws, ft, L, tg, sink, stg, wave);
     else if (tg.aligned) compact_mean_tile<true, UPD, true>(ws, ft, L, tg, sink, stg, wave);

@@ -826,13 +826,18 @@ static int32_t init_common(const acc_config* cfg, void* workspace_dev, size_t wo
     // streamed, three states in turn | one state again and again | one state and 1 GB of other traffic between its steps | the same and the
     // gradients written just before.  Delta: where the error memory exceeds the cache (LSTM set K = 99 %, W = 4, 941 -> 894 | 937 -> 892 |
     // 1018 -> 902 | 1025 -> 908; not below: ResNet-18 shapes K = 99 %, W = 4, 179 MB, 225 -> 219 | 199 -> 217 | 216 -> 228 | 197 -> 205, VGG-19 W = 2
-    // 224 -> 218 | 195 -> 218 | 219 -> 230 | 203 -> 210).  Lists: where there are more than 64 M elements (K = 10 %: ResNet-18 W = 8 326 -> 313 |
+    // 224 -> 218 | 195 -> 218 | 219 -> 230 | 203 -> 210; pairs, K = 30 %: odd sizes W = 8 (231 MiB) 311 -> 297 | 288 -> 287 | 311 -> 307 | 304 -> 302, VGG-19 W = 3
+    // (235 MiB) 324 -> 314 | 303 -> 305 | 323 -> 324 | 322 -> 324, ResNet-18 W = 6 (256 MiB) 346 -> 331 | 331 -> 322 | 349 -> 341 | 352 -> 345).  The holes layout, whose payload
+    // writes leave less room, later: K = 99 % odd sizes W = 8 284 -> 278 | 258 -> 276 | 274 -> 298 | 267 -> 279, VGG-19 W = 3 302 -> 302 | 274 -> 301 | 292 -> 321 |
+    // 286 -> 307, ResNet-18 W = 6 330 -> 317 | 304 -> 314 | 328 -> 341 | 323 -> 333, windows of four steps at K = 99 % and 2 % 2116 -> 2126 | 2093 -> 2124 | 2129 -> 2149 |
+    // 2103 -> 2124; odd sizes W = 10 (288 MiB) 370 -> 343 | 342 -> 341 | 371 -> 366 | 376 -> 373, windows 2392 -> 2347 | 2348 -> 2345 | 2394 -> 2374 | 2366 -> 2348.  Lists: where there are more than 64 M elements (K = 10 %: ResNet-18 W = 8 326 -> 313 |
     // 287 -> 292 | 316 -> 320 | 298 -> 303, VGG-19 W = 4 322 -> 308 | 284 -> 291 | 309 -> 317 | 293 -> 302, odd sizes W = 12 342 -> 330 | 301 -> 305 |
     // 329 -> 333 | 313 -> 318, LSTM W = 4 705 -> 704 | 686 -> 688 | 712 -> 714 | 708 -> 706: 4 % where nothing of a state stays in the cache, for 1 to 3 %
     // where some of it does; not below: LSTM W = 1, 51 M, 289 -> 296 | 263 -> 289 | 291 -> 310 | 265 -> 281, VGG-19 W = 1 123 -> 124 | 118 -> 123 |
     // 137 -> 142 | 126 -> 131).
     const int64_t elements = p.e_stride * cfg->n_workers;
     ws.delta_stream = 4 * elements > (int64_t(224) << 20) ? 1 : 0;
+    ws.delta_stream_holes = 4 * elements > (int64_t(280) << 20) ? 1 : 0;
     ws.lists_stream = elements > (int64_t(64) << 20) ? 1 : 0;
   }
   ws.bstate = at<uint32_t>(c, p.r_bstate);

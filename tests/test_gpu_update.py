@@ -70,19 +70,20 @@ def test_topk_fused_update_is_bit_exact(wd, crit, noncrit, initial):
     gpu.destroy()
 
 
-@pytest.mark.parametrize("crit,size", [(10, 0), (40, 0), (10, 8_400_000), (40, 8_400_000), (99, 8_400_000)])
+@pytest.mark.parametrize("crit,size", [(10, 0), (40, 0), (10, 8_400_000), (40, 8_400_000), (99, 8_400_000),
+                                       (99, 9_216_000)])
 def test_topk_update_beyond_what_stays_in_the_cache(crit, size):
     """Error memories of more than 64 MB and weights of more than 2 M elements: the first pass and the fused update change
     from plain to streaming access in the middle of a layer.  A dense layer, one of which few rows are used (its threshold is
     zero at K = 10 %), layers off the 16-byte boundary, a single tile; K = 40 % guesses a band, whose compaction reads Delta.  In flat
     buffers of 8.4 M elements (more than 192 MiB) weights and velocity are streamed from the first element and the compaction streams too: the candidate lists (more than 64 M elements) at K = 10 %, Delta (more than
-    224 MB) at K = 40 % and in the holes layout of K = 99 %."""
+    224 MiB) at K = 40 %, and in the holes layout of K = 99 % with 9.2 M (280 MiB)."""
     print(f"case topk update beyond the cache K={crit} size={size}", flush=True)
     layers = wl.make_layers([(1, 3, 0), (3000, 401, 1), (1, 64, 0), (1200, 768, 1), (1, 8192, 0), (120, 1024, 1)])
     N, W = wl.total_params(layers), 8
     assert N > (16 << 20) // 8
     if size:
-        assert size % 64 == 0 and size * W > 64 << 20 and 4 * size * W > 224 << 20
+        assert size % 64 == 0 and size * W > 64 << 20 and 4 * size * W > (280 if size > 9_000_000 else 224) << 20
         gpu, ora = H.make_pair_in(size, B.ACC_TOPK, layers, W, crit, 1)
     else:
         assert (W - 1) * N < (64 << 20) // 4 < W * N
