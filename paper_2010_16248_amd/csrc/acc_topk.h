@@ -2235,7 +2235,8 @@ constexpr int kMeanWaves = 2;
 constexpr int kMeanSplit = 4 / kMeanWaves;                  // workgroups per tile
 constexpr int kMeanLdsWords = kQuarterFloats + 2 * kPayRing > kChunkWords ? kQuarterFloats + 2 * kPayRing : kChunkWords;
 
-template <bool UPD>
+// LARGE: a context that streams Delta or the lists (Ws).
+template <bool UPD, bool LARGE>
 __device__ __forceinline__ void compact_mean_body(const Ws& ws, const Sink& sink) {
   const FlatTile ft = ws.ftiles[blockIdx.x / kMeanSplit];
   const LayerDev& L = ws.layers[ft.layer];
@@ -2254,14 +2255,14 @@ __device__ __forceinline__ void compact_mean_body(const Ws& ws, const Sink& sink
   // the payload layout of the layer at its level (k is the same for every worker)
   const uint32_t n_layer = (uint32_t)L.rows * (uint32_t)L.cols;
   const bool holes = payload_has_holes(n_layer, min(rfl(ws.sel[ft.layer].k), n_layer));
-  const bool ntd = (holes ? ws.delta_stream_holes : ws.delta_stream) != 0;   // uniform
+  const bool ntd = LARGE && (holes ? ws.delta_stream_holes : ws.delta_stream) != 0;   // uniform
   if (holes) {
     if (tg.aligned && ntd) compact_mean_tile<true, UPD, true, true>(ws, ft, L, tg, sink, stg, wave);
     else if (tg.aligned) compact_mean_tile<true, UPD, true>(ws, ft, L, tg, sink, stg, wave);
     else compact_mean_tile<false, UPD, true>(ws, ft, L, tg, sink, stg, wave);
   } else if (L.ntiles > 1 && rfl(ws.lflag[ft.layer]) == 0u) {
     // every worker's guess held and every list is complete: the candidates serve
-    if (tg.aligned && ws.lists_stream)
+    if (LARGE && tg.aligned && ws.lists_stream)
       gather_mean_tile<true, UPD, true>(ws, ft, L, tg, sink, reinterpret_cast<float*>(stg), stg + kQuarterFloats, wave);
     else if (tg.aligned) gather_mean_tile<true, UPD>(ws, ft, L, tg, sink, reinterpret_cast<float*>(stg), stg + kQuarterFloats, wave);
     else gather_mean_tile<false, UPD>(ws, ft, L, tg, sink, reinterpret_cast<float*>(stg), stg + kQuarterFloats, wave);
@@ -2272,13 +2273,24 @@ __device__ __forceinline__ void compact_mean_body(const Ws& ws, const Sink& sink
   }
 }
 
+// Kernels of their own for contexts that stream: with both kinds of access in one kernel small sets, whose steps wait for
+// instructions, took 1 to 3 % longer after a program's own kernels (three layers of 1024 x 512 at W = 1, K = 10 %, us per step 42.0, 41.2 so, with
+// the update 48.0 and 47.0; seven such layers K = 25 % 50.7 and 49.4; ResNet-18 W = 4 181.5 and 180.1).
 __global__ __launch_bounds__(kMeanWaves * kWave) void topk_compact_mean_kernel(const Ws ws, const Sink sink) {
-  compact_mean_body<false>(ws, sink);
+  compact_mean_body<false, false>(ws, sink);
+}
+
+__global__ __launch_bounds__(kMeanWaves * kWave) void topk_compact_mean_large_kernel(const Ws ws, const Sink sink) {
+  compact_mean_body<false, true>(ws, sink);
 }
 
 // The same pass with the optimizer step in place of the store of the mean.
 __global__ __launch_bounds__(kMeanWaves * kWave) void topk_compact_update_kernel(const Ws ws, const Sink sink) {
-  compact_mean_body<true>(ws, sink);
+  compact_mean_body<true, false>(ws, sink);
+}
+
+__global__ __launch_bounds__(kMeanWaves * kWave) void topk_compact_update_large_kernel(const Ws ws, const Sink sink) {
+  compact_mean_body<true, true>(ws, sink);
 }
 
 // ---- K6: dense mean of the W payloads (call-by-call path) ----------------------------------------

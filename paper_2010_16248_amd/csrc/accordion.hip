@@ -659,8 +659,15 @@ int launch_batch_micro(acc_ctx* c, const Sink& sink) {
 
 int launch_topk_compact_mean(acc_ctx* c, const Sink& sink) {
   const Ws& ws = c->ws;
-  if (sink.wt) ACC_LAUNCH(c, topk_compact_update_kernel, dim3(ws.n_ftiles * kMeanSplit), dim3(kMeanWaves * kWave), ws, sink);
-  else ACC_LAUNCH(c, topk_compact_mean_kernel, dim3(ws.n_ftiles * kMeanSplit), dim3(kMeanWaves * kWave), ws, sink);
+  const dim3 grid(ws.n_ftiles * kMeanSplit), block(kMeanWaves * kWave);
+  const bool large = ws.delta_stream || ws.lists_stream;
+  if (sink.wt) {
+    if (large) ACC_LAUNCH_AS(c, topk_compact_update_kernel, topk_compact_update_large_kernel, grid, block, ws, sink);
+    else ACC_LAUNCH(c, topk_compact_update_kernel, grid, block, ws, sink);
+  } else {
+    if (large) ACC_LAUNCH_AS(c, topk_compact_mean_kernel, topk_compact_mean_large_kernel, grid, block, ws, sink);
+    else ACC_LAUNCH(c, topk_compact_mean_kernel, grid, block, ws, sink);
+  }
   return ACC_OK;
 }
 
