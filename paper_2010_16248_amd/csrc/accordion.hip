@@ -508,7 +508,7 @@ void prof_end(acc_ctx* c, EventPair& p) { c->pending.push_back(p); }
 // --- launches of each stage for workers [w0, w0 + nw) ------------------------------------
 
 // What a step leaves to the 256 MB Infinity Cache until the next one: batched TopK steps the first kCachedError elements of the
-// workers' error memories, fused updates the first kCachedUpdate of weights and velocity (or none, see update_cached).  The rest goes through streaming
+// workers' error memories, fused updates the first kCachedUpdate of weights and velocity (or all or none, see update_cached).  The rest goes through streaming
 // loads and stores.  Everything accessed plainly, whatever does not fit is evicted while the next pass reads, dirty line by dirty line:
 // e = g + e over 3 x 179 MB in turn runs at 5.8 TB/s so, 6.2 streamed.  us per step, everything plain -> so, three states in turn | one state
 // again and again | one state and 1 GB of a program's own traffic between its steps | the same and the gradients written just before:
@@ -534,8 +534,14 @@ constexpr int64_t kCachedError = (int64_t(64) << 20) / 4, kCachedUpdate = (int64
 // 112 -> 111 | 107 -> 106, W = 2 K = 10 % (170 MiB) 144 -> 137 | 129 -> 131 | 142.6 -> 143 | 137 -> 138, odd sizes W = 3 (144 MiB) 133 -> 129 |
 // 119 -> 122.5 | 133 -> 134 | 128 -> 129.  PowerSGD: 16 MB at every size, ResNet-18 W = 2 129 -> 130.5 | 129 -> 130.5 | 138 -> 139 | 135.5 -> 136.5, VGG-19 W = 1
 // 157 -> 159 | 156 -> 158.5 | 167.5 -> 168.5 | 164.5 -> 165.5, W = 2 216 -> 216 | 212 -> 214.5 | 228 -> 229 | 221 -> 222, ResNet-18 W = 8 within 0.5 %.
+// Small contexts, up to 76 MiB of error memory, weights and velocity, leave everything to the cache.  Plain -> 16 MB plain and the rest streamed,
+// layers of 1024 x 512: TopK K = 25 % W = 1 2.6 M elements (30 MiB) 51.0 -> 55.5 | 50.8 -> 55.6 | 63 -> 63 | 62 -> 62, 5.2 M (60 MiB) 62.8 -> 66.6 | 62.5 -> 66.6 |
+// 75.6 -> 75.2 | 74.3 -> 73.9, W = 2 3.7 M (56 MiB) 66.1 -> 71.6 | 65.8 -> 72.1 | 79 -> 79 | 77 -> 77; PowerSGD W = 1 3.7 M (42 MiB) 52.4 -> 54.4 | 52.4 -> 54.6 |
+// 60 -> 60 | 59 -> 59, 6.3 M (72 MiB) 68.0 -> 70.6 | 67.3 -> 70.4 | 77 -> 78 | 76 -> 76; above, PowerSGD W = 2 5.2 M (80 MiB) 77.3 -> 76.7 | 74.1 -> 76.0 | 84 -> 84 |
+// 82 -> 83, TopK K = 25 % 89 -> 85 | 80 -> 84 | 94.5 -> 93 | 92.5 -> 91, W = 1 8.4 M (96 MiB) 94 -> 86 | 83 -> 87 | 94 -> 96 | 92 -> 95.
 int64_t update_cached(const acc_ctx* c) {
   const int64_t resident = 4 * c->plan.e_stride * (int64_t)c->cfg.n_workers + 8 * c->plan.N;
+  if (resident <= (int64_t(76) << 20)) return c->plan.N;
   return c->cfg.method == ACC_TOPK && resident > (int64_t(192) << 20) ? 0 : kCachedUpdate;
 }
 

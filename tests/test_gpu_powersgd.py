@@ -395,7 +395,7 @@ def test_streamed_and_plain_access_give_the_same_bits(mode, rows, is_matrix, abo
     shapes = EDGE_SHAPES + [(64, 1024, 1), (200, 260, 1)]
     small, large = wl.make_layers(shapes), wl.make_layers([(rows, 1000, is_matrix)] + shapes)
     N = wl.total_params(small)
-    assert 4 * N * W < 72 << 20 and above << 20 < 4 * lead * W and lead > (16 << 20) // 8
+    assert 4 * N * W < 72 << 20 and above << 20 < 4 * lead * W and lead > (16 << 20) // 8 and (4 * W + 8) * lead > 76 << 20
     assert above == 224 or 4 * (lead + N + 64) * W < 224 << 20
     rng = np.random.default_rng(len(mode))
     q0 = rng.standard_normal(sum(c for _, c, m in shapes if m) * 4).astype(np.float32)
