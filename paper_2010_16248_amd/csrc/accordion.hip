@@ -518,7 +518,7 @@ void prof_end(acc_ctx* c, EventPair& p) { c->pending.push_back(p); }
 //   271 -> 263 | 318 -> 292 | 300 -> 265; two windows of five steps of ResNet-18 1681 -> 1679 | 1653 -> 1649 | 1882 -> 1844 | 1711 -> 1625, of four
 //   of VGG-19 at K = 99 % and 2 %, W = 2 1431 -> 1465 | 1412 -> 1442 | 1614 -> 1617 | 1474 -> 1471.  32 MB instead of 64: ResNet-18 W = 4 169 | 164, but
 //   those VGG-19 windows 1483; 96 MB 187 | 162; none 170 | 169.
-//   weights and velocity, TopK: ResNet-18 W = 1 113 -> 95 | 89 -> 94 | 114 -> 109 | 107 -> 103, W = 4 215 -> 208 | 179 -> 184 | 212 -> 208 | 187 -> 185;
+//   weights and velocity (16 MB of them plain at every size; update_cached takes the small and the large contexts out), TopK: ResNet-18 W = 1 113 -> 95 | 89 -> 94 | 114 -> 109 | 107 -> 103, W = 4 215 -> 208 | 179 -> 184 | 212 -> 208 | 187 -> 185;
 //   VGG-19 W = 1 186 -> 177 | 153 -> 158 | 186 -> 181 | 173 -> 169; LSTM W = 1 422 -> 393 | 418 -> 369 | 415 -> 400 | 381 -> 371; odd sizes W = 3 135 -> 128 |
 //   111 -> 116 | 136 -> 136 | 125 -> 125; PowerSGD: ResNet-18 W = 1 103 -> 96 | 90 -> 96 | 106 -> 106 | 101 -> 101, W = 2 131 -> 127 | 121 -> 126 | 136 -> 135 |
 //   130 -> 128; VGG-19 W = 1 170 -> 159 | 151 -> 158 | 171 -> 168 | 163 -> 161; LSTM W = 1 643 -> 624 | 642 -> 608 | 636 -> 634 | 612 -> 612.
