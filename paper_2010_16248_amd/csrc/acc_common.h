@@ -60,7 +60,8 @@ struct PTile { int32_t layer, row0; };   // a block of rows of a matrix layer's 
 struct SelState {
   uint32_t b1;        // level-1 bin (key bits 30..20) that holds the k-th largest key
   uint32_t need2;     // entries still to be taken from bin b1
-  uint32_t mode;      // 0: b1 is one of the guessed bins (or decided); 1: the guess missed
+  uint32_t mode;      // 0: b1 is one of the guessed bins (or decided); 1: the guess missed; 2: bin 0, as guessed; 3: as 0,
+                      //   but (b1, b2) lies below the floor of the candidate lists
   uint32_t side;      // which of the guessed bins b1 is (0: the lowest)
   uint32_t b2;        // level-2 bin (key bits 19..14) within b1
   uint32_t need3;     // entries still to be taken from bin (b1, b2)
@@ -73,6 +74,7 @@ struct SelState {
   uint32_t fresh_nnz; // entries outside bin 0 in the last step whose threshold lay in bin 0 (everything
                       //   non-zero was kept then, so these were the gradient's own); 0: no such step yet.
                       //   Only steers the next guess.
+  uint32_t wary;      // steps for which the lists' floor still lies further down (see kListCells)
 };
 
 struct GradPtrs { const float* p[kMaxW]; };
@@ -118,11 +120,11 @@ struct Ws {
   uint32_t* qlist;             // W x q_stride x kQListCap: per quarter, its keys in bin (b1, b2)
   SelState* sel;               // W x L
   uint32_t* hist2m;            // W x L x 64: level-2 counts of b1 of a layer whose guess missed
-  uint32_t* lflag;             // L: nonzero = this step's compaction of the layer reads Delta (some worker's guess
-                               //   missed, or the guess was a band), not the candidate lists
+  uint32_t* lflag;             // L: bit 0 = this step's compaction of the layer reads Delta (some worker's guess
+                               //   missed, or the guess was a band), not the candidate lists; + 2 per worker whose lists are short
   uint2* b1hist;               // W x L x 2 (level): {b1 | largest recent move in level-2 cells << 11 | (last move in bins + 64) << 16 |
                                //   steps at rest << 24, step number} of the last step at this level
-  uint32_t* guess;             // W x L x 2 (level): lowest guessed level-1 bin | number of bins << 16 | first level-2 cell of it << 24,
+  uint32_t* guess;             // W x L x 2 (level): lowest guessed level-1 bin | number of bins << 16 | cells between it and the lists' floor << 24,
                                //   or a special value
   uint4* qinfo;                // W x q_stride: per wave quarter {entries above what is listed (one-bin and band
                                //   lists), listed entries, 0, exact zeros (one-bin and zero-guess lists)}

@@ -74,27 +74,31 @@ constexpr int kBandBins = 8, kBandKeepDiv = 6;
 __device__ __forceinline__ int guess_bins_for(uint32_t k, uint32_t n) {
   return (uint64_t)k * kBandKeepDiv > (uint64_t)n ? kBandBins : kGuessBins;
 }
-// A guess of kGuessBins bins may start inside its lowest bin, at one of its level-2 cells (a 64th of a bin):
-// the entries below that cell are no candidates.  The threshold of a run at rest moves by a cell or two per
-// step, and under error feedback the entries are densest just below it, so a floor at a whole bin lists
-// twice what is kept.  kFloorCells + kFloorPerMove m cells below the expected place, m = the largest recent
-// move, which fades slowly (faded_move); a level's first steps, and thresholds that move by half a bin
-// per step, keep the floor at a whole bin.  Against a floor at a whole bin, us per step, three states in turn:
-// ResNet-18 shapes K = 10 %, W = 4 203.1 -> 198.5, K = 1 %, W = 8 328 -> 305, LSTM set W = 16 2994 -> 2905, odd sizes
-// 115.6 -> 107.1, ten missed guesses in 1340 steps of 84 decisions.  Four cells less below a threshold at rest
-// or a move that fades by a quarter per step: 1 % faster there with ten times the misses; 16 + 6 m: 1 % slower, three misses.
+// All bins of a guess are counted, cell by cell (a cell is a 64th of a bin), but not all that is counted is listed: the
+// lists of a guess of kGuessBins bins start at a floor up to kFloorMost cells above its lowest bin.  Under error feedback the
+// entries are densest just below the threshold, so every cell the floor lies too low lists 0.06 % of the entries for nothing, written once and read
+// twice.  A threshold below the floor ("short" lists, mode 3) is decided as fast as any other, because its cell has been
+// counted; only the lists are of no use: the counting kernel reads that worker's Delta instead and marks the lists as incomplete, so
+// that the compaction does the same (ResNet-18 shapes at W = 4: 35 us more if it happens to every layer).  So the floor may lie close: kListCells + m cells below
+// the last threshold (further by its last move if that was down), m = the largest recent move, which fades slowly (faded_move) and stops
+// at kMoveMost.  After a short step it lies further down for kWarySteps steps, kFloorCells + kFloorPerMove m, where the
+// lowest counted bin lies as well; a level's first steps list everything they count.
+// us per step against a floor of 8 + 4 m cells, below which nothing was counted either: ResNet-18 shapes K = 10 %, W = 4 182.2 -> 180.7 (13 % of
+// the entries listed instead of 14.5; in the first twenty steps of a run 15 instead of 20), two windows of five steps 1679 -> 1667, K = 1 %, W = 1
+// with the update 96.4 -> 95.1, LSTM set W = 16 2353 -> 2366 (+- 20).
+constexpr int kListCells = 8, kWarySteps = 16, kFloorMost = 255;
 constexpr int kFloorCells = 8, kFloorPerMove = 4, kMoveMost = 31;
 __device__ __forceinline__ int faded_move(int m, uint32_t step) {
   return m >= 8 ? m - m / 8 : max(0, m - ((step & 3u) == 0u ? 1 : 0));
 }
 __device__ __forceinline__ uint32_t make_guess(int lo, int nb, int cell = 0) {
   const int at = max(1, min(kHistBins - nb, lo));
-  return (uint32_t)at | ((uint32_t)nb << 16) | (at == lo ? (uint32_t)cell << 24 : 0u);
+  return (uint32_t)at | ((uint32_t)nb << 16) | (at == lo ? (uint32_t)max(0, min(kFloorMost, cell)) << 24 : 0u);
 }
 __device__ __forceinline__ uint32_t guess_lo(uint32_t g) { return g & 0xffffu; }
 __device__ __forceinline__ uint32_t guess_nb(uint32_t g) { return (g >> 16) & 0xffu; }
 // the smallest key that is listed
-__device__ __forceinline__ uint32_t guess_floor(uint32_t g) { return (g & 0xffffu) << 20 | (g >> 24) << 14; }
+__device__ __forceinline__ uint32_t guess_floor(uint32_t g) { return ((g & 0xffffu) << 20) + ((g >> 24) << 14); }
 __device__ __forceinline__ uint32_t bin2_of(uint32_t key) { return (key >> 14) & 0x3fu; }
 __device__ __forceinline__ uint32_t bin3_of(uint32_t key) { return (key >> 6) & 0xffu; }
 __device__ __forceinline__ uint32_t bin4_of(uint32_t key) { return key & 0x3fu; }
@@ -314,8 +318,8 @@ __device__ __forceinline__ void cand_make_room(const Ws& ws, int64_t qslot, cons
   if (c.n_lds > (uint32_t)(kCandLds - 4 * kWave)) cand_write_out(ws, qslot, cl, c, lane, false);
 }
 
-// Pass A, one group: the candidates among the four elements of every lane (keys floor_key and up, which lies
-// in bin glo; glo >= 1, so a candidate is never an exact zero, and zeros are not counted: should the
+// Pass A, one group: the candidates among the four elements of every lane (keys floor_key and up, which is at or
+// above bin glo; glo >= 1, so a candidate is never an exact zero, and zeros are not counted: should the
 // threshold turn out to lie in bin 0 the guess has missed and the staging after a miss counts
 // them).  BAND: only the bins glo .. glo + gnb - 1 are listed, what lies above is counted.
 // mv: lane masks of the valid elements
@@ -329,20 +333,21 @@ __device__ __forceinline__ void stage_candidates(const CandList& cl, uint32_t* s
                                                  uint64_t mv0, uint64_t mv1, uint64_t mv2, uint64_t mv3,
                                                  const float4& d, uint32_t glo, uint32_t gnb, uint32_t floor_key,
                                                  uint32_t i_rel, int lane) {
-  uint32_t key[4], rel[4];
+  uint32_t key[4];
   uint64_t m[4];
 #pragma unroll
   for (int x = 0; x < 4; ++x) {
     key[x] = key_of(comp(d, x));
-    rel[x] = (key[x] >> 20) - glo;
+    const uint32_t rel = (key[x] >> 20) - glo;               // (an element outside the tile was loaded as zero)
+    if (rel < gnb && (!ZERO || key[x] != 0u)) atomicAdd(&sub2[rel * kL2Bins + bin2_of(key[x])], 1u);
     const uint64_t mvx = (x == 0 ? mv0 : x == 1 ? mv1 : x == 2 ? mv2 : mv3);
     if (ZERO) {
       m[x] = ballot64(key[x] != 0u);
       c.v_nz += (key[x] == 0u && (!MASKED || lane_bit(mvx))) ? 1u : 0u;
     } else if (BAND) {
       // inside the band: listed; above it: counted (a bin below glo wraps to a huge rel)
-      m[x] = ballot64(rel[x] < gnb);
-      const bool above = (int32_t)rel[x] >= (int32_t)gnb;
+      m[x] = ballot64(rel < gnb);
+      const bool above = (int32_t)rel >= (int32_t)gnb;
       c.v_hi += (above && (!MASKED || lane_bit(mvx))) ? 1u : 0u;
     } else {
       m[x] = ballot64(key[x] >= floor_key);
@@ -362,7 +367,6 @@ __device__ __forceinline__ void stage_candidates(const CandList& cl, uint32_t* s
     const uint32_t slot = sel ? place : (uint32_t)(kCandLds + lane);
     cl.val[slot] = __float_as_uint(comp(d, x));
     cl.idx[slot] = (uint16_t)(i_rel + x);
-    if (sel && rel[x] < gnb) atomicAdd(&sub2[rel[x] * kL2Bins + bin2_of(key[x])], 1u);
     place += sel ? 1u : 0u;
   }
   c.n_lds += total;
@@ -792,14 +796,15 @@ __device__ __forceinline__ QuarterHead load_quarter_head(const Ws& ws, int64_t q
 // Calls f(key, valid) with all 64 lanes for every key of bin b1 (zeros excluded) of one quarter
 // and returns the quarter's number of entries in bins above b1: from the quarter's list (the
 // candidates of pass A, or the keys of b1 alone with the entries above counted in info.x), or --
-// when the quarter has more entries than its list holds -- from Delta itself.
+// when the quarter has more entries than its list holds, or b1 has entries below the lists' floor (short) --
+// from Delta itself.
 // tl: tile within the layer, wave: quarter within the tile.
 template <class F>
 __device__ __forceinline__ uint32_t for_quarter_keys(const Ws& ws, const LayerDev& L, int w, int tl, int wave,
-                                                     int64_t qslot, const QuarterHead& h, uint32_t b1, int lane,
-                                                     F f) {
+                                                     int64_t qslot, const QuarterHead& h, uint32_t b1, bool is_short,
+                                                     int lane, F f) {
   const uint32_t n = rfl(h.info.y);
-  if (n <= (uint32_t)kCandCap) {
+  if (n <= (uint32_t)kCandCap && !is_short) {
     uint32_t above = rfl(h.info.x);
     auto visit = [&](uint32_t raw, uint32_t t) {
       const uint32_t key = raw & 0x7fffffffu;
@@ -834,15 +839,21 @@ __device__ __forceinline__ uint32_t for_quarter_keys(const Ws& ws, const LayerDe
   const WaveSpan sp = wave_span(tg, wave);
   const float* __restrict__ e = ws.e + (int64_t)w * ws.e_stride;
   uint32_t above = 0;
-  for (int q0 = sp.qbeg; q0 < sp.qend; q0 += kWave) {
-    const int qq = q0 + lane;
-    const float4 d = ld_span<false>(e, tg, sp, qq);
+  constexpr int U = 4;                                       // groups requested together
+  for (int q0 = sp.qbeg; q0 < sp.qend; q0 += U * kWave) {
+    float4 d[U];
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const uint32_t key = key_of(comp(d, c));
-      const bool valid = elem_valid<false>(tg, qq, c, qq < sp.qend);
-      above += (uint32_t)__popcll(ballot64(valid && (key >> 20) > b1));
-      f(key, valid && key != 0u && (key >> 20) == b1);
+    for (int u = 0; u < U; ++u) d[u] = ld_span<false>(e, tg, sp, q0 + u * kWave + lane);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int qq = q0 + u * kWave + lane;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const uint32_t key = key_of(comp(d[u], c));
+        const bool valid = elem_valid<false>(tg, qq, c, qq < sp.qend);
+        above += (uint32_t)__popcll(ballot64(valid && (key >> 20) > b1));
+        f(key, valid && key != 0u && (key >> 20) == b1);
+      }
     }
   }
   return above;
@@ -1025,8 +1036,6 @@ __global__ __launch_bounds__(kPickThreads) void topk_pick12_kernel(const Ws ws, 
   uint32_t c = 0u;
 #pragma unroll
   for (int st = 0; st < kStripes; ++st) c += reinterpret_cast<const uint32_t*>(&sub[st][0])[side * kL2Bins + lane];
-  // A guess that starts inside bin b1 holds only if the threshold lies at or above its floor
-  const bool hit = in_guess && (side != 0u || wave_sum_u32(c) >= need2);
   uint32_t zeros = 0u;
   if (zhit) {
     // the counts are those of the non-zero keys of bin 0; the rest of bin 0 are exact zeros, which
@@ -1035,6 +1044,8 @@ __global__ __launch_bounds__(kPickThreads) void topk_pick12_kernel(const Ws ws, 
     if (lane == 0) c += zeros;
   }
   const Pick p2 = wave_pick64(c, need2, lane);
+  // found, but below the lists' floor: the layer is counted and compacted from Delta
+  const bool is_short = in_guess && guess_nb(guess) == (uint32_t)kGuessBins && ((b1 << 20) | (p2.bin << 14)) < guess_floor(guess);
   if (lane == 0) {
     if (k_other != k) {
       // (the memory will adapt to the new level for some steps: a wide guess)
@@ -1042,20 +1053,21 @@ __global__ __launch_bounds__(kPickThreads) void topk_pick12_kernel(const Ws ws, 
           : make_guess((int)bo - kGuessMovingBelow, guess_bins_for(k_other, n_layer));
     }
     sp->b1 = b1; sp->need2 = need2; sp->k = k; sp->side = side; sp->zeros = zeros; sp->bin0 = bin0;
-    sp->mode = hit ? 0u : (zhit ? 2u : 1u);
+    sp->mode = is_short ? 3u : in_guess ? 0u : (zhit ? 2u : 1u);
     // the candidate lists of this layer cannot serve the compaction (a miss, or a band, which does
     // not list what lies above it): it reads Delta instead.  (Bin 0 guessed and found: the lists
     // hold every non-zero entry; the quarters that keep exact zeros go back to Delta one by one.)
-    if ((!hit && !zhit) || (guessed && guess_nb(guess) < (uint32_t)kGuessBins))
+    if ((!in_guess && !zhit) || (guessed && guess_nb(guess) < (uint32_t)kGuessBins))
       atomicOr(&ws.lflag[li], 1u);                         // cleared by the next step's first pass
-    if (!hit && !zhit) atomicAdd(&ws.stats[0], 1ull);      // layers re-staged (diagnostic counter)
-    if (hit || zhit) {
+    if (is_short) atomicAdd(&ws.lflag[li], 2u);            // workers whose lists the counting kernel marks
+    if (is_short || (!in_guess && !zhit)) atomicAdd(&ws.stats[0], 1ull);   // layers whose Delta is read again (diagnostic counter)
+    if (in_guess || zhit) {
       sp->b2 = p2.bin;
       sp->need3 = need2 - p2.above;                        // still needed from bin (b1, b2)
     }
   }
   // a missed layer's keys get staged tile by tile, with their level-2 counts added up here
-  if (!hit && !zhit) ws.hist2m[wl * kL2Bins + lane] = 0u;
+  if (!in_guess && !zhit) ws.hist2m[wl * kL2Bins + lane] = 0u;
 }
 
 struct CountLds {
@@ -1093,7 +1105,8 @@ __device__ __forceinline__ uint32_t count3_quarter(const Ws& ws, int w, const Co
   const uint32_t b2 = t.b2;
   uint32_t* list = ws.qlist + (t.qslot + quarter) * kQListCap;
   uint32_t n_gt = 0, n_cell = 0;                           // wave-uniform
-  const uint32_t above = for_quarter_keys(ws, ws.layers[t.ft.layer], w, t.ft.start >> kTileShift, quarter, t.qslot + quarter, qh, t.b1, lane,
+  const uint32_t above = for_quarter_keys(ws, ws.layers[t.ft.layer], w, t.ft.start >> kTileShift, quarter, t.qslot + quarter, qh, t.b1,
+                                          t.mode == 3u, lane,
                                           [&](uint32_t key, bool valid) {
     const uint32_t bb = bin2_of(key);
     const uint64_t mv = ballot64(valid);
@@ -1106,6 +1119,7 @@ __device__ __forceinline__ uint32_t count3_quarter(const Ws& ws, int w, const Co
     }
   });
   n_in = n_cell;
+  if (t.mode == 3u && lane == 0) reinterpret_cast<uint32_t*>(ws.qinfo + t.qslot + quarter)[1] = (uint32_t)kCandCap + 1u;   // an incomplete list
   return above + n_gt;
 }
 
@@ -1205,7 +1219,7 @@ __device__ __forceinline__ void pick3_body(const Ws& ws, int w0, uint32_t step_i
   // requested together: the selection's state (what thread 0 needs at the very end too)
   const uint32_t s_b1 = ld_here(&sp->b1), s_b2 = ld_here(&sp->b2), s_need2 = ld_here(&sp->need2), s_need3 = ld_here(&sp->need3),
                  s_zeros = ld_here(&sp->zeros), s_mode = ld_here(&sp->mode), s_bin0 = ld_here(&sp->bin0),
-                 s_fresh = ld_here(&sp->fresh_nnz), s_T = ld_here(&sp->T);
+                 s_fresh = ld_here(&sp->fresh_nnz), s_wary = ld_here(&sp->wary), s_T = ld_here(&sp->T);
   const uint32_t* bh = reinterpret_cast<const uint32_t*>(ws.b1hist + wl * 2);
   const uint32_t bh00 = ld_here(bh), bh01 = ld_here(bh + 1), bh10 = ld_here(bh + 2), bh11 = ld_here(bh + 3);
   const int lv = (int)rfl(ld_here(reinterpret_cast<const uint32_t*>(ws.level + li)));
@@ -1390,7 +1404,7 @@ __device__ __forceinline__ void pick3_body(const Ws& ws, int w0, uint32_t step_i
     auto sweep = [&](auto per_key, auto per_quarter) {
       for (int q = wave; q < nq; q += kPickWaves) {
         const QuarterHead qh = load_quarter_head(ws, qbase + q, lane);
-        const uint32_t above = for_quarter_keys(ws, L, w, q >> 2, q & 3, qbase + q, qh, b1, lane, per_key);
+        const uint32_t above = for_quarter_keys(ws, L, w, q >> 2, q & 3, qbase + q, qh, b1, false, lane, per_key);
         per_quarter(q, above);
       }
     };
@@ -1534,9 +1548,15 @@ __device__ __forceinline__ void pick3_body(const Ws& ws, int w0, uint32_t step_i
     if (b1 == 0u && nnz != 0u) { fresh = nnz; sp->fresh_nnz = nnz; }
     const bool runs_dry = fresh != 0u && (uint64_t)(nnz - min(k_now, nnz)) + fresh <= (uint64_t)k_now;
     const int nb = guess_bins_for(k_now, n_layer);
-    const int fine = cells + min(moved, 0) - (kFloorCells + kFloorPerMove * m);
+    // where the counted bins start, and the floor of the lists (see kListCells)
+    const uint32_t wary = mode == 3u ? (uint32_t)kWarySteps : max(rfl(s_wary), 1u) - 1u;
+    sp->wary = wary;
+    const int down = cells + min(moved, 0), fine = down - (kFloorCells + kFloorPerMove * m);
     int lo = centre - below, cell = 0;
-    if (nb == kGuessBins && consecutive && (fine >> 6) >= lo) { lo = fine >> 6; cell = fine & 63; }
+    if (nb == kGuessBins && consecutive) {
+      lo = max(lo, fine >> 6);
+      cell = (wary != 0u ? fine : down - (kListCells + m)) - (lo << 6);
+    }
     ws.guess[wl * 2 + lv] = (b1 == 0u || runs_dry) ? kGuessZero : make_guess(lo, nb, cell);
   }
 }
@@ -2235,6 +2255,10 @@ constexpr int kMeanWaves = 2;
 constexpr int kMeanSplit = 4 / kMeanWaves;                  // workgroups per tile
 constexpr int kMeanLdsWords = kQuarterFloats + 2 * kPayRing > kChunkWords ? kQuarterFloats + 2 * kPayRing : kChunkWords;
 
+// lflag of a layer: do the candidate lists serve its compaction?  (With incomplete lists of up to half of the workers they do, from Delta
+// where they don't.)
+__device__ __forceinline__ bool lists_serve(uint32_t lflag, int W) { return (lflag & 1u) == 0u && lflag <= (uint32_t)W; }
+
 // LARGE: a context that streams Delta or the lists (Ws).
 template <bool UPD, bool LARGE>
 __device__ __forceinline__ void compact_mean_body(const Ws& ws, const Sink& sink) {
@@ -2260,8 +2284,7 @@ __device__ __forceinline__ void compact_mean_body(const Ws& ws, const Sink& sink
     if (tg.aligned && ntd) compact_mean_tile<true, UPD, true, true>(ws, ft, L, tg, sink, stg, wave);
     else if (tg.aligned) compact_mean_tile<true, UPD, true>(ws, ft, L, tg, sink, stg, wave);
     else compact_mean_tile<false, UPD, true>(ws, ft, L, tg, sink, stg, wave);
-  } else if (L.ntiles > 1 && rfl(ws.lflag[ft.layer]) == 0u) {
-    // every worker's guess held and every list is complete: the candidates serve
+  } else if (L.ntiles > 1 && lists_serve(rfl(ws.lflag[ft.layer]), ws.W)) {
     if (LARGE && tg.aligned && ws.lists_stream)
       gather_mean_tile<true, UPD, true>(ws, ft, L, tg, sink, reinterpret_cast<float*>(stg), stg + kQuarterFloats, wave);
     else if (tg.aligned) gather_mean_tile<true, UPD>(ws, ft, L, tg, sink, reinterpret_cast<float*>(stg), stg + kQuarterFloats, wave);

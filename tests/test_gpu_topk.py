@@ -643,6 +643,35 @@ def test_a_guess_that_starts_inside_a_bin(crit):
     gpu.destroy()
 
 
+@pytest.mark.parametrize("workers,low", [(1, (0,)), (3, (1,)), (5, (0, 4)), (3, (0, 1, 2))])
+def test_lists_too_short_for_some_of_the_workers(workers, low):
+    """The lists' floor lies a few cells below the last threshold; the bins are counted from further down.  Memory and gradients
+    of some workers shrink by 3 %: their thresholds lie below the floor, in a cell that was counted, and their Delta is read
+    instead of the lists, for a minority of the workers beside the others' lists.  Every step exact, payloads included."""
+    print(f"case short lists W {workers} low {low}", flush=True)
+    layers = wl.make_layers([(1, 9 * 8192 + 3, 0), (1, 5, 0), (23, 1031, 1)])
+    N = wl.total_params(layers)
+    rng = np.random.default_rng(workers)
+    gpu, ora = H.make_pair(B.ACC_TOPK, layers, workers, 10, 5)
+    scale = np.ones(workers, np.float32)
+    misses = []
+    for step in range(38):
+        if step == 36:
+            for w in low:
+                scale[w] *= np.float32(0.97)
+                ora.e[w] *= np.float32(0.97)
+            gpu.set_state(H.oracle_state_blob(gpu, ora))
+        grads = [rng.standard_normal(N, dtype=np.float32) * scale[w] for w in range(workers)]
+        if step < 35:
+            ora.step(grads)
+            gpu.step_all([H.to_dev(g) for g in grads], H.dev_out(N))
+        else:
+            _check_step(gpu, ora, grads, f"W {workers} low {low} step {step}", check_state=step != 36)
+        misses.append(gpu.topk_stats()[0])
+    assert misses[36] - misses[35] >= len(low), "no list was short"
+    gpu.destroy()
+
+
 def test_layers_at_the_edges_of_the_level_2_slot_groups():
     """512 tiles share 32 slots of sixteen tiles, 513 tiles 17 slots of 32, 511 and 497 tiles leave the last slot
     unfilled or with one tile.  A count lost or added twice would miss the guess or move the threshold."""
