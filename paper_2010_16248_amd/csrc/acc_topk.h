@@ -272,14 +272,14 @@ struct CandList { uint32_t* val; uint16_t* idx; uint4* qi; };   // qi: the workg
 // v_hi, v_nz: per lane, summed over the wave when the quarter is finished.
 struct StageCounts { uint32_t n_lds, n_out, v_hi, v_nz; };
 
-// Layout of the lists in device memory: 64-entry chunks, chunk-major -- chunk c of quarter slot q
-// is entries (c * n_slots + q) * 64 ... + 63, n_slots = all quarter slots of all workers.  The first
-// chunks of all quarters are one dense region, the second chunks the next, and so on: a list
+// Layout of the lists in device memory: pairs of 64-entry chunks, pair-major -- pair p of quarter slot q
+// is entries (p * n_slots + q) * 128 ... + 127, n_slots = all quarter slots of all workers.  The first
+// pairs of all quarters are one dense region, the second pairs the next, and so on: a list
 // uses as many chunks as it has entries, so what is touched is dense (a fixed 4 KB slot per quarter
 // of which the first KB is used puts all the traffic on a few memory channels: 10 us per step on
-// ResNet-18 shapes).
+// ResNet-18 shapes).  In pairs, so that the compaction reads two entries per lane and instruction.
 __device__ __forceinline__ int64_t cand_at(const Ws& ws, int64_t qslot, uint32_t chunk, int lane) {
-  return ((int64_t)chunk * ws.n_qslots + qslot) * kWave + lane;
+  return (((int64_t)(chunk >> 1) * ws.n_qslots + qslot) * 2 + (chunk & 1u)) * kWave + lane;
 }
 
 // Writes the whole 64-entry chunks of the wave's LDS list out (final: the rest too) and moves what
@@ -1989,29 +1989,62 @@ __device__ __forceinline__ void compact_mean_tile(const Ws& ws, const FlatTile& 
 
 // The same pass from the candidate lists of pass A instead of Delta: for a layer whose guess held
 // for every worker, whose lists are complete and which keeps at most half of its entries, a wave
-// reads the (offset, value) candidates of its quarter worker by worker (6 bytes per candidate),
+// reads the (offset, value) candidates of its quarter worker by worker (6 bytes per candidate, two candidates per lane),
 // picks the selected ones with the same rule (key >= t_all, or equal to T within the tie quota,
 // in index order), writes them to the payload at consecutive positions (through a ring in LDS, whole
 // cache lines at a time) and adds the values into the quarter's dense sums in
 // LDS, workers in order from +0; the sums, divided by W, go out as the quarter's part of the
-// averaged gradient.  acc: the wave's kQuarterFloats floats of LDS.  NTL: the lists are read with the streaming hint
+// averaged gradient.  acc: the wave's kGatherWords words of LDS.  NTL: the lists are read with the streaming hint
 // (Ws::lists_stream).
-constexpr int kGatherChunks = 4;                            // 64-entry chunks of a candidate list requested together (2 to 8: within 2 us)
+// Bound by its instructions: the dense sums allow four waves per SIMD, and a wave waits for its own chain of compares,
+// ballots, prefix counts and LDS accesses (with its loads from one line and no stores it took 19 of 33 us on ResNet-18 shapes, W = 4, 2000
+// instructions per wave), and by its stores (payload 6 us there).  Two candidates per lane and three batches of 128 in flight instead of one and one of
+// 256: 32.5 -> 30.9 us there, LSTM set W = 16 422 -> 390, odd sizes W = 3 15.9 -> 15.0 (with it the division, see DivW).  Two waves per quarter, one for the sums and
+// one for the payload: the same, LSTM set 553 (lists are read twice); payload stored where it is selected: 40, LSTM set 690; half the sums in LDS at a
+// time, seven waves per SIMD: 27, LSTM set 440, before the second pass over the lists that it would need.
+constexpr int kPairAhead = 3;                               // batches of 128 candidates in flight
+constexpr int kPair = 2 * kWave;
 constexpr int kQuarterGroups = kTile / 16;                  // groups of a wave quarter at most
 constexpr int kQuarterFloats = 4 * kQuarterGroups;
 constexpr int kSinkGroups = 4;                              // groups of weights and velocity a lane requests together
-constexpr int kPayRing = 128;                               // a wave's payload ring in LDS: entries (indices, then values)
+constexpr int kPayRing = 256;                               // a wave's payload ring in LDS: entries (values, 16-bit offsets in the quarter)
+constexpr int kGatherWords = kQuarterFloats + kPayRing + kPayRing / 2;
+
+// Worker w's selection in the quarter, as scalars (mine: lane w holds it).
+struct WorkerSel { uint32_t t_all, k, T, ktie, eq_run, pos; bool ties; };
+
+__device__ __forceinline__ WorkerSel worker_sel(const QuarterSel& mine, int w) {
+  auto of = [&](uint32_t v) { return (uint32_t)__builtin_amdgcn_readlane((int)v, w); };
+  WorkerSel s;
+  s.t_all = of(mine.t_all); s.k = of(mine.k); s.T = of(mine.T); s.ktie = of(mine.ktie);
+  s.eq_run = of(mine.eq_before);
+  s.pos = of(mine.gt_before) + min(s.ktie, s.eq_run);
+  s.ties = (of(mine.flags) & 1u) != 0u;
+  return s;
+}
+
+// x / W, rounded once.  W a power of two: x * (1 / W) is the same real number.  Else from the product with the fp64 reciprocal,
+// which is within 2^-52 of x / W: a quotient of 24 bits by at most five is no closer than 2^-30 to a
+// midpoint of two fp32 numbers, and a quotient that is one (a denormal) is an fp64 number, to which the product rounds.
+// (Three instructions instead of a division's twelve.)
+struct DivW {
+  bool pow2; float rw; double rd;
+  __device__ __forceinline__ explicit DivW(int W) : pow2((W & (W - 1)) == 0), rw(1.0f / (float)W), rd(1.0 / (double)W) {}
+  __device__ __forceinline__ float4 operator()(const float4& a) const {
+    return pow2 ? make_float4(a.x * rw, a.y * rw, a.z * rw, a.w * rw)
+                : make_float4((float)((double)a.x * rd), (float)((double)a.y * rd), (float)((double)a.z * rd), (float)((double)a.w * rd));
+  }
+};
 
 template <bool AL, bool UPD, bool NTL = false>
 __device__ __forceinline__ void gather_mean_tile(const Ws& ws, const FlatTile& ft, const LayerDev& L,
-                                                 const TileGeom& tg, const Sink sink, float* acc, uint32_t* ring,
-                                                 int wave) {
+                                                 const TileGeom& tg, const Sink sink, float* acc, int wave) {
   const int lane = threadIdx.x & 63;
   const WaveSpan span = wave_span(tg, wave);
   const int ng = span.qend - span.qbeg;                    // groups of the quarter, wave-uniform
   if (ng <= 0) return;
-  int32_t* const ring_idx = reinterpret_cast<int32_t*>(ring);
-  float* const ring_val = reinterpret_cast<float*>(ring + kPayRing);
+  float* const ring_val = acc + kQuarterFloats;
+  uint16_t* const ring_off = reinterpret_cast<uint16_t*>(ring_val + kPayRing);
   const int64_t qslot_local = L.qoff + 4 * (int64_t)(ft.start >> kTileShift) + wave;
   const int W = ws.W;
   const int64_t pay_off = L.pay_off, pay_stride = ws.pay_stride, q_stride = ws.q_stride;
@@ -2027,31 +2060,21 @@ __device__ __forceinline__ void gather_mean_tile(const Ws& ws, const FlatTile& f
     mine = load_quarter_sel(ws, lane, ft.layer, qslot_local);
     n_mine = ws.qinfo[(int64_t)lane * q_stride + qslot_local].y;   // beyond kCandCap: the list is incomplete
   }
-  // A batch = up to kGatherChunks 64-entry chunks of one worker's list, requested together; the next
-  // batch (the rest of this worker's list, else the head of the next worker's) is requested before
-  // the current one is processed, whether or not anybody will look at it, so that a batch has the
-  // processing of the one before it to arrive.
-  constexpr int U = kGatherChunks;
-  // Chunks beyond the list's end (n entries) are not asked for: the list's last chunk is asked for again, which the
-  // nearest cache answers.  (Asked for all the same, up to half of what a batch read was of no use: ResNet-18 shapes
-  // at W = 4 197.2 us per step, 194.2 so; two windows of five steps 1734 -> 1686; LSTM set at W = 16 2856 -> 2821.)
-  auto load_batch = [&](int w, uint32_t t0, uint32_t n, uint32_t (&v)[U], uint32_t (&ix)[U]) {
-    const int64_t qslot = (int64_t)w * q_stride + qslot_local;
-    const uint32_t last = (max(n, 1u) - 1u) / kWave;
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int64_t a = cand_at(ws, qslot, min(t0 / kWave + u, last), lane);
-      if (NTL) {
-        v[u] = __builtin_nontemporal_load(cand_val + a);
-        ix[u] = __builtin_nontemporal_load(cand_idx + a);
-      } else {
-        v[u] = cand_val[a];
-        ix[u] = cand_idx[a];
-      }
-    }
+  // A batch: 128 candidates, entries 2 lane and 2 lane + 1 in each lane.  last: the offset of the list's last pair of entries in it (lanes
+  // beyond ask for that again, so no line is requested for nothing).
+  struct Batch { uint2 v; uint32_t x; };
+  auto load_batch = [&](int64_t at, uint32_t last, Batch& b) {   // at, last: wave-uniform
+    const uint32_t i = min(2u * (uint32_t)lane, last);
+    typedef uint32_t u2 __attribute__((ext_vector_type(2)));
+    const u2* pv = reinterpret_cast<const u2*>((const char*)(cand_val + at) + 4u * i);
+    const uint32_t* px = reinterpret_cast<const uint32_t*>((const char*)(cand_idx + at) + 2u * i);
+    const u2 t = NTL ? __builtin_nontemporal_load(pv) : *pv;
+    b.v = make_uint2(t.x, t.y);
+    b.x = NTL ? __builtin_nontemporal_load(px) : *px;
   };
-  uint32_t cv[U], ci[U];
-  load_batch(0, 0u, (uint32_t)kCandCap, cv, ci);           // its length is not known yet
+  constexpr int D = kPairAhead;
+  Batch batch[D];
+  load_batch(qslot_local * kPair, (uint32_t)(kPair - 2), batch[0]);   // worker 0's first; the list's length is not known yet
   // The weights and the velocity of the quarter in two batches of kSinkGroups groups per lane: the first is
   // requested before the workers' lists are gone through, the second before the first is used.  (One
   // group at a time, requested when it was needed, left a quarter eight dependent round trips: ResNet-18
@@ -2083,25 +2106,126 @@ __device__ __forceinline__ void gather_mean_tile(const Ws& ws, const FlatTile& f
   __builtin_amdgcn_wave_barrier();
   // index of the quarter's first element in the layer
   const int32_t i_quarter = (int32_t)(tg.a0 + 4 * (int64_t)span.qbeg - L.offset);
-  for (int w = 0; w < W; ++w) {
-    const uint32_t n_listed = (uint32_t)__builtin_amdgcn_readlane((int)n_mine, w);
-    const uint32_t t_all = (uint32_t)__builtin_amdgcn_readlane((int)mine.t_all, w);
-    const uint32_t k = (uint32_t)__builtin_amdgcn_readlane((int)mine.k, w);
-    const bool ties = ((uint32_t)__builtin_amdgcn_readlane((int)mine.flags, w) & 1u) != 0u;
-    const uint32_t T = (uint32_t)__builtin_amdgcn_readlane((int)mine.T, w);
-    const uint32_t ktie = (uint32_t)__builtin_amdgcn_readlane((int)mine.ktie, w);
-    uint32_t eq_run = (uint32_t)__builtin_amdgcn_readlane((int)mine.eq_before, w);
-    uint32_t pos_run = (uint32_t)__builtin_amdgcn_readlane((int)mine.gt_before, w) + min(ktie, eq_run);
-    int32_t* __restrict__ pidx = pay_idx + (int64_t)w * pay_stride + pay_off;
-    float* __restrict__ pval = pay_val + (int64_t)w * pay_stride + pay_off;
-    // This worker's list cannot serve this quarter -- it overflowed, or the threshold is zero and
-    // some of the quarter's exact zeros, which no list holds, are kept (the tie quota is not used
-    // up before it): the quarter is taken from Delta, group by group, with the same selection rule.
-    const bool from_delta = n_listed > (uint32_t)kCandCap || (T == 0u && ties && eq_run < ktie);   // wave-uniform
-    const uint32_t n = from_delta ? 0u : n_listed;
-    if (from_delta) {
+
+  // The worker whose list is gone through; everything here is wave-uniform.  The payload leaves through the ring in LDS, 64
+  // entries at a time from a 256-byte boundary of the values to the next: whole cache lines but for the two ends of a
+  // worker's quarter.  (Stored where they were selected, a chunk's 20 to 40 entries per instruction: ResNet-18 shapes K = 10 %, W = 4
+  // 198.3 us per step, 196.6 so; LSTM set, W = 16 2931, 2878.  Whole lines that do not start on a boundary gain nothing.)
+  int w = 0;
+  uint32_t t = 0u, n = 0u;                                 // next entry, entries of the list
+  WorkerSel sel = {0u, 0u, 0u, 0u, 0u, 0u, false};
+  uint32_t al = 0u, end = 0u, out = 0u;                    // end, out: positions + al behind the last entry in the ring, of the first that has not left
+  int32_t* pidx = nullptr;
+  float* pval = nullptr;
+  auto flush_block = [&]() {
+    __builtin_amdgcn_wave_barrier();
+    const uint32_t j = (out & ~(uint32_t)(kWave - 1)) + lane, slot = j & (kPayRing - 1);
+    if (j >= out && j < end && j - al < sel.k) {           // < k: always true for consistent state
+      const uint32_t boff = (j - al) << 2;                 // 32 bits: the payload of a worker is far below 4 GiB
+      __builtin_nontemporal_store(i_quarter + (int32_t)ring_off[slot], (int32_t*)((char*)pidx + boff));
+      __builtin_nontemporal_store(ring_val[slot], (float*)((char*)pval + boff));
+    }
+    out = min(end, (out & ~(uint32_t)(kWave - 1)) + kWave);
+    __builtin_amdgcn_wave_barrier();
+  };
+  auto put = [&](uint32_t pos, uint32_t off, float v) {
+    const uint32_t slot = pos & (kPayRing - 1);
+    ring_off[slot] = (uint16_t)off;
+    ring_val[slot] = v;
+    // offsets are unique within a worker's list, and a wave's LDS operations keep their order
+    acc[off] += v;
+  };
+  auto begin_worker = [&]() {
+    sel = worker_sel(mine, w);
+    n = (uint32_t)__builtin_amdgcn_readlane((int)n_mine, w);
+    pidx = pay_idx + (int64_t)w * pay_stride + pay_off;
+    pval = pay_val + (int64_t)w * pay_stride + pay_off;
+    al = (uint32_t)(reinterpret_cast<uintptr_t>(pval) >> 2) & (uint32_t)(kWave - 1);
+    end = out = sel.pos + al;
+  };
+  auto use = [&](const Batch& b) {
+    if (t == 0u) begin_worker();
+    const uint32_t e = t + 2u * (uint32_t)lane;
+    const uint64_t mv0 = ballot64(e < n), mv1 = ballot64(e + 1u < n);
+    const uint32_t key0 = b.v.x & 0x7fffffffu, key1 = b.v.y & 0x7fffffffu;
+    uint64_t m0 = ballot64(key0 >= sel.t_all) & mv0, m1 = ballot64(key1 >= sel.t_all) & mv1;
+    if (sel.ties) {
+      const uint64_t q0 = ballot64(key0 == sel.T) & mv0, q1 = ballot64(key1 == sel.T) & mv1;
+      if ((q0 | q1) != 0) {
+        const uint32_t rank = sel.eq_run + lanes_below(q0, lane) + lanes_below(q1, lane);
+        m0 |= ballot64(rank < sel.ktie) & q0;
+        m1 |= ballot64(rank + (lane_bit(q0) ? 1u : 0u) < sel.ktie) & q1;
+        sel.eq_run += (uint32_t)__popcll(q0) + (uint32_t)__popcll(q1);
+      }
+    }
+    m0 = scalar_mask(m0);
+    m1 = scalar_mask(m1);
+    const uint32_t pos = end + lanes_below(m0, lane) + lanes_below(m1, lane);
+    if (lane_bit(m0)) put(pos, b.x & 0xffffu, __uint_as_float(b.v.x));
+    if (lane_bit(m1)) put(pos + (lane_bit(m0) ? 1u : 0u), b.x >> 16, __uint_as_float(b.v.y));
+    end += (uint32_t)__popcll(m0) + (uint32_t)__popcll(m1);
+    // 128 entries at most and the 63 that may have been waiting: two blocks at most are complete
+    while ((end ^ out) >= (uint32_t)kWave) flush_block();
+    t += kPair;
+    if (t >= n) {
+      if (end != out) flush_block();
+      t = 0u;
+      ++w;
+    }
+  };
+  // A worker's list cannot serve this quarter -- it overflowed, or the threshold is zero and some of the quarter's exact
+  // zeros, which no list holds, are kept (the tie quota is not used up before it): the quarter is taken from that worker's
+  // Delta, group by group, with the same selection rule.
+  const uint64_t m_delta = ballot64(n_mine > (uint32_t)kCandCap ||
+                                    (mine.T == 0u && (mine.flags & 1u) != 0u && mine.eq_before < mine.ktie));
+  if (m_delta == 0) {
+    // One sequence of batches over all workers, D of them in flight.  The next to request: entries p_t .. of worker p_w's list of
+    // p_n, at p_at.  (Unconditional: a request behind a branch would make every wait in the loop a wait for all of them.  Behind
+    // the last list one and the same address is asked for.)
+    int p_w = 0;
+    uint32_t p_t = 0u, p_n = (uint32_t)__builtin_amdgcn_readlane((int)n_mine, 0);
+    int64_t p_list = qslot_local * kPair, p_at = p_list;
+    const int64_t pair_stride = ws.n_qslots * kPair, list_stride = q_stride * kPair;
+    auto advance = [&]() {
+      p_t += kPair;
+      p_at += pair_stride;
+      if (p_t >= p_n) {
+        p_t = 0u;
+        if (p_w + 1 < W) {
+          ++p_w;
+          p_list += list_stride;
+          p_n = (uint32_t)__builtin_amdgcn_readlane((int)n_mine, p_w);
+        } else {
+          p_n = 1u;
+        }
+        p_at = p_list;
+      }
+    };
+    auto request = [&](Batch& b) {
+      load_batch(p_at, (max(p_n - p_t, 1u) - 1u) & ~1u, b);   // (an empty list: its first entries, unused)
+      advance();
+    };
+    advance();                                               // the first is on its way
+#pragma unroll
+    for (int b = 1; b < D; ++b) request(batch[b]);
+    while (w < W) {
+#pragma unroll
+      for (int b = 0; b < D; ++b) {
+        if (w < W) use(batch[b]);
+        request(batch[b]);
+      }
+    }
+  } else {
+    while (w < W) {
+      if (((m_delta >> w) & 1ull) == 0) {
+        Batch b;
+        load_batch(((int64_t)w * q_stride + qslot_local) * kPair + (int64_t)(t / kPair) * ws.n_qslots * kPair, (uint32_t)(kPair - 2), b);
+        use(b);
+        continue;
+      }
+      begin_worker();
       const float* __restrict__ e = ws.e + (int64_t)w * ws.e_stride;
-      const SelCommon sc = {t_all, ties};
+      const SelCommon sc = {sel.t_all, sel.ties};
       for (int g0 = 0; g0 < ng; g0 += kWave) {
         const int q = span.qbeg + g0 + lane;
         const bool qa = q < span.qend;
@@ -2114,11 +2238,10 @@ __device__ __forceinline__ void gather_mean_tile(const Ws& ws, const FlatTile& f
           mv[c] = valid_mask<AL>(tg, q, c, qa, m_span);
           key[c] = key_of(comp(d, c));
         }
-        group_select(sc, [&]() { SelTies t; t.T = T; t.ktie = ktie; return t; }, eq_run, key, mv, lane, msel);
-        // Payload positions in index order: lane by lane, component by component.  The entries
-        // pass through a ring in LDS (slot = position mod kPayRing), half a wave at a time -- 128
-        // entries at most --, and leave it through consecutive lanes at consecutive positions.
-        uint32_t pos = pos_run, total = 0u, total_lo = 0u;
+        group_select(sc, [&]() { SelTies s; s.T = sel.T; s.ktie = sel.ktie; return s; }, sel.eq_run, key, mv, lane, msel);
+        // Payload positions in index order: lane by lane, component by component; the entries go through the ring half a
+        // wave at a time, 128 at most.
+        uint32_t pos = end, total = 0u, total_lo = 0u;
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
           pos += lanes_below(msel[c], lane);
@@ -2127,93 +2250,25 @@ __device__ __forceinline__ void gather_mean_tile(const Ws& ws, const FlatTile& f
         }
 #pragma unroll
         for (int half = 0; half < 2; ++half) {
-          const uint32_t h_lo = pos_run + (half ? total_lo : 0u), h_hi = pos_run + (half ? total : total_lo);
-          if (h_hi == h_lo) continue;                        // wave-uniform
           if ((lane >> 5) == half) {
-            uint32_t p = pos;
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
               if (lane_bit(msel[c])) {
-                const int32_t off = 4 * (g0 + lane) + c;     // offset in the quarter
-                ring_idx[p & (kPayRing - 1)] = i_quarter + off;
-                ring_val[p & (kPayRing - 1)] = comp(d, c);
-                acc[off] += comp(d, c);
-                ++p;
+                put(pos, (uint32_t)(4 * (g0 + lane) + c), comp(d, c));
+                ++pos;
               }
             }
           }
-          __builtin_amdgcn_wave_barrier();
-          for (uint32_t j0 = h_lo; j0 < h_hi; j0 += kWave) {
-            const uint32_t j = j0 + lane;
-            if (j < h_hi && j < k) {                         // < k: always true for consistent state
-              __builtin_nontemporal_store(ring_idx[j & (kPayRing - 1)], pidx + j);
-              __builtin_nontemporal_store(ring_val[j & (kPayRing - 1)], pval + j);
-            }
-          }
-          __builtin_amdgcn_wave_barrier();
-        }
-        pos_run += total;
-      }
-    }
-    // The payload leaves through the ring in LDS, 64 entries at a time from a 256-byte boundary of the values
-    // to the next: whole cache lines but for the two ends of a worker's quarter.  (Stored where they were selected, a
-    // chunk's 20 to 40 entries per instruction: ResNet-18 shapes K = 10 %, W = 4 198.3 us per step, 196.6 so;
-    // LSTM set, W = 16 2931, 2878.  Whole lines that do not start on a boundary gain nothing.)
-    const uint32_t al = (uint32_t)(reinterpret_cast<uintptr_t>(pval) >> 2) & (uint32_t)(kWave - 1);
-    uint32_t pos_out = pos_run + al;                         // first position (+ al) that has not left
-    auto flush_block = [&]() {
-      __builtin_amdgcn_wave_barrier();
-      const uint32_t j = (pos_out & ~(uint32_t)(kWave - 1)) + lane, end = pos_run + al;
-      if (j >= pos_out && j < end && j - al < k) {           // < k: always true for consistent state
-        const uint32_t boff = (j - al) << 2;
-        __builtin_nontemporal_store(ring_idx[j & (kPayRing - 1)], (int32_t*)((char*)pidx + boff));
-        __builtin_nontemporal_store(ring_val[j & (kPayRing - 1)], (float*)((char*)pval + boff));
-      }
-      pos_out = min(end, (pos_out & ~(uint32_t)(kWave - 1)) + kWave);
-      __builtin_amdgcn_wave_barrier();
-    };
-    for (uint32_t t0 = 0u; t0 < n || t0 == 0u; t0 += U * kWave) {
-      uint32_t nv[U], ni[U];
-      const bool more = t0 + U * kWave < n;
-      const uint32_t n_next = w + 1 < W ? (uint32_t)__builtin_amdgcn_readlane((int)n_mine, w + 1) : 0u;
-      load_batch(more ? w : min(w + 1, W - 1), more ? t0 + U * kWave : 0u, more ? n : min(n_next, (uint32_t)kCandCap), nv, ni);
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const uint32_t t = t0 + u * kWave + lane;
-        if (t0 + u * kWave < n) {                            // wave-uniform
-          const uint32_t key = cv[u] & 0x7fffffffu;
-          const uint64_t mvalid = ballot64(t < n);
-          uint64_t msel = ballot64(key >= t_all) & mvalid;
-          if (ties) {                                        // wave-uniform
-            const uint64_t meq = ballot64(key == T) & mvalid;
-            if (meq != 0) {
-              const uint32_t rank = eq_run + lanes_below(meq, lane);
-              msel |= ballot64(rank < ktie) & meq;
-              eq_run += (uint32_t)__popcll(meq);
-            }
-          }
-          msel = scalar_mask(msel);
-          if (lane_bit(msel)) {
-            const uint32_t pos = pos_run + al + lanes_below(msel, lane);
-            ring_idx[pos & (kPayRing - 1)] = i_quarter + (int32_t)ci[u];
-            ring_val[pos & (kPayRing - 1)] = __uint_as_float(cv[u]);
-            // offsets are unique within a worker's list, and a wave's LDS operations keep their order
-            acc[ci[u]] += __uint_as_float(cv[u]);
-          }
-          pos_run += (uint32_t)__popcll(msel);
-          // a chunk adds 64 entries at most to the 63 that may be waiting: one block at most is complete
-          if (((pos_run + al) ^ pos_out) >= (uint32_t)kWave) flush_block();
+          end += half ? total - total_lo : total_lo;
+          while ((end ^ out) >= (uint32_t)kWave) flush_block();
         }
       }
-#pragma unroll
-      for (int u = 0; u < U; ++u) { cv[u] = nv[u]; ci[u] = ni[u]; }
+      if (end != out) flush_block();
+      ++w;
     }
-    if (n != 0u && pos_run + al != pos_out) flush_block();
   }
   __builtin_amdgcn_wave_barrier();
-  const float fw = (float)W;
-  const bool pow2 = (W & (W - 1)) == 0;                     // then x / W and x * (1 / W) round alike
-  const float rw = 1.0f / fw;
+  const DivW mean_of(W);
   for (int g0 = 0; g0 < ng; g0 += SG * kWave) {
     float4 wn[SG], vn[SG];
     load_sink(g0 + SG * kWave, wn, vn);
@@ -2222,9 +2277,7 @@ __device__ __forceinline__ void gather_mean_tile(const Ws& ws, const FlatTile& f
       const int g = g0 + j * kWave + lane;
       const int q = span.qbeg + g;
       if (g < ng) {
-        const float4 a = acc4[g];
-        const float4 v = pow2 ? make_float4(a.x * rw, a.y * rw, a.z * rw, a.w * rw)
-                              : make_float4(a.x / fw, a.y / fw, a.z / fw, a.w / fw);
+        const float4 v = mean_of(acc4[g]);
         if (UPD) {
           nesterov4(v, wq[j], vq[j], sink);
           if (wv_stream) {
@@ -2253,7 +2306,7 @@ __device__ __forceinline__ void gather_mean_tile(const Ws& ws, const FlatTile& f
 // four on ResNet-18 shapes, the same as one).
 constexpr int kMeanWaves = 2;
 constexpr int kMeanSplit = 4 / kMeanWaves;                  // workgroups per tile
-constexpr int kMeanLdsWords = kQuarterFloats + 2 * kPayRing > kChunkWords ? kQuarterFloats + 2 * kPayRing : kChunkWords;
+constexpr int kMeanLdsWords = kGatherWords > kChunkWords ? kGatherWords : kChunkWords;
 
 // lflag of a layer: do the candidate lists serve its compaction?  (With incomplete lists of up to half of the workers they do, from Delta
 // where they don't.)
@@ -2286,9 +2339,9 @@ __device__ __forceinline__ void compact_mean_body(const Ws& ws, const Sink& sink
     else compact_mean_tile<false, UPD, true>(ws, ft, L, tg, sink, stg, wave);
   } else if (L.ntiles > 1 && lists_serve(rfl(ws.lflag[ft.layer]), ws.W)) {
     if (LARGE && tg.aligned && ws.lists_stream)
-      gather_mean_tile<true, UPD, true>(ws, ft, L, tg, sink, reinterpret_cast<float*>(stg), stg + kQuarterFloats, wave);
-    else if (tg.aligned) gather_mean_tile<true, UPD>(ws, ft, L, tg, sink, reinterpret_cast<float*>(stg), stg + kQuarterFloats, wave);
-    else gather_mean_tile<false, UPD>(ws, ft, L, tg, sink, reinterpret_cast<float*>(stg), stg + kQuarterFloats, wave);
+      gather_mean_tile<true, UPD, true>(ws, ft, L, tg, sink, reinterpret_cast<float*>(stg), wave);
+    else if (tg.aligned) gather_mean_tile<true, UPD>(ws, ft, L, tg, sink, reinterpret_cast<float*>(stg), wave);
+    else gather_mean_tile<false, UPD>(ws, ft, L, tg, sink, reinterpret_cast<float*>(stg), wave);
   } else {
     if (tg.aligned && ntd) compact_mean_tile<true, UPD, false, true>(ws, ft, L, tg, sink, stg, wave);
     else if (tg.aligned) compact_mean_tile<true, UPD, false>(ws, ft, L, tg, sink, stg, wave);
