@@ -52,7 +52,7 @@ struct LayerDev {
 // qslot0: slot of the tile's first wave quarter in a worker's per-quarter arrays (the layer's qoff +
 // 4 * tile within the layer), so that a kernel can request them before it has the layer's entry.
 struct FlatTile { int32_t layer, start, count, qslot0; };
-struct MatTile { int32_t layer, row0, col0, pad; };
+struct MatTile { int32_t layer, row0, col0, id; };
 struct QTile { int32_t layer, col0; };
 struct PTile { int32_t layer, row0; };   // a block of rows of a matrix layer's P (PowerSGD, mean over workers)
 
@@ -150,8 +150,28 @@ struct Ws {
   int32_t pmean_in_orth;       // PowerSGD: the orthogonalisation sums the partials of P itself
   int32_t n_ftiles, n_mtiles, n_qmtiles, n_qtiles, n_vectiles, n_mat, n_ptiles;
   int32_t n_t2slots;           // TopK: slots of t2 per worker
+  int32_t xcd_runs;            // runs of tiles go to one XCD (tile_of_block)
   float eta;
 };
+
+// ---- which tile a workgroup takes ----------------------------------------------------
+// Workgroups go round robin over the eight XCDs, each with an L2 of its own, so neighbouring tiles -- which share cache lines (rows and
+// layers that do not start on one), rows of Q, partial sums, histograms and per-quarter records -- met in eight different caches.  So runs of
+// kXcdRun tiles go to one XCD: of every 8 kXcdRun workgroups those of XCD x take the x-th run.  (Short runs, so that
+// the chip as a whole still streams through the tensors in order.)  us per step, round robin -> runs of 32: PowerSGD ResNet-18 shapes W = 1 with the update
+// 96.3 -> 92.4 (93.6 when every workgroup works its tile out instead of finding it in the table), odd sizes W = 3 119.4 -> 116.0 (117.2), the rest in that way: W = 2 127.7 -> 125.5, W = 4 159.6 -> 158.0, odd sizes W = 8 234.9 -> 228.6, VGG-19 W = 4 274.4 -> 272.4, with the update W = 1
+// 158.4 -> 156.1, call by call 112.2 -> 111.3, LSTM W = 1 514.6 -> 517.3, small sets +- 1 %; batch-size mode ResNet-18 W = 1 297.5 -> 291.8, W = 4 740 -> 735,
+// VGG-19 W = 4 637 -> 640, LSTM W = 2 the same; TopK LSTM W = 16 2335 -> 2232, W = 8 K = 1 % 1031 -> 1000, smaller contexts (LSTM W = 4, VGG-19,
+// ResNet-18, odd sizes) within 1 % either way, which therefore stay round robin (Ws::xcd_runs).  Runs of 8, 64, 128: LSTM W = 16 2321, 2264, 2314; PowerSGD ResNet-18
+// W = 1 94.9, 93.7, 96.1, odd sizes 116.7, 118.3, 118.6.
+constexpr int kXcds = 8, kXcdRun = 32;
+__device__ __host__ __forceinline__ int tile_of_block(int b, int n) {
+  constexpr int span = kXcds * kXcdRun;
+  if (b >= n - n % span) return b;                           // the rest stays as it is
+  return (b / span * kXcds + b % kXcds) * kXcdRun + b % span / kXcds;
+}
+// Flat tiles: see Ws::xcd_runs.
+__device__ __forceinline__ int flat_tile_of_block(const Ws& ws, int b, int n) { return ws.xcd_runs != 0 ? tile_of_block(b, n) : b; }
 
 // ---- wave64 helpers ---------------------------------------------------------------
 

@@ -307,7 +307,7 @@ __device__ __forceinline__ void ef_p_tile(const Ws& ws, const LayerDev& L, const
   }
   if (HASA) {
     const double tsum = block_sum4_d(a_sq, red4);
-    if (threadIdx.x == 0) ws.norm_part_m[blockIdx.x] = tsum;
+    if (threadIdx.x == 0) ws.norm_part_m[mt.id] = tsum;
   }
 }
 

@@ -34,7 +34,7 @@ __global__ __launch_bounds__(256) void norm_refresh_kernel(const Ws ws) {
       s += (double)a * (double)a;
     }
     s = block_sum4_d(s, red);
-    if (tid == 0) ws.norm_part_m[mt] = s;
+    if (tid == 0) ws.norm_part_m[t.id] = s;
   }
 }
 

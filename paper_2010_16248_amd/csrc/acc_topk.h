@@ -670,7 +670,8 @@ __device__ __forceinline__ void ef_hist_body(const Ws& ws, const GradPtrs& gp, i
   __shared__ double red4[4];
   __shared__ uint4 qi[4];
   const int w = w0 + blockIdx.y;
-  const FlatTile ft = ws.ftiles[blockIdx.x];
+  const int tile_id = flat_tile_of_block(ws, blockIdx.x, ws.n_ftiles);
+  const FlatTile ft = ws.ftiles[tile_id];
   // Everything else the tile depends on is requested together, as soon as its layer is known: the
   // flags, the layer's level and the guesses of both levels (one of them is the one to use).
   const uint32_t* gp2 = ws.guess + ((int64_t)w * ws.L + ft.layer) * 2;
@@ -689,7 +690,7 @@ __device__ __forceinline__ void ef_hist_body(const Ws& ws, const GradPtrs& gp, i
   // everything from here on is uniform over the workgroup
   auto tile = [&](auto al, auto select, auto zb, auto em, uint32_t guess) {
     ef_hist_tile<decltype(al)::value, decltype(select)::value, decltype(zb)::value, decltype(em)::value>(
-        ws, gp, w, blockIdx.x, ft, L, tg, hist, cl, sub2, red4, guess, fresh, pending);
+        ws, gp, w, tile_id, ft, L, tg, hist, cl, sub2, red4, guess, fresh, pending);
   };
   constexpr std::true_type yes;
   constexpr std::false_type no;
@@ -1133,7 +1134,7 @@ __global__ __launch_bounds__(256) void topk_count3_kernel(const Ws ws, int w0) {
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   CountTile t;
-  t.ft = ws.ftiles[blockIdx.x];
+  t.ft = ws.ftiles[flat_tile_of_block(ws, blockIdx.x, ws.n_ftiles)];
   t.qslot = (int64_t)w * ws.q_stride + t.ft.qslot0;
   const QuarterHead qh = load_quarter_head(ws, t.qslot + wave, lane);
   load_count_state(ws, w, t);
@@ -1157,7 +1158,8 @@ __global__ __launch_bounds__(256) void topk_count3_wide_kernel(const Ws ws, int 
   const int w = w0 + blockIdx.y;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int tile = (int)blockIdx.x * 4 + wave;
+  const int block = flat_tile_of_block(ws, blockIdx.x, (ws.n_ftiles + 3) / 4);
+  const int tile = block * 4 + wave;
   CountTile t;
   t.ft = ws.ftiles[min(tile, ws.n_ftiles - 1)];
   t.qslot = (int64_t)w * ws.q_stride + t.ft.qslot0;
@@ -1181,7 +1183,7 @@ __global__ __launch_bounds__(256) void topk_count3_wide_kernel(const Ws ws, int 
   for (int u = 0; u < 4; ++u) {                            // uniform over the workgroup
     const uint32_t b1 = rfl(missed[u]);
     if (b1 == kNoGuess) continue;
-    count3_missed(ws, w, ws.ftiles[(int)blockIdx.x * 4 + u], b1, CountLds{rare, sub2, qi}, wave);
+    count3_missed(ws, w, ws.ftiles[block * 4 + u], b1, CountLds{rare, sub2, qi}, wave);
     __syncthreads();                                       // the block of LDS serves the next tile
   }
 }
@@ -1761,7 +1763,7 @@ __device__ __forceinline__ void compact_tile(const Ws& ws, int w, const FlatTile
 
 __global__ __launch_bounds__(256) void topk_compact_kernel(const Ws ws, int w0) {
   const int w = w0 + blockIdx.y;
-  const FlatTile ft = ws.ftiles[blockIdx.x];
+  const FlatTile ft = ws.ftiles[flat_tile_of_block(ws, blockIdx.x, ws.n_ftiles)];
   const LayerDev& L = ws.layers[ft.layer];
   const TileGeom tg = tile_geom(L, ft);
   if (blockIdx.x == 0 && threadIdx.x == 0) {
@@ -2315,7 +2317,8 @@ __device__ __forceinline__ bool lists_serve(uint32_t lflag, int W) { return (lfl
 // LARGE: a context that streams Delta or the lists (Ws).
 template <bool UPD, bool LARGE>
 __device__ __forceinline__ void compact_mean_body(const Ws& ws, const Sink& sink) {
-  const FlatTile ft = ws.ftiles[blockIdx.x / kMeanSplit];
+  const int block = flat_tile_of_block(ws, blockIdx.x, ws.n_ftiles * kMeanSplit);
+  const FlatTile ft = ws.ftiles[block / kMeanSplit];
   const LayerDev& L = ws.layers[ft.layer];
   const TileGeom tg = tile_geom(L, ft);
   if (blockIdx.x == 0 && threadIdx.x == 0) {
@@ -2328,7 +2331,7 @@ __device__ __forceinline__ void compact_mean_body(const Ws& ws, const Sink& sink
   __shared__ __attribute__((aligned(16))) uint32_t stage[kMeanWaves][kMeanLdsWords];
   const int lw = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   uint32_t* stg = stage[lw];
-  const int wave = (int)(blockIdx.x % kMeanSplit) * kMeanWaves + lw;   // the quarter of the tile
+  const int wave = block % kMeanSplit * kMeanWaves + lw;   // the quarter of the tile
   // the payload layout of the layer at its level (k is the same for every worker)
   const uint32_t n_layer = (uint32_t)L.rows * (uint32_t)L.cols;
   const bool holes = payload_has_holes(n_layer, min(rfl(ws.sel[ft.layer].k), n_layer));
@@ -2376,7 +2379,7 @@ __device__ __forceinline__ void sparse_mean_body(const Ws& ws, const Sink& sink)
   __shared__ float acc[kTile];
   __shared__ uint16_t hole[kTile];                         // tile-local offsets of the dropped entries
   const int tid = threadIdx.x;
-  const FlatTile ft = ws.ftiles[blockIdx.x];
+  const FlatTile ft = ws.ftiles[flat_tile_of_block(ws, blockIdx.x, ws.n_ftiles)];
   const LayerDev& L = ws.layers[ft.layer];
   const TileGeom tg = tile_geom(L, ft);
   if (blockIdx.x == 0 && tid == 0) {

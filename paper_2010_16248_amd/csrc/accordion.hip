@@ -93,6 +93,12 @@ void choose_tiling(const acc_config* c, Plan& p) {
   while (p.qrows > 32 && workgroups(p.qrows) < kComputeUnits) p.qrows /= 2;
 }
 
+// PowerSGD's tiles in the order in which workgroups take them (tile_of_block; in the tables, so that small sets pay nothing for it).
+void run_order(std::vector<MatTile>& tiles) {
+  const std::vector<MatTile> in_order = tiles;
+  for (size_t b = 0; b < tiles.size(); ++b) tiles[b] = in_order[(size_t)tile_of_block((int)b, (int)tiles.size())];
+}
+
 // coarse: the tallest tiles, which need the least workspace.
 int make_plan_tiled(const acc_config* c, Plan& p, char* err, bool coarse) {
   if (!c) return fail(err, ACC_EINVAL, "config is NULL");
@@ -199,7 +205,7 @@ int make_plan_tiled(const acc_config* c, Plan& p, char* err, bool coarse) {
             mt.layer = i;
             mt.row0 = rb * p.mrows;
             mt.col0 = cc * kMatCols;
-            mt.pad = 0;
+            mt.id = (int32_t)p.mtiles.size();
             p.mtiles.push_back(mt);
           }
         for (int r0 = 0; r0 < l.rows; r0 += kPmeanRows) p.ptiles.push_back(PTile{i, r0});
@@ -245,6 +251,8 @@ int make_plan_tiled(const acc_config* c, Plan& p, char* err, bool coarse) {
   // 186 -> 189, W = 8 (231 MiB) 251 -> 242 | 244 -> 241 | 220 -> 220 | 215 -> 215, W = 12 (346 MiB) 361 -> 339 | 358 -> 337 | 362 -> 343 | 366 -> 346.
   p.q_stream = 4 * p.e_stride * c->n_workers > (int64_t(224) << 20) ? kQAllRows
                : 4 * aligned_rows * c->n_workers > (int64_t(72) << 20) ? kQAlignedRows : kQPlain;
+  run_order(p.mtiles);
+  run_order(p.qmtiles);
   p.q_stride = 4 * ntile + nl;
 
   // workspace layout, 256-byte aligned regions
@@ -874,6 +882,7 @@ static int32_t init_common(const acc_config* cfg, void* workspace_dev, size_t wo
   ws.n_ptiles = (int32_t)p.ptiles.size();
   ws.n_vectiles = (int32_t)p.vectiles.size();
   ws.n_mat = (int32_t)p.matlayers.size();
+  ws.xcd_runs = cfg->method == ACC_BATCH || p.e_stride * cfg->n_workers > (int64_t(1) << 28) ? 1 : 0;
   ws.eta = cfg->eta;
 
   const int nl_ = cfg->n_layers;

@@ -235,3 +235,21 @@ def test_errors_of_the_batch_mode():
     gpu.step_all([g], out)
     assert np.all(out.cpu().numpy() == 1.0)
     gpu.destroy()
+
+
+@pytest.mark.parametrize("tiles", [256, 257, 519])
+def test_runs_of_tiles_for_one_die(tiles):
+    """Every 256 tiles of a launch are taken in another order; what is left over keeps its own."""
+    print(f"case batch runs of tiles {tiles}", flush=True)
+    layers = [(0, 1, 8192 * (tiles - 1) + 5, 0)]
+    gpu, ora = _make(layers, 2, 2, initial_level=0)
+    rng = np.random.default_rng(tiles)
+    for step in range(3):
+        grads = [rng.standard_normal(ora.N, dtype=np.float32) for _ in range(2)]
+        ref, _ = ora.micro_step(grads)
+        out = H.dev_out(ora.N)
+        gpu.step_all([H.to_dev(g) for g in grads], out)
+        if ref is not None:
+            H.assert_bits_equal(out.cpu().numpy(), ref, f"tiles {tiles} step {step}")
+        _check_state(gpu, ora, f"tiles {tiles} step {step}")
+    gpu.destroy()

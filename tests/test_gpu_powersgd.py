@@ -527,3 +527,21 @@ def test_a_step_in_a_workspace_that_holds_only_the_tallest_tiles(monkeypatch):
         _forced_step(gpu, ora, grads, f"step {step}")
     assert torch.all(behind == 0xA5)
     gpu.destroy()
+
+
+@pytest.mark.parametrize("tiles", [255, 256, 257, 513])
+def test_runs_of_tiles_for_one_die(tiles):
+    """Every 256 tiles of a launch are taken in another order; what is left over keeps its own.  Two layers of `tiles` and 300
+    tiles of 16 rows: factors, D, residuals, accumulator and the norms, whose partial sums lie by tile."""
+    print(f"case runs of tiles {tiles}", flush=True)
+    layers = wl.make_layers([(16 * tiles, 5, 1), (16 * 300 - 3, 4, 1), (1, 77, 0)])
+    q0 = wl.q_init(layers, 2, 3)
+    gpu, ora = H.make_pair(B.ACC_POWERSGD, layers, 1, 2, 1, q_init=q0)
+    rng = np.random.default_rng(tiles)
+    for step in range(2):
+        _forced_step(gpu, ora, [(rng.standard_normal(ora.N) * 0.01).astype(np.float32)], f"tiles {tiles} step {step}")
+    ora.detect_regime(0.1, 0.1)
+    gpu.detect_regime(0.1, 0.1)
+    _, cur = gpu.get_norms()
+    np.testing.assert_allclose(cur, ora.norm_curr, rtol=1e-6)
+    gpu.destroy()

@@ -808,3 +808,34 @@ def test_a_tile_per_wave_in_the_counting_kernel():
         gpu.destroy()
     for i, (a, b) in enumerate(zip(*results)):
         assert np.array_equal(np.ascontiguousarray(a).view(np.uint8), np.ascontiguousarray(b).view(np.uint8)), f"output {i}"
+
+
+def test_runs_of_tiles_for_one_die():
+    """Contexts of more than 1 GiB of error memory take every 256 tiles (half tiles in the compaction) in another order; the
+    last 11 of these 1035 keep their own.  32 workers, two steps, against the sorted magnitudes on the device."""
+    import torch
+    print("case runs of tiles", flush=True)
+    W, n = 32, 1035 * 8192 - 5
+    layers = wl.make_layers([(1, n, 0)])
+    gpu = B.Accordion(B.ACC_TOPK, H.layer_tuples(layers), W, 10, 1)
+    k = (n * 10 + 99) // 100
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(7)
+    memory = [torch.zeros(n, device="cuda:0") for _ in range(W)]
+    out = torch.empty(n, device="cuda:0")
+    for step in range(2):
+        grads = [torch.randn(n, generator=gen, device="cuda:0") for _ in range(W)]
+        gpu.step_all(grads, out)
+        mean = torch.zeros(n, device="cuda:0")
+        for w in range(W):
+            d = memory[w].add_(grads[w])
+            keep = torch.sort(d.view(torch.int32) & 0x7fffffff, descending=True, stable=True).indices[:k]
+            mean[keep] += d[keep]
+            if w in (0, 17, 31):
+                idx, val = gpu.get_payload(w, 0)
+                ref = torch.sort(keep).values
+                assert np.array_equal(idx, ref.cpu().numpy()), f"step {step}: indices of worker {w}"
+                H.assert_bits_equal(val, d[ref].cpu().numpy(), f"step {step}: values of worker {w}")
+            d[keep] = 0.0
+        H.assert_bits_equal(out.cpu().numpy(), (mean / W).cpu().numpy(), f"step {step}: mean")
+    gpu.destroy()
