@@ -266,6 +266,8 @@ constexpr int kCandCap = 1024;                   // candidates of a wave quarter
 constexpr int kCandLds = 512;                    // a wave's list in LDS
 constexpr int kCandLdsSlots = kCandLds + kWave;  // + one slot per lane that takes the writes of unselected elements
 
+constexpr int kPair = 2 * kWave;                 // entries that lie together (cand_at)
+
 struct CandList { uint32_t* val; uint16_t* idx; uint4* qi; };   // qi: the workgroup's four quarter records
 
 // n_lds: entries in the LDS list; n_out: entries already written out (both wave-uniform);
@@ -774,23 +776,26 @@ __device__ __forceinline__ void restage_tile(const Ws& ws, int w, const FlatTile
 
 // ---- the per-layer decisions ---------------------------------------------------------------------
 
-// The first kEagerChunks 64-entry chunks of a quarter's list are requested together with its
+// The first 128 entries of a quarter's list (two per lane) are requested together with its
 // counts (the slot always exists; what lies past the count is ignored later), the rest once the
 // count is there and only as far as it reaches: a quarter lists 60 to 500 candidates on Gaussian
 // or Laplacian gradients at K = 1 % to 10 %, and chunks requested for nothing are read from memory
-// all the same (eight early chunks were 0.8 GB per step on the LSTM set at K = 1 %).
-constexpr int kEagerChunks = 2;
+// all the same (eight early chunks were 0.8 GB per step on the LSTM set at K = 1 %).  Two entries per lane and request instead of one, and
+// the rare walk over Delta not unrolled: the counting kernel 12.6 -> 11.7 us on ResNet-18 shapes W = 4, K = 99 % 9.8 -> 8.7, odd sizes 6.8 -> 6.5; steps
+// 179.5 -> 178.1, two windows of five steps 1657 -> 1642, odd sizes 96.3 -> 94.8, LSTM set the same.
 struct QuarterHead {
   uint4 info;                      // see stage_finish
-  uint32_t chunk[kEagerChunks];    // the calling lane's entries of the first chunks
+  uint32_t first[2];               // entries 2 lane and 2 lane + 1
 };
 
 __device__ __forceinline__ QuarterHead load_quarter_head(const Ws& ws, int64_t qslot, int lane) {
   QuarterHead h;
   const uint32_t* qi = reinterpret_cast<const uint32_t*>(ws.qinfo + qslot);
   h.info = make_uint4(ld_here(qi), ld_here(qi + 1), ld_here(qi + 2), ld_here(qi + 3));
-#pragma unroll
-  for (int ch = 0; ch < kEagerChunks; ++ch) h.chunk[ch] = ld_here(ws.cand_val + cand_at(ws, qslot, (uint32_t)ch, lane));
+  const uint64_t v = __hip_atomic_load(reinterpret_cast<const uint64_t*>(ws.cand_val + qslot * kPair) + lane, __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_WAVEFRONT);   // see ld_here
+  h.first[0] = (uint32_t)v;
+  h.first[1] = (uint32_t)(v >> 32);
   return h;
 }
 
@@ -814,20 +819,25 @@ __device__ __forceinline__ uint32_t for_quarter_keys(const Ws& ws, const LayerDe
       above += (uint32_t)__popcll(ballot64(bin > b1) & mvalid);
       f(key, t < n && bin == b1);
     };
-#pragma unroll
-    for (int ch = 0; ch < kEagerChunks; ++ch)
-      if (n > (uint32_t)(ch * kWave)) visit(h.chunk[ch], (uint32_t)(ch * kWave + lane));   // uniform condition
-    constexpr int U = 4;
-    for (uint32_t t0 = kEagerChunks * kWave; t0 < n; t0 += U * kWave) {
-      uint32_t raw[U];
+    visit(h.first[0], 2u * (uint32_t)lane);
+    visit(h.first[1], 2u * (uint32_t)lane + 1u);
+    constexpr int U = 2;                                      // pairs of chunks requested together
+    for (uint32_t t0 = kPair; t0 < n; t0 += U * kPair) {
+      uint2 raw[U];
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        raw[u] = 0u;
-        if (n > t0 + u * kWave) raw[u] = ws.cand_val[cand_at(ws, qslot, t0 / kWave + u, lane)];   // uniform condition
+        raw[u] = make_uint2(0u, 0u);
+        if (n > t0 + u * kPair)                               // uniform condition; lanes beyond the end ask for the last pair of entries
+          raw[u] = reinterpret_cast<const uint2*>(ws.cand_val + ((int64_t)(t0 / kPair + u) * ws.n_qslots + qslot) * kPair)[
+              min((uint32_t)lane, (n - 1u - (t0 + u * kPair)) >> 1)];
       }
 #pragma unroll
-      for (int u = 0; u < U; ++u)
-        if (n > t0 + u * kWave) visit(raw[u], t0 + u * kWave + lane);                         // uniform condition
+      for (int u = 0; u < U; ++u) {
+        if (n > t0 + u * kPair) {                             // uniform condition
+          visit(raw[u].x, t0 + u * kPair + 2u * (uint32_t)lane);
+          visit(raw[u].y, t0 + u * kPair + 2u * (uint32_t)lane + 1u);
+        }
+      }
     }
     return above;
   }
@@ -840,21 +850,15 @@ __device__ __forceinline__ uint32_t for_quarter_keys(const Ws& ws, const LayerDe
   const WaveSpan sp = wave_span(tg, wave);
   const float* __restrict__ e = ws.e + (int64_t)w * ws.e_stride;
   uint32_t above = 0;
-  constexpr int U = 4;                                       // groups requested together
-  for (int q0 = sp.qbeg; q0 < sp.qend; q0 += U * kWave) {
-    float4 d[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) d[u] = ld_span<false>(e, tg, sp, q0 + u * kWave + lane);
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int qq = q0 + u * kWave + lane;
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        const uint32_t key = key_of(comp(d[u], c));
-        const bool valid = elem_valid<false>(tg, qq, c, qq < sp.qend);
-        above += (uint32_t)__popcll(ballot64(valid && (key >> 20) > b1));
-        f(key, valid && key != 0u && (key >> 20) == b1);
-      }
+  for (int q0 = sp.qbeg; q0 < sp.qend; q0 += kWave) {
+    const int qq = q0 + lane;
+    const float4 d = ld_span<false>(e, tg, sp, qq);
+#pragma unroll 1
+    for (int c = 0; c < 4; ++c) {
+      const uint32_t key = key_of(comp(d, c));
+      const bool valid = elem_valid<false>(tg, qq, c, qq < sp.qend);
+      above += (uint32_t)__popcll(ballot64(valid && (key >> 20) > b1));
+      f(key, valid && key != 0u && (key >> 20) == b1);
     }
   }
   return above;
@@ -2005,7 +2009,6 @@ __device__ __forceinline__ void compact_mean_tile(const Ws& ws, const FlatTile& 
 // one for the payload: the same, LSTM set 553 (lists are read twice); payload stored where it is selected: 40, LSTM set 690; half the sums in LDS at a
 // time, seven waves per SIMD: 27, LSTM set 440, before the second pass over the lists that it would need.
 constexpr int kPairAhead = 3;                               // batches of 128 candidates in flight
-constexpr int kPair = 2 * kWave;
 constexpr int kQuarterGroups = kTile / 16;                  // groups of a wave quarter at most
 constexpr int kQuarterFloats = 4 * kQuarterGroups;
 constexpr int kSinkGroups = 4;                              // groups of weights and velocity a lane requests together
