@@ -57,6 +57,18 @@ constexpr bool kPsgdStreamG = true;     // gradients: read once per step
 constexpr bool kPsgdStreamA = true;     // accumulator: read and written once per step
 constexpr bool kPsgdStreamOut = true;   // averaged gradient: written once, read by nobody here
 
+// Rows that do not start on a 16-byte boundary share their first and last cache line with their neighbours, which other
+// workgroups read and write: streamed, such a line may have to be fetched twice, plain, the gradients push the error memory out of the caches.
+// Since neighbouring tiles meet in one L2 (tile_of_block) streaming wins wherever the error memory is of a size for that to matter.  The
+// context has more than kUStreamBytes of it; gradients, accumulator, D, weights and velocity of unaligned rows are then streamed as those of
+// aligned rows always are.  Odd sizes, us per step, plain -> streamed, three states in turn | one state again and again | one state and 1 GB of other traffic
+// between its steps | the same and the gradients written just before: W = 2 (58 MiB) 92.1 -> 84.3 | 82.9 -> 83.9 | 104.8 -> 99.5 | 94.9 -> 94.4, W = 3 (86 MiB)
+// 115.5 -> 107.7 | 104.0 -> 104.6 | 131.0 -> 123.1 | 117.6 -> 117.2, call by call 145.0 -> 137.1 | 132.6 -> 133.1 | 165.8 -> 156.8 | 147.4 -> 147.5, W = 6
+// 183.0 -> 180.0 | 170.3 -> 162.5 | 203.9 -> 189.6 | 190.9 -> 179.5, W = 8 232.7 -> 225.1 | 231.4 -> 222.0 | 266.2 -> 257.8 | 254.7 -> 236.5; below the line
+// W = 1 (29 MiB) 65.7 -> 62.4 | 58.2 -> 62.0 | 76.8 -> 71.2 | 71.8 -> 69.2, smaller layers W = 3 (35 MiB) 59.5 -> 58.1 | 53.7 -> 57.9 | 71.4 -> 66.6 |
+// 68.6 -> 65.7, W = 4 (11 MiB) 36.8 -> 39.3 | 36.3 -> 40.0 | 47.4 -> 45.5 | 45.6 -> 44.8.  Kernels of their own, so that small sets fetch no more code.
+constexpr int64_t kUStreamBytes = int64_t(48) << 20;
+
 // The lane's four elements of a row, loaded whatever the lane owns (every address lies inside the row);
 // row: the row's first element.  STREAM: non-temporal.
 template <int MODE, bool STREAM = false>
@@ -70,9 +82,8 @@ __device__ __forceinline__ void load_row(const float* __restrict__ row, int c, i
   }
 }
 
-// Stores what the lane owns.  Streaming stores on aligned rows only: an unaligned row shares its first and
-// last cache line with its neighbours, which the caches put together.
-template <int MODE, bool STREAM = false>
+// Stores what the lane owns.  STREAM: non-temporal, on unaligned rows only with US (see kUStreamBytes).
+template <int MODE, bool STREAM = false, bool US = false>
 __device__ __forceinline__ void store_row(float* __restrict__ row, const LaneCols& lc, const float (&d)[4]) {
   if (MODE == kRowAligned) {
     if (lc.own0 == 0) {
@@ -81,7 +92,8 @@ __device__ __forceinline__ void store_row(float* __restrict__ row, const LaneCol
     }
   } else if (MODE == kRowUnaligned) {
     if (lc.own0 == 0) {
-      st16(row + lc.c, make_float4(d[0], d[1], d[2], d[3]));
+      if (STREAM && US) st16_stream(row + lc.c, make_float4(d[0], d[1], d[2], d[3]));
+      else st16(row + lc.c, make_float4(d[0], d[1], d[2], d[3]));
     } else {
 #pragma unroll
       for (int v = 1; v < 4; ++v)
@@ -161,22 +173,22 @@ struct EfTile {
 
 // Rows i0 and i0 + 4 (a row beyond the tile: every lane asks for one and the same 16 bytes of the last
 // row and nobody looks at them; a request behind a branch would make every wait a wait for all requests).
-template <int MODE, bool HASA>
+template <int MODE, bool HASA, bool US>
 __device__ __forceinline__ void ef_load(const EfTile& t, int i0, EfRows& r) {
 #pragma unroll
   for (int b = 0; b < kEfRows; ++b) {
     const int i = i0 + 4 * b;
     const int64_t rb = (int64_t)min(i, t.row_end - 1) * t.cols;
     const int c = i < t.row_end ? t.lc.c : 0;
-    load_row<MODE, kPsgdStreamG && MODE == kRowAligned>(t.g + rb, c, t.cols, r.g[b]);
+    load_row<MODE, kPsgdStreamG && (MODE == kRowAligned || US)>(t.g + rb, c, t.cols, r.g[b]);
     load_row<MODE>(t.e + rb, c, t.cols, r.e[b]);
-    if (HASA) load_row<MODE, kPsgdStreamA && MODE == kRowAligned>(t.Asrc + rb, c, t.cols, r.a[b]);
+    if (HASA) load_row<MODE, kPsgdStreamA && (MODE == kRowAligned || US)>(t.Asrc + rb, c, t.cols, r.a[b]);
   }
 }
 
 // rp > 0: the memory still holds the previous step's Delta; its residual is Delta - P^ Q~^T with
 // the previous P^ (its rows of the tile are in ps) and Q~ (= the warm start, first rp columns).
-template <int R, int MODE, bool HASA>
+template <int R, int MODE, bool HASA, bool US>
 __device__ __forceinline__ void ef_rows(const EfTile& t, int i0, EfRows& r, const float (&q)[4][kMaxRank], int rp,
                                         const float (*ps)[kMaxRank], int row0, int rmax, bool a_fresh, double& a_sq) {
   const int lane = threadIdx.x & 63;
@@ -205,7 +217,7 @@ __device__ __forceinline__ void ef_rows(const EfTile& t, int i0, EfRows& r, cons
         float a[4];
 #pragma unroll
         for (int v = 0; v < 4; ++v) a[v] = owns<MODE>(t.lc, v) ? (a_fresh ? 0.f : r.a[b][v]) + r.g[b][v] : 0.f;
-        store_row<MODE, kPsgdStreamA>(t.A + rb, t.lc, a);
+        store_row<MODE, kPsgdStreamA, US>(t.A + rb, t.lc, a);
 #pragma unroll
         for (int v = 0; v < 4; ++v) a_sq += (double)a[v] * (double)a[v];
       }
@@ -256,20 +268,20 @@ __device__ __forceinline__ void ef_rows(const EfTile& t, int i0, EfRows& r, cons
   }
 }
 
-template <int R, int MODE, bool HASA>
+template <int R, int MODE, bool HASA, bool US>
 __device__ __forceinline__ double ef_loop(const EfTile& t, int i0, EfRows& cur, const float (&q)[4][kMaxRank], int rp,
                                           const float (*ps)[kMaxRank], int row0, int rmax, bool a_fresh) {
   double a_sq = 0.0;     // worker 0: the lane's share of the tile's sum of squares of A
   for (; i0 < t.row_end; i0 += 4 * kEfRows) {
     EfRows nxt;
-    ef_load<MODE, HASA>(t, i0 + 4 * kEfRows, nxt);
-    ef_rows<R, MODE, HASA>(t, i0, cur, q, rp, ps, row0, rmax, a_fresh, a_sq);
+    ef_load<MODE, HASA, US>(t, i0 + 4 * kEfRows, nxt);
+    ef_rows<R, MODE, HASA, US>(t, i0, cur, q, rp, ps, row0, rmax, a_fresh, a_sq);
     cur = nxt;
   }
   return a_sq;
 }
 
-template <int MODE, bool HASA>
+template <int MODE, bool HASA, bool US>
 __device__ __forceinline__ void ef_p_tile(const Ws& ws, const LayerDev& L, const MatTile& mt, const float* __restrict__ g,
                                           float* __restrict__ e, double* __restrict__ ppart, int level, int rp_used,
                                           uint32_t pending, uint32_t fresh, int w, float (*ps)[kMaxRank], double* red4) {
@@ -288,7 +300,7 @@ __device__ __forceinline__ void ef_p_tile(const Ws& ws, const LayerDev& L, const
   // requested together: the first rows, Q's rows, and the previous P^ rows of the tile (for LDS)
   const int i0 = mt.row0 + wave;
   EfRows first;
-  ef_load<MODE, HASA>(t, i0, first);
+  ef_load<MODE, HASA, US>(t, i0, first);
   float q[4][kMaxRank];
   load_q_rows<MODE>(ws, L, t.lc, q);
   const int pr = threadIdx.x >> 2, pk = threadIdx.x & 3;
@@ -300,10 +312,10 @@ __device__ __forceinline__ void ef_p_tile(const Ws& ws, const LayerDev& L, const
   __syncthreads();
   double a_sq;
   switch (r) {
-    case 1: a_sq = ef_loop<1, MODE, HASA>(t, i0, first, q, rp, ps, mt.row0, ws.rmax, a_fresh); break;
-    case 2: a_sq = ef_loop<2, MODE, HASA>(t, i0, first, q, rp, ps, mt.row0, ws.rmax, a_fresh); break;
-    case 3: a_sq = ef_loop<3, MODE, HASA>(t, i0, first, q, rp, ps, mt.row0, ws.rmax, a_fresh); break;
-    default: a_sq = ef_loop<4, MODE, HASA>(t, i0, first, q, rp, ps, mt.row0, ws.rmax, a_fresh); break;
+    case 1: a_sq = ef_loop<1, MODE, HASA, US>(t, i0, first, q, rp, ps, mt.row0, ws.rmax, a_fresh); break;
+    case 2: a_sq = ef_loop<2, MODE, HASA, US>(t, i0, first, q, rp, ps, mt.row0, ws.rmax, a_fresh); break;
+    case 3: a_sq = ef_loop<3, MODE, HASA, US>(t, i0, first, q, rp, ps, mt.row0, ws.rmax, a_fresh); break;
+    default: a_sq = ef_loop<4, MODE, HASA, US>(t, i0, first, q, rp, ps, mt.row0, ws.rmax, a_fresh); break;
   }
   if (HASA) {
     const double tsum = block_sum4_d(a_sq, red4);
@@ -314,7 +326,8 @@ __device__ __forceinline__ void ef_p_tile(const Ws& ws, const LayerDev& L, const
 // *ws.pending: bit w set = worker w's memory holds the previous Delta (see the top of this file).
 // The mask lives on the device (set by the decompress pass, cleared when the residual is written
 // out), so a captured graph of a step stays valid whatever happens between its replays.
-__global__ __launch_bounds__(256) void psgd_ef_p_kernel(const Ws ws, const GradPtrs gp, int w0) {
+template <bool US>
+__device__ __forceinline__ void ef_p_body(const Ws& ws, const GradPtrs& gp, int w0) {
   __shared__ float ps[kMatRows][kMaxRank];
   __shared__ double red4[4];
   const int w = w0 + blockIdx.y;
@@ -348,14 +361,18 @@ __global__ __launch_bounds__(256) void psgd_ef_p_kernel(const Ws ws, const GradP
   double* ppart = ws.Ppart + (int64_t)w * ws.ppart_stride;
   // worker 0 also updates A
   switch (2 * row_mode(L) + (w == 0 ? 1 : 0)) {
-    case 2 * kRowAligned: ef_p_tile<kRowAligned, false>(ws, L, t, g, e, ppart, level, rp_used, pending, fresh, w, ps, red4); break;
-    case 2 * kRowAligned + 1: ef_p_tile<kRowAligned, true>(ws, L, t, g, e, ppart, level, rp_used, pending, fresh, w, ps, red4); break;
-    case 2 * kRowUnaligned: ef_p_tile<kRowUnaligned, false>(ws, L, t, g, e, ppart, level, rp_used, pending, fresh, w, ps, red4); break;
-    case 2 * kRowUnaligned + 1: ef_p_tile<kRowUnaligned, true>(ws, L, t, g, e, ppart, level, rp_used, pending, fresh, w, ps, red4); break;
-    case 2 * kRowNarrow: ef_p_tile<kRowNarrow, false>(ws, L, t, g, e, ppart, level, rp_used, pending, fresh, w, ps, red4); break;
-    default: ef_p_tile<kRowNarrow, true>(ws, L, t, g, e, ppart, level, rp_used, pending, fresh, w, ps, red4); break;
+    case 2 * kRowAligned: ef_p_tile<kRowAligned, false, false>(ws, L, t, g, e, ppart, level, rp_used, pending, fresh, w, ps, red4); break;
+    case 2 * kRowAligned + 1: ef_p_tile<kRowAligned, true, false>(ws, L, t, g, e, ppart, level, rp_used, pending, fresh, w, ps, red4); break;
+    case 2 * kRowUnaligned: ef_p_tile<kRowUnaligned, false, US>(ws, L, t, g, e, ppart, level, rp_used, pending, fresh, w, ps, red4); break;
+    case 2 * kRowUnaligned + 1: ef_p_tile<kRowUnaligned, true, US>(ws, L, t, g, e, ppart, level, rp_used, pending, fresh, w, ps, red4); break;
+    case 2 * kRowNarrow: ef_p_tile<kRowNarrow, false, false>(ws, L, t, g, e, ppart, level, rp_used, pending, fresh, w, ps, red4); break;
+    default: ef_p_tile<kRowNarrow, true, false>(ws, L, t, g, e, ppart, level, rp_used, pending, fresh, w, ps, red4); break;
   }
 }
+
+__global__ __launch_bounds__(256) void psgd_ef_p_kernel(const Ws ws, const GradPtrs gp, int w0) { ef_p_body<false>(ws, gp, w0); }
+
+__global__ __launch_bounds__(256) void psgd_ef_p_stream_kernel(const Ws ws, const GradPtrs gp, int w0) { ef_p_body<true>(ws, gp, w0); }
 
 // ---- aggregate 0: P_bar = mean over workers (and column chunks), Gram-Schmidt -----------
 //
@@ -808,7 +825,7 @@ __global__ __launch_bounds__(256) void psgd_qmean_kernel(const Ws ws) {
 // on sink.wt / sink.vel and is not stored.
 enum DecompWhat { kDecompStore = 0, kDecompResidual = 1, kDecompUpdate = 2 };
 
-template <int WHAT, int MODE, bool NT = false>
+template <int WHAT, int MODE, bool NT = false, bool US = false>
 __device__ __forceinline__ void decomp_tile(const Ws& ws, const LayerDev& L, const MatTile& t, float* __restrict__ e,
                                             const Sink& sink, int r, float (*ps)[kMaxRank]) {
   constexpr bool RESIDUAL = WHAT == kDecompResidual;
@@ -870,10 +887,10 @@ __device__ __forceinline__ void decomp_tile(const Ws& ws, const LayerDev& L, con
         } else if (UPD) {
 #pragma unroll
           for (int v = 0; v < 4; ++v) nesterov(D[v], d[IN ? b : 0][v], vv[UPD ? b : 0][v], sink.lr, sink.mu, sink.wd);
-          store_row<MODE, NT>(src + rb, lc, d[IN ? b : 0]);
-          store_row<MODE, NT>(vel + rb, lc, vv[UPD ? b : 0]);
+          store_row<MODE, NT, US>(src + rb, lc, d[IN ? b : 0]);
+          store_row<MODE, NT, US>(vel + rb, lc, vv[UPD ? b : 0]);
         } else {
-          store_row<MODE, kPsgdStreamOut>(out + rb, lc, D);
+          store_row<MODE, kPsgdStreamOut, US>(out + rb, lc, D);
         }
       }
     }
@@ -888,7 +905,7 @@ __device__ __forceinline__ void decomp_tile(const Ws& ws, const LayerDev& L, con
   }
 }
 
-template <int WHAT>
+template <int WHAT, bool US = false>
 __device__ __forceinline__ void decomp_any(const Ws& ws, const LayerDev& L, const MatTile& t, float* __restrict__ e,
                                            const Sink& sink, int r, float (*ps)[kMaxRank]) {
   switch (row_mode(L)) {                                     // uniform over the workgroup
@@ -898,14 +915,19 @@ __device__ __forceinline__ void decomp_any(const Ws& ws, const LayerDev& L, cons
       else
         decomp_tile<WHAT, kRowAligned>(ws, L, t, e, sink, r, ps);
       break;
-    case kRowUnaligned: decomp_tile<WHAT, kRowUnaligned>(ws, L, t, e, sink, r, ps); break;
+    case kRowUnaligned:
+      if (US && WHAT == kDecompUpdate && L.offset + (int64_t)t.row0 * L.cols >= sink.wv_cached)
+        decomp_tile<WHAT, kRowUnaligned, US && WHAT == kDecompUpdate, US>(ws, L, t, e, sink, r, ps);
+      else
+        decomp_tile<WHAT, kRowUnaligned, false, US>(ws, L, t, e, sink, r, ps);
+      break;
     default: decomp_tile<WHAT, kRowNarrow>(ws, L, t, e, sink, r, ps); break;
   }
 }
 
 // The averaged decompressed gradient: D on matrix layers, the plain mean on 1-D layers (which keep
 // no memory: their e is cleared for every worker).
-template <bool UPD>
+template <bool UPD, bool US>
 __device__ __forceinline__ void decomp_body(const Ws& ws, const Sink& sink) {
   __shared__ float ps[kMatRows][kMaxRank];
   if (blockIdx.x == 0 && threadIdx.x == 0) {
@@ -934,16 +956,24 @@ __device__ __forceinline__ void decomp_body(const Ws& ws, const Sink& sink) {
   const MatTile t = ws.mtiles[blockIdx.x];
   const LayerDev& L = ws.layers[t.layer];
   const int r = ws.rank_used[t.layer];                     // written by the orthogonalisation of this step
-  decomp_any<UPD ? kDecompUpdate : kDecompStore>(ws, L, t, nullptr, sink, r, ps);
+  decomp_any<UPD ? kDecompUpdate : kDecompStore, US>(ws, L, t, nullptr, sink, r, ps);
 }
 
 __global__ __launch_bounds__(256) void psgd_decomp_kernel(const Ws ws, const Sink sink) {
-  decomp_body<false>(ws, sink);
+  decomp_body<false, false>(ws, sink);
+}
+
+__global__ __launch_bounds__(256) void psgd_decomp_stream_kernel(const Ws ws, const Sink sink) {
+  decomp_body<false, true>(ws, sink);
 }
 
 // The same pass with the optimizer step in place of the store of D.
 __global__ __launch_bounds__(256) void psgd_decomp_update_kernel(const Ws ws, const Sink sink) {
-  decomp_body<true>(ws, sink);
+  decomp_body<true, false>(ws, sink);
+}
+
+__global__ __launch_bounds__(256) void psgd_decomp_update_stream_kernel(const Ws ws, const Sink sink) {
+  decomp_body<true, true>(ws, sink);
 }
 
 // e_w = Delta_w - D for the workers whose bit is set in *ws.pending, in place; the caller clears

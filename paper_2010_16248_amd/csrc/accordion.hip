@@ -41,6 +41,7 @@ struct Plan {
   std::vector<int32_t> matlayers;
   int32_t rmax = 0;
   int32_t pmean_in_orth = 0, q_stream = 0;   // PowerSGD: see Ws, QStream
+  bool u_stream = false;   // PowerSGD: unaligned rows are streamed (kUStreamBytes), where they are more than a sixteenth
   int32_t mrows = kMatRows, qrows = kQRows;   // PowerSGD: rows of the two kinds of matrix tiles
   int64_t N = 0, e_stride = 0;
   int64_t q_total = 0;   // floats of Q in the caller's layout (rows of rmax floats)
@@ -251,6 +252,8 @@ int make_plan_tiled(const acc_config* c, Plan& p, char* err, bool coarse) {
   // 186 -> 189, W = 8 (231 MiB) 251 -> 242 | 244 -> 241 | 220 -> 220 | 215 -> 215, W = 12 (346 MiB) 361 -> 339 | 358 -> 337 | 362 -> 343 | 366 -> 346.
   p.q_stream = 4 * p.e_stride * c->n_workers > (int64_t(224) << 20) ? kQAllRows
                : 4 * aligned_rows * c->n_workers > (int64_t(72) << 20) ? kQAlignedRows : kQPlain;
+  const int64_t mat = p.n_model - p.vec_total;
+  p.u_stream = 16 * (mat - aligned_rows) > mat && 4 * p.e_stride * c->n_workers > kUStreamBytes;
   run_order(p.mtiles);
   run_order(p.qmtiles);
   p.q_stride = 4 * ntile + nl;
@@ -594,7 +597,8 @@ int launch_phase0(acc_ctx* c, int w0, int nw) {
   }
   if (c->cfg.method == ACC_POWERSGD) {
     const int gx = ws.n_mtiles + (w0 == 0 ? ws.n_vectiles : 0);
-    if (gx > 0) ACC_LAUNCH(c, psgd_ef_p_kernel, dim3(gx, nw), dim3(256), ws, c->grads, w0);
+    if (gx > 0 && c->plan.u_stream) ACC_LAUNCH_AS(c, psgd_ef_p_kernel, psgd_ef_p_stream_kernel, dim3(gx, nw), dim3(256), ws, c->grads, w0);
+    else if (gx > 0) ACC_LAUNCH(c, psgd_ef_p_kernel, dim3(gx, nw), dim3(256), ws, c->grads, w0);
   } else {
     const int rc = launch_topk_select(c, w0, nw, 1);   // the compaction reads Delta once more
     if (rc != ACC_OK) return rc;
@@ -643,8 +647,13 @@ int launch_decompress(acc_ctx* c, const Sink& sink) {
   const Ws& ws = c->ws;
   if (c->cfg.method == ACC_POWERSGD) {
     const dim3 grid(ws.n_mtiles + ws.n_vectiles);
-    if (sink.wt) ACC_LAUNCH(c, psgd_decomp_update_kernel, grid, dim3(256), ws, sink);
-    else ACC_LAUNCH(c, psgd_decomp_kernel, grid, dim3(256), ws, sink);
+    if (c->plan.u_stream) {
+      if (sink.wt) ACC_LAUNCH_AS(c, psgd_decomp_update_kernel, psgd_decomp_update_stream_kernel, grid, dim3(256), ws, sink);
+      else ACC_LAUNCH_AS(c, psgd_decomp_kernel, psgd_decomp_stream_kernel, grid, dim3(256), ws, sink);
+    } else {
+      if (sink.wt) ACC_LAUNCH(c, psgd_decomp_update_kernel, grid, dim3(256), ws, sink);
+      else ACC_LAUNCH(c, psgd_decomp_kernel, grid, dim3(256), ws, sink);
+    }
   } else {
     if (sink.wt) ACC_LAUNCH(c, topk_sparse_update_kernel, dim3(ws.n_ftiles), dim3(256), ws, sink);
     else ACC_LAUNCH(c, topk_sparse_mean_kernel, dim3(ws.n_ftiles), dim3(256), ws, sink);

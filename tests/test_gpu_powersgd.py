@@ -545,3 +545,44 @@ def test_runs_of_tiles_for_one_die(tiles):
     _, cur = gpu.get_norms()
     np.testing.assert_allclose(cur, ora.norm_curr, rtol=1e-6)
     gpu.destroy()
+
+
+@pytest.mark.parametrize("rank", [1, 4])
+def test_unaligned_rows_of_a_context_that_streams_them(rank):
+    """More than 48 MiB of error memory, nearly all of it in rows that start anywhere: gradients, accumulator, D, weights and
+    velocity of such rows are streamed.  Factors, D, residuals and accumulator against the oracle; call by call the same bits; the
+    update against the same recurrence on the stored D.  Last chunks of one, two and three columns, a narrow layer, an aligned one."""
+    print(f"case streamed unaligned rows rank {rank}", flush=True)
+    layers = wl.make_layers([(1201, 2001, 1), (3, 5, 1), (997, 3330, 1), (70, 259, 1), (50, 3, 1), (64, 512, 1), (1, 33, 0), (300, 2817, 1)])
+    W = 2
+    q0 = wl.q_init(layers, max(rank, 2), 3)
+    gpu, ora = H.make_pair(B.ACC_POWERSGD, layers, W, rank, 2, q_init=q0)
+    assert 4 * W * ora.N > 48 << 20
+    lt = H.layer_tuples(layers)
+    calls, upd, plain = (B.Accordion(B.ACC_POWERSGD, lt, W, rank, 2, q_init=q0) for _ in range(3))
+    rng = np.random.default_rng(rank)
+    w_ref = (rng.standard_normal(ora.N) * 0.05).astype(np.float32)
+    v_ref = np.zeros(ora.N, np.float32)
+    w_dev, v_dev = H.to_dev(w_ref), H.to_dev(v_ref)
+    outs = [H.dev_out(ora.N) for _ in range(2)]
+    for step in range(2):
+        grads = [(rng.standard_normal(ora.N) * 0.01).astype(np.float32) for _ in range(W)]
+        _forced_step(gpu, ora, grads, f"rank {rank} step {step}")
+        H.assert_bits_equal(gpu.unpack_state(gpu.get_state())["A"], ora.A, f"step {step}: accumulator")
+        dev = [H.to_dev(g) for g in grads]
+        plain.step_all(dev, outs[0])
+        for w in range(W):
+            calls.compress_step(w, dev[w], 0)
+        calls.aggregate(0)
+        for w in range(W):
+            calls.compress_step(w, None, 1)
+        calls.aggregate(1)
+        calls.decompress(outs[1])
+        d = outs[0].cpu().numpy()
+        H.assert_bits_equal(outs[1].cpu().numpy(), d, f"step {step}: call by call")
+        upd.step_all_update(dev, w_dev, v_dev, 0.1, 0.9)
+        w_ref, v_ref = orc.nesterov_update(w_ref, v_ref, d, 0.1, 0.9)
+        H.assert_bits_equal(w_dev.cpu().numpy(), w_ref, f"step {step}: weights")
+        H.assert_bits_equal(v_dev.cpu().numpy(), v_ref, f"step {step}: velocity")
+    for c in (gpu, calls, upd, plain):
+        c.destroy()
