@@ -247,10 +247,12 @@ int make_plan_tiled(const acc_config* c, Plan& p, char* err, bool coarse) {
   // 172 -> 158 | 156 -> 158 | 172 -> 165 | 157 -> 153, W = 2 (85 MiB) 103.7 -> 102.5 | 101.1 -> 102.4 | 114 -> 109 | 105 -> 103, VGG-19 W = 1 (78 MiB)
   // 116 -> 115 | 113.7 -> 115.0 | 128 -> 123 | 119 -> 115, W = 4 (314 MiB) 319 -> 274 | 315 -> 272 | 321 -> 281 | 319 -> 282; LSTM W = 1 (196 MiB)
   // 541 -> 513 | 496 -> 503 | 535 -> 529 | 514 -> 507; the next smaller set measured is ResNet-18 W = 1 (43 MiB): 75.3 -> 76.0 three states in turn.
-  // Unaligned rows (the odd-sized set, of which 6 % are aligned), from 224 MiB of error memory on: W = 3 (86 MiB) 119 -> 118.5 | 108 -> 111 |
-  // 120 -> 124 | 111 -> 116, W = 6 (173 MiB) 194 -> 192 | 181 -> 191 | 165 -> 171 | 159 -> 165, W = 7 (202 MiB) 223 -> 218 | 214 -> 217 | 193 -> 196 |
-  // 186 -> 189, W = 8 (231 MiB) 251 -> 242 | 244 -> 241 | 220 -> 220 | 215 -> 215, W = 12 (346 MiB) 361 -> 339 | 358 -> 337 | 362 -> 343 | 366 -> 346.
-  p.q_stream = 4 * p.e_stride * c->n_workers > (int64_t(224) << 20) ? kQAllRows
+  // Unaligned rows (the odd-sized set, of which 6 % are aligned, its other passes streamed: kUStreamBytes), from 248 MiB of error memory on: W = 2 (58 MiB)
+  // 85.0 -> 90.4 | 84.3 -> 90.0 | 99.8 -> 103.8 | 95.3 -> 98.2, W = 3 108.0 -> 112.8 | 104.7 -> 112.6 | 123.5 -> 130.9 | 117.6 -> 121.6, W = 6 (173 MiB)
+  // 180.1 -> 179.1 | 162.8 -> 177.8 | 189.6 -> 207.9 | 180.0 -> 189.1, W = 8 (231 MiB) 224.0 -> 225.0 | 202.7 -> 222.2 | 233.4 -> 257.4 | 220.4 -> 236.3,
+  // W = 9 (259 MiB) 255.1 -> 248.3 | 234.0 -> 246.4 | 274.9 -> 283.5 | 259.9 -> 269.1, W = 10 (288 MiB) 294.0 -> 272.7 | 285.7 -> 270.3 | 324.9 -> 307.8 |
+  // 305.5 -> 298.8, W = 12 347 -> 322 | 343 -> 318 | 382 -> 355 | 371 -> 348.
+  p.q_stream = 4 * p.e_stride * c->n_workers > (int64_t(248) << 20) ? kQAllRows
                : 4 * aligned_rows * c->n_workers > (int64_t(72) << 20) ? kQAlignedRows : kQPlain;
   const int64_t mat = p.n_model - p.vec_total;
   p.u_stream = 16 * (mat - aligned_rows) > mat && 4 * p.e_stride * c->n_workers > kUStreamBytes;

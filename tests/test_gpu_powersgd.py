@@ -427,6 +427,13 @@ def test_streamed_and_plain_access_give_the_same_bits(mode, rows, is_matrix, abo
         H.assert_bits_equal(a, b, mode)
 
 
+@pytest.mark.parametrize("mode", ["step", "calls", "update"])
+def test_right_product_that_streams_all_rows(mode):
+    """The same behind a vector of 8.3 M elements: 253 MiB of error memory, where the right product streams all rows (from 248)."""
+    assert 4 * 8300 * 1000 * 8 > 248 << 20
+    test_streamed_and_plain_access_give_the_same_bits(mode, 8300, 0, 224)
+
+
 def test_a_configuration_at_the_limit_of_the_static_workspace_keeps_its_tiles():
     """Flatter tiles need a little more workspace; what fits the static array with the tallest tiles only gets those."""
     print("case static workspace limit", flush=True)
