@@ -62,7 +62,7 @@ struct SelState {
   uint32_t need2;     // entries still to be taken from bin b1
   uint32_t mode;      // 0: b1 is one of the guessed bins (or decided); 1: the guess missed; 2: bin 0, as guessed; 3: as 0,
                       //   but (b1, b2) lies below the floor of the candidate lists
-  uint32_t side;      // which of the guessed bins b1 is (0: the lowest)
+  uint32_t wary;      // steps for which the lists' floor still lies further down (see kListCells)
   uint32_t b2;        // level-2 bin (key bits 19..14) within b1
   uint32_t need3;     // entries still to be taken from bin (b1, b2)
   uint32_t zeros;     // exact zeros of the layer (filled in when b1 == 0)
@@ -74,7 +74,6 @@ struct SelState {
   uint32_t fresh_nnz; // entries outside bin 0 in the last step whose threshold lay in bin 0 (everything
                       //   non-zero was kept then, so these were the gradient's own); 0: no such step yet.
                       //   Only steers the next guess.
-  uint32_t wary;      // steps for which the lists' floor still lies further down (see kListCells)
 };
 
 struct GradPtrs { const float* p[kMaxW]; };
@@ -170,7 +169,7 @@ __device__ __host__ __forceinline__ int tile_of_block(int b, int n) {
   if (b >= n - n % span) return b;                           // the rest stays as it is
   return (b / span * kXcds + b % kXcds) * kXcdRun + b % span / kXcds;
 }
-// Flat tiles: see Ws::xcd_runs.
+// Flat tiles: see Ws::xcd_runs.  (TopK contexts that are reordered are large enough for the kernels that stream, and only those ask.)
 __device__ __forceinline__ int flat_tile_of_block(const Ws& ws, int b, int n) { return ws.xcd_runs != 0 ? tile_of_block(b, n) : b; }
 
 // ---- wave64 helpers ---------------------------------------------------------------

@@ -59,8 +59,8 @@ constexpr bool kPsgdStreamOut = true;   // averaged gradient: written once, read
 
 // Rows that do not start on a 16-byte boundary share their first and last cache line with their neighbours, which other
 // workgroups read and write: streamed, such a line may have to be fetched twice, plain, the gradients push the error memory out of the caches.
-// Since neighbouring tiles meet in one L2 (tile_of_block) streaming wins wherever the error memory is of a size for that to matter.  The
-// context has more than kUStreamBytes of it; gradients, accumulator, D, weights and velocity of unaligned rows are then streamed as those of
+// Since neighbouring tiles meet in one L2 (tile_of_block) streaming wins wherever the error memory is of a size for that to matter: in contexts of
+// more than kUStreamBytes of it (the kernels with US) gradients, accumulator, D, weights and velocity of unaligned rows are streamed as those of
 // aligned rows always are.  Odd sizes, us per step, plain -> streamed, three states in turn | one state again and again | one state and 1 GB of other traffic
 // between its steps | the same and the gradients written just before: W = 2 (58 MiB) 92.1 -> 84.3 | 82.9 -> 83.9 | 104.8 -> 99.5 | 94.9 -> 94.4, W = 3 (86 MiB)
 // 115.5 -> 107.7 | 104.0 -> 104.6 | 131.0 -> 123.1 | 117.6 -> 117.2, call by call 145.0 -> 137.1 | 132.6 -> 133.1 | 165.8 -> 156.8 | 147.4 -> 147.5, W = 6
@@ -820,7 +820,7 @@ __global__ __launch_bounds__(256) void psgd_qmean_kernel(const Ws ws) {
 
 // ---- decompress: D = P^ Q_bar^T (the residual stays implicit) ----------------------------------
 
-// NT (the update of aligned rows): weights and velocity beyond Sink::wv_cached are streamed.
+// NT (the update): weights and velocity beyond Sink::wv_cached are streamed (unaligned rows: in contexts with US, see kUStreamBytes).
 // WHAT 0: writes D of the tile to sink.out.  1: e = Delta - D in place.  2: D drives the optimizer step
 // on sink.wt / sink.vel and is not stored.
 enum DecompWhat { kDecompStore = 0, kDecompResidual = 1, kDecompUpdate = 2 };

@@ -672,7 +672,7 @@ __device__ __forceinline__ void ef_hist_body(const Ws& ws, const GradPtrs& gp, i
   __shared__ double red4[4];
   __shared__ uint4 qi[4];
   const int w = w0 + blockIdx.y;
-  const int tile_id = flat_tile_of_block(ws, blockIdx.x, ws.n_ftiles);
+  const int tile_id = LARGE ? flat_tile_of_block(ws, blockIdx.x, ws.n_ftiles) : (int)blockIdx.x;
   const FlatTile ft = ws.ftiles[tile_id];
   // Everything else the tile depends on is requested together, as soon as its layer is known: the
   // flags, the layer's level and the guesses of both levels (one of them is the one to use).
@@ -1057,7 +1057,7 @@ __global__ __launch_bounds__(kPickThreads) void topk_pick12_kernel(const Ws ws, 
       ws.guess[wl * 2 + (1 - lv)] = (bo == 0u) ? kGuessZero
           : make_guess((int)bo - kGuessMovingBelow, guess_bins_for(k_other, n_layer));
     }
-    sp->b1 = b1; sp->need2 = need2; sp->k = k; sp->side = side; sp->zeros = zeros; sp->bin0 = bin0;
+    sp->b1 = b1; sp->need2 = need2; sp->k = k; sp->zeros = zeros; sp->bin0 = bin0;
     sp->mode = is_short ? 3u : in_guess ? 0u : (zhit ? 2u : 1u);
     // the candidate lists of this layer cannot serve the compaction (a miss, or a band, which does
     // not list what lies above it): it reads Delta instead.  (Bin 0 guessed and found: the lists
@@ -1138,7 +1138,7 @@ __global__ __launch_bounds__(256) void topk_count3_kernel(const Ws ws, int w0) {
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   CountTile t;
-  t.ft = ws.ftiles[flat_tile_of_block(ws, blockIdx.x, ws.n_ftiles)];
+  t.ft = ws.ftiles[blockIdx.x];
   t.qslot = (int64_t)w * ws.q_stride + t.ft.qslot0;
   const QuarterHead qh = load_quarter_head(ws, t.qslot + wave, lane);
   load_count_state(ws, w, t);
@@ -2320,7 +2320,7 @@ __device__ __forceinline__ bool lists_serve(uint32_t lflag, int W) { return (lfl
 // LARGE: a context that streams Delta or the lists (Ws).
 template <bool UPD, bool LARGE>
 __device__ __forceinline__ void compact_mean_body(const Ws& ws, const Sink& sink) {
-  const int block = flat_tile_of_block(ws, blockIdx.x, ws.n_ftiles * kMeanSplit);
+  const int block = LARGE ? flat_tile_of_block(ws, blockIdx.x, ws.n_ftiles * kMeanSplit) : (int)blockIdx.x;
   const FlatTile ft = ws.ftiles[block / kMeanSplit];
   const LayerDev& L = ws.layers[ft.layer];
   const TileGeom tg = tile_geom(L, ft);
