@@ -329,7 +329,7 @@ def measure(name, args, steps, warmup, pool, full):
     if use_events:
         gpu.set_profiling({"all": 1, "dominant": 2, "sampled": 3}[kernel_events])
     words0 = gpu.payload_words()[1]
-    stats0 = gpu.topk_stats() if w.method == B.ACC_TOPK else None
+    stats0 = gpu.topk_stats() + (gpu.topk_short_lists(),) if w.method == B.ACC_TOPK else None
     torch.cuda.synchronize()
     bs0 = gpu.batch_status() if is_batch else None
     t0 = time.perf_counter()
@@ -427,9 +427,9 @@ def measure(name, args, steps, warmup, pool, full):
         "payload_words_last_step": words_last, "critical_layers_at_end": int(levels.sum()),
     }
     if stats0 is not None:
-        s1 = gpu.topk_stats()
-        res["topk_paths"] = {"layer_steps": steps * W * len(layers), "guess_missed": s1[0] - stats0[0],
-                             "tie_sweeps": s1[1] - stats0[1]}
+        s1, short = gpu.topk_stats(), gpu.topk_short_lists()
+        res["topk_paths"] = {"layer_steps": steps * W * len(layers), "guess_missed": s1[0] - stats0[0] - (short - stats0[2]),
+                             "lists_short": short - stats0[2], "tie_sweeps": s1[1] - stats0[1]}
     gpu.destroy()
     del base, out
     torch.cuda.empty_cache()

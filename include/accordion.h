@@ -283,10 +283,14 @@ int32_t accordion_payload_words(acc_ctx* ctx, int64_t* last_step, int64_t* cumul
 /* TopK diagnostics since init (they describe which path the selection took, never its result):
  * restaged_layers = (worker, layer) pairs whose threshold lay below the entries the
  * error-feedback pass had listed, on a guess: Delta was read once more for them, and a
- * layer whose threshold bin had not even been counted was decided by sweeps of one workgroup (slow);
+ * layer whose threshold bin had not even been counted was decided by sweeps of one workgroup (slow;
+ * accordion_topk_short_lists tells the two apart);
  * swept_layers = pairs whose guess held but whose tie class was too large for the per-quarter
  * key lists, decided by the same sweeps. */
 int32_t accordion_topk_stats(acc_ctx* ctx, int64_t* restaged_layers, int64_t* swept_layers);
+/* Of the restaged layers of accordion_topk_stats, those whose lists were merely too short: the threshold bin had been
+ * counted, so the layer was decided as fast as any other and only its lists were of no use.  The rest are missed guesses. */
+int32_t accordion_topk_short_lists(acc_ctx* ctx, int64_t* short_layers);
 
 /* Overlap of the kept coordinates of two workers in the last step (Sec. 4.3: how much the
  * Top-K supports of a pair of stochastic gradients overlap; the paper reports > 90 % for

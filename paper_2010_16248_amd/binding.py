@@ -55,7 +55,7 @@ EXPORTS = [
     "accordion_get_norms", "accordion_get_payload", "accordion_get_factors",
     "accordion_payload_words", "accordion_state_bytes", "accordion_get_state", "accordion_set_state",
     "accordion_set_profiling", "accordion_get_profile", "accordion_stage_name",
-    "accordion_probe_copy", "accordion_topk_stats", "accordion_flush",
+    "accordion_probe_copy", "accordion_topk_stats", "accordion_topk_short_lists", "accordion_flush",
 ]
 ACC_N_STAGES = 48     # upper bound of the stage numbers; accordion_stage_name is NULL beyond the last
 
@@ -106,6 +106,7 @@ def load_library() -> C.CDLL:
         "accordion_get_profile": [vp, i32, C.POINTER(C.c_double), C.POINTER(i64)],
         "accordion_probe_copy": [vp, vp, i64, vp],
         "accordion_topk_stats": [vp, C.POINTER(i64), C.POINTER(i64)],
+        "accordion_topk_short_lists": [vp, C.POINTER(i64)],
     }
     for name, args in sig.items():
         fn = getattr(lib, name)
@@ -330,10 +331,17 @@ class Accordion:
         return int(a.value), int(b.value)
 
     def topk_stats(self) -> Tuple[int, int]:
-        """(layers whose guess missed, layers sent to the sweeps by a large tie class) since init."""
+        """(layers whose Delta was read again, because the guess missed or the lists were too short; layers sent to the
+        sweeps by a large tie class) since init."""
         a, b = C.c_int64(0), C.c_int64(0)
         _check(self._lib, self.ctx, self._lib.accordion_topk_stats(self.ctx, C.byref(a), C.byref(b)))
         return int(a.value), int(b.value)
+
+    def topk_short_lists(self) -> int:
+        """Those of topk_stats()[0] whose lists were merely too short: the guess held, the layer was decided without sweeps."""
+        a = C.c_int64(0)
+        _check(self._lib, self.ctx, self._lib.accordion_topk_short_lists(self.ctx, C.byref(a)))
+        return int(a.value)
 
     def state_bytes(self) -> int:
         out = C.c_size_t(0)

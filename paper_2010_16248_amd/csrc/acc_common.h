@@ -89,7 +89,8 @@ struct Ws {
   int32_t* rank_used;          // per layer, rank of the last PowerSGD step
   unsigned long long* words;   // [0] per step at current levels, [1] last step, [2] cumulative,
                                // [3] steps in the current detection window (MSDR detector)
-  unsigned long long* stats;   // TopK diagnostics: [0] (worker, layer) pairs re-staged, [1] decided by sweeps
+  unsigned long long* stats;   // TopK diagnostics: [0] (worker, layer) pairs whose Delta was read again, [1] decided by sweeps,
+                               //   [2] of [0], those whose lists were merely short
   float* A;                    // accumulated gradient, N
   float* e;                    // W x e_stride error memory (holds Delta during a step)
   int64_t e_stride;

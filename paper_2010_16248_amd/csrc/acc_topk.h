@@ -1064,7 +1064,10 @@ __global__ __launch_bounds__(kPickThreads) void topk_pick12_kernel(const Ws ws, 
     // hold every non-zero entry; the quarters that keep exact zeros go back to Delta one by one.)
     if ((!in_guess && !zhit) || (guessed && guess_nb(guess) < (uint32_t)kGuessBins))
       atomicOr(&ws.lflag[li], 1u);                         // cleared by the next step's first pass
-    if (is_short) atomicAdd(&ws.lflag[li], 2u);            // workers whose lists the counting kernel marks
+    if (is_short) {
+      atomicAdd(&ws.lflag[li], 2u);                        // workers whose lists the counting kernel marks
+      atomicAdd(&ws.stats[2], 1ull);
+    }
     if (is_short || (!in_guess && !zhit)) atomicAdd(&ws.stats[0], 1ull);   // layers whose Delta is read again (diagnostic counter)
     if (in_guess || zhit) {
       sp->b2 = p2.bin;

@@ -282,7 +282,7 @@ int make_plan_tiled(const acc_config* c, Plan& p, char* err, bool coarse) {
   reg(p.r_norm_curr, 4 * (int64_t)nl);
   reg(p.r_has_old, 4 * (int64_t)nl);
   reg(p.r_rank_used, 4 * (int64_t)nl);
-  reg(p.r_words, 8 * 6);
+  reg(p.r_words, 8 * 7);
   reg(p.r_A, 4 * p.e_stride);
   reg(p.r_e, 4 * p.e_stride * W);
   reg(p.r_norm_part, 8 * ntile);
@@ -1256,6 +1256,17 @@ int32_t accordion_topk_stats(acc_ctx* c, int64_t* restaged_layers, int64_t* swep
   ACC_HIP(c, hipMemcpy(s, c->ws.stats, sizeof(s), hipMemcpyDeviceToHost));
   *restaged_layers = (int64_t)s[0];
   *swept_layers = (int64_t)s[1];
+  return ACC_OK;
+}
+
+int32_t accordion_topk_short_lists(acc_ctx* c, int64_t* short_layers) {
+  ACC_USABLE(c);
+  if (c->cfg.method != ACC_TOPK) return fail(c->err, ACC_EINVAL, "TopK statistics exist for TopK only");
+  if (!short_layers) return fail(c->err, ACC_EINVAL, "host pointer is NULL");
+  ACC_HIP(c, hipStreamSynchronize(c->stream));
+  unsigned long long s = 0;
+  ACC_HIP(c, hipMemcpy(&s, c->ws.stats + 2, sizeof(s), hipMemcpyDeviceToHost));
+  *short_layers = (int64_t)s;
   return ACC_OK;
 }
 

@@ -109,6 +109,7 @@ def test_init_rejects_null_and_small_workspace_without_a_gpu(lib):
     # calls on a NULL context fail cleanly
     assert lib.accordion_compress_step(None, 0, None, 0) == B.ACC_EINVAL
     assert lib.accordion_destroy(None) == B.ACC_EINVAL
+    assert lib.accordion_topk_short_lists(None, C.byref(C.c_int64(0))) == B.ACC_EINVAL
 
 
 def test_binding_fails_loudly_when_library_is_missing(monkeypatch):

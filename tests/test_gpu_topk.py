@@ -654,7 +654,7 @@ def test_lists_too_short_for_some_of_the_workers(workers, low):
     rng = np.random.default_rng(workers)
     gpu, ora = H.make_pair(B.ACC_TOPK, layers, workers, 10, 5)
     scale = np.ones(workers, np.float32)
-    misses = []
+    short, restaged = [], []
     for step in range(38):
         if step == 36:
             for w in low:
@@ -667,8 +667,10 @@ def test_lists_too_short_for_some_of_the_workers(workers, low):
             gpu.step_all([H.to_dev(g) for g in grads], H.dev_out(N))
         else:
             _check_step(gpu, ora, grads, f"W {workers} low {low} step {step}", check_state=step != 36)
-        misses.append(gpu.topk_stats()[0])
-    assert misses[36] - misses[35] >= len(low), "no list was short"
+        short.append(gpu.topk_short_lists())
+        restaged.append(gpu.topk_stats()[0])
+    assert short[36] - short[35] >= len(low), "no list was short"
+    assert restaged[36] - restaged[35] == short[36] - short[35], "a guess was missed instead"
     gpu.destroy()
 
 
