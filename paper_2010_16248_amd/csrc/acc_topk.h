@@ -2181,99 +2181,101 @@ __device__ __forceinline__ void gather_mean_tile(const Ws& ws, const FlatTile& f
       ++w;
     }
   };
-  // A worker's list cannot serve this quarter -- it overflowed, or the threshold is zero and some of the quarter's exact
-  // zeros, which no list holds, are kept (the tie quota is not used up before it): the quarter is taken from that worker's
+  // Workers whose list cannot serve this quarter -- it overflowed or is marked as incomplete, or the threshold is zero and some of the quarter's
+  // exact zeros, which no list holds, are kept (the tie quota is not used up before it): the quarter is taken from that worker's
   // Delta, group by group, with the same selection rule.
   const uint64_t m_delta = ballot64(n_mine > (uint32_t)kCandCap ||
                                     (mine.T == 0u && (mine.flags & 1u) != 0u && mine.eq_before < mine.ktie));
-  if (m_delta == 0) {
-    // One sequence of batches over all workers, D of them in flight.  The next to request: entries p_t .. of worker p_w's list of
-    // p_n, at p_at.  (Unconditional: a request behind a branch would make every wait in the loop a wait for all of them.  Behind
-    // the last list one and the same address is asked for.)
-    int p_w = 0;
-    uint32_t p_t = 0u, p_n = (uint32_t)__builtin_amdgcn_readlane((int)n_mine, 0);
-    int64_t p_list = qslot_local * kPair, p_at = p_list;
-    const int64_t pair_stride = ws.n_qslots * kPair, list_stride = q_stride * kPair;
-    auto advance = [&]() {
-      p_t += kPair;
-      p_at += pair_stride;
-      if (p_t >= p_n) {
-        p_t = 0u;
-        if (p_w + 1 < W) {
-          ++p_w;
-          p_list += list_stride;
-          p_n = (uint32_t)__builtin_amdgcn_readlane((int)n_mine, p_w);
-        } else {
-          p_n = 1u;
-        }
-        p_at = p_list;
+  auto next_delta = [&](int from) { const uint64_t m = m_delta >> from; return m != 0 ? from + (int)__builtin_ctzll(m) : W; };
+  // The lists of the workers up to the next of these are one sequence of batches, D of them in flight.  The next to request: entries p_t ..
+  // of worker p_w's list of p_n, at p_at.  (Unconditional: a request behind a branch would make every wait in the loop a wait for all of
+  // them.  Behind the last list of the sequence, and for an empty list, one address is asked for and nobody looks at what comes.)
+  int w_stop = next_delta(0), p_w = 0;
+  uint32_t p_t = 0u, p_n = w_stop != 0 ? (uint32_t)__builtin_amdgcn_readlane((int)n_mine, 0) : 1u;
+  int64_t p_list = qslot_local * kPair, p_at = p_list;
+  const int64_t pair_stride = ws.n_qslots * kPair, list_stride = q_stride * kPair;
+  auto advance = [&]() {
+    p_t += kPair;
+    p_at += pair_stride;
+    if (p_t >= p_n) {
+      p_t = 0u;
+      if (p_w + 1 < w_stop) {
+        ++p_w;
+        p_list += list_stride;
+        p_n = (uint32_t)__builtin_amdgcn_readlane((int)n_mine, p_w);
+      } else {
+        p_n = 1u;
       }
-    };
-    auto request = [&](Batch& b) {
-      load_batch(p_at, (max(p_n - p_t, 1u) - 1u) & ~1u, b);   // (an empty list: its first entries, unused)
-      advance();
-    };
-    advance();                                               // the first is on its way
+      p_at = p_list;
+    }
+  };
+  auto request = [&](Batch& b) {
+    load_batch(p_at, (max(p_n - p_t, 1u) - 1u) & ~1u, b);
+    advance();
+  };
+  advance();                                                 // the first is on its way
 #pragma unroll
-    for (int b = 1; b < D; ++b) request(batch[b]);
-    while (w < W) {
+  for (int b = 1; b < D; ++b) request(batch[b]);
+  for (;;) {
+    while (w < w_stop) {
 #pragma unroll
       for (int b = 0; b < D; ++b) {
-        if (w < W) use(batch[b]);
+        if (w < w_stop) use(batch[b]);
         request(batch[b]);
       }
     }
-  } else {
-    while (w < W) {
-      if (((m_delta >> w) & 1ull) == 0) {
-        Batch b;
-        load_batch(((int64_t)w * q_stride + qslot_local) * kPair + (int64_t)(t / kPair) * ws.n_qslots * kPair, (uint32_t)(kPair - 2), b);
-        use(b);
-        continue;
+    if (w >= W) break;
+    // Worker w from its Delta; the lists behind it are requested first.
+    begin_worker();
+    w_stop = next_delta(w + 1);
+    p_t = 0u;
+    p_w = min(w + 1, W - 1);
+    p_n = w + 1 < w_stop ? (uint32_t)__builtin_amdgcn_readlane((int)n_mine, p_w) : 1u;
+    p_list = p_at = (qslot_local + (int64_t)p_w * q_stride) * kPair;
+#pragma unroll
+    for (int b = 0; b < D; ++b) request(batch[b]);
+    const float* __restrict__ e = ws.e + (int64_t)w * ws.e_stride;
+    const SelCommon sc = {sel.t_all, sel.ties};
+    for (int g0 = 0; g0 < ng; g0 += kWave) {
+      const int q = span.qbeg + g0 + lane;
+      const bool qa = q < span.qend;
+      const float4 d = ld_span<AL>(e, tg, span, q);
+      const uint64_t m_span = ballot64(qa);
+      uint32_t key[4];
+      uint64_t mv[4], msel[4];
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        mv[c] = valid_mask<AL>(tg, q, c, qa, m_span);
+        key[c] = key_of(comp(d, c));
       }
-      begin_worker();
-      const float* __restrict__ e = ws.e + (int64_t)w * ws.e_stride;
-      const SelCommon sc = {sel.t_all, sel.ties};
-      for (int g0 = 0; g0 < ng; g0 += kWave) {
-        const int q = span.qbeg + g0 + lane;
-        const bool qa = q < span.qend;
-        const float4 d = ld_span<AL>(e, tg, span, q);
-        const uint64_t m_span = ballot64(qa);
-        uint32_t key[4];
-        uint64_t mv[4], msel[4];
+      group_select(sc, [&]() { SelTies s; s.T = sel.T; s.ktie = sel.ktie; return s; }, sel.eq_run, key, mv, lane, msel);
+      if ((msel[0] | msel[1] | msel[2] | msel[3]) == 0) continue;   // wave-uniform
+      // Payload positions in index order: lane by lane, component by component; the entries go through the ring half a
+      // wave at a time, 128 at most.
+      uint32_t pos = end, total = 0u, total_lo = 0u;
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          mv[c] = valid_mask<AL>(tg, q, c, qa, m_span);
-          key[c] = key_of(comp(d, c));
-        }
-        group_select(sc, [&]() { SelTies s; s.T = sel.T; s.ktie = sel.ktie; return s; }, sel.eq_run, key, mv, lane, msel);
-        // Payload positions in index order: lane by lane, component by component; the entries go through the ring half a
-        // wave at a time, 128 at most.
-        uint32_t pos = end, total = 0u, total_lo = 0u;
+      for (int c = 0; c < 4; ++c) {
+        pos += lanes_below(msel[c], lane);
+        total += (uint32_t)__popcll(msel[c]);
+        total_lo += (uint32_t)__popcll(msel[c] & 0xffffffffull);
+      }
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          pos += lanes_below(msel[c], lane);
-          total += (uint32_t)__popcll(msel[c]);
-          total_lo += (uint32_t)__popcll(msel[c] & 0xffffffffull);
-        }
+      for (int half = 0; half < 2; ++half) {
+        if ((lane >> 5) == half) {
 #pragma unroll
-        for (int half = 0; half < 2; ++half) {
-          if ((lane >> 5) == half) {
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-              if (lane_bit(msel[c])) {
-                put(pos, (uint32_t)(4 * (g0 + lane) + c), comp(d, c));
-                ++pos;
-              }
+          for (int c = 0; c < 4; ++c) {
+            if (lane_bit(msel[c])) {
+              put(pos, (uint32_t)(4 * (g0 + lane) + c), comp(d, c));
+              ++pos;
             }
           }
-          end += half ? total - total_lo : total_lo;
-          while ((end ^ out) >= (uint32_t)kWave) flush_block();
         }
+        end += half ? total - total_lo : total_lo;
+        while ((end ^ out) >= (uint32_t)kWave) flush_block();
       }
-      if (end != out) flush_block();
-      ++w;
     }
+    if (end != out) flush_block();
+    ++w;
   }
   __builtin_amdgcn_wave_barrier();
   const DivW mean_of(W);

@@ -674,6 +674,69 @@ def test_lists_too_short_for_some_of_the_workers(workers, low):
     gpu.destroy()
 
 
+@pytest.mark.parametrize("workers,tiles,pad,low,dense", [(5, 30, 0, (1,), (3,)), (4, 30, 3, (0, 3), (2,)), (6, 11, 0, (2, 3), ()),
+                                                          (32, 650, 0, (0, 7, 31), (8,))])
+def test_short_lists_beside_overflowed_ones(workers, tiles, pad, low, dense):
+    """Workers `low` have short lists, workers `dense` lists that overflow (all they keep lies in few quarters) and the others
+    lists that serve, in one compaction; the last case counts with a tile per wave and streams the lists.  Every gradient has exactly
+    k entries that are not zero, so the memory is empty after each step and the threshold is the smallest of them: at cell 50 of a
+    bin until the run is at rest, then 30 cells lower for `low`, below the floor of the lists (8 cells and at most twice the largest
+    recent move, which has faded to 5) but in a bin that was counted."""
+    import torch
+    print(f"case short beside overflowed W {workers} tiles {tiles} pad {pad}", flush=True)
+    n = tiles * 8192 // 10 * 10
+    layers = wl.make_layers(([(1, pad, 0)] if pad else []) + [(1, n, 0)])
+    N, li, k = wl.total_params(layers), len(layers) - 1, n // 10
+    assert workers * tiles < 20000 or N * workers > 64 << 20
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(workers)
+    smallest = lambda cell: 1.0 + (192 + cell) / 512.0
+    grads, base = [], []
+    for w in range(workers):
+        at = torch.arange(k, device="cuda:0") if w in dense else \
+            10 * torch.arange(k, device="cuda:0") + torch.randint(10, (k,), generator=gen, device="cuda:0")
+        u = torch.rand(k, generator=gen, device="cuda:0")
+        u[0] = 0.0
+        sign = 1.0 - 2.0 * torch.randint(2, (k,), generator=gen, device="cuda:0")
+        g = torch.zeros(N, device="cuda:0")
+        if pad:
+            g[0] = 1.0
+        base.append((at, u, sign))
+        grads.append(g)
+
+    def fill(w, cell):
+        at, u, sign = base[w]
+        s = smallest(cell)
+        grads[w][pad + at] = sign * torch.clamp(s * (1.0 + u), min=s)
+    for w in range(workers):
+        fill(w, 50)
+    gpu = B.Accordion(B.ACC_TOPK, H.layer_tuples(layers), workers, 10, 1)
+    out = torch.empty(N, device="cuda:0")
+    for step in range(28):
+        if step == 26:
+            for w in low:
+                fill(w, 20)
+        if step == 25:
+            before = gpu.topk_short_lists(), gpu.topk_stats()[0]
+        gpu.step_all(grads, out)
+        if step < 25:
+            continue
+        mean = torch.zeros(N, device="cuda:0")
+        for g in grads:
+            mean += g
+        H.assert_bits_equal(out.cpu().numpy(), mean.cpu().numpy() / np.float32(workers), f"step {step}: mean")
+        for w in sorted({*low, *dense, workers // 2, workers - 1}):
+            idx, val = gpu.get_payload(w, li)
+            ref = torch.nonzero(grads[w][pad:])[:, 0]
+            assert np.array_equal(idx, ref.cpu().numpy()), f"step {step}: indices of worker {w}"
+            H.assert_bits_equal(val, grads[w][pad + ref].cpu().numpy(), f"step {step}: values of worker {w}")
+        now = gpu.topk_short_lists(), gpu.topk_stats()[0]
+        expected = len(low) if step == 26 else 0
+        assert (now[0] - before[0], now[1] - before[1]) == (expected, expected), f"step {step}: short lists, restaged layers"
+        before = now
+    gpu.destroy()
+
+
 def test_layers_at_the_edges_of_the_level_2_slot_groups():
     """512 tiles share 32 slots of sixteen tiles, 513 tiles 17 slots of 32, 511 and 497 tiles leave the last slot
     unfilled or with one tile.  A count lost or added twice would miss the guess or move the threshold."""
