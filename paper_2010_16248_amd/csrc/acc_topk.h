@@ -2318,9 +2318,11 @@ constexpr int kMeanWaves = 2;
 constexpr int kMeanSplit = 4 / kMeanWaves;                  // workgroups per tile
 constexpr int kMeanLdsWords = kGatherWords > kChunkWords ? kGatherWords : kChunkWords;
 
-// lflag of a layer: do the candidate lists serve its compaction?  (With incomplete lists of up to half of the workers they do, from Delta
-// where they don't.)
-__device__ __forceinline__ bool lists_serve(uint32_t lflag, int W) { return (lflag & 1u) == 0u && lflag <= (uint32_t)W; }
+// lflag of a layer: do the candidate lists serve its compaction?  With incomplete lists of up to a third of the workers they do, from Delta
+// where they don't.  One step in which s of W workers have short lists, us, all from Delta | the others from their lists: a layer of 10 M entries W = 2
+// s = 1 135 | 136, W = 4 s = 1 193 | 176, s = 2 208 | 205, s = 3 219 | 231; of 5 M entries W = 8 s = 1 169 | 143, s = 2 177 | 159, s = 4 185 | 185,
+// s = 6 198 | 218, W = 16 s = 1 265 | 227, s = 4 281 | 271, s = 8 316 | 333, s = 16 379 | 492; of 1 M entries W = 4 s = 1 56 | 59, s = 2 57 | 73.
+__device__ __forceinline__ bool lists_serve(uint32_t lflag, int W) { return (lflag & 1u) == 0u && 3u * (lflag >> 1) <= (uint32_t)W; }
 
 // LARGE: a context that streams Delta or the lists (Ws).
 template <bool UPD, bool LARGE>

@@ -674,11 +674,11 @@ def test_lists_too_short_for_some_of_the_workers(workers, low):
     gpu.destroy()
 
 
-@pytest.mark.parametrize("workers,tiles,pad,low,dense", [(5, 30, 0, (1,), (3,)), (4, 30, 3, (0, 3), (2,)), (6, 11, 0, (2, 3), ()),
+@pytest.mark.parametrize("workers,tiles,pad,low,dense", [(5, 30, 0, (1,), (3,)), (7, 30, 3, (0, 6), (2,)), (6, 11, 0, (2, 3), ()), (4, 30, 3, (0, 3), (2,)),
                                                           (32, 650, 0, (0, 7, 31), (8,))])
 def test_short_lists_beside_overflowed_ones(workers, tiles, pad, low, dense):
     """Workers `low` have short lists, workers `dense` lists that overflow (all they keep lies in few quarters) and the others
-    lists that serve, in one compaction; the last case counts with a tile per wave and streams the lists.  Every gradient has exactly
+    lists that serve, in one compaction (of a third of the workers at most; beyond, in the fourth case, Delta serves them all); the last case counts with a tile per wave and streams the lists.  Every gradient has exactly
     k entries that are not zero, so the memory is empty after each step and the threshold is the smallest of them: at cell 50 of a
     bin until the run is at rest, then 30 cells lower for `low`, below the floor of the lists (8 cells and at most twice the largest
     recent move, which has faded to 5) but in a bin that was counted."""
