@@ -776,26 +776,26 @@ __device__ __forceinline__ void restage_tile(const Ws& ws, int w, const FlatTile
 
 // ---- the per-layer decisions ---------------------------------------------------------------------
 
-// The first 128 entries of a quarter's list (two per lane) are requested together with its
+// The first kEagerChunks 64-entry chunks of a quarter's list are requested together with its
 // counts (the slot always exists; what lies past the count is ignored later), the rest once the
 // count is there and only as far as it reaches: a quarter lists 60 to 500 candidates on Gaussian
 // or Laplacian gradients at K = 1 % to 10 %, and chunks requested for nothing are read from memory
-// all the same (eight early chunks were 0.8 GB per step on the LSTM set at K = 1 %).  Two entries per lane and request instead of one, and
-// the rare walk over Delta not unrolled: the counting kernel 12.6 -> 11.7 us on ResNet-18 shapes W = 4, K = 99 % 9.8 -> 8.7, odd sizes 6.8 -> 6.5; steps
-// 179.5 -> 178.1, two windows of five steps 1657 -> 1642, odd sizes 96.3 -> 94.8, LSTM set the same.
+// all the same (eight early chunks were 0.8 GB per step on the LSTM set at K = 1 %).  A chunk is one 4-byte load per lane, and one beyond the
+// count is not gone through.  Counting kernel, us, two neighbouring entries per lane with one 8-byte load and no chunk skipped -> so:
+// ResNet-18 shapes W = 4 11.7 -> 10.5 (12.0 with the walk over Delta unrolled, whose code every launch fetched), K = 99 % 9.1 -> 7.2 (8.0),
+// odd sizes W = 3 6.3 -> 5.6 (6.5), LSTM set W = 2 26.0 -> 23.2, W = 16 168.9 -> 166.6.
+constexpr int kEagerChunks = 2;
 struct QuarterHead {
   uint4 info;                      // see stage_finish
-  uint32_t first[2];               // entries 2 lane and 2 lane + 1
+  uint32_t chunk[kEagerChunks];    // the calling lane's entries of the first chunks
 };
 
 __device__ __forceinline__ QuarterHead load_quarter_head(const Ws& ws, int64_t qslot, int lane) {
   QuarterHead h;
   const uint32_t* qi = reinterpret_cast<const uint32_t*>(ws.qinfo + qslot);
   h.info = make_uint4(ld_here(qi), ld_here(qi + 1), ld_here(qi + 2), ld_here(qi + 3));
-  const uint64_t v = __hip_atomic_load(reinterpret_cast<const uint64_t*>(ws.cand_val + qslot * kPair) + lane, __ATOMIC_RELAXED,
-                                       __HIP_MEMORY_SCOPE_WAVEFRONT);   // see ld_here
-  h.first[0] = (uint32_t)v;
-  h.first[1] = (uint32_t)(v >> 32);
+#pragma unroll
+  for (int ch = 0; ch < kEagerChunks; ++ch) h.chunk[ch] = ld_here(ws.cand_val + cand_at(ws, qslot, (uint32_t)ch, lane));
   return h;
 }
 
@@ -819,25 +819,20 @@ __device__ __forceinline__ uint32_t for_quarter_keys(const Ws& ws, const LayerDe
       above += (uint32_t)__popcll(ballot64(bin > b1) & mvalid);
       f(key, t < n && bin == b1);
     };
-    visit(h.first[0], 2u * (uint32_t)lane);
-    visit(h.first[1], 2u * (uint32_t)lane + 1u);
-    constexpr int U = 2;                                      // pairs of chunks requested together
-    for (uint32_t t0 = kPair; t0 < n; t0 += U * kPair) {
-      uint2 raw[U];
+#pragma unroll
+    for (int ch = 0; ch < kEagerChunks; ++ch)
+      if (n > (uint32_t)(ch * kWave)) visit(h.chunk[ch], (uint32_t)(ch * kWave + lane));   // uniform condition
+    constexpr int U = 4;
+    for (uint32_t t0 = kEagerChunks * kWave; t0 < n; t0 += U * kWave) {
+      uint32_t raw[U];
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        raw[u] = make_uint2(0u, 0u);
-        if (n > t0 + u * kPair)                               // uniform condition; lanes beyond the end ask for the last pair of entries
-          raw[u] = reinterpret_cast<const uint2*>(ws.cand_val + ((int64_t)(t0 / kPair + u) * ws.n_qslots + qslot) * kPair)[
-              min((uint32_t)lane, (n - 1u - (t0 + u * kPair)) >> 1)];
+        raw[u] = 0u;
+        if (n > t0 + u * kWave) raw[u] = ws.cand_val[cand_at(ws, qslot, t0 / kWave + u, lane)];   // uniform condition
       }
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        if (n > t0 + u * kPair) {                             // uniform condition
-          visit(raw[u].x, t0 + u * kPair + 2u * (uint32_t)lane);
-          visit(raw[u].y, t0 + u * kPair + 2u * (uint32_t)lane + 1u);
-        }
-      }
+      for (int u = 0; u < U; ++u)
+        if (n > t0 + u * kWave) visit(raw[u], t0 + u * kWave + lane);                         // uniform condition
     }
     return above;
   }
