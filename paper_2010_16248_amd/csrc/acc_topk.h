@@ -335,21 +335,22 @@ __device__ __forceinline__ void stage_candidates(const CandList& cl, uint32_t* s
                                                  uint64_t mv0, uint64_t mv1, uint64_t mv2, uint64_t mv3,
                                                  const float4& d, uint32_t glo, uint32_t gnb, uint32_t floor_key,
                                                  uint32_t i_rel, int lane) {
-  uint32_t key[4];
+  uint32_t key[4], rel[4];
   uint64_t m[4];
 #pragma unroll
   for (int x = 0; x < 4; ++x) {
     key[x] = key_of(comp(d, x));
-    const uint32_t rel = (key[x] >> 20) - glo;               // (an element outside the tile was loaded as zero)
-    if (rel < gnb && (!ZERO || key[x] != 0u)) atomicAdd(&sub2[rel * kL2Bins + bin2_of(key[x])], 1u);
+    rel[x] = (key[x] >> 20) - glo;
+    // more is counted than listed (an element outside the tile was loaded as zero); what the other two guesses count is what they list
+    if (!BAND && !ZERO && rel[x] < gnb) atomicAdd(&sub2[rel[x] * kL2Bins + bin2_of(key[x])], 1u);
     const uint64_t mvx = (x == 0 ? mv0 : x == 1 ? mv1 : x == 2 ? mv2 : mv3);
     if (ZERO) {
       m[x] = ballot64(key[x] != 0u);
       c.v_nz += (key[x] == 0u && (!MASKED || lane_bit(mvx))) ? 1u : 0u;
     } else if (BAND) {
       // inside the band: listed; above it: counted (a bin below glo wraps to a huge rel)
-      m[x] = ballot64(rel < gnb);
-      const bool above = (int32_t)rel >= (int32_t)gnb;
+      m[x] = ballot64(rel[x] < gnb);
+      const bool above = (int32_t)rel[x] >= (int32_t)gnb;
       c.v_hi += (above && (!MASKED || lane_bit(mvx))) ? 1u : 0u;
     } else {
       m[x] = ballot64(key[x] >= floor_key);
@@ -369,6 +370,7 @@ __device__ __forceinline__ void stage_candidates(const CandList& cl, uint32_t* s
     const uint32_t slot = sel ? place : (uint32_t)(kCandLds + lane);
     cl.val[slot] = __float_as_uint(comp(d, x));
     cl.idx[slot] = (uint16_t)(i_rel + x);
+    if ((BAND || ZERO) && sel && rel[x] < gnb) atomicAdd(&sub2[rel[x] * kL2Bins + bin2_of(key[x])], 1u);
     place += sel ? 1u : 0u;
   }
   c.n_lds += total;
