@@ -81,12 +81,17 @@ __device__ __forceinline__ int guess_bins_for(uint32_t k, uint32_t n) {
 // counted; only the lists are of no use: the counting kernel reads that worker's Delta instead and marks the lists as incomplete, so
 // that the compaction does the same (ResNet-18 shapes at W = 4: 35 us more if it happens to every layer).  So the floor may lie close: kListCells + m cells below
 // the last threshold (further by its last move if that was down), m = the largest recent move, which fades slowly (faded_move) and stops
-// at kMoveMost.  After a short step it lies further down for kWarySteps steps, kFloorCells + kFloorPerMove m, where the
+// at kMoveMost; kListCells + 2 m in layers of less than kSmallListLayer entries, whose thresholds scatter more and whose lists are no bytes to speak
+// of, while a short list holds up the whole step: three states in turn, us per step, m -> 2 m (short lists in one and the same run): 20 layers of up to
+// 600 x 800 W = 2 40.2 -> 39.7 (720 -> 145), with the update 45.5 -> 44.8, four small layers 36.2 -> 36.2 (105 -> 45), ResNet-18 shapes W = 4 176.4 -> 177.1
+// (1370 -> 680), two windows of five steps 1627.7 -> 1629.4, W = 1 with the update 94.3 -> 93.6; 4 m there: 40.5, 45.2, 36.4, 177, 1630, 94.6; 2 m in all
+// layers: ResNet-18 shapes W = 4 178.5, windows 1650.  After a short step it lies further down for kWarySteps steps, kFloorCells + kFloorPerMove m, where the
 // lowest counted bin lies as well; a level's first steps list everything they count.
 // us per step against a floor of 8 + 4 m cells, below which nothing was counted either: ResNet-18 shapes K = 10 %, W = 4 182.2 -> 180.7 (13 % of
 // the entries listed instead of 14.5; in the first twenty steps of a run 15 instead of 20), two windows of five steps 1679 -> 1667, K = 1 %, W = 1
 // with the update 96.4 -> 95.1, LSTM set W = 16 2353 -> 2366 (+- 20).
 constexpr int kListCells = 8, kWarySteps = 16, kFloorMost = 255;
+constexpr uint32_t kSmallListLayer = 1u << 19;
 constexpr int kFloorCells = 8, kFloorPerMove = 4, kMoveMost = 31;
 __device__ __forceinline__ int faded_move(int m, uint32_t step) {
   return m >= 8 ? m - m / 8 : max(0, m - ((step & 3u) == 0u ? 1 : 0));
@@ -1561,7 +1566,7 @@ __device__ __forceinline__ void pick3_body(const Ws& ws, int w0, uint32_t step_i
     int lo = centre - below, cell = 0;
     if (nb == kGuessBins && consecutive) {
       lo = max(lo, fine >> 6);
-      cell = (wary != 0u ? fine : down - (kListCells + m)) - (lo << 6);
+      cell = (wary != 0u ? fine : down - (kListCells + (n_layer < kSmallListLayer ? 2 * m : m))) - (lo << 6);
     }
     ws.guess[wl * 2 + lv] = (b1 == 0u || runs_dry) ? kGuessZero : make_guess(lo, nb, cell);
   }
