@@ -134,7 +134,7 @@ __device__ __forceinline__ void batch_micro_body(const Ws& ws, const GradPtrs& g
     ws.stats[0] += exch ? 1ull : 0ull;                     // exchanges
     ws.stats[1] += 1ull;                                   // micro-steps
   }
-  const FlatTile ft = ws.ftiles[flat_tile_of_block(ws, blockIdx.x, ws.n_ftiles)];
+  const FlatTile ft = ws.ftiles[blockIdx.x];
   const LayerDev& L = ws.layers[ft.layer];
   const TileGeom tg = tile_geom(L, ft);
   const bool nts = tg.a0 >= sums_cached;                   // uniform, like all that follows

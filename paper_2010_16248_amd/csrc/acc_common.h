@@ -157,12 +157,17 @@ struct Ws {
 // ---- which tile a workgroup takes ----------------------------------------------------
 // Workgroups go round robin over the eight XCDs, each with an L2 of its own, so neighbouring tiles -- which share cache lines (rows and
 // layers that do not start on one), rows of Q, partial sums, histograms and per-quarter records -- met in eight different caches.  So runs of
-// kXcdRun tiles go to one XCD: of every 8 kXcdRun workgroups those of XCD x take the x-th run.  (Short runs, so that
-// the chip as a whole still streams through the tensors in order.)  us per step, round robin -> runs of 32: PowerSGD ResNet-18 shapes W = 1 with the update
+// kXcdRun workgroups' tiles go to one XCD: of every 8 kXcdRun workgroups those of XCD x take the x-th run.  (Short runs, so that
+// the chip as a whole still streams through the tensors in order.  A workgroup takes a tile in most kernels, four in the counting kernel with a
+// tile per wave, half a tile in the compaction.)  us per step, round robin -> runs of 32: PowerSGD ResNet-18 shapes W = 1 with the update
 // 96.3 -> 92.4 (93.6 when every workgroup works its tile out instead of finding it in the table), odd sizes W = 3 119.4 -> 116.0 (117.2), the rest in that way: W = 2 127.7 -> 125.5, W = 4 159.6 -> 158.0, odd sizes W = 8 234.9 -> 228.6, VGG-19 W = 4 274.4 -> 272.4, with the update W = 1
-// 158.4 -> 156.1, call by call 112.2 -> 111.3, LSTM W = 1 514.6 -> 517.3, small sets +- 1 %; batch-size mode ResNet-18 W = 1 297.5 -> 291.8, W = 4 740 -> 735,
-// VGG-19 W = 4 637 -> 640, LSTM W = 2 the same; TopK LSTM W = 16 2335 -> 2232, W = 8 K = 1 % 1031 -> 1000, smaller contexts (LSTM W = 4, VGG-19,
-// ResNet-18, odd sizes) within 1 % either way, which therefore stay round robin (Ws::xcd_runs).  Runs of 8, 64, 128: LSTM W = 16 2321, 2264, 2314; PowerSGD ResNet-18
+// 158.4 -> 156.1, call by call 112.2 -> 111.3, LSTM W = 1 514.6 -> 517.3, small sets +- 1 %; TopK from
+// 1 GiB of error memory on, LSTM W = 16 2335 -> 2232; both in the same buffers, K = 10 % where nothing is said: LSTM W = 8 1217 -> 1203, W = 6 949 -> 938, K = 1 %
+// 821 -> 792, VGG-19 W = 16 1045 -> 1024, K = 1 % with the update 957 -> 924, odd sizes W = 8 829 -> 814, ResNet-18 K = 99 % W = 32 1690 -> 1661, K = 10 % W = 24
+// and 32 the same; below: VGG-19 W = 13 854 -> 836, LSTM W = 5 819 -> 814, W = 4 689 -> 684, ResNet-18 W = 16 571 -> 575, still smaller contexts within 1 % either
+// way, which stay round robin (Ws::xcd_runs).  Batch-size mode, whose passes share nothing between tiles, stays so too, one large batch of four micro-steps:
+// ResNet-18 W = 1 144.8 -> 144.7, W = 4 343 -> 344, VGG-19 W = 4 637 -> 643, W = 8 1257 -> 1274, LSTM W = 2 919 -> 918, odd sizes W = 1 109.0 -> 110.2, smaller layers W = 4
+// 67.9 -> 68.8, W = 1 28.4 -> 29.0, four small layers 34.2 -> 35.1.  Runs of 8, 64, 128: LSTM W = 16 2321, 2264, 2314; PowerSGD ResNet-18
 // W = 1 94.9, 93.7, 96.1, odd sizes 116.7, 118.3, 118.6.
 constexpr int kXcds = 8, kXcdRun = 32;
 __device__ __host__ __forceinline__ int tile_of_block(int b, int n) {

@@ -893,7 +893,7 @@ static int32_t init_common(const acc_config* cfg, void* workspace_dev, size_t wo
   ws.n_ptiles = (int32_t)p.ptiles.size();
   ws.n_vectiles = (int32_t)p.vectiles.size();
   ws.n_mat = (int32_t)p.matlayers.size();
-  ws.xcd_runs = cfg->method == ACC_BATCH || p.e_stride * cfg->n_workers > (int64_t(1) << 28) ? 1 : 0;
+  ws.xcd_runs = cfg->method == ACC_TOPK && p.e_stride * cfg->n_workers > (int64_t(1) << 28) ? 1 : 0;
   ws.eta = cfg->eta;
 
   const int nl_ = cfg->n_layers;

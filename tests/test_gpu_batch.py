@@ -239,7 +239,8 @@ def test_errors_of_the_batch_mode():
 
 @pytest.mark.parametrize("tiles", [256, 257, 519])
 def test_runs_of_tiles_for_one_die(tiles):
-    """Every 256 tiles of a launch are taken in another order; what is left over keeps its own."""
+    """Tile counts around the 256 that make up a run for every die, where a launch would be reordered, and twice that: the passes
+    of this mode take their tiles in order."""
     print(f"case batch runs of tiles {tiles}", flush=True)
     layers = [(0, 1, 8192 * (tiles - 1) + 5, 0)]
     gpu, ora = _make(layers, 2, 2, initial_level=0)
