@@ -1772,7 +1772,7 @@ __device__ __forceinline__ void compact_tile(const Ws& ws, int w, const FlatTile
 
 __global__ __launch_bounds__(256) void topk_compact_kernel(const Ws ws, int w0) {
   const int w = w0 + blockIdx.y;
-  const FlatTile ft = ws.ftiles[flat_tile_of_block(ws, blockIdx.x, ws.n_ftiles)];
+  const FlatTile ft = ws.ftiles[blockIdx.x];
   const LayerDev& L = ws.layers[ft.layer];
   const TileGeom tg = tile_geom(L, ft);
   if (blockIdx.x == 0 && threadIdx.x == 0) {
@@ -2391,7 +2391,7 @@ __device__ __forceinline__ void sparse_mean_body(const Ws& ws, const Sink& sink)
   __shared__ float acc[kTile];
   __shared__ uint16_t hole[kTile];                         // tile-local offsets of the dropped entries
   const int tid = threadIdx.x;
-  const FlatTile ft = ws.ftiles[flat_tile_of_block(ws, blockIdx.x, ws.n_ftiles)];
+  const FlatTile ft = ws.ftiles[blockIdx.x];
   const LayerDev& L = ws.layers[ft.layer];
   const TileGeom tg = tile_geom(L, ft);
   if (blockIdx.x == 0 && tid == 0) {
