@@ -61,12 +61,17 @@ constexpr bool kPsgdStreamOut = true;   // averaged gradient: written once, read
 // workgroups read and write: streamed, such a line may have to be fetched twice, plain, the gradients push the error memory out of the caches.
 // Since neighbouring tiles meet in one L2 (tile_of_block) streaming wins wherever the error memory is of a size for that to matter: in contexts of
 // more than kUStreamBytes of it (the kernels with US) gradients, accumulator, D, weights and velocity of unaligned rows are streamed as those of
-// aligned rows always are.  Odd sizes, us per step, plain -> streamed, three states in turn | one state again and again | one state and 1 GB of other traffic
-// between its steps | the same and the gradients written just before: W = 2 (58 MiB) 92.1 -> 84.3 | 82.9 -> 83.9 | 104.8 -> 99.5 | 94.9 -> 94.4, W = 3 (86 MiB)
-// 115.5 -> 107.7 | 104.0 -> 104.6 | 131.0 -> 123.1 | 117.6 -> 117.2, call by call 145.0 -> 137.1 | 132.6 -> 133.1 | 165.8 -> 156.8 | 147.4 -> 147.5, W = 6
-// 183.0 -> 180.0 | 170.3 -> 162.5 | 203.9 -> 189.6 | 190.9 -> 179.5, W = 8 232.7 -> 225.1 | 231.4 -> 222.0 | 266.2 -> 257.8 | 254.7 -> 236.5; below the line
-// W = 1 (29 MiB) 65.7 -> 62.4 | 58.2 -> 62.0 | 76.8 -> 71.2 | 71.8 -> 69.2, smaller layers W = 3 (35 MiB) 59.5 -> 58.1 | 53.7 -> 57.9 | 71.4 -> 66.6 |
-// 68.6 -> 65.7, W = 4 (11 MiB) 36.8 -> 39.3 | 36.3 -> 40.0 | 47.4 -> 45.5 | 45.6 -> 44.8.  Kernels of their own, so that small sets fetch no more code.
+// aligned rows always are.  us per step, plain -> streamed, both in the same buffers, three states in turn | one state again and again | one state and 1 GB of
+// other traffic between its steps | the same and the gradients written just before.  Odd sizes W = 2 (58 MiB) 92.3 -> 84.6 | 83.0 -> 83.8 | 94.5 -> 95.6 |
+// 90.7 -> 93.5, W = 3 (86 MiB) 115.8 -> 108.1 | 104.1 -> 104.8 | 118.7 -> 117.8 | 113.3 -> 116.1, W = 4 138.0 -> 135.4 | 126.3 -> 125.9 | 141.4 -> 140.6 | 136.3 -> 138.9,
+// W = 6 (173 MiB) 183.2 -> 179.7 | 170.5 -> 163.0 | 186.6 -> 181.5 | 187.5 -> 178.9, with the update W = 2 112.1 -> 103.5 | 98.8 -> 102.9 | 115.3 -> 116.1 | 111.5 -> 113.5,
+// W = 6 201.6 -> 200.6 | 193.4 -> 182.9 | 205.3 -> 203.5 | 205.9 -> 200.3, call by call W = 2 107.7 -> 99.6 | 98.1 -> 99.3 | 112.5 -> 111.7 | 106.7 -> 110.1; ten layers of up to
+// 2400 x 2400 W = 2 (57 MiB) 96.0 -> 90.0 | 85.8 -> 89.3 | 100.9 -> 100.1 | 98.2 -> 99.8; 30 of up to 700 x 1000 W = 3 (50 MiB) 79.1 -> 74.0 | 69.3 -> 73.2 | 85.0 -> 83.5 |
+// 81.2 -> 82.0.  So above 150 MiB every regime gains; between the line and there a program that goes through several states or lets them grow cold gains 2 to 8 %,
+// one whose steps follow each other or whose gradients still lie in the caches loses 1 to 3 % (up to 5 % with nothing between the steps); below the line
+// W = 1 (29 MiB) 66.4 -> 62.9 | 59.0 -> 62.3 | 71.6 -> 69.8 | 69.2 -> 69.1, and layers of up to 600 x 800 W = 4 (11 MiB) 36.8 -> 39.3 | 36.3 -> 40.0 | 47.4 -> 45.5 |
+// 45.6 -> 44.8.  With the accumulator plain W = 3 112.1 | 103.4 | 116.2 | 115.8, with the gradients plain 114.5 | 105.9 | 121.8 | 114.9.  Kernels of their own, so that small
+// sets fetch no more code.
 constexpr int64_t kUStreamBytes = int64_t(48) << 20;
 
 // The lane's four elements of a row, loaded whatever the lane owns (every address lies inside the row);

@@ -251,9 +251,16 @@ int make_plan_tiled(const acc_config* c, Plan& p, char* err, bool coarse) {
   // 85.0 -> 90.4 | 84.3 -> 90.0 | 99.8 -> 103.8 | 95.3 -> 98.2, W = 3 108.0 -> 112.8 | 104.7 -> 112.6 | 123.5 -> 130.9 | 117.6 -> 121.6, W = 6 (173 MiB)
   // 180.1 -> 179.1 | 162.8 -> 177.8 | 189.6 -> 207.9 | 180.0 -> 189.1, W = 8 (231 MiB) 224.0 -> 225.0 | 202.7 -> 222.2 | 233.4 -> 257.4 | 220.4 -> 236.3,
   // W = 9 (259 MiB) 255.1 -> 248.3 | 234.0 -> 246.4 | 274.9 -> 283.5 | 259.9 -> 269.1, W = 10 (288 MiB) 294.0 -> 272.7 | 285.7 -> 270.3 | 324.9 -> 307.8 |
-  // 305.5 -> 298.8, W = 12 347 -> 322 | 343 -> 318 | 382 -> 355 | 371 -> 348.
+  // 305.5 -> 298.8, W = 12 347 -> 322 | 343 -> 318 | 382 -> 355 | 371 -> 348.  Between 231 and 288 MiB the regimes disagree; both in the same
+  // buffers: W = 8 225.6 -> 223.8 | 201.5 -> 220.8 | 222.9 -> 241.4 | 221.3 -> 232.9, W = 9 254.5 -> 246.9 | 235.5 -> 245.9 | 260.1 -> 267.2 | 260.4 -> 265.5, with the
+  // update 274.9 -> 268.0 | 258.3 -> 266.7 | 281.0 -> 287.6 | 281.3 -> 286.0, call by call 388.6 -> 371.0 | 377.3 -> 369.2 | 405.6 -> 391.8 | 402.3 -> 388.7,
+  // W = 10 290.8 -> 271.0 | 284.7 -> 269.7 | 299.9 -> 291.4 | 304.0 -> 297.2; ten layers of up to 2400 x 2400 W = 11 (316 MiB) 310.1 -> 301.9 | 289.6 -> 300.0 |
+  // 317.1 -> 321.8 | 324.3 -> 328.8.  So at 248 MiB, where a call-by-call step gains in all of them, a batched one loses up to 5 % in three.
   p.q_stream = 4 * p.e_stride * c->n_workers > (int64_t(248) << 20) ? kQAllRows
                : 4 * aligned_rows * c->n_workers > (int64_t(72) << 20) ? kQAlignedRows : kQPlain;
+  // (Of 12 M elements, aligned and unaligned rows, W = 4 | W = 2 with the update, plain -> streamed, three states in turn: a hundredth unaligned 187.8 -> 187.9 |
+  // 144.3 -> 144.6, 3 % 188.7 -> 187.2 | 145.8 -> 146.7, 6 % 189.2 -> 187.9 | 145.8 -> 145.2, 12 % 190.2 -> 187.9 | 146.1 -> 145.2, 25 % 188.8 -> 186.3 |
+  // 155.9 -> 148.3: below an eighth the two hardly differ, and a sixteenth keeps models with a few such layers on the smaller kernels.)
   const int64_t mat = p.n_model - p.vec_total;
   p.u_stream = 16 * (mat - aligned_rows) > mat && 4 * p.e_stride * c->n_workers > kUStreamBytes;
   run_order(p.mtiles);
