@@ -812,7 +812,12 @@ __device__ __forceinline__ QuarterHead load_quarter_head(const Ws& ws, int64_t q
 // when the quarter has more entries than its list holds, or b1 has entries below the lists' floor (short) --
 // from Delta itself.
 // tl: tile within the layer, wave: quarter within the tile.
-template <class F>
+// The walk over Delta takes one component at a time (all four unrolled are code that every launch fetches, 1 us of the counting kernel without
+// such quarters); AHEAD: with the next groups' load under way.  Counting kernel, us, unrolled | rolled | AHEAD: LSTM set, whose dense rows
+// overflow, K = 25 % W = 1 17.8 | 19.4 | 18.0, K = 10 % W = 2 30.0 | 27.5 | 25.9.  Not in the kernel with a tile per wave, which holds four copies of this (LSTM
+// W = 16 180.3, with the components rotated through one register 176.5, AHEAD 190.4, K = 1 % W = 8 41.0 and 45.2), nor in the sweeps of the last
+// pick kernels, which are rare (44.4 and 45.1 us for the big one on LSTM W = 2).
+template <bool AHEAD, class F>
 __device__ __forceinline__ uint32_t for_quarter_keys(const Ws& ws, const LayerDev& L, int w, int tl, int wave,
                                                      int64_t qslot, const QuarterHead& h, uint32_t b1, bool is_short,
                                                      int lane, F f) {
@@ -852,12 +857,21 @@ __device__ __forceinline__ uint32_t for_quarter_keys(const Ws& ws, const LayerDe
   const WaveSpan sp = wave_span(tg, wave);
   const float* __restrict__ e = ws.e + (int64_t)w * ws.e_stride;
   uint32_t above = 0;
+  float4 next;
+  if (AHEAD) next = ld_span<false>(e, tg, sp, sp.qbeg + lane);
   for (int q0 = sp.qbeg; q0 < sp.qend; q0 += kWave) {
     const int qq = q0 + lane;
-    const float4 d = ld_span<false>(e, tg, sp, qq);
+    float4 d;
+    if (AHEAD) {
+      d = next;
+      next = ld_span<false>(e, tg, sp, qq + kWave);
+    } else {
+      d = ld_span<false>(e, tg, sp, qq);
+    }
 #pragma unroll 1
     for (int c = 0; c < 4; ++c) {
-      const uint32_t key = key_of(comp(d, c));
+      const uint32_t key = key_of(d.x);
+      d.x = d.y; d.y = d.z; d.z = d.w;
       const bool valid = elem_valid<false>(tg, qq, c, qq < sp.qend);
       above += (uint32_t)__popcll(ballot64(valid && (key >> 20) > b1));
       f(key, valid && key != 0u && (key >> 20) == b1);
@@ -1110,12 +1124,14 @@ __device__ __forceinline__ void count3_missed(const Ws& ws, int w, const FlatTil
 }
 
 // One wave quarter: the keys of cell (b1, b2) go to its short list; n_in: their number.  Returns the entries above the cell.
+// AHEAD: see for_quarter_keys.
+template <bool AHEAD>
 __device__ __forceinline__ uint32_t count3_quarter(const Ws& ws, int w, const CountTile& t, int quarter, const QuarterHead& qh,
                                                    int lane, uint32_t& n_in) {
   const uint32_t b2 = t.b2;
   uint32_t* list = ws.qlist + (t.qslot + quarter) * kQListCap;
   uint32_t n_gt = 0, n_cell = 0;                           // wave-uniform
-  const uint32_t above = for_quarter_keys(ws, ws.layers[t.ft.layer], w, t.ft.start >> kTileShift, quarter, t.qslot + quarter, qh, t.b1,
+  const uint32_t above = for_quarter_keys<AHEAD>(ws, ws.layers[t.ft.layer], w, t.ft.start >> kTileShift, quarter, t.qslot + quarter, qh, t.b1,
                                           t.mode == 3u, lane,
                                           [&](uint32_t key, bool valid) {
     const uint32_t bb = bin2_of(key);
@@ -1153,7 +1169,7 @@ __global__ __launch_bounds__(256) void topk_count3_kernel(const Ws ws, int w0) {
     return;
   }
   uint32_t n_in;
-  const uint32_t n_above = count3_quarter(ws, w, t, wave, qh, lane, n_in);
+  const uint32_t n_above = count3_quarter<true>(ws, w, t, wave, qh, lane, n_in);
   if (lane == 0) { ws.gtq[t.qslot + wave] = n_above; ws.eqq[t.qslot + wave] = n_in; }
 }
 
@@ -1183,7 +1199,7 @@ __global__ __launch_bounds__(256) void topk_count3_wide_kernel(const Ws ws, int 
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       uint32_t n_in;
-      const uint32_t n_above = count3_quarter(ws, w, t, q, qh[q], lane, n_in);
+      const uint32_t n_above = count3_quarter<false>(ws, w, t, q, qh[q], lane, n_in);
       if (lane == q) { above = n_above; in = n_in; }
     }
     if (lane < 4) { ws.gtq[t.qslot + lane] = above; ws.eqq[t.qslot + lane] = in; }
@@ -1415,7 +1431,7 @@ __device__ __forceinline__ void pick3_body(const Ws& ws, int w0, uint32_t step_i
     auto sweep = [&](auto per_key, auto per_quarter) {
       for (int q = wave; q < nq; q += kPickWaves) {
         const QuarterHead qh = load_quarter_head(ws, qbase + q, lane);
-        const uint32_t above = for_quarter_keys(ws, L, w, q >> 2, q & 3, qbase + q, qh, b1, false, lane, per_key);
+        const uint32_t above = for_quarter_keys<false>(ws, L, w, q >> 2, q & 3, qbase + q, qh, b1, false, lane, per_key);
         per_quarter(q, above);
       }
     };
