@@ -88,8 +88,8 @@ __device__ __forceinline__ int guess_bins_for(uint32_t k, uint32_t n) {
 // layers: ResNet-18 shapes W = 4 178.5, windows 1650.  After a short step it lies further down for kWarySteps steps, kFloorCells + kFloorPerMove m, where the
 // lowest counted bin lies as well; a level's first steps list everything they count.
 // us per step against a floor of 8 + 4 m cells, below which nothing was counted either: ResNet-18 shapes K = 10 %, W = 4 182.2 -> 180.7 (13 % of
-// the entries listed instead of 14.5; in the first twenty steps of a run 15 instead of 20), two windows of five steps 1679 -> 1667, K = 1 %, W = 1
-// with the update 96.4 -> 95.1, LSTM set W = 16 2353 -> 2366 (+- 20).
+// the entries listed instead of 14.5; in the first twenty steps of a run 15 instead of 20), two windows of five steps 1679 -> 1667; K = 1 %, W = 1
+// with the update, odd sizes and the LSTM set (W = 16 2353 -> 2366, +- 20) the same.
 constexpr int kListCells = 8, kWarySteps = 16, kFloorMost = 255;
 constexpr uint32_t kSmallListLayer = 1u << 19;
 constexpr int kFloorCells = 8, kFloorPerMove = 4, kMoveMost = 31;
@@ -2028,7 +2028,8 @@ __device__ __forceinline__ void compact_mean_tile(const Ws& ws, const FlatTile& 
 // instructions per wave), and by its stores (payload 6 us there).  Two candidates per lane and three batches of 128 in flight instead of one and one of
 // 256: 32.5 -> 30.9 us there, LSTM set W = 16 422 -> 390, odd sizes W = 3 15.9 -> 15.0 (with it the division, see DivW).  Two waves per quarter, one for the sums and
 // one for the payload: the same, LSTM set 553 (lists are read twice); payload stored where it is selected: 40, LSTM set 690; half the sums in LDS at a
-// time, seven waves per SIMD: 27, LSTM set 440, before the second pass over the lists that it would need.
+// time, seven waves per SIMD: 27, LSTM set 440, before the second pass over the lists that it would need.  (Since lists beside one that
+// cannot serve are requested ahead too: ResNet-18 shapes 28.9, LSTM set 364.)
 constexpr int kPairAhead = 3;                               // batches of 128 candidates in flight
 constexpr int kQuarterGroups = kTile / 16;                  // groups of a wave quarter at most
 constexpr int kQuarterFloats = 4 * kQuarterGroups;
