@@ -165,9 +165,10 @@ struct Ws {
 // 1 GiB of error memory on, LSTM W = 16 2335 -> 2232; both in the same buffers, K = 10 % where nothing is said: LSTM W = 8 1217 -> 1203, W = 6 949 -> 938, K = 1 %
 // 821 -> 792, VGG-19 W = 16 1045 -> 1024, K = 1 % with the update 957 -> 924, odd sizes W = 8 829 -> 814, ResNet-18 K = 99 % W = 32 1690 -> 1661, K = 10 % W = 24
 // and 32 the same; below: VGG-19 W = 13 854 -> 836, LSTM W = 5 819 -> 814, W = 4 689 -> 684, ResNet-18 W = 16 571 -> 575, still smaller contexts within 1 % either
-// way, which stay round robin (Ws::xcd_runs).  Batch-size mode, whose passes share nothing between tiles, stays so too, one large batch of four micro-steps:
-// ResNet-18 W = 1 144.8 -> 144.7, W = 4 343 -> 344, VGG-19 W = 4 637 -> 643, W = 8 1257 -> 1274, LSTM W = 2 919 -> 918, odd sizes W = 1 109.0 -> 110.2, smaller layers W = 4
-// 67.9 -> 68.8, W = 1 28.4 -> 29.0, four small layers 34.2 -> 35.1.  Runs of 8, 64, 128: LSTM W = 16 2321, 2264, 2314; PowerSGD ResNet-18
+// way, which stay round robin (Ws::xcd_runs).  Batch-size mode, whose passes share nothing between tiles, stays so too.  One large batch of four micro-steps: ResNet-18
+// W = 1 144.3 -> 144.0, W = 4 344.1 -> 344.6, W = 8 655 -> 658, VGG-19 W = 1 255.3 -> 253.5, W = 4 638 -> 644, W = 8 1253 -> 1276, LSTM W = 1 592 -> 590, W = 3 1294 -> 1308, odd sizes
+// W = 1 109.0 -> 110.2, smaller layers W = 4 67.9 -> 68.8, W = 1 28.4 -> 29.0, four small layers 34.2 -> 35.1; of more ResNet-18 W = 4 737.5 -> 732.6 (eight), W = 2 329.4 -> 326.9
+// (six): up to 0.8 % gained where the sums stay in the cache, up to 1.8 % lost where they are streamed and 2.6 % in small sets.  Runs of 8, 64, 128: LSTM W = 16 2321, 2264, 2314; PowerSGD ResNet-18
 // W = 1 94.9, 93.7, 96.1, odd sizes 116.7, 118.3, 118.6.
 constexpr int kXcds = 8, kXcdRun = 32;
 __device__ __host__ __forceinline__ int tile_of_block(int b, int n) {
