@@ -438,7 +438,7 @@ __device__ __forceinline__ void group_select(const SelCommon& sc, TieF tie, uint
                                              uint64_t (&msel)[4]) {
 #pragma unroll
   for (int c = 0; c < 4; ++c) msel[c] = ballot64(key[c] >= sc.t_all) & mv[c];
-  if (sc.ties) {                                            // wave-uniform
+  if (__builtin_expect(sc.ties, 0)) {                       // wave-uniform
     const SelTies t = tie();
     uint64_t meq[4];
 #pragma unroll
@@ -783,10 +783,11 @@ __device__ __forceinline__ void restage_tile(const Ws& ws, int w, const FlatTile
 
 // ---- the per-layer decisions ---------------------------------------------------------------------
 
-// The branches of the decision kernels and of the compaction that ordinary steps never take (missed guesses, sweeps, quarters from Delta) are marked
-// as such, so that their code lies behind the rest: a kernel of a few microseconds waits for the instructions it runs over.  us without -> with:
-// last pick kernel LSTM set W = 1 9.9 -> 9.1, ResNet-18 shapes W = 4 10.5 -> 10.1, compaction there 29.1 -> 28.5; steps LSTM W = 1 K = 25 % 315.9 -> 314.5, ResNet-18
-// shapes W = 4 176.0 -> 175.4, W = 1 77.0 -> 76.6, four small layers W = 1 33.5 -> 33.2, two layers of 186 k entries together 28.4 -> 28.1.
+// The branches of the decision kernels, of the compaction and of the selection rule that ordinary steps hardly take (missed guesses, sweeps, quarters from
+// Delta, ties within a quarter) are marked as such, so that their code lies behind the rest: a kernel of a few microseconds waits for the instructions
+// it runs over.  us without -> with: last pick kernel LSTM set W = 1 9.9 -> 9.1, ResNet-18 shapes W = 4 10.5 -> 10.1, compaction there 29.1 -> 28.5; steps LSTM W = 1 K = 25 % 315.9 -> 314.5, ResNet-18
+// shapes W = 4 176.0 -> 175.4, W = 1 77.0 -> 76.6, four small layers W = 1 33.5 -> 32.8,
+// two layers of 186 k entries together 28.4 -> 27.8.
 
 // The first kEagerChunks 64-entry chunks of a quarter's list are requested together with its
 // counts (the slot always exists; what lies past the count is ignored later), the rest once the
