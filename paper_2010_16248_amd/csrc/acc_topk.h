@@ -785,9 +785,9 @@ __device__ __forceinline__ void restage_tile(const Ws& ws, int w, const FlatTile
 
 // The branches of the decision kernels, of the compaction and of the selection rule that ordinary steps hardly take (missed guesses, sweeps, quarters from
 // Delta, ties within a quarter) are marked as such, so that their code lies behind the rest: a kernel of a few microseconds waits for the instructions
-// it runs over.  us without -> with: last pick kernel LSTM set W = 1 9.9 -> 9.1, ResNet-18 shapes W = 4 10.5 -> 10.1, compaction there 29.1 -> 28.5; steps LSTM W = 1 K = 25 % 315.9 -> 314.5, ResNet-18
-// shapes W = 4 176.0 -> 175.4, W = 1 77.0 -> 76.6, four small layers W = 1 33.5 -> 32.8,
-// two layers of 186 k entries together 28.4 -> 27.8.
+// it runs over.  us without -> with: last pick kernel LSTM set W = 1 9.9 -> 9.1, ResNet-18 shapes W = 4 10.5 -> 10.1, compaction there 29.1 -> 28.7; steps
+// LSTM W = 1 K = 25 % 315.9 -> 314.5, W = 2 K = 10 % 430.0 -> 428.2, ResNet-18 shapes W = 4 176.0 -> 175.3, W = 1 77.0 -> 76.6, four small layers W = 1 33.4 -> 32.8, two
+// layers of 185 k entries together 28.4 -> 27.9.
 
 // The first kEagerChunks 64-entry chunks of a quarter's list are requested together with its
 // counts (the slot always exists; what lies past the count is ignored later), the rest once the
